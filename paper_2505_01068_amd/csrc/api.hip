@@ -88,7 +88,7 @@ static int validate_shape(const im_shape_t* s) {
 }
 
 // Which kernel family serves this shape.
-enum Path { PATH_ROWLANE, PATH_MFMA, PATH_NONE };
+enum Path { PATH_SMALLHEAD, PATH_MFMA, PATH_NONE };
 static Path pick_path(const im_shape_t* s) {
   const int dh = s->d_model / s->n_heads;
   if (s->dtype == IM_DTYPE_BF16 && mfma_supports(s->d_model, dh)) {
@@ -98,7 +98,7 @@ static Path pick_path(const im_shape_t* s) {
     if (max_seg * 3L * s->d_model * 2L < (1L << 31) && 3L * s->d_model * 2L < (1L << 24)) return PATH_MFMA;
     return PATH_NONE;
   }
-  if (rowlane_supports(dh)) return PATH_ROWLANE;
+  if (smallhead_supports(dh)) return PATH_SMALLHEAD;
   return PATH_NONE;
 }
 static int check_supported(const im_shape_t* s) {
@@ -230,8 +230,8 @@ static int scratch_of_current_device(char** out) {
 }
 
 // ---------------------------------------------------------------------------------------------
-// forward on the ALU path; `res` (same layout as y) is added to y when not NULL.
-static int fwd_rowlane(const im_shape_t* s, const void* x, const void* wq, const void* wk, const void* wv,
+// forward of the small-head path; `res` (same layout as y) is added to y when not NULL.
+static int fwd_smallhead(const im_shape_t* s, const void* x, const void* wq, const void* wk, const void* wv,
                        const void* wo, const void* bq, const void* bk, const void* bv, const void* bo,
                        const int32_t* valid_len, const uint8_t* key_pad, void* y, const void* res, char* sv,
                        hipStream_t st) {
@@ -260,7 +260,7 @@ static int fwd_rowlane(const im_shape_t* s, const void* x, const void* wq, const
   if (rc) return rc;
 
   { ProfScope ps(PF_ATTN_FWD, st);
-  rc = launch_rowlane_fwd(g, bf, qkv, qkv + d * es, qkv + 2 * d * es, 3 * d, valid_len, key_pad, o, d, lse2, st); }
+  rc = launch_smallhead_fwd(g, bf, qkv, qkv + d * es, qkv + 2 * d * es, 3 * d, valid_len, key_pad, o, d, lse2, st); }
   if (rc) return rc;
 
   ProfScope ps2(PF_PROJ_FWD, st);
@@ -274,7 +274,7 @@ static int fwd_rowlane(const im_shape_t* s, const void* x, const void* wq, const
   return check_hip("im_attention_fwd launch");
 }
 
-static int bwd_rowlane(const im_shape_t* s, const void* x, const void* wq, const void* wk, const void* wv,
+static int bwd_smallhead(const im_shape_t* s, const void* x, const void* wq, const void* wk, const void* wv,
                        const void* wo, const int32_t* valid_len, const uint8_t* key_pad, const char* sv,
                        const void* dy, void* dx, void* dwq, void* dwk, void* dwv, void* dwo, void* dbq, void* dbk,
                        void* dbv, void* dbo, char* ws, hipStream_t st) {
@@ -343,7 +343,7 @@ static int bwd_rowlane(const im_shape_t* s, const void* x, const void* wq, const
     ProfScope ps(PF_WGRAD, st);
     if ((rc = launch_gemm_alu(p, bf, bf, 0, st))) return rc;
   }
-  rc = launch_rowlane_bwd(g, bf, qkv, qkv + d * es, qkv + 2 * d * es, 3 * d, o, d_o, d, lse2, valid_len, key_pad,
+  rc = launch_smallhead_bwd(g, bf, qkv, qkv + d * es, qkv + 2 * d * es, 3 * d, o, d_o, d, lse2, valid_len, key_pad,
                           delta, dqkv, dqkv + d * es, dqkv + 2 * d * es, 3 * d, st);
   if (rc) return rc;
 
@@ -487,7 +487,7 @@ int im_attention_fwd(const im_shape_t* shape, const void* x, const void* wq, con
   if (path == PATH_MFMA)
     return mfma_attention_fwd(shape, x, wq, wk, wv, wo, bq, bk, bv, bo, valid_len, key_pad, y, nullptr, sv, L.qkv,
                               L.o, L.lse, L.extra, ws, as_stream(hip_stream));
-  return fwd_rowlane(shape, x, wq, wk, wv, wo, bq, bk, bv, bo, valid_len, key_pad, y, nullptr, sv,
+  return fwd_smallhead(shape, x, wq, wk, wv, wo, bq, bk, bv, bo, valid_len, key_pad, y, nullptr, sv,
                      as_stream(hip_stream));
 }
 
@@ -516,7 +516,7 @@ int im_attention_bwd(const im_shape_t* shape, const void* x, const void* wq, con
     launch_reduce_list(later, as_stream(hip_stream));
     return check_hip("im_attention_bwd launch");
   }
-  return bwd_rowlane(shape, x, wq, wk, wv, wo, valid_len, key_pad, (const char*)saved, dy, dx, dwq, dwk, dwv, dwo, dbq,
+  return bwd_smallhead(shape, x, wq, wk, wv, wo, valid_len, key_pad, (const char*)saved, dy, dx, dwq, dwk, dwv, dwo, dbq,
                      dbk, dbv, dbo, (char*)workspace, as_stream(hip_stream));
 }
 
@@ -550,7 +550,7 @@ int im_attention_fwd_noalloc(const im_shape_t* shape, const void* x, const void*
   if (path == PATH_MFMA)
     return mfma_attention_fwd(shape, x, wq, wk, wv, wo, bq, bk, bv, bo, valid_len, key_pad, y, nullptr, sv, L.qkv,
                               L.o, L.lse, L.extra, sv + L.total, as_stream(hip_stream));
-  return fwd_rowlane(shape, x, wq, wk, wv, wo, bq, bk, bv, bo, valid_len, key_pad, y, nullptr, sv,
+  return fwd_smallhead(shape, x, wq, wk, wv, wo, bq, bk, bv, bo, valid_len, key_pad, y, nullptr, sv,
                      as_stream(hip_stream));
 }
 
@@ -623,7 +623,7 @@ int gsit_layer_fwd(const im_shape_t* shape, int32_t d_ff, const void* x, const v
                             tail_fused ? nullptr : h, x, aw, L.qkv, L.o, L.lse, L.extra, aw + L.total, st,
                             ln1_fused ? LnArgs{ln1_g, ln1_b, ln_eps} : LnArgs{nullptr, nullptr, 0.f});
   else
-    rc = fwd_rowlane(shape, u, wq, wk, wv, wo, bq, bk, bv, bo, valid_len, key_pad, h, x, aw, st);
+    rc = fwd_smallhead(shape, u, wq, wk, wv, wo, bq, bk, bv, bo, valid_len, key_pad, h, x, aw, st);
   if (rc) return rc;
   if (tail_fused) {
     ProfScope ps(PF_MISC, st);
@@ -811,7 +811,7 @@ int gsit_layer_fwd_train(const im_shape_t* shape, int32_t d_ff, const void* x, c
                             ws + L.u + align256((size_t)R * d * (bf ? 2 : 4)), st,
                             ln1_fused ? LnArgs{p->ln1_g, p->ln1_b, ln_eps} : LnArgs{nullptr, nullptr, 0.f});
   else
-    rc = fwd_rowlane(shape, u, p->wq, p->wk, p->wv, p->wo, p->bq, p->bk, p->bv, p->bo, valid_len, key_pad, h, x,
+    rc = fwd_smallhead(shape, u, p->wq, p->wk, p->wv, p->wo, p->bq, p->bk, p->bv, p->bo, valid_len, key_pad, h, x,
                      sv + L.att, st);
   if (rc) return rc;
   if (!ln2_fused && (rc = launch_layernorm(h, p->ln2_g, p->ln2_b, u, (int)R, (int)d, ln_eps, bf, st))) return rc;
@@ -937,7 +937,7 @@ int gsit_layer_bwd(const im_shape_t* shape, int32_t d_ff, const void* x, const g
                             dh, dv, gr->wq, gr->wk, gr->wv, gr->wo, gr->bq, gr->bk, gr->bv, gr->bo, ws + L.attws, st,
                             mm ? &later : nullptr);
   else
-    rc = bwd_rowlane(shape, u, p->wq, p->wk, p->wv, p->wo, valid_len, key_pad, sv + L.att, dh, dv, gr->wq, gr->wk, gr->wv,
+    rc = bwd_smallhead(shape, u, p->wq, p->wk, p->wv, p->wo, valid_len, key_pad, sv + L.att, dh, dv, gr->wq, gr->wk, gr->wv,
                      gr->wo, gr->bq, gr->bk, gr->bv, gr->bo, ws + L.attws, st);
   if (rc) return rc;
   // dx = dh + LN1 backward(du)

@@ -202,14 +202,14 @@ int launch_colsum_multi(const void* const* a, const long* lda, float* const* out
 void launch_zero_seg_rows(const Geo& g, int s, int bf16, void* p, long ld, int col0, int ncols, hipStream_t st);
 void launch_fill_seg_stat(const Geo& g, int s, float* stat, float value, hipStream_t st);
 
-// row-per-lane attention for small head dims (plain ALU)
-int launch_rowlane_fwd(const Geo& g, int bf16, const void* q, const void* k, const void* v, long ld,
+// attention for small head dims in fp32 arithmetic (attn_split.hip); g's tiles have 64 rows
+int launch_smallhead_fwd(const Geo& g, int bf16, const void* q, const void* k, const void* v, long ld,
                        const int32_t* valid_len, const uint8_t* key_pad, void* o, long ldo, float* lse2,
                        hipStream_t st);
-int launch_rowlane_bwd(const Geo& g, int bf16, const void* q, const void* k, const void* v, long ld, const void* o,
+int launch_smallhead_bwd(const Geo& g, int bf16, const void* q, const void* k, const void* v, long ld, const void* o,
                        const void* d_o, long ldo, const float* lse2, const int32_t* valid_len, const uint8_t* key_pad,
                        float* delta, void* dq, void* dk, void* dv, long ldg, hipStream_t st);
-bool rowlane_supports(int dh);
+bool smallhead_supports(int dh);
 
 // LayerNorm rows
 int launch_layernorm(const void* x, const void* gamma, const void* beta, void* y, int R, int d, float eps, int bf16,

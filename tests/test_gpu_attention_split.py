@@ -1,0 +1,52 @@
+"""Small-head attention in fp32 arithmetic on the bf16 matrix cores: every head dimension the kernels are instantiated or
+padded for, the edges of the 16-row blocks, 32-row steps and 64-row tiles, and the moving softmax reference."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2505_01068_amd import synth
+from tests.gpu_util import Problem
+
+pytestmark = pytest.mark.gpu
+
+
+def say(msg):
+    print(msg, flush=True)
+
+
+@pytest.mark.parametrize("dh", range(1, 17))
+def test_every_head_dimension(dh):
+    # one, two and four k-steps of the score product; one to four row blocks of the transposed operand
+    say(f"[case] split attention dh={dh}")
+    g = synth.attention_inputs(2, (17, 65, 33), 3 * dh, 3, "fp32", "valid_len", seed=700 + dh, bias=True)
+    Problem(g, oracle.NAMED_PATTERNS["self_only"]).check(what=f"split/dh{dh}")
+
+
+@pytest.mark.parametrize("seg", [(1, 15, 16), (17, 31, 32), (33, 63, 64), (65, 127, 128), (129, 1, 2)])
+@pytest.mark.parametrize("padding", ["none", "key_pad"])
+def test_block_step_and_tile_edges(seg, padding):
+    say(f"[case] split attention seg={seg} padding={padding}")
+    g = synth.attention_inputs(3, seg, 40, 8, "fp32", padding, seed=731)
+    for name in ("ifm_forward", "ifm_backward", "dense"):
+        Problem(g, oracle.NAMED_PATTERNS[name]).check(what=f"split/{seg}/{name}")
+
+
+def test_rows_and_samples_without_a_valid_key():
+    say("[case] split attention, no valid key")
+    g = synth.attention_inputs(3, (20, 70, 40), 40, 8, "fp32", "valid_len", seed=741)
+    g["valid_len"][0, :] = 0            # no key at all
+    g["valid_len"][1, 1] = 0            # one segment's keys missing
+    g["key_pad"] = np.zeros((3, 130), dtype=np.uint8)
+    g["key_pad"][2, 20:52] = 1          # the first 32-row step of a segment masked: the reference comes later
+    for name in ("ifm_forward", "dense"):
+        Problem(g, oracle.NAMED_PATTERNS[name]).check(what=f"split/no-key/{name}")
+
+
+def test_moving_reference():
+    # scores that grow along the keys move the softmax reference in many steps.  |scores| reach 40 in the exponent of 2,
+    # where one fp32 rounding of a score is 2.4e-6 of its probability; the bar of 1e-5 of the largest element stays.
+    say("[case] split attention, growing scores")
+    g = synth.attention_inputs(2, (40, 200, 130), 40, 8, "fp32", "none", seed=751)
+    for s0, n in ((0, 40), (40, 200), (240, 130)):
+        g["x"][:, s0:s0 + n] *= np.linspace(0.05, 3.0, n, dtype=np.float32)[None, :, None]
+    Problem(g, oracle.IM_IFM_FORWARD).check(what="split/growing")
