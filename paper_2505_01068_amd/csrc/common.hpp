@@ -176,6 +176,9 @@ struct GemmDesc {
   int kb, kt;
   long sab, sbb;
 };
+// fp32 operands on the bf16 matrix cores (gemm_split.hip); launch_gemm_alu sends all it serves there
+bool gemm_split_ok(const GemmDesc& g);
+void launch_gemm_split(const GemmDesc& g, hipStream_t st);
 int launch_gemm_alu(const GemmDesc& g, int a_bf16, int b_bf16, int c_bf16, hipStream_t st);
 size_t gemm_alu_partial_bytes(int M, int N, int K, int* split_k);
 

@@ -1,0 +1,210 @@
+// fp32 GEMMs of the narrow models on the bf16 matrix cores.
+//
+// An fp32 number is the sum of three bf16 numbers (8 + 8 + 8 significand bits, rounded to nearest); a product of two of
+// them is taken as x1 y1 + x1 y2 + x2 y1 + x2 y2 + x1 y3 + x3 y1, each exact in fp32 and accumulated in fp32.  The
+// dropped terms are below 2^-26 of the product, a quarter of an fp32 rounding.  Six 32x32x16 bf16 instructions (15.5 ns
+// each) replace eight 32x32x2 fp32 ones (27 ns each, and those take the vector ALU's issue slots).
+#include "mfma_common.hpp"
+
+namespace imattn {
+
+// eight fp32 values -> the operands of their three parts
+__device__ __forceinline__ void split_parts8(const float (&x)[8], bf16x8 (&out)[3]) {
+  float r[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) r[i] = x[i];
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    u32x4 w;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      w[i] = pack_bf16(r[2 * i], r[2 * i + 1]);
+      if (k < 2) {
+        r[2 * i] -= __uint_as_float(w[i] << 16);
+        r[2 * i + 1] -= __uint_as_float(w[i] & 0xffff0000u);
+      }
+    }
+    out[k] = as_bf16x8(w);
+  }
+}
+// The large term into `big`, the five small ones into `rest`.  The instruction rounds its sum towards minus infinity by a
+// tenth of a unit in the last place of its largest addend on average (measured; fp32 multiply-adds round to nearest): all
+// six terms in one accumulator would take that step six times at full size, a bias that a column sum over the rows of
+// the result (a LayerNorm or bias gradient) adds up -- 1.4e-6 instead of 4e-7 relative over 8400 rows.
+__device__ __forceinline__ void mfma32_split(const bf16x8 (&a)[3], const bf16x8 (&b)[3], f32x16& big, f32x16& rest) {
+  rest = mfma32(a[2], b[0], rest);
+  big = mfma32(a[0], b[0], big);
+  rest = mfma32(a[0], b[2], rest);
+  rest = mfma32(a[1], b[1], rest);
+  rest = mfma32(a[1], b[0], rest);
+  rest = mfma32(a[0], b[1], rest);
+}
+
+// C[M, N] = A[M, K] B[K, N] (+ bias) (GELU) (+ res).  A row-major; B element (k, n) at k sbk + n sbn with one of the two
+// strides 1 (BT: sbk == 1), possibly in up to three buffers by columns or by rows of B.
+// A workgroup of 4 waves owns 64 rows x 64 columns, a wave 32 x 32.  K is walked in chunks of KS 16-deep k-steps: the
+// weight's parts go to LDS in operand order (each wave splits its share), the wave's own 32 rows are read straight into
+// the operand layout (lane = row, eight consecutive k) and split in registers.  At 30 000 rows and K = 40 the whole
+// kernel is one chunk: one memory round trip, one barrier, 18 matrix instructions per wave; it is bound by that chain
+// (a wave waits half of its life) and by launch latency.  64 columns per wave halve the splitting of A but leave fewer
+// waves to overlap the chain: QKV projection 12.3 instead of 10.4 us at 29 600 x 40 x 120, out 12.3 instead of 6.6.
+// The result has lane = column: a store is 128 contiguous bytes per row, and no alignment or width is required.
+// Measured against the kernels it replaced (fp32 matrix instruction with the weight in LDS up to N = K = 128, a 64 x 64
+// vector-ALU tile for the rest): QKV 11.8 -> 10.4 us, output projection 8.0 -> 6.6 (29 600 rows, d = 40); MLP products
+// at 33 600 x 40 x 160 and 33 600 x 160 x 40: 38 -> 14 .. 16 us; 48 x 32 x 96: 11 -> 4.5 us.
+// The weight's column nn (and, with row blocks, row kk) -> its buffer and the index inside it.
+__device__ __forceinline__ const float* gs_buffer(const float* b0, const float* b1, const float* b2, int& i, int per) {
+  const int sel = (i >= per) + (i >= 2 * per);
+  i -= sel * per;
+  return sel == 0 ? b0 : sel == 1 ? b1 : b2;
+}
+template <int KS, bool BT, bool OCT, bool GELU>
+__global__ __launch_bounds__(256, 3) void gemm_split_kernel(GemmDesc g) {
+  constexpr int UNITS = KS * 2, UPW = (UNITS + 3) / 4;   // (k-step, 32-column block) units of the weight; per wave
+  __shared__ u32x4 sB[UNITS * 3 * 64];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lo = lane & 31, h = lane >> 5, wr = wave & 1, wc = wave >> 1;
+  const int m0 = blockIdx.x * 64 + wr * 32, n0 = blockIdx.y * 64;
+  const int K = g.K, N = g.N;
+  const float* const arow = (const float*)g.A + (long)min(m0 + lo, g.M - 1) * g.sam;
+  const int ldw = (int)(BT ? g.sbn : g.sbk);
+  const float *const b0 = (const float*)g.B[0], *const b1 = (const float*)g.B[1], *const b2 = (const float*)g.B[2];
+
+  float a[KS][8], w[UPW][8];
+  // Requests a chunk.  Nothing here reads what it requests (elements past K are zeroed when the chunk is split): a
+  // select on a loaded value between two requests would be a memory round trip.
+  auto load = [&](int k0) {
+    if (OCT) {
+#pragma unroll
+      for (int s = 0; s < KS; ++s) {
+        const float* const p = arow + min(k0 + 16 * s + 8 * h, K - 8);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) a[s][e] = p[e];
+      }
+    } else {
+#pragma unroll
+      for (int s = 0; s < KS; ++s)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) a[s][e] = arow[min(k0 + 16 * s + 8 * h + e, K - 1)];
+    }
+#pragma unroll
+    for (int i = 0; i < UPW; ++i) {
+      const int u = min(4 * i + wave, UNITS - 1);
+      const int s = u >> 1, nb = u & 1, k = k0 + 16 * s + 8 * h;
+      int nn = min(n0 + nb * 32 + lo, N - 1);
+      const float* bp = g.b_split == 1 ? gs_buffer(b0, b1, b2, nn, g.n_per) : b0;
+      if (OCT) {
+        int kk = min(k, K - 8);
+        if (g.b_split == 2) bp = gs_buffer(b0, b1, b2, kk, g.k_per);
+        const float* const p = bp + (unsigned)(BT ? nn * ldw + kk : kk * ldw + nn);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) w[i][e] = p[BT ? e : e * ldw];
+      } else {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          int kk = min(k + e, K - 1);
+          const float* const q = g.b_split == 2 ? gs_buffer(b0, b1, b2, kk, g.k_per) : bp;
+          w[i][e] = q[BT ? nn * ldw + kk : kk * ldw + nn];
+        }
+      }
+    }
+  };
+  auto mask = [&](float (&v)[8], int ku) {   // zeros past K (ku: the k-step's first k)
+    if (ku + 16 > K)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) v[e] = ku + 8 * h + e < K ? v[e] : 0.f;
+  };
+  const int c0 = n0 + wc * 32;
+  load(0);
+  f32x16 acc, rest;
+  {
+    int nn = min(c0 + lo, N - 1);
+    const float* const bp = g.bias_split ? gs_buffer((const float*)g.bias[0], (const float*)g.bias[1], (const float*)g.bias[2], nn, g.n_per)
+                                         : (const float*)g.bias[0];
+    const float bv = bp ? bp[nn] : 0.f;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      acc[r] = bv;
+      rest[r] = 0.f;
+    }
+  }
+  for (int k0 = 0; k0 < K; k0 += 16 * KS) {
+    if (k0 > 0) __syncthreads();
+#pragma unroll
+    for (int i = 0; i < UPW; ++i) {
+      const int u = 4 * i + wave;
+      if (UNITS % 4 != 0 && u >= UNITS) break;
+      bf16x8 p[3];
+      mask(w[i], k0 + 16 * (u >> 1));
+      split_parts8(w[i], p);
+#pragma unroll
+      for (int q = 0; q < 3; ++q) sB[(u * 3 + q) * 64 + lane] = __builtin_bit_cast(u32x4, p[q]);
+    }
+    bf16x8 pa[KS][3];
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+      mask(a[s], k0 + 16 * s);
+      split_parts8(a[s], pa[s]);
+    }
+    if (k0 + 16 * KS < K) load(k0 + 16 * KS);
+    __syncthreads();
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+      bf16x8 b[3];
+#pragma unroll
+      for (int q = 0; q < 3; ++q) b[q] = as_bf16x8(sB[((s * 2 + wc) * 3 + q) * 64 + lane]);
+      mfma32_split(pa[s], b, acc, rest);
+    }
+  }
+  // rows m0 + 8 q + j (+ 4 for the upper lanes): the row's address is scalar, the lane adds its column
+  const int n = c0 + lo;
+  if (n >= N) return;
+  const unsigned off = 4 * h * (unsigned)g.ldc + n;
+  const bool all = m0 + 32 <= g.M;
+  float rv[16];
+  if (g.res)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int m = m0 + 8 * (r >> 2) + (r & 3);
+      rv[r] = all || m + 4 * h < g.M ? ((const float*)g.res + m * g.ldc)[off] : 0.f;
+    }
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    const int m = m0 + 8 * (r >> 2) + (r & 3);
+    float v = acc[r] + rest[r];
+    if (GELU) v = 0.5f * v * (1.f + erff(v * 0.70710678118654752440f));
+    if (g.res) v += rv[r];
+    if (all || m + 4 * h < g.M) ((float*)g.C[0] + m * g.ldc)[off] = v;
+  }
+}
+
+bool gemm_split_ok(const GemmDesc& g) {
+  return g.split_k <= 1 && g.kb <= 1 && !g.c_split && g.sak == 1 && (g.sbn == 1 || g.sbk == 1);
+}
+void launch_gemm_split(const GemmDesc& g, hipStream_t st) {
+  const bool bt = g.sbn != 1;
+  // Octets of k are inside or outside K, and inside one row block of the weight, as a whole: all widths that are
+  // multiples of 8 (one address and two 16-byte loads per octet).  Both forms in one kernel cost every width the 16-byte
+  // loads: the compiler merges the two branches' requests into one list of 4-byte loads at computed addresses (QKV
+  // projection at 29 600 x 40 x 120: 18.4 us instead of 10.4).
+  const bool oct = g.K % 8 == 0 && (g.b_split != 2 || g.k_per % 8 == 0);
+  // k-steps per chunk: one chunk up to K = 64, two up to K = 128 (33 600 x 120 x 40: 10.6 us with two chunks of four
+  // k-steps, 11.5 with four of two), beyond that short ones (33 600 x 160 x 40: 16 us with chunks of two, 20 with chunks
+  // of four or five, whose next chunk waits in registers that cost resident waves)
+  const int nk = (g.K + 15) / 16, ks = nk <= 4 ? nk : nk <= 8 ? (nk + 1) / 2 : 2;
+  const dim3 grid((g.M + 63) / 64, (g.N + 63) / 64);
+#define GS_LAUNCH(KS, OCT)                                                                                          \
+  do {                                                                                                              \
+    if (bt && g.gelu) hipLaunchKernelGGL((gemm_split_kernel<KS, true, OCT, true>), grid, dim3(256), 0, st, g);      \
+    else if (bt) hipLaunchKernelGGL((gemm_split_kernel<KS, true, OCT, false>), grid, dim3(256), 0, st, g);          \
+    else if (g.gelu) hipLaunchKernelGGL((gemm_split_kernel<KS, false, OCT, true>), grid, dim3(256), 0, st, g);      \
+    else hipLaunchKernelGGL((gemm_split_kernel<KS, false, OCT, false>), grid, dim3(256), 0, st, g);                 \
+  } while (0)
+  if (!oct) GS_LAUNCH(4, false);
+  else if (ks <= 2) GS_LAUNCH(2, true);
+  else if (ks == 3) GS_LAUNCH(3, true);
+  else GS_LAUNCH(4, true);
+#undef GS_LAUNCH
+}
+
+}  // namespace imattn

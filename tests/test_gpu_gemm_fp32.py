@@ -1,0 +1,26 @@
+"""fp32 GEMMs on the bf16 matrix cores (gemm_split.hip), through the encoder layer: every product of a layer forward
+(three-buffer QKV with biases, residual, GELU) at the edges of the 64 x 64 tiles, of the 16-deep k-steps and of the chunk
+sizes, with widths that are and are not multiples of 8."""
+import pytest
+import torch
+
+import oracle
+from paper_2505_01068_amd import binding as B, synth
+from tests.gpu_util import TOL, assert_close, to_dev
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("d,H,d_ff", [(8, 1, 24), (16, 2, 40), (40, 8, 160), (48, 6, 192), (64, 8, 256), (80, 8, 320),
+                                      (96, 6, 96), (20, 4, 52), (33, 3, 70), (42, 7, 161)])
+@pytest.mark.parametrize("batch,seg", [(1, (1, 3, 2)), (3, (5, 9, 7)), (2, (13, 40, 12))])   # 6, 63 and 130 rows
+def test_layer_products(d, H, d_ff, batch, seg):
+    print(f"[case] fp32 GEMM d={d} d_ff={d_ff} rows={batch * sum(seg)}", flush=True)
+    g = synth.attention_inputs(batch, seg, d, H, "fp32", "none", seed=801, with_dy=False)
+    p = synth.layer_params(d, d_ff, 801, 0, dtype="fp32")
+    lm = oracle.NAMED_PATTERNS["self_only"]
+    shape = B.make_shape(batch, seg, d, H, lm, g["scale"], "fp32")
+    ws = torch.empty(B.gsit_layer_sizes(shape, d_ff), dtype=torch.uint8, device="cuda")
+    y = B.gsit_layer_fwd(shape, d_ff, to_dev(g["x"], "fp32"), {k: to_dev(v, "fp32") for k, v in p.items()}, workspace=ws)
+    torch.cuda.synchronize()
+    assert_close(y, oracle.gsit_layer_forward(g["x"], p, seg, lm, H, g["scale"]), TOL["fp32"], f"layer d={d} d_ff={d_ff}")
