@@ -189,13 +189,13 @@ static size_t bwd_workspace_bytes(const im_shape_t* s) {
   n += align256(R * d * es);                                          // dO
   n += align256(R * 3 * d * es);                                      // dQ | dK | dV
   n += align256((size_t)s->n_heads * R * sizeof(float));   // delta
+  if (s->dtype == IM_DTYPE_F32)   // both gradients' partial results and column sums stay until the reduction at the end
+    return n + align256(wgrad_split_bytes((int)d, (int)d, (int)R)) + align256(wgrad_split_bytes((int)d, (int)(3 * d), (int)R));
   size_t pb = std::max(gemm_alu_partial_bytes((int)d, (int)(3 * d), (int)R, nullptr),
                        gemm_alu_partial_bytes((int)d, (int)d, (int)R, nullptr));
-  if (mfma_linear_ok(s->dtype == IM_DTYPE_BF16, d, d))
+  if (mfma_linear_ok(1, d, d))
     pb = std::max(pb, std::max(mfma_wgrad_partial_bytes((int)d, (int)(3 * d), (int)R), mfma_wgrad_partial_bytes((int)d, (int)d, (int)R)));
   if (wgrad_small_ok((int)d, (int)(3 * d), (int)d)) pb = std::max(pb, wgrad_small_partial_bytes((int)d, (int)(3 * d), (int)R));
-  if (wgrad_mfma_ok((int)d, (int)(3 * d), (int)R, 0))
-    pb = std::max(pb, wgrad_mfma_partial_bytes((int)d, (int)(3 * d), (int)R) + wgrad_mfma_partial_bytes((int)d, (int)d, (int)R));
   n += align256(pb);
   n += align256(4 * colsum_partial_bytes((int)R, (int)d));            // dbo, dbq, dbk, dbv in one launch
   n += align256(3 * d * d * sizeof(float));                           // sinks for unwanted weight gradients
@@ -274,10 +274,13 @@ static int fwd_smallhead(const im_shape_t* s, const void* x, const void* wq, con
   return check_hip("im_attention_fwd launch");
 }
 
+// later / wlater: second-stage sums resp. fp32 weight gradients that the caller launches at the end of its own pass
+// (NULL: launched here); with wlater the operands (x, dy and the workspace) stay as they are until then.
 static int bwd_smallhead(const im_shape_t* s, const void* x, const void* wq, const void* wk, const void* wv,
-                       const void* wo, const int32_t* valid_len, const uint8_t* key_pad, const char* sv,
-                       const void* dy, void* dx, void* dwq, void* dwk, void* dwv, void* dwo, void* dbq, void* dbk,
-                       void* dbv, void* dbo, char* ws, hipStream_t st) {
+                         const void* wo, const int32_t* valid_len, const uint8_t* key_pad, const char* sv,
+                         const void* dy, void* dx, void* dwq, void* dwk, void* dwv, void* dwo, void* dbq, void* dbk,
+                         void* dbv, void* dbo, char* ws, hipStream_t st, ReduceList* later = nullptr,
+                         WgradSplitList* wlater = nullptr) {
   const int bf = s->dtype == IM_DTYPE_BF16;
   const size_t es = bf ? 2 : 4;
   Geo g;
@@ -292,21 +295,8 @@ static int bwd_smallhead(const im_shape_t* s, const void* x, const void* wq, con
   char* d_o = (char*)b.take(R * d * es);
   char* dqkv = (char*)b.take(R * 3 * d * es);
   float* delta = (float*)b.take((size_t)g.H * R * sizeof(float));
-  int split = 1;
-  size_t pbytes = std::max(gemm_alu_partial_bytes((int)d, (int)(3 * d), (int)R, &split),
-                           gemm_alu_partial_bytes((int)d, (int)d, (int)R, nullptr));
   // bf16 GEMMs go to the matrix cores whenever the widths allow 16-byte chunks
   const bool mm = mfma_linear_ok(bf, d, d);
-  if (mm) pbytes = std::max(pbytes, std::max(mfma_wgrad_partial_bytes((int)d, (int)(3 * d), (int)R), mfma_wgrad_partial_bytes((int)d, (int)d, (int)R)));
-  // narrow models (d <= 64) off the matrix cores: the dedicated tall-skinny weight-gradient kernel
-  const bool ws_small = !mm && wgrad_small_ok((int)d, (int)(3 * d), (int)d);
-  if (ws_small) pbytes = std::max(pbytes, wgrad_small_partial_bytes((int)d, (int)(3 * d), (int)R));
-  // ... and tall fp32 inputs on the fp32 matrix instruction
-  const bool ws_mfma = !mm && wgrad_mfma_ok((int)d, (int)(3 * d), (int)R, bf);
-  if (ws_mfma) pbytes = std::max(pbytes, wgrad_mfma_partial_bytes((int)d, (int)(3 * d), (int)R) + wgrad_mfma_partial_bytes((int)d, (int)d, (int)R));
-  float* partial = (float*)b.take(pbytes);
-  float* cpart = (float*)b.take(4 * colsum_partial_bytes((int)R, (int)d));
-  float* sink = (float*)b.take(3 * d * d * sizeof(float));
 
   GemmDesc p;
   int rc;
@@ -318,65 +308,74 @@ static int bwd_smallhead(const im_shape_t* s, const void* x, const void* wq, con
   { ProfScope ps(PF_PROJ_BWD, st);
     if (mm) mfma_dgrad(dy, d, wo, nullptr, nullptr, d, 0, d_o, d, (int)R, (int)d, (int)d, st);
     else if ((rc = launch_gemm_alu(p, bf, bf, bf, st))) return rc; }
-  // dWo = O^T dy
-  if (dwo && mm) {
-    ProfScope ps(PF_WGRAD, st);
-    mfma_wgrad(o, d, dy, d, (float*)dwo, nullptr, nullptr, 0, (int)d, (int)d, (int)R, partial, st);
-  } else if (dwo && ws_mfma) {
-    // with dWq | dWk | dWv below when those are wanted too (one pair of launches for both), else alone
-    if (!(dwq || dwk || dwv)) {
-      ProfScope ps(PF_WGRAD, st);
-      launch_wgrad_mfma_f32((const float*)o, d, (const float*)dy, d, (int)R, (int)d, (int)d, partial, (float*)dwo, nullptr,
-                            nullptr, 0, st);
-    }
-  } else if (dwo && ws_small) {
-    ProfScope ps(PF_WGRAD, st);
-    const int nb = launch_wgrad_small(o, d, dy, d, (int)R, (int)d, (int)d, bf, partial, st);
-    launch_wgrad_small_reduce(partial, nb, (int)d, (int)d, (float*)dwo, nullptr, nullptr, 0, st);
-  } else if (dwo) {
-    memset(&p, 0, sizeof(p));
-    p.A = o; p.sam = 1; p.sak = d;
-    p.B[0] = dy; p.sbk = d; p.sbn = 1;
-    p.C[0] = dwo; p.ldc = d; p.M = (int)d; p.N = (int)d; p.K = (int)R;
-    gemm_alu_partial_bytes((int)d, (int)d, (int)R, &p.split_k);
-    p.partial = partial;
-    ProfScope ps(PF_WGRAD, st);
-    if ((rc = launch_gemm_alu(p, bf, bf, 0, st))) return rc;
-  }
   rc = launch_smallhead_bwd(g, bf, qkv, qkv + d * es, qkv + 2 * d * es, 3 * d, o, d_o, d, lse2, valid_len, key_pad,
-                          delta, dqkv, dqkv + d * es, dqkv + 2 * d * es, 3 * d, st);
+                            delta, dqkv, dqkv + d * es, dqkv + 2 * d * es, 3 * d, st);
   if (rc) return rc;
 
-  // dWq | dWk | dWv = x^T [dQ | dK | dV]
-  if ((dwq || dwk || dwv) && mm) {
+  if (!bf) {
+    // dWo = O^T dy with dbo, dWq | dWk | dWv = x^T [dQ | dK | dV] with dbq | dbk | dbv: one launch, one reduction
+    float* po = (float*)b.take(wgrad_split_bytes((int)d, (int)d, (int)R));
+    float* pw = (float*)b.take(wgrad_split_bytes((int)d, (int)(3 * d), (int)R));
+    ReduceList red0;
+    WgradSplitList wl0;
+    red0.n = wl0.n = wl0.tiles = 0;
+    ReduceList* red = later ? later : &red0;
+    WgradSplitList* wl = wlater ? wlater : &wl0;
+    wgrad_split_push(wl, red, (const float*)x, d, (const float*)dqkv, 3 * d, (int)R, (int)d, (int)(3 * d), pw, (int)d,
+                     (float*)dwq, (float*)dwk, (float*)dwv, (float*)dbq, (float*)dbk, (float*)dbv);
+    wgrad_split_push(wl, red, (const float*)o, d, (const float*)dy, d, (int)R, (int)d, (int)d, po, 0, (float*)dwo, nullptr, nullptr,
+                     (float*)dbo, nullptr, nullptr);
     ProfScope ps(PF_WGRAD, st);
-    mfma_wgrad(x, d, dqkv, 3 * d, (float*)dwq, (float*)dwk, (float*)dwv, (int)d, (int)d, (int)(3 * d), (int)R, partial, st);
-  } else if ((dwq || dwk || dwv) && ws_mfma) {
+    if (!wlater) launch_wgrad_split(*wl, st);
+    if (!later) launch_reduce_list(*red, st);
+  } else {
+    int split = 1;
+    size_t pbytes = std::max(gemm_alu_partial_bytes((int)d, (int)(3 * d), (int)R, &split),
+                             gemm_alu_partial_bytes((int)d, (int)d, (int)R, nullptr));
+    if (mm) pbytes = std::max(pbytes, std::max(mfma_wgrad_partial_bytes((int)d, (int)(3 * d), (int)R), mfma_wgrad_partial_bytes((int)d, (int)d, (int)R)));
+    // narrow models (d <= 64) off the matrix cores: the dedicated tall-skinny weight-gradient kernel
+    const bool ws_small = !mm && wgrad_small_ok((int)d, (int)(3 * d), (int)d);
+    if (ws_small) pbytes = std::max(pbytes, wgrad_small_partial_bytes((int)d, (int)(3 * d), (int)R));
+    float* partial = (float*)b.take(pbytes);
+    float* cpart = (float*)b.take(4 * colsum_partial_bytes((int)R, (int)d));
+    float* sink = (float*)b.take(3 * d * d * sizeof(float));
     ProfScope ps(PF_WGRAD, st);
-    if (dwo) launch_wgrad_mfma_f32_attn((const float*)x, (const float*)dqkv, (const float*)o, (const float*)dy, (int)R, (int)d,
-                                        partial, (float*)dwq, (float*)dwk, (float*)dwv, (float*)dwo, st);
-    else launch_wgrad_mfma_f32((const float*)x, d, (const float*)dqkv, 3 * d, (int)R, (int)d, (int)(3 * d), partial,
-                               (float*)dwq, (float*)dwk, (float*)dwv, (int)d, st);
-  } else if ((dwq || dwk || dwv) && ws_small) {
-    ProfScope ps(PF_WGRAD, st);
-    const int nb = launch_wgrad_small(x, d, dqkv, 3 * d, (int)R, (int)d, (int)(3 * d), bf, partial, st);
-    launch_wgrad_small_reduce(partial, nb, (int)d, (int)(3 * d), (float*)dwq, (float*)dwk, (float*)dwv, (int)d, st);
-  } else if (dwq || dwk || dwv) {
-    memset(&p, 0, sizeof(p));
-    p.A = x; p.sam = 1; p.sak = d;
-    p.B[0] = dqkv; p.sbk = 3 * d; p.sbn = 1;
-    p.C[0] = dwq ? dwq : sink; p.C[1] = dwk ? dwk : sink + d * d; p.C[2] = dwv ? dwv : sink + 2 * d * d;
-    p.c_split = 1; p.n_per = (int)d; p.ldc = d; p.M = (int)d; p.N = (int)(3 * d); p.K = (int)R;
-    p.split_k = split; p.partial = partial;
-    ProfScope ps(PF_WGRAD, st);
-    if ((rc = launch_gemm_alu(p, bf, bf, 0, st))) return rc;
-  }
-  if (dbo || dbq || dbk || dbv) {  // column sums of dy and of the dQ | dK | dV column blocks, one pair of launches
-    const void* src[4] = {dy, dqkv, dqkv + d * es, dqkv + 2 * d * es};
-    const long lds4[4] = {d, 3 * d, 3 * d, 3 * d};
-    float* dbs[4] = {(float*)dbo, (float*)dbq, (float*)dbk, (float*)dbv};
-    ProfScope ps(PF_WGRAD, st);
-    if ((rc = launch_colsum_multi(src, lds4, dbs, 4, (int)R, (int)d, bf, cpart, st))) return rc;
+    // dWo = O^T dy
+    if (dwo && mm) {
+      mfma_wgrad(o, d, dy, d, (float*)dwo, nullptr, nullptr, 0, (int)d, (int)d, (int)R, partial, st);
+    } else if (dwo && ws_small) {
+      const int nb = launch_wgrad_small(o, d, dy, d, (int)R, (int)d, (int)d, partial, st);
+      launch_wgrad_small_reduce(partial, nb, (int)d, (int)d, (float*)dwo, nullptr, nullptr, 0, st);
+    } else if (dwo) {
+      memset(&p, 0, sizeof(p));
+      p.A = o; p.sam = 1; p.sak = d;
+      p.B[0] = dy; p.sbk = d; p.sbn = 1;
+      p.C[0] = dwo; p.ldc = d; p.M = (int)d; p.N = (int)d; p.K = (int)R;
+      gemm_alu_partial_bytes((int)d, (int)d, (int)R, &p.split_k);
+      p.partial = partial;
+      if ((rc = launch_gemm_alu(p, bf, bf, 0, st))) return rc;
+    }
+    // dWq | dWk | dWv = x^T [dQ | dK | dV]
+    if ((dwq || dwk || dwv) && mm) {
+      mfma_wgrad(x, d, dqkv, 3 * d, (float*)dwq, (float*)dwk, (float*)dwv, (int)d, (int)d, (int)(3 * d), (int)R, partial, st);
+    } else if ((dwq || dwk || dwv) && ws_small) {
+      const int nb = launch_wgrad_small(x, d, dqkv, 3 * d, (int)R, (int)d, (int)(3 * d), partial, st);
+      launch_wgrad_small_reduce(partial, nb, (int)d, (int)(3 * d), (float*)dwq, (float*)dwk, (float*)dwv, (int)d, st);
+    } else if (dwq || dwk || dwv) {
+      memset(&p, 0, sizeof(p));
+      p.A = x; p.sam = 1; p.sak = d;
+      p.B[0] = dqkv; p.sbk = 3 * d; p.sbn = 1;
+      p.C[0] = dwq ? dwq : sink; p.C[1] = dwk ? dwk : sink + d * d; p.C[2] = dwv ? dwv : sink + 2 * d * d;
+      p.c_split = 1; p.n_per = (int)d; p.ldc = d; p.M = (int)d; p.N = (int)(3 * d); p.K = (int)R;
+      p.split_k = split; p.partial = partial;
+      if ((rc = launch_gemm_alu(p, bf, bf, 0, st))) return rc;
+    }
+    if (dbo || dbq || dbk || dbv) {  // column sums of dy and of the dQ | dK | dV column blocks, one pair of launches
+      const void* src[4] = {dy, dqkv, dqkv + d * es, dqkv + 2 * d * es};
+      const long lds4[4] = {d, 3 * d, 3 * d, 3 * d};
+      float* dbs[4] = {(float*)dbo, (float*)dbq, (float*)dbk, (float*)dbv};
+      if ((rc = launch_colsum_multi(src, lds4, dbs, 4, (int)R, (int)d, bf, cpart, st))) return rc;
+    }
   }
   // dx = dQ Wq^T + dK Wk^T + dV Wv^T
   if (dx && mm && d % 64 == 0) {  // the contraction is split over three weights: whole 64-deep k-tiles per weight
@@ -745,11 +744,17 @@ static LayerTrain layer_train_layout(const im_shape_t* s, int32_t d_ff) {
   L.dh = off; off += align256(R * d * es);
   L.t = off; off += align256(R * d * es);
   L.split_w1 = L.split_w2 = 1;
-  size_t p1 = gemm_alu_partial_bytes((int)d, d_ff, (int)R, &L.split_w1);
-  size_t p2 = gemm_alu_partial_bytes(d_ff, (int)d, (int)R, &L.split_w2);
-  if (mfma_linear_ok(s->dtype == IM_DTYPE_BF16, d, d_ff) && mfma_linear_ok(1, d_ff, d)) {
-    p1 = std::max(p1, mfma_wgrad_partial_bytes((int)d, d_ff, (int)R));
-    p2 = std::max(p2, mfma_wgrad_partial_bytes(d_ff, (int)d, (int)R));
+  size_t p1, p2;
+  if (s->dtype == IM_DTYPE_F32) {
+    p1 = wgrad_split_bytes((int)d, d_ff, (int)R);
+    p2 = wgrad_split_bytes(d_ff, (int)d, (int)R);
+  } else {
+    p1 = gemm_alu_partial_bytes((int)d, d_ff, (int)R, &L.split_w1);
+    p2 = gemm_alu_partial_bytes(d_ff, (int)d, (int)R, &L.split_w2);
+    if (mfma_linear_ok(1, d, d_ff) && mfma_linear_ok(1, d_ff, d)) {
+      p1 = std::max(p1, mfma_wgrad_partial_bytes((int)d, d_ff, (int)R));
+      p2 = std::max(p2, mfma_wgrad_partial_bytes(d_ff, (int)d, (int)R));
+    }
   }
   // every second-stage sum of the backward may be postponed to one launch at its end (ReduceList): each set of
   // partials keeps a region of its own
@@ -873,11 +878,17 @@ int gsit_layer_bwd(const im_shape_t* shape, int32_t d_ff, const void* x, const g
   float* cpart3 = (float*)(ws + L.cpart3);
   ReduceList later;   // second-stage sums postponed to one launch at the end (matrix-core path, small outputs)
   later.n = 0;
+  WgradSplitList wl;   // fp32: all four weight gradients (and the bias gradients beside them) in one launch
+  wl.n = wl.tiles = 0;
   GemmDesc g;
   const bool mm = mfma_linear_ok(bf, d, d_ff) && mfma_linear_ok(bf, d_ff, d);  // bf16 GEMMs on the matrix cores
+  ReduceList* const defer = mm || !bf ? &later : nullptr;
 
   // y = h + a W2 + b2
-  if (gr->w2 && mm) {
+  if (!bf) {
+    wgrad_split_push(&wl, &later, (const float*)a, d_ff, (const float*)dy, d, (int)R, d_ff, (int)d, partial, 0, (float*)gr->w2, nullptr,
+                     nullptr, (float*)gr->b2, nullptr, nullptr);
+  } else if (gr->w2 && mm) {
     mfma_wgrad(a, d_ff, dy, d, (float*)gr->w2, nullptr, nullptr, 0, d_ff, (int)d, (int)R, partial, st, &later);
   } else if (gr->w2) {  // dW2 = a^T dy
     memset(&g, 0, sizeof(g));
@@ -885,7 +896,7 @@ int gsit_layer_bwd(const im_shape_t* shape, int32_t d_ff, const void* x, const g
     g.C[0] = gr->w2; g.ldc = d; g.M = d_ff; g.N = (int)d; g.K = (int)R; g.split_k = L.split_w2; g.partial = partial;
     if ((rc = launch_gemm_alu(g, bf, bf, 0, st))) return rc;
   }
-  // (db2 = column sums of dy: taken further down, together with the second LayerNorm's parameter gradients)
+  // (bf16: db2 = column sums of dy: taken further down, together with the second LayerNorm's parameter gradients)
   // dz = (dy W2^T) * GELU'(z)
   const bool dz_fused = mm && mfma_gemm_small_tile((int)R, d_ff, (int)d, false);   // GELU' in the GEMM's epilogue
   if (mm) {
@@ -899,7 +910,10 @@ int gsit_layer_bwd(const im_shape_t* shape, int32_t d_ff, const void* x, const g
   if (!dz_fused && (rc = launch_gelu_bwd(zpre, dz, R * (long)d_ff, bf, st))) return rc;
   // z = v W1 + b1 with v = LN(h; ln2)
   if ((rc = launch_layernorm(h, p->ln2_g, p->ln2_b, v, (int)R, (int)d, ln_eps, bf, st))) return rc;
-  if (gr->w1 && mm) {
+  if (!bf) {
+    wgrad_split_push(&wl, &later, (const float*)v, d, (const float*)dz, d_ff, (int)R, (int)d, d_ff, partial1, 0, (float*)gr->w1, nullptr,
+                     nullptr, (float*)gr->b1, nullptr, nullptr);
+  } else if (gr->w1 && mm) {
     mfma_wgrad(v, d, dz, d_ff, (float*)gr->w1, nullptr, nullptr, 0, (int)d, d_ff, (int)R, partial1, st, &later);
   } else if (gr->w1) {  // dW1 = v^T dz
     memset(&g, 0, sizeof(g));
@@ -907,11 +921,11 @@ int gsit_layer_bwd(const im_shape_t* shape, int32_t d_ff, const void* x, const g
     g.C[0] = gr->w1; g.ldc = d_ff; g.M = (int)d; g.N = d_ff; g.K = (int)R; g.split_k = L.split_w1; g.partial = partial1;
     if ((rc = launch_gemm_alu(g, bf, bf, 0, st))) return rc;
   }
-  if (gr->b1) {
+  if (gr->b1 && bf) {
     const void* src1[1] = {dz};
     const long ld1[1] = {d_ff};
     float* out1[1] = {(float*)gr->b1};
-    if ((rc = launch_colsum_multi(src1, ld1, out1, 1, (int)R, d_ff, bf, cpart, st, mm ? &later : nullptr))) return rc;
+    if ((rc = launch_colsum_multi(src1, ld1, out1, 1, (int)R, d_ff, bf, cpart, st, defer))) return rc;
   }
   if (mm) {  // dv = dz W1^T
     mfma_dgrad(dz, d_ff, p->w1, nullptr, nullptr, d_ff, 0, dv, d, (int)R, (int)d, d_ff, st);
@@ -926,8 +940,8 @@ int gsit_layer_bwd(const im_shape_t* shape, int32_t d_ff, const void* x, const g
   {  // gradients of the LayerNorm gain and bias: column sums of dy * xhat and of dy; and db2 = column sums of dy
     const void* src[3] = {t, dv, dy};
     const long ld3[3] = {d, d, d};
-    float* out3[3] = {(float*)gr->ln2_g, (float*)gr->ln2_b, (float*)gr->b2};
-    if ((rc = launch_colsum_multi(src, ld3, out3, 3, (int)R, (int)d, bf, cpart2, st, mm ? &later : nullptr))) return rc;
+    float* out3[3] = {(float*)gr->ln2_g, (float*)gr->ln2_b, bf ? (float*)gr->b2 : nullptr};
+    if ((rc = launch_colsum_multi(src, ld3, out3, 3, (int)R, (int)d, bf, cpart2, st, defer))) return rc;
   }
   // h = x + IMAttention(u), u = LN(x; ln1): attention backward with upstream gradient dh; its dx is du (into dv)
   if ((rc = launch_layernorm(x, p->ln1_g, p->ln1_b, u, (int)R, (int)d, ln_eps, bf, st))) return rc;
@@ -935,18 +949,19 @@ int gsit_layer_bwd(const im_shape_t* shape, int32_t d_ff, const void* x, const g
   if (pick_path(shape) == PATH_MFMA)
     rc = mfma_attention_bwd(shape, u, p->wq, p->wk, p->wv, p->wo, valid_len, key_pad, sv + L.att, A.qkv, A.o, A.lse, A.extra,
                             dh, dv, gr->wq, gr->wk, gr->wv, gr->wo, gr->bq, gr->bk, gr->bv, gr->bo, ws + L.attws, st,
-                            mm ? &later : nullptr);
+                            defer);
   else
     rc = bwd_smallhead(shape, u, p->wq, p->wk, p->wv, p->wo, valid_len, key_pad, sv + L.att, dh, dv, gr->wq, gr->wk, gr->wv,
-                     gr->wo, gr->bq, gr->bk, gr->bv, gr->bo, ws + L.attws, st);
+                     gr->wo, gr->bq, gr->bk, gr->bv, gr->bo, ws + L.attws, st, bf ? nullptr : &later, bf ? nullptr : &wl);
   if (rc) return rc;
+  launch_wgrad_split(wl, st);
   // dx = dh + LN1 backward(du)
   if ((rc = launch_layernorm_bwd(x, p->ln1_g, dv, dh, dx, t, (int)R, (int)d, ln_eps, bf, st))) return rc;
   {
     const void* src[2] = {t, dv};
     const long ld2[2] = {d, d};
     float* out2[2] = {(float*)gr->ln1_g, (float*)gr->ln1_b};
-    if ((rc = launch_colsum_multi(src, ld2, out2, 2, (int)R, (int)d, bf, cpart3, st, mm ? &later : nullptr))) return rc;
+    if ((rc = launch_colsum_multi(src, ld2, out2, 2, (int)R, (int)d, bf, cpart3, st, defer))) return rc;
   }
   launch_reduce_list(later, st);
   return check_hip("gsit_layer_bwd launch");

@@ -186,12 +186,13 @@ size_t gemm_alu_partial_bytes(int M, int N, int K, int* split_k);
 // split-K partials [nparts][M][N] (outputs as mfma_wgrad's) and over the row-block partials of column sums (M = 1).
 // Each is a few microseconds of launch latency on its own.  A postponed job's partial buffer must stay untouched
 // until launch_reduce_list.
-struct ReduceJob { const float* partial; int nparts, M, N, n_per; float* o[3]; };
+struct ReduceJob { const float* partial; int nparts, M, N, n_per; long stride; float* o[3]; };   // stride: of a partial result, % 4 == 0
 struct ReduceList { ReduceJob job[16]; int n; };
 // N % 4 == 0, at most 65536 output quads and at most 8 MB of partials (a larger set is read back faster right after
 // it was written, while it is still in the last-level cache): the job can go on a list
 bool reduce_deferrable(int M, int N, int nparts);
-void reduce_push(ReduceList* l, const float* partial, int nparts, int M, int N, float* o0, float* o1, float* o2, int n_per);
+void reduce_push(ReduceList* l, const float* partial, int nparts, int M, int N, float* o0, float* o1, float* o2, int n_per,
+                 long stride = 0);   // 0: M * N
 void launch_reduce_list(const ReduceList& l, hipStream_t st);
 // column sums of a [R, n] matrix (bias gradients), deterministic two-stage
 int launch_colsum(const void* a, long lda, int R, int n, int a_bf16, float* out, float* partial, hipStream_t st);
@@ -218,24 +219,31 @@ bool smallhead_supports(int dh);
 int launch_layernorm(const void* x, const void* gamma, const void* beta, void* y, int R, int d, float eps, int bf16,
                      hipStream_t st);
 
-// weight gradient of a narrow layer, C[M,N] = A[R,M]^T G[R,N] with M <= 64, N <= 256 (see gemm_alu.hip):
-// writes and returns a number of partial [M,N] matrices that the caller sums in a fixed order
+// weight gradient of a narrow bf16 layer off the matrix cores, C[M,N] = A[R,M]^T G[R,N] with M <= 64, N <= 256 (see
+// gemm_alu.hip): writes and returns a number of partial [M,N] matrices that the caller sums in a fixed order
 bool wgrad_small_ok(int M, int N, int n_per);
 size_t wgrad_small_partial_bytes(int M, int N, int R);
 void launch_wgrad_small_reduce(const float* partial, int nz, int M, int N, float* o0, float* o1, float* o2, int n_per,
                                hipStream_t st);
-int launch_wgrad_small(const void* A, long lda, const void* G, long ldg, int R, int M, int N, int in_bf16, float* partial,
-                       hipStream_t st);
-// the same for fp32 operands of a tall matrix (R >= 1024, M <= 64, N <= 128) on the fp32 matrix instruction; sums the
-// partial results itself: C into o0 (n_per == 0) or column blocks of n_per columns into o0 | o1 | o2 (NULL = dropped)
-bool wgrad_mfma_ok(int M, int N, int R, int in_bf16);
-size_t wgrad_mfma_partial_bytes(int M, int N, int R);
-void launch_wgrad_mfma_f32(const float* A, long lda, const float* G, long ldg, int R, int M, int N, float* partial,
-                           float* o0, float* o1, float* o2, int n_per, hipStream_t st);
-// both weight gradients of an attention block (d <= 42: 3 d <= 128) in one pair of launches; NULL outputs are dropped;
-// partial: wgrad_mfma_partial_bytes(d, 3 d, R) + wgrad_mfma_partial_bytes(d, d, R) bytes
-void launch_wgrad_mfma_f32_attn(const float* X, const float* dQKV, const float* O, const float* dY, int R, int d,
-                                float* partial, float* q0, float* q1, float* q2, float* dwo, hipStream_t st);
+int launch_wgrad_small(const void* A, long lda, const void* G, long ldg, int R, int M, int N, float* partial, hipStream_t st);
+// fp32 weight gradients over the same R rows in one launch (gemm_split.hip).  push: C[M,N] = A^T G into w0 (n_per == 0) or
+// column blocks of n_per columns into w0 | w1 | w2 (NULL = dropped), the column sums of G into b0 | b1 | b2 likewise;
+// partial: wgrad_split_bytes, untouched until the reduction list has run.
+struct WgradSplit {
+  const float *A, *G;
+  long lda, ldg;
+  int M, N, stride;
+  unsigned tn_magic;
+  float *partial, *csum;
+};
+struct WgradSplitList {
+  WgradSplit p[4];
+  int n, tiles, R, rows;   // tiles: of the largest problem
+};
+size_t wgrad_split_bytes(int M, int N, int R);
+void wgrad_split_push(WgradSplitList* l, ReduceList* red, const float* A, long lda, const float* G, long ldg, int R, int M, int N,
+                      float* partial, int n_per, float* w0, float* w1, float* w2, float* b0, float* b1, float* b2);
+void launch_wgrad_split(const WgradSplitList& l, hipStream_t st);
 
 // encoder-layer backward pieces: a = GELU(z); g <- g * GELU'(z) in place; LayerNorm backward of rows
 // (dx = input gradient + res (res may be NULL), t = dy * xhat for the gamma gradient)

@@ -1,7 +1,5 @@
-// fp32-ALU GEMM with strided operands, used for the projections of the small
-// multimodal-sentiment shapes (d = 32..64: the whole weight fits in a few LDS
-// tiles and the work is bandwidth / launch bound, not MFMA bound) and as the
-// fp32 path of the library.  Also: deterministic column sums and LayerNorm.
+// fp32-ALU GEMM with strided operands for bf16 tensors whose widths the matrix-core kernels do not take (rows that are
+// not whole 16-byte chunks); fp32 tensors go to gemm_split.hip.  Also: deterministic column sums and LayerNorm.
 #include <type_traits>
 #include "common.hpp"
 
@@ -163,8 +161,6 @@ __global__ __launch_bounds__(256) void gemm_splitk_reduce_kernel(GemmDev g) {
   }
 }
 
-typedef float f32x16s __attribute__((ext_vector_type(16)));
-
 size_t gemm_alu_partial_bytes(int M, int N, int K, int* split_k) {
   // Split only reductions that are much longer than the output is wide (weight gradients).
   int s = 1;
@@ -197,7 +193,6 @@ int launch_gemm_alu(const GemmDesc& d, int a_bf16, int b_bf16, int c_bf16, hipSt
   dim3 grid((g.N + GA_BN - 1) / GA_BN, (g.M + GA_BM - 1) / GA_BM, g.split_k), block(GA_THREADS);
   const int key = (a_bf16 ? 4 : 0) | (b_bf16 ? 2 : 0) | (c_bf16 ? 1 : 0);
   switch (key) {
-    case 0: hipLaunchKernelGGL((gemm_alu_kernel<float, float, float>), grid, block, 0, st, g); break;
     case 7: hipLaunchKernelGGL((gemm_alu_kernel<bf16_t, bf16_t, bf16_t>), grid, block, 0, st, g); break;
     case 6: hipLaunchKernelGGL((gemm_alu_kernel<bf16_t, bf16_t, float>), grid, block, 0, st, g); break;
     default: set_error("gemm_alu: unsupported operand type combination %d", key); return IM_ERR_UNSUPPORTED;
@@ -208,7 +203,7 @@ int launch_gemm_alu(const GemmDesc& d, int a_bf16, int b_bf16, int c_bf16, hipSt
 }
 
 // ---- column sums (bias gradients): stage 1 sums blocks of rows, stage 2 sums the blocks in order ----
-// ---- weight gradient of a narrow layer: C[M, N] = A[R, M]^T G[R, N], M <= 64, N <= 256, R long ----
+// ---- weight gradient of a narrow bf16 layer: C[M, N] = A[R, M]^T G[R, N], M <= 64, N <= 256, R long ----
 // The general GEMM above spends its time in a latency-bound loop of R / split 16-deep k-tiles.  Here a
 // block stages WS_RB rows of A and G in LDS with all loads in flight at once and every thread keeps a
 // TM x TN patch of the output in registers (thread (ty, tx): rows ty + 8 i, columns tx + 32 j, so the
@@ -216,8 +211,8 @@ int launch_gemm_alu(const GemmDesc& d, int a_bf16, int b_bf16, int c_bf16, hipSt
 // reduces the partials in a fixed order.
 constexpr int WS_RB = 32;
 constexpr int WS_MAX_BLOCKS = 1024;
-template <typename T, int TM, int TN>
-__global__ __launch_bounds__(256) void wgrad_small_kernel(const T* __restrict__ A, long lda, const T* __restrict__ G,
+template <int TM, int TN>
+__global__ __launch_bounds__(256) void wgrad_small_kernel(const bf16_t* __restrict__ A, long lda, const bf16_t* __restrict__ G,
                                                           long ldg, int R, int M, int N, float* __restrict__ partial) {
   __shared__ float sm[WS_RB * (64 + 256)];
   float* sA = sm;
@@ -315,379 +310,6 @@ void launch_wgrad_small_reduce(const float* partial, int nz, int M, int N, float
                      o1, o2, n_per);
 }
 
-// The same weight gradient on the fp32 matrix instruction: C = A^T G is a product whose contraction runs over the
-// rows, and both operands are read exactly as they lie in memory -- lane (c = lane % 32, h = lane / 32) takes
-// column c of row r + h, a coalesced 128-byte piece per half wave; no LDS in the loop.  A workgroup of 4 waves owns
-// `rows_per_wg` consecutive rows, a quarter each; the four accumulator sets are added through LDS as
-// (w0 + w2) + (w1 + w3), a fixed order, and the workgroup writes one partial result IN ACCUMULATOR ORDER
-// ([block][register quad][lane][4]: 16-byte stores, no index arithmetic); wgrad_mfma_reduce_kernel adds the
-// partials in a fixed order and undoes the layout.  Columns past M resp. N read the last valid column: they only
-// reach accumulator rows / columns that nobody reads.
-struct WgradProblem {
-  const float* A;
-  long lda;
-  const float* G;
-  long ldg;
-  int M, N;
-  float* partial;
-  float *o0, *o1, *o2;   // outputs of the reduction (see wgrad_mfma_reduce_kernel)
-  int n_per;
-  int n_off;             // column of the whole gradient that column 0 of this problem is (a gradient split by columns)
-};
-template <int MB, int NB>
-__device__ __forceinline__ void wgrad_mfma_body(const float* __restrict__ A, long lda, const float* __restrict__ G, long ldg,
-                                                int R, int M, int N, int rows_per_wg, float* __restrict__ partial,
-                                                float* red_base) {
-  constexpr int NBLK = MB * NB;
-  float(*red)[NBLK * 16 * 64] = (float(*)[NBLK * 16 * 64])red_base;
-  const int lane = threadIdx.x & 63, c = lane & 31, h = lane >> 5;
-  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // scalar: the row range of the wave is wave-uniform
-  const int rpw = rows_per_wg >> 2;   // a multiple of 16
-  const long row0 = (long)blockIdx.x * rows_per_wg + (long)w * rpw;
-  f32x16s acc[MB][NB];
-#pragma unroll
-  for (int i = 0; i < MB; ++i)
-#pragma unroll
-    for (int j = 0; j < NB; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-  int ca[MB], cg[NB];
-#pragma unroll
-  for (int i = 0; i < MB; ++i) ca[i] = min(i * 32 + c, M - 1);
-#pragma unroll
-  for (int j = 0; j < NB; ++j) cg[j] = min(j * 32 + c, N - 1);
-  const bool full = row0 + rpw <= R;   // wave-uniform: only the last rows of the matrix need the row test
-  // Eight rows (four contraction steps) per group; the next group's 4 (MB + NB) loads are in flight while the
-  // current group is multiplied.  rpw is a multiple of 16: two groups per trip, in two fixed register sets.
-  float a0[4][MB], g0[4][NB], a1[4][MB], g1[4][NB];
-  // A pair of rows per contraction step: the pair's address is wave-uniform (scalar registers), the lane adds its
-  // row of the pair and its column as one 32-bit offset that never changes.
-  int la[MB], lg[NB];
-#pragma unroll
-  for (int i = 0; i < MB; ++i) la[i] = h * (int)lda + ca[i];
-#pragma unroll
-  for (int j = 0; j < NB; ++j) lg[j] = h * (int)ldg + cg[j];
-  auto load = [&](int r, float (&a)[4][MB], float (&g)[4][NB]) {
-    if (full) {
-      const float* pa = A + (row0 + r) * lda;
-      const float* pg = G + (row0 + r) * ldg;
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-#pragma unroll
-        for (int i = 0; i < MB; ++i) a[u][i] = pa[2 * u * lda + la[i]];
-#pragma unroll
-        for (int j = 0; j < NB; ++j) g[u][j] = pg[2 * u * ldg + lg[j]];
-      }
-    } else {
-      // the last rows of the matrix: every load is issued, at an address inside the matrix, and rows past the end
-      // are replaced by zeros afterwards
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const long row = row0 + r + 2 * u;
-        const long rc = row < R ? row : (long)R - 1;
-        const bool pair = row + 1 < R;   // wave-uniform: the second row of the pair exists
-        const bool ok = row + h < R;
-        const float* pa = A + rc * lda;
-        const float* pg = G + rc * ldg;
-#pragma unroll
-        for (int i = 0; i < MB; ++i) {
-          const float v = pa[pair ? la[i] : ca[i]];
-          a[u][i] = ok ? v : 0.f;
-        }
-#pragma unroll
-        for (int j = 0; j < NB; ++j) {
-          const float v = pg[pair ? lg[j] : cg[j]];
-          g[u][j] = ok ? v : 0.f;
-        }
-      }
-    }
-  };
-  auto multiply = [&](const float (&a)[4][MB], const float (&g)[4][NB]) {
-#pragma unroll
-    for (int u = 0; u < 4; ++u)
-#pragma unroll
-      for (int i = 0; i < MB; ++i)
-#pragma unroll
-        for (int j = 0; j < NB; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[u][i], g[u][j], acc[i][j], 0, 0, 0);
-  };
-  load(0, a0, g0);
-  for (int r = 0; r < rpw; r += 16) {
-    load(r + 8, a1, g1);
-    multiply(a0, g0);
-    if (r + 16 < rpw) load(r + 16, a0, g0);
-    multiply(a1, g1);
-  }
-  // (w0 + w2) + (w1 + w3) through LDS, 16 bytes per lane and access
-  auto put = [&](float* dst) {
-#pragma unroll
-    for (int i = 0; i < MB; ++i)
-#pragma unroll
-      for (int j = 0; j < NB; ++j)
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-          *(float4*)(dst + (((i * NB + j) * 4 + q) * 64 + lane) * 4) =
-              make_float4(acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]);
-  };
-  auto add = [&](const float* src) {
-#pragma unroll
-    for (int i = 0; i < MB; ++i)
-#pragma unroll
-      for (int j = 0; j < NB; ++j)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const float4 v = *(const float4*)(src + (((i * NB + j) * 4 + q) * 64 + lane) * 4);
-          acc[i][j][4 * q] += v.x; acc[i][j][4 * q + 1] += v.y; acc[i][j][4 * q + 2] += v.z; acc[i][j][4 * q + 3] += v.w;
-        }
-  };
-  if (w >= 2) put(red[w - 2]);
-  __syncthreads();
-  if (w < 2) add(red[w]);
-  __syncthreads();
-  if (w == 1) put(red[0]);
-  __syncthreads();
-  if (w != 0) return;
-  add(red[0]);
-  put(partial + (long)blockIdx.x * (NBLK * 16 * 64));
-}
-template <int MB, int NB>
-__global__ __launch_bounds__(256) void wgrad_mfma_f32_kernel(WgradProblem p, int R, int rows_per_wg) {
-  __shared__ __attribute__((aligned(16))) float red[2 * MB * NB * 16 * 64];
-  wgrad_mfma_body<MB, NB>(p.A, p.lda, p.G, p.ldg, R, p.M, p.N, rows_per_wg, p.partial, red);
-}
-// two weight gradients over the same rows in one launch (blockIdx.y picks the problem)
-template <int MB0, int NB0, int MB1, int NB1>
-__global__ __launch_bounds__(256) void wgrad_mfma_f32_pair_kernel(WgradProblem p0, WgradProblem p1, int R, int rows_per_wg) {
-  constexpr int NBLK = MB0 * NB0 > MB1 * NB1 ? MB0 * NB0 : MB1 * NB1;
-  __shared__ __attribute__((aligned(16))) float red[2 * NBLK * 16 * 64];
-  if (blockIdx.y == 0) wgrad_mfma_body<MB0, NB0>(p0.A, p0.lda, p0.G, p0.ldg, R, p0.M, p0.N, rows_per_wg, p0.partial, red);
-  else wgrad_mfma_body<MB1, NB1>(p1.A, p1.lda, p1.G, p1.ldg, R, p1.M, p1.N, rows_per_wg, p1.partial, red);
-}
-
-// Three problems of 2 x 2 blocks over the same rows (blockIdx.y picks the problem).  For 32 < d <= 42 the wide
-// gradient [dWq | dWk | dWv] is split at column 64 into two such problems beside dWo.  Here a wave owns one BLOCK
-// and all rows of the workgroup instead of all blocks and a quarter of the rows: 16 accumulator registers, no sum
-// across the waves at the end, and room for the loads of three groups of eight rows in flight behind the group being
-// multiplied at several workgroups per CU.  The partial result has the layout of wgrad_mfma_body.
-__global__ __launch_bounds__(256) void wgrad_mfma_f32_tri_kernel(WgradProblem p0, WgradProblem p1, WgradProblem p2, int R,
-                                                                 int rows_per_wg) {
-  const WgradProblem& p = blockIdx.y == 0 ? p0 : blockIdx.y == 1 ? p1 : p2;
-  const float* __restrict__ A = p.A;
-  const float* __restrict__ G = p.G;
-  const long lda = p.lda, ldg = p.ldg;
-  const int lane = threadIdx.x & 63, c = lane & 31, h = lane >> 5;
-  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int bi = w >> 1, bj = w & 1;
-  const long row0 = (long)blockIdx.x * rows_per_wg;   // rows_per_wg is a multiple of 32
-  const int ca = min(bi * 32 + c, p.M - 1), cg = min(bj * 32 + c, p.N - 1);
-  const int la = h * (int)lda + ca, lg = h * (int)ldg + cg;
-  const bool full = row0 + rows_per_wg <= R;   // uniform: only the last rows of the matrix need the row test
-  f32x16s acc;
-#pragma unroll
-  for (int r = 0; r < 16; ++r) acc[r] = 0.f;
-  float a[4][4], g[4][4];   // [register set][contraction step of the group]
-  auto multiply = [&](const float (&av)[4], const float (&gv)[4]) {
-#pragma unroll
-    for (int u = 0; u < 4; ++u) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(av[u], gv[u], acc, 0, 0, 0);
-  };
-  // The whole loop exists twice, with and without the row test, and its last trip is peeled: no branch between a
-  // group's loads and its use, so the waits count exactly the loads requested after it.
-  auto run = [&](auto full_tag) {
-    constexpr bool FULL = decltype(full_tag)::value;
-    auto load = [&](int r, float (&av)[4], float (&gv)[4]) {
-      if constexpr (FULL) {
-        const float* pa = A + (row0 + r) * lda;
-        const float* pg = G + (row0 + r) * ldg;
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          av[u] = pa[2 * u * lda + la];
-          gv[u] = pg[2 * u * ldg + lg];
-        }
-      } else {
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {   // every load is issued, inside the matrix; rows past the end become zeros
-          const long row = row0 + r + 2 * u;
-          const long rc = row < R ? row : (long)R - 1;
-          const bool pair = row + 1 < R, ok = row + h < R;
-          const float va = A[rc * lda + (pair ? la : ca)];
-          const float vg = G[rc * ldg + (pair ? lg : cg)];
-          av[u] = ok ? va : 0.f;
-          gv[u] = ok ? vg : 0.f;
-        }
-      }
-    };
-    load(0, a[0], g[0]);
-    load(8, a[1], g[1]);
-    load(16, a[2], g[2]);
-    int r = 0;
-    for (; r + 32 < rows_per_wg; r += 32) {
-      load(r + 24, a[3], g[3]);
-      multiply(a[0], g[0]);
-      load(r + 32, a[0], g[0]);
-      multiply(a[1], g[1]);
-      load(r + 40, a[1], g[1]);
-      multiply(a[2], g[2]);
-      load(r + 48, a[2], g[2]);
-      multiply(a[3], g[3]);
-    }
-    load(r + 24, a[3], g[3]);
-    multiply(a[0], g[0]);
-    multiply(a[1], g[1]);
-    multiply(a[2], g[2]);
-    multiply(a[3], g[3]);
-  };
-  if (full) run(std::true_type{});
-  else run(std::false_type{});
-  float* dst = p.partial + (long)blockIdx.x * (4 * 16 * 64);
-#pragma unroll
-  for (int q = 0; q < 4; ++q)
-    *(float4*)(dst + (((bi * 2 + bj) * 4 + q) * 64 + lane) * 4) =
-        make_float4(acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]);
-}
-
-// out[m, n] = sum_z partial[z] (accumulator order, see above), z ascending in 16 interleaved groups that are then
-// added in a fixed order; column block s of n_per columns goes to o<s> (NULL = dropped) when n_per > 0.
-// A thread sums one accumulator QUAD (16 bytes: four rows of one column) of its share of the partial results, so
-// the 16 threads of a group read 256 contiguous bytes of every partial result; grid.x covers the quads of the
-// largest problem, 16 per workgroup.
-__global__ __launch_bounds__(256) void wgrad_mfma_reduce_kernel(WgradProblem p0, WgradProblem p1, WgradProblem p2, int nz) {
-  __shared__ float4 red[16][16];
-  const WgradProblem& p = blockIdx.y == 0 ? p0 : blockIdx.y == 1 ? p1 : p2;
-  const float4* __restrict__ partial = (const float4*)p.partial;
-  const int M = p.M, N = p.N, NB = (N + 31) / 32, nblk = ((M + 31) / 32) * NB, n_per = p.n_per;
-  const int o = threadIdx.x & 15, g = threadIdx.x >> 4;
-  const int nquad = nblk * 4 * 64;          // quads of one partial result: [block][register quad][lane]
-  const int i = blockIdx.x * 16 + o;
-  float4 s[4];
-#pragma unroll
-  for (int k = 0; k < 4; ++k) s[k] = make_float4(0.f, 0.f, 0.f, 0.f);
-  if (i < nquad) {
-    // eight partial results per trip, all requested (at an index inside the array) before the first is added
-    for (int z = g; z < nz; z += 128) {
-      float4 v[8];
-#pragma unroll
-      for (int k = 0; k < 8; ++k) v[k] = partial[(long)min(z + 16 * k, nz - 1) * nquad + i];
-#pragma unroll
-      for (int k = 0; k < 8; ++k) {
-        if (z + 16 * k < nz) {
-          float4& t = s[k & 3];
-          t.x += v[k].x; t.y += v[k].y; t.z += v[k].z; t.w += v[k].w;
-        }
-      }
-    }
-  }
-  red[g][o] = make_float4((s[0].x + s[1].x) + (s[2].x + s[3].x), (s[0].y + s[1].y) + (s[2].y + s[3].y),
-                          (s[0].z + s[1].z) + (s[2].z + s[3].z), (s[0].w + s[1].w) + (s[2].w + s[3].w));
-  __syncthreads();
-  if (g == 0 && i < nquad) {
-    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-#pragma unroll
-    for (int k = 0; k < 16; ++k) { v.x += red[k][o].x; v.y += red[k][o].y; v.z += red[k][o].z; v.w += red[k][o].w; }
-    // quad q of lane (c, h) in block (bi, bj): rows 32 bi + 8 q + 4 h + 0..3, column 32 bj + c
-    const int lane = i & 63, q = (i >> 6) & 3, blk = i >> 8, bi = blk / NB, bj = blk - bi * NB;
-    const int n = bj * 32 + (lane & 31), m0 = bi * 32 + 8 * q + 4 * (lane >> 5);
-    if (n < N) {
-      const float vv[4] = {v.x, v.y, v.z, v.w};
-      float* dst = p.o0;
-      long ld = N, col = n;
-      if (n_per > 0) {
-        const int gn = n + p.n_off;
-        dst = (gn / n_per == 0) ? p.o0 : (gn / n_per == 1) ? p.o1 : p.o2;
-        ld = n_per; col = gn % n_per;
-      }
-      if (dst) {
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-          if (m0 + j < M) dst[(long)(m0 + j) * ld + col] = vv[j];
-      }
-    }
-  }
-}
-
-static int wgrad_mfma_rows_per_wg(int R) {
-  // at most 1024 workgroups = partial results, and at least 128 rows each (measured at 29 600 rows, 40 x 120:
-  // 64 rows 22 us, 128 rows 17 us, 256 rows 25 us including the reduction); a multiple of 64: every wave then has
-  // a multiple of 16 rows = two groups of four steps per trip
-  const int rows = std::max((R + 1023) / 1024, 128);
-  return ((rows + 63) / 64) * 64;
-}
-bool wgrad_mfma_ok(int M, int N, int R, int in_bf16) { return !in_bf16 && M <= 64 && N <= 128 && R >= 1024; }
-size_t wgrad_mfma_partial_bytes(int M, int N, int R) {
-  const int rows = wgrad_mfma_rows_per_wg(R);
-  return (size_t)((R + rows - 1) / rows) * ((M + 31) / 32) * ((N + 31) / 32) * 16 * 64 * sizeof(float);
-}
-// Up to two gradients with 33..64 rows through wgrad_mfma_f32_tri_kernel: `a` (at most 128 columns; more than 64
-// only with column-block outputs) becomes one or two problems of at most 64 columns, `b` (optional, at most 64
-// columns) one more.  The partial results lie one problem after the other from `partial` on.  A gradient's bits do
-// not depend on what else the launch computes.
-static void launch_wgrad_mfma_f32_tri(const WgradProblem* a, const WgradProblem* b, int R, float* partial, hipStream_t st) {
-  // rows per workgroup: a multiple of 32, those of the layout that the workspace is sized for
-  const int rows3 = (wgrad_mfma_rows_per_wg(R) + 31) / 32 * 32;
-  const int blocks3 = (R + rows3 - 1) / rows3;
-  const long pstride = (long)blocks3 * 4 * 16 * 64;
-  WgradProblem ps[3];
-  int n = 0;
-  auto push = [&](const WgradProblem& src, int col0, int ncols) {
-    ps[n] = src;
-    ps[n].G = src.G + col0;
-    ps[n].N = ncols;
-    ps[n].n_off = col0;
-    ps[n].partial = partial + n * pstride;
-    ++n;
-  };
-  if (a->N > 64) { push(*a, 0, 64); push(*a, 64, a->N - 64); }
-  else push(*a, 0, a->N);
-  if (b) push(*b, 0, b->N);
-  for (int k = n; k < 3; ++k) ps[k] = ps[0];
-  hipLaunchKernelGGL(wgrad_mfma_f32_tri_kernel, dim3(blocks3, n), dim3(256), 0, st, ps[0], ps[1], ps[2], R, rows3);
-  hipLaunchKernelGGL(wgrad_mfma_reduce_kernel, dim3(4 * 16, n), dim3(256), 0, st, ps[0],
-                     ps[1], ps[2], blocks3);
-}
-// C[M, N] = A[R, M]^T G[R, N] into o0 (n_per == 0) or column blocks of n_per columns into o0 | o1 | o2
-void launch_wgrad_mfma_f32(const float* A, long lda, const float* G, long ldg, int R, int M, int N, float* partial,
-                           float* o0, float* o1, float* o2, int n_per, hipStream_t st) {
-  const int rows = wgrad_mfma_rows_per_wg(R);
-  const int blocks = (R + rows - 1) / rows;
-  const int MB = (M + 31) / 32, NB = (N + 31) / 32;
-  const WgradProblem p{A, lda, G, ldg, M, N, partial, o0, o1, o2, n_per};
-  if (MB == 2 && (N <= 64 || n_per > 0)) {
-    launch_wgrad_mfma_f32_tri(&p, nullptr, R, partial, st);
-    return;
-  }
-#define WM_LAUNCH(MBV, NBV) hipLaunchKernelGGL((wgrad_mfma_f32_kernel<MBV, NBV>), dim3(blocks), dim3(256), 0, st, p, R, rows)
-  if (MB == 1) {
-    if (NB == 1) WM_LAUNCH(1, 1); else if (NB == 2) WM_LAUNCH(1, 2); else if (NB == 3) WM_LAUNCH(1, 3); else WM_LAUNCH(1, 4);
-  } else {
-    if (NB == 1) WM_LAUNCH(2, 1); else if (NB == 2) WM_LAUNCH(2, 2); else if (NB == 3) WM_LAUNCH(2, 3); else WM_LAUNCH(2, 4);
-  }
-#undef WM_LAUNCH
-  hipLaunchKernelGGL(wgrad_mfma_reduce_kernel, dim3(MB * NB * 16, 1), dim3(256), 0, st, p, p, p, blocks);
-}
-// The two weight gradients of an attention block in one pair of launches:
-//   [dWq | dWk | dWv] = X^T [dQ | dK | dV]  (d x 3d, column blocks of d columns into q0 | q1 | q2, NULL = dropped)
-//   dWo               = O^T dY              (d x d)
-// partial: wgrad_mfma_partial_bytes(d, 3 d, R) + wgrad_mfma_partial_bytes(d, d, R) bytes.
-void launch_wgrad_mfma_f32_attn(const float* X, const float* dQKV, const float* O, const float* dY, int R, int d,
-                                float* partial, float* q0, float* q1, float* q2, float* dwo, hipStream_t st) {
-  const int MB = (d + 31) / 32, NB0 = (3 * d + 31) / 32;
-  if (MB == 2) {
-    const WgradProblem wide{X, d, dQKV, 3L * d, d, 3 * d, partial, q0, q1, q2, d, 0};
-    const WgradProblem wo{O, d, dY, d, d, d, nullptr, dwo, nullptr, nullptr, 0, 0};
-    launch_wgrad_mfma_f32_tri(&wide, &wo, R, partial, st);
-    return;
-  }
-  const int rows = wgrad_mfma_rows_per_wg(R);
-  const int blocks = (R + rows - 1) / rows;
-  float* partial1 = partial + wgrad_mfma_partial_bytes(d, 3 * d, R) / sizeof(float);
-  const WgradProblem p0{X, d, dQKV, 3L * d, d, 3 * d, partial, q0, q1, q2, d};
-  const WgradProblem p1{O, d, dY, d, d, d, partial1, dwo, nullptr, nullptr, 0};
-  const dim3 grid(blocks, 2), block(256);
-  if (NB0 == 3) hipLaunchKernelGGL((wgrad_mfma_f32_pair_kernel<1, 3, 1, 1>), grid, block, 0, st, p0, p1, R, rows);
-  else if (NB0 == 2) hipLaunchKernelGGL((wgrad_mfma_f32_pair_kernel<1, 2, 1, 1>), grid, block, 0, st, p0, p1, R, rows);
-  else hipLaunchKernelGGL((wgrad_mfma_f32_pair_kernel<1, 1, 1, 1>), grid, block, 0, st, p0, p1, R, rows);
-  hipLaunchKernelGGL(wgrad_mfma_reduce_kernel, dim3(MB * NB0 * 16, 2), dim3(256), 0, st, p0, p1, p1, blocks);
-}
-
 bool wgrad_small_ok(int M, int N, int n_per) {
   (void)n_per;
   return M >= 1 && M <= 64 && N >= 1 && N <= 256;
@@ -698,29 +320,22 @@ int wgrad_small_blocks(int R) {
 }
 size_t wgrad_small_partial_bytes(int M, int N, int R) { return (size_t)wgrad_small_blocks(R) * M * N * sizeof(float); }
 
-template <typename T, int TM>
-static void launch_wgrad_small_tn(const T* A, long lda, const T* G, long ldg, int R, int M, int N, float* partial, int blocks,
-                                  hipStream_t st) {
+template <int TM>
+static void launch_wgrad_small_tn(const bf16_t* A, long lda, const bf16_t* G, long ldg, int R, int M, int N, float* partial,
+                                  int blocks, hipStream_t st) {
   const int tn = (N + 31) / 32;
-  if (tn <= 2) hipLaunchKernelGGL((wgrad_small_kernel<T, TM, 2>), dim3(blocks), dim3(256), 0, st, A, lda, G, ldg, R, M, N, partial);
-  else if (tn <= 4) hipLaunchKernelGGL((wgrad_small_kernel<T, TM, 4>), dim3(blocks), dim3(256), 0, st, A, lda, G, ldg, R, M, N, partial);
-  else if (tn <= 6) hipLaunchKernelGGL((wgrad_small_kernel<T, TM, 6>), dim3(blocks), dim3(256), 0, st, A, lda, G, ldg, R, M, N, partial);
-  else hipLaunchKernelGGL((wgrad_small_kernel<T, TM, 8>), dim3(blocks), dim3(256), 0, st, A, lda, G, ldg, R, M, N, partial);
-}
-template <typename T>
-static void launch_wgrad_small_t(const T* A, long lda, const T* G, long ldg, int R, int M, int N, float* partial, int blocks,
-                                 hipStream_t st) {
-  const int tm = (M + 7) / 8;
-  if (tm <= 4) launch_wgrad_small_tn<T, 4>(A, lda, G, ldg, R, M, N, partial, blocks, st);
-  else if (tm <= 5) launch_wgrad_small_tn<T, 5>(A, lda, G, ldg, R, M, N, partial, blocks, st);
-  else launch_wgrad_small_tn<T, 8>(A, lda, G, ldg, R, M, N, partial, blocks, st);
+  if (tn <= 2) hipLaunchKernelGGL((wgrad_small_kernel<TM, 2>), dim3(blocks), dim3(256), 0, st, A, lda, G, ldg, R, M, N, partial);
+  else if (tn <= 4) hipLaunchKernelGGL((wgrad_small_kernel<TM, 4>), dim3(blocks), dim3(256), 0, st, A, lda, G, ldg, R, M, N, partial);
+  else if (tn <= 6) hipLaunchKernelGGL((wgrad_small_kernel<TM, 6>), dim3(blocks), dim3(256), 0, st, A, lda, G, ldg, R, M, N, partial);
+  else hipLaunchKernelGGL((wgrad_small_kernel<TM, 8>), dim3(blocks), dim3(256), 0, st, A, lda, G, ldg, R, M, N, partial);
 }
 // Writes wgrad_small_blocks(R) partial [M, N] matrices; returns that count (the number of partials to reduce).
-int launch_wgrad_small(const void* A, long lda, const void* G, long ldg, int R, int M, int N, int in_bf16, float* partial,
-                       hipStream_t st) {
-  const int blocks = wgrad_small_blocks(R);
-  if (in_bf16) launch_wgrad_small_t<bf16_t>((const bf16_t*)A, lda, (const bf16_t*)G, ldg, R, M, N, partial, blocks, st);
-  else launch_wgrad_small_t<float>((const float*)A, lda, (const float*)G, ldg, R, M, N, partial, blocks, st);
+int launch_wgrad_small(const void* A, long lda, const void* G, long ldg, int R, int M, int N, float* partial, hipStream_t st) {
+  const int blocks = wgrad_small_blocks(R), tm = (M + 7) / 8;
+  const bf16_t *a = (const bf16_t*)A, *g = (const bf16_t*)G;
+  if (tm <= 4) launch_wgrad_small_tn<4>(a, lda, g, ldg, R, M, N, partial, blocks, st);
+  else if (tm <= 5) launch_wgrad_small_tn<5>(a, lda, g, ldg, R, M, N, partial, blocks, st);
+  else launch_wgrad_small_tn<8>(a, lda, g, ldg, R, M, N, partial, blocks, st);
   return blocks;
 }
 
@@ -832,6 +447,8 @@ size_t colsum_partial_bytes(int R, int n) { return (size_t)((R + CS_ROWS - 1) / 
 // One launch for a list of second-stage sums (blockIdx.y = job).  A block is 16 output quads x 16 lanes over the
 // partials: lane zl adds partials zl, zl + 16, ... in ascending order, then the 16 lane sums are added in a fixed
 // order through LDS -- the same order as colsum_stage2 and the parallel split-K reduction use on their own.
+// ODD: some job's rows or column blocks are not whole quads.
+template <bool ODD>
 __global__ __launch_bounds__(256) void reduce_list_kernel(ReduceList l) {
   __shared__ float4 red[16][16];
   const ReduceJob& j = l.job[blockIdx.y];
@@ -845,12 +462,12 @@ __global__ __launch_bounds__(256) void reduce_list_kernel(ReduceList l) {
     for (; z + 48 < j.nparts; z += 64) {   // four requests in flight; added in the same ascending order
       float4 v[4];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) v[u] = *(const float4*)(j.partial + (z + 16 * u) * n_out + i);
+      for (int u = 0; u < 4; ++u) v[u] = *(const float4*)(j.partial + (z + 16 * u) * j.stride + i);
 #pragma unroll
       for (int u = 0; u < 4; ++u) { s.x += v[u].x; s.y += v[u].y; s.z += v[u].z; s.w += v[u].w; }
     }
     for (; z < j.nparts; z += 16) {
-      const float4 v = *(const float4*)(j.partial + z * n_out + i);
+      const float4 v = *(const float4*)(j.partial + z * j.stride + i);
       s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
     }
   }
@@ -861,30 +478,49 @@ __global__ __launch_bounds__(256) void reduce_list_kernel(ReduceList l) {
     const float4 v = red[k][ql];
     s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
   }
-  const int m = (int)(i / j.N), n = (int)(i % j.N);
-  float* o = j.o[0];
-  long at = i;
-  if (j.n_per > 0) {
-    const int sel = n / j.n_per;
-    o = sel == 0 ? j.o[0] : sel == 1 ? j.o[1] : j.o[2];
-    at = (long)m * j.n_per + n % j.n_per;
+  if (!ODD) {   // the quad lies in one row of one output
+    const int m = (int)(i / j.N), n = (int)(i % j.N);
+    float* o = j.o[0];
+    long at = i;
+    if (j.n_per > 0) {
+      const int sel = n / j.n_per;
+      o = sel == 0 ? j.o[0] : sel == 1 ? j.o[1] : j.o[2];
+      at = (long)m * j.n_per + n % j.n_per;
+    }
+    if (!o) return;
+    o[at] = s.x; o[at + 1] = s.y; o[at + 2] = s.z; o[at + 3] = s.w;   // caller pointers: no alignment assumed
+    return;
   }
-  if (!o) return;
-  o[at] = s.x; o[at + 1] = s.y; o[at + 2] = s.z; o[at + 3] = s.w;   // caller pointers: no alignment assumed
+  const float v[4] = {s.x, s.y, s.z, s.w};
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    if (i + u >= n_out) break;
+    const int m = (int)((i + u) / j.N), n = (int)((i + u) % j.N), sel = j.n_per > 0 ? n / j.n_per : 0;
+    float* const o = sel == 0 ? j.o[0] : sel == 1 ? j.o[1] : j.o[2];
+    if (o) o[j.n_per > 0 ? (long)m * j.n_per + n % j.n_per : i + u] = v[u];
+  }
 }
 bool reduce_deferrable(int M, int N, int nparts) {
   return N % 4 == 0 && (long)M * N <= 4L * 65536 && (long)M * N * nparts * 4 <= (8L << 20);
 }
-void reduce_push(ReduceList* l, const float* partial, int nparts, int M, int N, float* o0, float* o1, float* o2, int n_per) {
+void reduce_push(ReduceList* l, const float* partial, int nparts, int M, int N, float* o0, float* o1, float* o2, int n_per,
+                 long stride) {
   ReduceJob& j = l->job[l->n++];
+  j.stride = stride ? stride : (long)M * N;
   j.partial = partial; j.nparts = nparts; j.M = M; j.N = N; j.n_per = n_per;
   j.o[0] = o0; j.o[1] = o1; j.o[2] = o2;
 }
 void launch_reduce_list(const ReduceList& l, hipStream_t st) {
   if (l.n == 0) return;
   long mx = 0;
-  for (int i = 0; i < l.n; ++i) mx = std::max(mx, (long)l.job[i].M * l.job[i].N);
-  hipLaunchKernelGGL(reduce_list_kernel, dim3((unsigned)((mx + 63) / 64), l.n), dim3(256), 0, st, l);
+  bool odd = false;
+  for (int i = 0; i < l.n; ++i) {
+    mx = std::max(mx, (long)l.job[i].M * l.job[i].N);
+    odd = odd || l.job[i].N % 4 != 0 || l.job[i].n_per % 4 != 0;
+  }
+  const dim3 grid((unsigned)((mx + 63) / 64), l.n);
+  if (odd) hipLaunchKernelGGL(reduce_list_kernel<true>, grid, dim3(256), 0, st, l);
+  else hipLaunchKernelGGL(reduce_list_kernel<false>, grid, dim3(256), 0, st, l);
 }
 
 int launch_colsum_multi(const void* const* a, const long* lda, float* const* out, int count, int R, int n, int a_bf16,

@@ -207,4 +207,116 @@ void launch_gemm_split(const GemmDesc& g, hipStream_t st) {
 #undef GS_LAUNCH
 }
 
+// ---- weight gradients: C[M, N] = A[R, M]^T G[R, N], and the column sums of G (the bias gradient beside it) ----
+// The contraction runs over the rows and the operands are read as they lie in memory: lane (c = lane % 32, h) takes
+// column c of rows 8 h .. 8 h + 7 of a 16-row step, 128 contiguous bytes per half wave and request.  A workgroup owns a
+// 64 x 64 tile of C (blockIdx.y) over its rows (blockIdx.x): each wave requests and splits one 32-column block of A or
+// G, the parts meet in LDS in operand order, and a wave multiplies one 32 x 32 block of C.  Partial results leave in
+// row-major order and are summed in a fixed order by the reduction list.  Several gradients over the same rows share a
+// launch (blockIdx.z).
+// Bound: memory for the tall inputs (29 600 rows, [dWq|dWk|dWv] and dWo of d = 40: 28 MB read, 6 MB of partial results
+// written, 12.9 us at 4.8 TB/s of copy rate plus a launch; fp32 matrix instructions: 16.5 us.  33 600 rows, all four
+// gradients of an encoder layer of 40 x 160: 28 us, the vector-ALU kernel took 38 us each for the two of the MLP; the
+// bias gradients cost nothing).  At a few thousand rows a workgroup's chain of steps, 0.5 us each, and the launch: 2850
+// rows 5 us (8.2), 9600 rows 7.5 us (6.3, with 75 longer workgroups whose bias gradients were another pair of launches).
+// More steps in flight did not help: the chain is splitting, LDS and matrix instructions, not the requests.
+__global__ __launch_bounds__(256, 4) void wgrad_split_kernel(WgradSplitList l) {
+  __shared__ u32x4 frag[2][4][3][64];   // [step parity][A block 0, 1, G block 0, 1][part][lane]
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lo = lane & 31, h = lane >> 5;
+  const WgradSplit& p = l.p[blockIdx.z];
+  const int tm = p.tn_magic ? __umulhi(blockIdx.y, p.tn_magic) : blockIdx.y, tn = blockIdx.y - tm * ((p.N + 63) >> 6);
+  if (tm * 64 >= p.M) return;
+  // this wave's share of the operands: a 32-column block of A (waves 0, 1) or G (2, 3); and its block of C
+  const bool is_g = wave >= 2;
+  const int ld = (int)(is_g ? p.ldg : p.lda), width = is_g ? p.N : p.M, x0 = (is_g ? tn : tm) * 64 + (wave & 1) * 32;
+  const int m0 = tm * 64 + (wave & 1) * 32, n0 = tn * 64 + (wave >> 1) * 32;
+  const bool stage = x0 < width, mine = m0 < p.M && n0 < p.N;
+  const int r0 = blockIdx.x * l.rows, nrows = min(l.rows, l.R - r0), nst = (nrows + 15) >> 4;
+  const float* const X = (is_g ? p.G : p.A) + (long)r0 * ld;
+  const int col = min(x0 + lo, width - 1);
+  const unsigned off = 8 * h * ld + col;
+  f32x16 big, rest;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) big[r] = rest[r] = 0.f;
+  float cs = 0.f, v[8];
+  auto load = [&](int s) {
+    if (16 * s + 16 <= nrows) {   // a whole step: row addresses are scalar, the lane adds a fixed offset
+#pragma unroll
+      for (int e = 0; e < 8; ++e) v[e] = (X + (long)(16 * s + e) * ld)[off];
+    } else {   // the matrix's last rows: rows past the end are read again (and dropped when split)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) v[e] = X[(long)min(16 * s + 8 * h + e, nrows - 1) * ld + col];
+    }
+  };
+  if (stage) load(0);
+  for (int s = 0; s < nst; ++s) {
+    if (stage) {
+      if (16 * s + 16 > nrows)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] = 16 * s + 8 * h + e < nrows ? v[e] : 0.f;
+      bf16x8 q[3];
+      cs += ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
+      split_parts8(v, q);
+#pragma unroll
+      for (int k = 0; k < 3; ++k) frag[s & 1][wave][k][lane] = __builtin_bit_cast(u32x4, q[k]);
+      if (s + 1 < nst) load(s + 1);
+    }
+    __syncthreads();   // one per step: the other parity's readers have passed it
+    if (mine) {
+      bf16x8 pa[3], pg[3];
+#pragma unroll
+      for (int k = 0; k < 3; ++k) {
+        pa[k] = as_bf16x8(frag[s & 1][wave & 1][k][lane]);
+        pg[k] = as_bf16x8(frag[s & 1][2 + (wave >> 1)][k][lane]);
+      }
+      mfma32_split(pa, pg, big, rest);
+    }
+  }
+  if (p.csum && is_g && tm == 0 && x0 + lo < p.N) {
+    cs += __shfl_xor(cs, 32);
+    if (h == 0) p.csum[(long)blockIdx.x * ((p.N + 3) & ~3) + x0 + lo] = cs;
+  }
+  const int n = n0 + lo;
+  if (!p.partial || m0 >= p.M || n >= p.N) return;
+  float* const out = p.partial + (long)blockIdx.x * p.stride + n;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    const int m = m0 + 8 * (r >> 2) + 4 * h + (r & 3);
+    if (m < p.M) out[m * p.N] = big[r] + rest[r];
+  }
+}
+
+// rows per workgroup: about 224 partial results, so that a reduction reads what a few hundred workgroups wrote
+static int wgrad_split_rows(int R) {
+  const int rows = ((R + 223) / 224 + 15) & ~15;
+  return rows < 32 ? 32 : rows;
+}
+static int wgrad_split_parts(int R) { const int rows = wgrad_split_rows(R); return (R + rows - 1) / rows; }
+size_t wgrad_split_bytes(int M, int N, int R) {
+  return (size_t)wgrad_split_parts(R) * (((long)M * N + 3) / 4 * 4 + (N + 3) / 4 * 4) * sizeof(float);
+}
+void wgrad_split_push(WgradSplitList* l, ReduceList* red, const float* A, long lda, const float* G, long ldg, int R, int M, int N,
+                      float* partial, int n_per, float* w0, float* w1, float* w2, float* b0, float* b1, float* b2) {
+  const bool w = w0 || w1 || w2, b = b0 || b1 || b2;
+  if (!w && !b) return;
+  WgradSplit& p = l->p[l->n++];
+  const int parts = wgrad_split_parts(R);
+  p.A = A; p.G = G; p.lda = lda; p.ldg = ldg; p.M = M; p.N = N;
+  p.stride = (int)(((long)M * N + 3) / 4 * 4);
+  p.partial = w ? partial : nullptr;
+  p.csum = b ? partial + (long)parts * p.stride : nullptr;
+  const unsigned tn = (N + 63) / 64, tiles = (M + 63) / 64 * tn;
+  p.tn_magic = tn == 1 ? 0u : (unsigned)(((1ull << 32) + tn - 1) / tn);   // t / tn = mulhi(t, magic) for t tn < 2^32; 0: tn is 1
+  l->tiles = l->tiles > (int)tiles ? l->tiles : (int)tiles;
+  l->R = R;
+  l->rows = wgrad_split_rows(R);
+  if (w) reduce_push(red, p.partial, parts, M, N, w0, w1, w2, n_per, p.stride);
+  if (b) reduce_push(red, p.csum, parts, 1, N, b0, b1, b2, n_per, (N + 3) / 4 * 4);
+}
+void launch_wgrad_split(const WgradSplitList& l, hipStream_t st) {
+  if (l.n == 0) return;
+  hipLaunchKernelGGL(wgrad_split_kernel, dim3((l.R + l.rows - 1) / l.rows, l.tiles, l.n), dim3(256), 0, st, l);
+}
+
 }  // namespace imattn

@@ -6,7 +6,7 @@ import torch
 
 import oracle
 from paper_2505_01068_amd import binding as B, synth
-from tests.gpu_util import TOL, assert_close, to_dev
+from tests.gpu_util import TOL, assert_close, grad_scale, to_dev
 
 pytestmark = pytest.mark.gpu
 
@@ -24,3 +24,33 @@ def test_layer_products(d, H, d_ff, batch, seg):
     y = B.gsit_layer_fwd(shape, d_ff, to_dev(g["x"], "fp32"), {k: to_dev(v, "fp32") for k, v in p.items()}, workspace=ws)
     torch.cuda.synchronize()
     assert_close(y, oracle.gsit_layer_forward(g["x"], p, seg, lm, H, g["scale"]), TOL["fp32"], f"layer d={d} d_ff={d_ff}")
+
+
+@pytest.mark.parametrize("d,H,d_ff", [(8, 1, 24), (40, 8, 160), (64, 8, 256), (33, 3, 70), (42, 7, 161)])
+@pytest.mark.parametrize("batch,seg", [(1, (1, 3, 2)), (3, (11, 9, 13)), (5, (40, 31, 30))])   # 6, 99 and 505 rows
+def test_layer_weight_gradients(d, H, d_ff, batch, seg):
+    # 32-row workgroups with whole, partial and single 16-row steps; blocks and quads that end inside a row
+    print(f"[case] fp32 weight gradients d={d} d_ff={d_ff} rows={batch * sum(seg)}", flush=True)
+    g = synth.attention_inputs(batch, seg, d, H, "fp32", "none", seed=811)
+    p = synth.layer_params(d, d_ff, 811, 0, dtype="fp32")
+    lm = oracle.IM_IFM_FORWARD
+    shape = B.make_shape(batch, seg, d, H, lm, g["scale"], "fp32")
+    sb, wb = B.gsit_layer_train_sizes(shape, d_ff)
+    saved, ws = (torch.empty(n, dtype=torch.uint8, device="cuda") for n in (sb, wb))
+    x, dy, pd = to_dev(g["x"], "fp32"), to_dev(g["dy"], "fp32"), {k: to_dev(v, "fp32") for k, v in p.items()}
+    B.gsit_layer_fwd_train(shape, d_ff, x, pd, saved, workspace=ws)
+    grads = {k: torch.empty(v.shape, dtype=torch.float32, device="cuda") for k, v in pd.items()}
+    dx = B.gsit_layer_bwd(shape, d_ff, x, pd, saved, dy, grads, workspace=ws)
+    torch.cuda.synchronize()
+    ref = oracle.gsit_layer_backward(g["x"], p, g["dy"], seg, lm, H, g["scale"])
+    floor = 2.0 ** -23 * max(float(abs(v).max()) for k, v in ref.items() if k != "attn_dk")
+    dk_sum = abs(ref["attn_dk"]).sum(axis=(0, 1)).max()
+    assert_close(dx, ref["dx"], TOL["fp32"], "dx")
+    for n, v in grads.items():
+        assert_close(v, ref["d" + n], TOL["fp32"], "d" + n, grad_scale(n, ref["d" + n], floor, dk_sum))
+    # a gradient's bits do not depend on which others are asked for
+    for want in (("w1",), ("b1", "bq"), ("wk", "bo", "w2")):
+        some = {k: torch.full_like(grads[k], float("nan")) for k in want}
+        B.gsit_layer_bwd(shape, d_ff, x, pd, saved, dy, some, workspace=ws)
+        for k in want:
+            assert torch.equal(some[k], grads[k]), k
