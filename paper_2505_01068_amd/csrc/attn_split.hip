@@ -90,9 +90,9 @@ __device__ __forceinline__ void step_pos(int t, int& blk, int& m) {
 }
 
 // Score operand of one row: slot s = DH term + column holds part {0,0,0,1,1,2}[term] on the query side and
-// {0,1,2,0,1,0}[term] on the key side; slot 6 DH holds `mask`.
+// {0,1,2,0,1,0}[term] on the key side; slot 6 DH holds `mask`.  neg: the row enters with the other sign.
 template <int DH, bool QSIDE>
-__device__ __forceinline__ void store_score_row(u32x4* S, int blk, int m, const float (&p)[3][DH], float mask) {
+__device__ __forceinline__ void store_score_row(u32x4* S, int blk, int m, const float (&p)[3][DH], float mask, bool neg = false) {
   using C = SplitCfg<DH>;
   constexpr int QP[6] = {0, 0, 0, 1, 1, 2}, KP[6] = {0, 1, 2, 0, 1, 0};
 #pragma unroll
@@ -106,7 +106,7 @@ __device__ __forceinline__ void store_score_row(u32x4* S, int blk, int m, const 
         const int s = 8 * q + 2 * i + k;
         v[k] = s < 6 * DH ? p[QSIDE ? QP[s / DH] : KP[s / DH]][s % DH] : s == 6 * DH ? mask : 0.f;
       }
-      w[i] = top_pair(v[0], v[1]);
+      w[i] = top_pair(v[0], v[1]) ^ (neg ? 0x80008000u : 0u);
     }
     S[blk * C::BLK + (q >> 2) * 64 + (q & 3) * 16 + m] = w;
   }
@@ -117,9 +117,11 @@ __device__ __forceinline__ bf16x8 score_frag(const u32x4* S, int blk, int s, int
 }
 
 // Transposed operand of one row: column r of the row's 16 NTB columns holds part r / DH of head column r % DH, column
-// 3 DH the value one (ONES).  Stored [step][16-column block][32 rows][16]; read back transposed.
+// 3 DH the value one (ONES).  Stored [step][16-column block][32 rows][16]; read back transposed.  The rows of odd steps
+// are stored with the other sign (see accumulate_tr), those with neg once more.
 template <int DH, int NTB, bool ONES>
-__device__ __forceinline__ void store_tr_row(bf16_t* Tr, int blk, int m, const float (&p)[3][DH]) {
+__device__ __forceinline__ void store_tr_row(bf16_t* Tr, int blk, int m, const float (&p)[3][DH], bool neg = false) {
+  const unsigned flip = neg != ((blk & 2) != 0) ? 0x80008000u : 0u;
 #pragma unroll
   for (int q = 0; q < 2 * NTB; ++q) {
     u32x4 w;
@@ -131,7 +133,7 @@ __device__ __forceinline__ void store_tr_row(bf16_t* Tr, int blk, int m, const f
         const int r = 8 * q + 2 * i + k;
         v[k] = r < 3 * DH ? p[r / DH][r % DH] : (ONES && r == 3 * DH) ? 1.f : 0.f;
       }
-      w[i] = top_pair(v[0], v[1]);
+      w[i] = top_pair(v[0], v[1]) ^ flip;
     }
     *(u32x4*)(Tr + ((((blk >> 1) * NTB + (q >> 1)) * 32 + (blk & 1) * 16 + m) << 4) + (q & 1) * 8) = w;
   }
@@ -173,7 +175,10 @@ __host__ __device__ constexpr bool tr_needed(int k, int rb, bool ones) {
 }
 // acc += the step's product.  The three parts' instructions start from zero and the step's sum is added with a rounding to
 // nearest: the instruction itself rounds towards minus infinity (by 0.7 of a unit of its largest addend on average,
-// measured), which a long accumulator would collect three times per step.
+// measured), which a long accumulator would collect three times per step.  What the step's own products lose that way has
+// one sign too, and the bias gradients add it over all rows: odd steps multiply the operand with the other sign and are
+// subtracted, which turns the rounding around (the dQ and dK/dV kernels do the same to dP between odd and even query
+// rows).  Without, dbq was off by 2.4e-6 at 20 x 39/480/461 rows.
 template <int DH, int NTB, bool ONES>
 __device__ __forceinline__ void accumulate_tr(const bf16_t* Tr, int st, const bf16x8 (&b)[3], f32x4 (&acc)[NTB], int lane) {
 #pragma unroll
@@ -183,7 +188,8 @@ __device__ __forceinline__ void accumulate_tr(const bf16_t* Tr, int st, const bf
 #pragma unroll
     for (int k = 2; k >= 0; --k)
       if (tr_needed<DH>(k, rb, ONES && rb == NTB - 1)) x = mfma16(a, b[k], x);
-    acc[rb] += x;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) acc[rb][i] = fmaf(x[i], (st & 1) ? -1.f : 1.f, acc[rb][i]);
   }
 }
 
@@ -448,7 +454,7 @@ void split_fwd_kernel(SplitGeo g, int tile_base, const T* __restrict__ Q, const 
 
 // dQ (and delta = rowsum(dO * O)): own rows are queries, keys are streamed.
 // delta comes from the matrix cores with the operand order of dP = dO V^T, so that a row with a single key (O = V bit
-// for bit) has dP - delta = 0 exactly.
+// for bit) has dP - delta = 0 exactly.  Odd query rows carry -dO: their dP, delta (stored so) and dS have the other sign.
 template <typename T, int DH, bool EXACT>
 __global__ __launch_bounds__(256, DH > 5 ? 2 : 4)
 void split_dq_kernel(SplitGeo g, int tile_base, const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ V,
@@ -506,7 +512,8 @@ void split_dq_kernel(SplitGeo g, int tile_base, const T* __restrict__ Q, const T
 #pragma unroll
     for (int e = 0; e < DH; ++e) raw[e] = wave == 2 ? raw[e] : raw[e] * g.scale_log2e;
     split_rows<DH>(raw, part);
-    store_score_row<DH, true>(sOwn + (wave == 2 ? S_UNITS : 0), lane >> 4, lane & 15, part, wave == 2 ? 0.f : 1.f);
+    store_score_row<DH, true>(sOwn + (wave == 2 ? S_UNITS : 0), lane >> 4, lane & 15, part, wave == 2 ? 0.f : 1.f,
+                              wave == 2 && (lane & 1));
     if (wave == 3 && !O_LATE) {
       split_rows<DH>(raw2, part);
       store_score_row<DH, false>(sOwn + O_AT, lane >> 4, lane & 15, part, 0.f);
@@ -585,7 +592,7 @@ void split_dq_kernel(SplitGeo g, int tile_base, const T* __restrict__ Q, const T
 #pragma unroll
     for (int i = 0; i < (DH + 3) / 4; ++i) {
       const int e = (lane >> 4) + 4 * i;
-      if (e < dh) stf(o + e, part_sum<DH, NTB>(X, n, e) * g.scale);
+      if (e < dh) stf(o + e, part_sum<DH, NTB>(X, n, e) * ((row & 1) ? -g.scale : g.scale));
     }
   }
 }
@@ -636,8 +643,9 @@ void split_dkv_kernel(SplitGeo g, int tile_base, const T* __restrict__ Q, const 
       split_rows<DH>(raw, part);
       int blk, mm;
       step_pos(lane, blk, mm);
-      store_score_row<DH, true>(buf + (wave ? S_UNITS : 0), blk, mm, part, wave ? 0.f : 1.f);
-      store_tr_row<DH, NTB, false>((bf16_t*)(buf + 2 * S_UNITS + (wave ? T_UNITS : 0)), blk, mm, part);
+      // odd query rows: -dO (and -delta from the dQ kernel) give -dS, which meets -Q; dV takes dO as it is
+      store_score_row<DH, true>(buf + (wave ? S_UNITS : 0), blk, mm, part, wave ? 0.f : 1.f, wave && (lane & 1));
+      store_tr_row<DH, NTB, false>((bf16_t*)(buf + 2 * S_UNITS + (wave ? T_UNITS : 0)), blk, mm, part, !wave && (lane & 1));
       ((float*)(buf + STAT_AT))[(wave ? SPLIT_ROWS : 0) + blk * 16 + mm] =
           wave ? (in ? stat : 0.f) : (in && stat != IM_NEG_INF) ? -stat : IM_NEG_INF;
     }

@@ -50,3 +50,27 @@ def test_moving_reference():
     for s0, n in ((0, 40), (40, 200), (240, 130)):
         g["x"][:, s0:s0 + n] *= np.linspace(0.05, 3.0, n, dtype=np.float32)[None, :, None]
     Problem(g, oracle.IM_IFM_FORWARD).check(what="split/growing")
+
+
+def test_bias_gradients_collect_no_rounding():
+    # dbq and dbv add dQ and dV over 19 600 rows.  A rounding to nearest per row is 6e-8 times the square root of the number
+    # of rows against a sum that grows the same way: the 2-norm error stays a few 1e-7.  A rounding with one sign grows with
+    # the number of rows itself; the bar of 1.4e-6 lies between (measured 9.1e-7 and 2.4e-6 at this shape).
+    say("[case] split attention, bias gradients of many rows")
+    seg, d, H, batch = (39, 480, 461), 32, 4, 20
+    g = synth.attention_inputs(batch, seg, d, H, "fp32", "valid_len", seed=761, bias=True)
+    pr = Problem(g, oracle.NAMED_PATTERNS["structure3_a"])
+    pr.fwd()
+    grads = pr.bwd()
+    ref = {"dbq": 0.0, "dbv": 0.0}
+    for b0 in range(0, batch, 4):   # the dense oracle walks the batch four elements at a time
+        sl = slice(b0, b0 + 4)
+        _, cache = oracle.forward(g["x"][sl], g["wq"], g["wk"], g["wv"], g["wo"], seg, pr.lm, H, g["scale"], bq=g["bq"], bk=g["bk"],
+                                  bv=g["bv"], bo=g["bo"], valid_len=g["valid_len"][sl], return_cache=True)
+        part = oracle.backward(cache, g["dy"][sl])
+        for k in ref:
+            ref[k] = ref[k] + part[k]
+    for k, r in ref.items():
+        err = np.linalg.norm(grads[k].double().cpu().numpy() - r) / np.linalg.norm(r)
+        say(f"    {k} {err:.1e}")
+        assert err < 1.4e-6, (k, err)
