@@ -399,6 +399,216 @@ __global__ __launch_bounds__(256, 3) void mfma_gemm_pair_kernel(MGemm p) {
 }
 
 // ------------------------------------------------------------------------------------------
+// Row-major A, 64 x 128 or 128 x 128 tiles whose operands come through an asynchronous global->LDS ring.
+//
+// The launches of a width-256 layer (8 400 rows: 33 to 132 tiles of 256 x 256) hold too few large tiles for 256 CUs,
+// and in the register-staged kernel above a workgroup that is alone on its CU waits a memory round trip per 64-deep
+// k-tile.  Here two stages of 24 KB (MB = 1, 64 rows) resp. 32 KB (MB = 2, 128 rows) leave room for three resp. two
+// workgroups per CU, one stage is in flight while the other is multiplied, and one barrier separates stages.  The
+// output leaves through LDS as fp32 (GELU, GELU' and the residual act on unrounded sums), eight lanes to a
+// 128-byte row segment, and the residual is read in the same coalesced form.
+// Row-major tiles: 128-byte rows, chunk c of row r at c ^ sw_f(r); k-major tile [64][16 chunks]: chunk c of row k at
+// c ^ ((k & 3) << 2).  k order and rounding are those of the kernel above: results are bit for bit the same.
+// Measured against the better of the two kernels it replaced here: 8 400 x 256 x 1024 + residual 33.8 -> 13.6 us,
+// 8 400 x 256 x 256 + residual 18.7 -> 7.1, 8 400 x 1024 x 256 with GELU' 23.6 -> 15.7, 29 600 x 64 x 256 + residual
+// 10.3 -> 7.2, 4 000 x 512 x 2048 + residual 55 -> 21, 16 000 x 1536 x 512 41 -> 36.  Three, four or six stages (one or two
+// workgroups per CU instead of two or three) were slower in every shape: resident waves hide more than deeper rings.
+constexpr int RK = 64;
+constexpr int ring_stage_bytes(int mb) { return (64 * mb + GN) * RK * 2; }
+constexpr int ring_lds_bytes(int mb) { return 2 * ring_stage_bytes(mb); }
+
+template <bool BKM, bool EPI, int MB>
+__global__ __launch_bounds__(256, 2) void mfma_gemm_ring_kernel(MGemm p) {
+  extern __shared__ __attribute__((aligned(1024))) bf16_t smem[];
+  constexpr int ROWS = 64 * MB, STB = ring_stage_bytes(MB);
+  constexpr int CA = 2 * MB, CB = 4;   // 16-byte chunks per thread, operand and stage
+  const int tid = threadIdx.x, lane = tid & 63, lo = lane & 31, hi = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave >> 1, wn = wave & 1;
+  int bx, by, bz;
+  xcd_block_index(bx, by, bz);
+  const int m0 = by * ROWS, n0 = bx * GN;
+  const int n_it = p.K / RK;   // K % 64 == 0 is required by the launcher
+
+  const bf16_t* ga[CA];
+  const bf16_t* gb[CB];   // k-major B: source pointer
+  long gboff[CB];         // m-major B: offset inside one matrix (K may be split over B[])
+#pragma unroll
+  for (int j = 0; j < CA; ++j) {
+    const int slot = (wave * CA + j) * 64 + lane, r = slot >> 3, c = (slot & 7) ^ sw_f(r);
+    ga[j] = p.A + (long)min(m0 + r, p.M - 1) * p.lda + c * 8;
+  }
+#pragma unroll
+  for (int j = 0; j < CB; ++j) {
+    const int slot = (wave * CB + j) * 64 + lane;
+    if (BKM) {
+      const int k = slot >> 4, c = (slot & 15) ^ ((k & 3) << 2);
+      const int col = min(n0 + c * 8, p.N - 8);
+      const bf16_t* mat = p.B[0];
+      int cc = col;
+      if (p.b_nper > 0) {
+        const int bi = (col >= p.b_nper) + (col >= 2 * p.b_nper);
+        mat = bi == 0 ? p.B[0] : bi == 1 ? p.B[1] : p.B[2];
+        cc = col - bi * p.b_nper;
+      }
+      gb[j] = mat + (long)k * p.ldb + cc;
+      gboff[j] = 0;
+    } else {
+      const int r = slot >> 3, c = (slot & 7) ^ sw_f(r);
+      gb[j] = nullptr;
+      gboff[j] = (long)min(n0 + r, p.N - 1) * p.ldb + c * 8;
+    }
+  }
+  auto issue = [&](int it) {
+    char* base = (char*)smem + (it & 1) * STB;
+#pragma unroll
+    for (int j = 0; j < CA; ++j) dma16(ga[j] + (long)it * RK, base + (wave * CA + j) * 1024);
+    const bf16_t* mat = p.B[0];
+    int kk = it * RK;
+    if (!BKM && p.b_kper > 0) {
+      const int bi = (kk >= p.b_kper) + (kk >= 2 * p.b_kper);
+      mat = bi == 0 ? p.B[0] : bi == 1 ? p.B[1] : p.B[2];
+      kk -= bi * p.b_kper;
+    }
+#pragma unroll
+    for (int j = 0; j < CB; ++j)
+      dma16(BKM ? gb[j] + (long)it * RK * p.ldb : mat + gboff[j] + kk, base + ROWS * RK * 2 + (wave * CB + j) * 1024);
+  };
+
+  issue(0);
+  f32x16 acc[2][MB];   // [n block][m block], registers 4i..4i+3 = columns n = 8i + 4hi + 0..3; start at the bias
+  {
+    int nq[8];
+    float bq[8][4];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) nq[q] = n0 + wn * 64 + (q >> 2) * 32 + 8 * (q & 3) + 4 * hi;
+    bias4_many<8>(p, p.bias, nq, bq);
+#pragma unroll
+    for (int q = 0; q < 8; ++q)
+#pragma unroll
+      for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+        for (int jj = 0; jj < 4; ++jj) acc[q >> 2][mb][4 * (q & 3) + jj] = bq[q][jj];
+  }
+  // this lane's transpose-read offset inside the k-major tile (k-step and second half are constants on top)
+  const int tj = lane & 15, tg = lane >> 4;
+  const int tkr = 8 * (tg >> 1) + (tj >> 2);
+  int offT[2];
+#pragma unroll
+  for (int x = 0; x < 2; ++x) {
+    const int col = wn * 64 + x * 32 + 16 * (tg & 1) + 4 * (tj & 3);
+    offT[x] = (tkr * 16 + ((col >> 3) ^ ((tkr & 3) << 2))) * 16 + (col & 7) * 2;
+  }
+  for (int it = 0; it < n_it; ++it) {
+    // stage `it` has landed, and (past the barrier) every wave is done with the stage the next copies overwrite
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    if (it + 1 < n_it) issue(it + 1);
+    const char* st = (const char*)smem + (it & 1) * STB;
+    const bf16_t* sA = (const bf16_t*)st;
+    const char* sB = st + ROWS * RK * 2;
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      bf16x8 fa[MB], fb[2];
+#pragma unroll
+      for (int x = 0; x < MB; ++x) fa[x] = lds_frag_sw(sA, wm * 32 * MB + x * 32, lo, s * 2 + hi);
+#pragma unroll
+      for (int x = 0; x < 2; ++x) {
+        if (BKM) {
+          typedef v4i16 __attribute__((address_space(3))) * lds_v4_ptr;
+          union { v4i16 h[2]; bf16x8 v; } f;
+          f.h[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4_ptr)(sB + offT[x] + s * 4096));
+          f.h[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4_ptr)(sB + offT[x] + s * 4096 + 1024));
+          fb[x] = f.v;
+        } else {
+          fb[x] = lds_frag_sw((const bf16_t*)sB, wn * 64 + x * 32, lo, s * 2 + hi);
+        }
+      }
+#pragma unroll
+      for (int nb = 0; nb < 2; ++nb)
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) acc[nb][mb] = mfma32(fb[nb], fa[mb], acc[nb][mb]);
+    }
+  }
+
+  // ---- epilogue: 32 rows x 64 columns at a time through the wave's own share of the idle ring ----
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  __builtin_amdgcn_s_barrier();   // every wave has finished reading the last stage
+  asm volatile("" ::: "memory");
+  constexpr int EP_LD = 68;       // floats per staged row
+  static_assert(4 * 32 * EP_LD * 4 <= ring_lds_bytes(MB), "the four staging areas lie in the ring");
+  float* stg = (float*)smem + wave * (32 * EP_LD);
+  const int row8 = lane >> 3, n = n0 + wn * 64 + (lane & 7) * 8;
+  const float cs = (p.scale0_on && n < p.n_per) ? p.scale0 : 1.f;   // n_per % 8 == 0 is required by the launcher then
+#pragma unroll
+  for (int mb = 0; mb < MB; ++mb) {
+    const int mr = m0 + wm * 32 * MB + mb * 32 + row8;
+    u32x4 rv[4];
+    if constexpr (EPI) {
+      if (p.res) {
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+          rv[t] = *(const u32x4*)(p.res + (long)min(mr + 8 * t, p.M - 1) * p.ldc + min(n, p.N - 8));
+      }
+    }
+#pragma unroll
+    for (int nb = 0; nb < 2; ++nb)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        *(float4*)(stg + lo * EP_LD + nb * 32 + 8 * i + 4 * hi) =
+            make_float4(acc[nb][mb][4 * i], acc[nb][mb][4 * i + 1], acc[nb][mb][4 * i + 2], acc[nb][mb][4 * i + 3]);
+    // the wave's LDS accesses execute in order; the compiler must keep them so across lanes
+    asm volatile("" ::: "memory");
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      const float4 a = *(const float4*)(stg + (row8 + 8 * t) * EP_LD + (lane & 7) * 8);
+      const float4 b = *(const float4*)(stg + (row8 + 8 * t) * EP_LD + (lane & 7) * 8 + 4);
+      float v[8] = {a.x * cs, a.y * cs, a.z * cs, a.w * cs, b.x * cs, b.y * cs, b.z * cs, b.w * cs};
+      const bool in = mr + 8 * t < p.M && n < p.N;   // N % 8 == 0
+      bf16_t* const out = p.C + (long)(mr + 8 * t) * p.ldc + n;
+      if constexpr (EPI) {
+        if (p.gelu == MGEMM_GELU_BOTH) {   // C = the pre-activation, C2 = GELU of it as rounded
+          u32x4 pre, act;
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            pre[q] = pack_bf16(v[2 * q], v[2 * q + 1]);
+            act[q] = pack_bf16(gelu_erf_f(__uint_as_float(pre[q] << 16)), gelu_erf_f(__uint_as_float(pre[q] & 0xffff0000u)));
+          }
+          if (in) {
+            *(u32x4*)out = pre;
+            *(u32x4*)(p.C2 + (long)(mr + 8 * t) * p.ldc + n) = act;
+          }
+          continue;
+        }
+        if (p.gelu == MGEMM_GELU_GRAD) {
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            v[2 * q] *= gelu_grad_f(__uint_as_float(rv[t][q] << 16));
+            v[2 * q + 1] *= gelu_grad_f(__uint_as_float(rv[t][q] & 0xffff0000u));
+          }
+        } else {
+          if (p.gelu) {
+#pragma unroll
+            for (int q = 0; q < 8; ++q) v[q] = gelu_erf_f(v[q]);
+          }
+          if (p.res) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+              v[2 * q] += __uint_as_float(rv[t][q] << 16);
+              v[2 * q + 1] += __uint_as_float(rv[t][q] & 0xffff0000u);
+            }
+          }
+        }
+      }
+      const u32x4 pk = {pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3]), pack_bf16(v[4], v[5]), pack_bf16(v[6], v[7])};
+      if (in) *(u32x4*)out = pk;
+    }
+    asm volatile("" ::: "memory");   // the next block's writes stay behind these reads
+  }
+}
+
+// ------------------------------------------------------------------------------------------
 // Q|K|V projection of narrow models (d = 64 or 128), optionally with the LayerNorm of the input rows inside.
 //
 // At these widths the whole problem is a few hundred rows per CU and the 128 x 128 tile kernel spends its time
@@ -589,7 +799,7 @@ typedef __attribute__((address_space(3))) void* lds_void_ptr;
 typedef const __attribute__((address_space(1))) void* glb_void_ptr;
 
 // NWV waves per workgroup: 8 (each wave 128 x 64, two waves per SIMD) or 4 (each wave 128 x 128, one wave per SIMD).
-template <bool AKM, bool BKM, bool EPI, int NWV>
+template <bool AKM, bool BKM, int NWV>
 __global__ __launch_bounds__(NWV * 64) void mfma_gemm_dma_kernel(MGemm p) {
   extern __shared__ __attribute__((aligned(1024))) bf16_t smem[];
   constexpr int NWN = NWV / 2;          // wave grid: 2 (rows) x NWN (columns)
@@ -788,18 +998,6 @@ __global__ __launch_bounds__(NWV * 64) void mfma_gemm_dma_kernel(MGemm p) {
     for (int mq = 0; mq < 2; ++mq) {
       const int mb = half * 2 + mq;
       const int m = m0 + wm * 128 + mb * 32 + lo;
-      u32x2 rvs[NBN][4];   // the row's residual values, all requested before the first is added
-      if constexpr (EPI) {
-        if (p.res) {
-#pragma unroll
-          for (int nb = 0; nb < NBN; ++nb)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-              const int n = n0 + wn * WCOLS + nb * 32 + 8 * i + 4 * hi;
-              rvs[nb][i] = *(const u32x2*)(p.res + (long)min(m, p.M - 1) * p.ldc + (n < p.N ? n : 0));
-            }
-        }
-      }
 #pragma unroll
       for (int nb = 0; nb < NBN; ++nb)
 #pragma unroll
@@ -810,17 +1008,6 @@ __global__ __launch_bounds__(NWV * 64) void mfma_gemm_dma_kernel(MGemm p) {
           const float cs = (p.scale0_on && n < p.n_per) ? p.scale0 : 1.f;
 #pragma unroll
           for (int j = 0; j < 4; ++j) v[j] = acc[nb][mb][4 * i + j] * cs;
-          if constexpr (EPI) {
-            if (p.gelu) {
-#pragma unroll
-              for (int j = 0; j < 4; ++j) v[j] = gelu_erf_f(v[j]);
-            }
-            if (p.res && (interior || (m < p.M && n < p.N))) {
-              const u32x2 rv = rvs[nb][i];
-              v[0] += __uint_as_float(rv[0] << 16); v[1] += __uint_as_float(rv[0] & 0xffff0000u);
-              v[2] += __uint_as_float(rv[1] << 16); v[3] += __uint_as_float(rv[1] & 0xffff0000u);
-            }
-          }
           const u32x2 pk = {pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3])};
           *(u32x2*)(stg + (mq * 32 + lo) * EP_LD + nl) = pk;
         }
@@ -857,7 +1044,6 @@ constexpr int T_STAGE_BYTES = T_A_BYTES + DN * DK * 2;         // 34 KB
 constexpr int T_LDS_BYTES = DSTAGES * T_STAGE_BYTES;           // 136 KB
 constexpr int T_STG_BYTES = 10240;                             // epilogue staging per wave: 64 rows x 72 bf16 (9216) rounded up
 
-template <bool EPI>
 __global__ __launch_bounds__(TWAVES * 64) void mfma_gemm_dma12_kernel(MGemm p) {
   extern __shared__ __attribute__((aligned(1024))) bf16_t smem[];
   constexpr int NBN = 2, MBW = 3, WCOLS = 64, NT_THREADS = TWAVES * 64;
@@ -988,16 +1174,6 @@ __global__ __launch_bounds__(TWAVES * 64) void mfma_gemm_dma12_kernel(MGemm p) {
     const int m = m0 + wm * 96 + mb * 32 + lo;
 #pragma unroll
     for (int nb = 0; nb < NBN; ++nb) {
-      u32x2 rvs[4];   // the row's residual values of this column block, requested together (168 registers: not all eight)
-      if constexpr (EPI) {
-        if (p.res) {
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            const int n = n0 + wn * WCOLS + nb * 32 + 8 * i + 4 * hi;
-            rvs[i] = *(const u32x2*)(p.res + (long)min(m, p.M - 1) * p.ldc + (n < p.N ? n : 0));
-          }
-        }
-      }
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const int nl = nb * 32 + 8 * i + 4 * hi;
@@ -1006,17 +1182,6 @@ __global__ __launch_bounds__(TWAVES * 64) void mfma_gemm_dma12_kernel(MGemm p) {
         const float cs = (p.scale0_on && n < p.n_per) ? p.scale0 : 1.f;
 #pragma unroll
         for (int j = 0; j < 4; ++j) v[j] = acc[nb][mb][4 * i + j] * cs;
-        if constexpr (EPI) {
-          if (p.gelu) {
-#pragma unroll
-            for (int j = 0; j < 4; ++j) v[j] = gelu_erf_f(v[j]);
-          }
-          if (p.res && (interior || (m < p.M && n < p.N))) {
-            const u32x2 rv = rvs[i];
-            v[0] += __uint_as_float(rv[0] << 16); v[1] += __uint_as_float(rv[0] & 0xffff0000u);
-            v[2] += __uint_as_float(rv[1] << 16); v[3] += __uint_as_float(rv[1] & 0xffff0000u);
-          }
-        }
         const u32x2 pk = {pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3])};
         *(u32x2*)(stg + lo * EP_LD + nl) = pk;
       }
@@ -1482,21 +1647,13 @@ __global__ __launch_bounds__(256) void mfma_splitk_reduce_par_kernel(const float
   }
 }
 
-// Which kernel (measured on MI355X, C5 shapes):
-//  - weight gradients (both operands k-major, long contraction over token rows): the asynchronous
-//    256 x 256 kernel is 1.5x faster than the 128 x 128 kernel;
-//  - projections with row-major activations and k-major weights (QKV, output projection; K = d):
-//    the 256 x 256 kernel needs half the L1 traffic per flop and wins by 1.2-1.35x;
-//  - both operands row-major (dO, dx): the 128 x 128 kernel with three workgroups per CU wins (also against
-//    the large-tile kernel with 8 waves: 0.122 vs 0.142 ms for the two GEMMs).
+// Where the 256 x 256 tiles apply: k-major B, whole 32-deep k-tiles, a contraction long enough to fill their ring.
+// Weight gradients (both operands k-major, contraction over token rows) take them whenever they do, at 1.5x the
+// 128 x 128 kernel; projections only under large_tiles_fill below.
 static bool use_dma(int M, int N, int K, bool akm = true, bool bkm = true) {
   if (!(bkm && M >= DM && N >= DN && K % DK == 0 && M % 8 == 0 && N % 8 == 0)) return false;
   return akm ? K >= 64 * DK : K >= 8 * DK;
 }
-
-// true if a row-major-A, k-major-B (forward linear) or all-row-major (data gradient) GEMM of this shape runs on the
-// 128 x 128 kernel, whose epilogue knows MGEMM_GELU_BOTH and MGEMM_GELU_GRAD
-bool mfma_gemm_small_tile(int M, int N, int K, bool b_kmajor) { return !use_dma(M, N, K, false, b_kmajor); }
 
 int mfma_gemm_split(int M, int N, int K) {
   if (use_dma(M, N, K)) {
@@ -1517,55 +1674,99 @@ int mfma_gemm_split(int M, int N, int K) {
 }
 
 constexpr int DMA_WAVES = 8;   // waves per workgroup of the large-tile kernel
-template <bool AKM, bool BKM, bool EPI>
+template <bool AKM, bool BKM>
 static void launch_dma(const MGemm& p, hipStream_t st) {
   static bool configured = false;  // raise the dynamic-LDS limit once per instantiation (128 KB > the 64 KB default)
   if (!configured) {
-    (void)hipFuncSetAttribute((const void*)mfma_gemm_dma_kernel<AKM, BKM, EPI, DMA_WAVES>,
+    (void)hipFuncSetAttribute((const void*)mfma_gemm_dma_kernel<AKM, BKM, DMA_WAVES>,
                               hipFuncAttributeMaxDynamicSharedMemorySize, DMA_LDS_BYTES);
     configured = true;
   }
   dim3 grid((p.N + DN - 1) / DN, (p.M + DM - 1) / DM, p.split_k);
-  hipLaunchKernelGGL((mfma_gemm_dma_kernel<AKM, BKM, EPI, DMA_WAVES>), grid, dim3(DMA_WAVES * 64), DMA_LDS_BYTES, st, p);
+  hipLaunchKernelGGL((mfma_gemm_dma_kernel<AKM, BKM, DMA_WAVES>), grid, dim3(DMA_WAVES * 64), DMA_LDS_BYTES, st, p);
 }
-// the 288-row variant when its workgroups need fewer (weighted) rounds of the CUs than the 256-row tiles
-static bool use_dma12(const MGemm& p) {
-  if (p.split_k > 1 || p.partial || p.M < TM || p.b_kper > 0) return false;
-  static int cus = 0;   // compute units of the device (the first device that launches; one GPU per process)
+static int cu_count() {   // of the device (the first device that launches; one GPU per process)
+  static int cus = 0;
   if (cus == 0) {
     int dev = 0, n = 0;
     if (hipGetDevice(&dev) == hipSuccess && hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && n > 0) cus = n;
     else cus = 256;
   }
-  const long nt = (p.N + DN - 1) / DN;
+  return cus;
+}
+// the 288-row variant when its workgroups need fewer (weighted) rounds of the CUs than the 256-row tiles
+static bool use_dma12(const MGemm& p) {
+  if (p.split_k > 1 || p.partial || p.M < TM || p.b_kper > 0) return false;
+  const long cus = cu_count(), nt = (p.N + DN - 1) / DN;
   const long t256 = (long)((p.M + DM - 1) / DM) * nt, t288 = (long)((p.M + TM - 1) / TM) * nt;
   const double r256 = (double)((t256 + cus - 1) / cus), r288 = (double)((t288 + cus - 1) / cus) * (double)TM / DM;
   return r288 < r256;
 }
-template <bool EPI>
+// Row-major A: the 256- / 288-row tiles only where they fill their last round of the CUs (one workgroup each) to 95 %.
+// 36 864 x 512 and x 1536 (exact rounds of 288): 26 against 29 us of the ring kernel, 73 against 76..80; 32 768 x 512
+// (one round of 256): 25.3 / 26.5.  Not full: 16 384 x 512 20.7 / 14.9, 16 000 x 1536 41 / 36.
+// With a residual the ring wins there too (65 536 x 256: 24.7 / 20.8), so the large tiles have the plain epilogue only.
+static bool large_tiles_fill(const MGemm& p) {
+  const long rows = use_dma12(p) ? TM : DM, cus = cu_count();
+  const long t = ((p.M + rows - 1) / rows) * ((p.N + DN - 1) / DN), slots = (t + cus - 1) / cus * cus;
+  return 20 * t >= 19 * slots;
+}
 static void launch_dma12(const MGemm& p, hipStream_t st) {
   static bool configured = false;
   if (!configured) {
-    (void)hipFuncSetAttribute((const void*)mfma_gemm_dma12_kernel<EPI>, hipFuncAttributeMaxDynamicSharedMemorySize, T_LDS_BYTES);
+    (void)hipFuncSetAttribute((const void*)mfma_gemm_dma12_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, T_LDS_BYTES);
     configured = true;
   }
   dim3 grid((p.N + DN - 1) / DN, (p.M + TM - 1) / TM, 1);
-  hipLaunchKernelGGL((mfma_gemm_dma12_kernel<EPI>), grid, dim3(TWAVES * 64), T_LDS_BYTES, st, p);
+  hipLaunchKernelGGL((mfma_gemm_dma12_kernel), grid, dim3(TWAVES * 64), T_LDS_BYTES, st, p);
+}
+template <bool BKM, bool EPI, int MB>
+static void launch_ring(const MGemm& p, hipStream_t st) {
+  static bool configured = false;
+  if (!configured) {
+    (void)hipFuncSetAttribute((const void*)mfma_gemm_ring_kernel<BKM, EPI, MB>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                              ring_lds_bytes(MB));
+    configured = true;
+  }
+  dim3 grid((p.N + GN - 1) / GN, (p.M + 64 * MB - 1) / (64 * MB), 1);
+  hipLaunchKernelGGL((mfma_gemm_ring_kernel<BKM, EPI, MB>), grid, dim3(256), ring_lds_bytes(MB), st, p);
+}
+// Forms the ring kernel takes: row-major A, whole 64-deep k-tiles (per weight, where K is split over several) and
+// everything it copies or stores in 16-byte units aligned to that.
+static bool ring_form(const MGemm& p) {
+  auto al16 = [](const void* q) { return (reinterpret_cast<uintptr_t>(q) & 15) == 0; };
+  return !p.a_kmajor && p.split_k == 1 && !p.partial && !p.ln_g && p.K >= RK && p.K % RK == 0 && p.M >= 1 && p.N >= 8 &&
+         p.N % 8 == 0 && p.lda % 8 == 0 && p.ldb % 8 == 0 && p.ldc % 8 == 0 && p.b_kper % RK == 0 && p.b_nper % 8 == 0 &&
+         (!p.scale0_on || p.n_per % 8 == 0) && al16(p.A) && al16(p.B[0]) && al16(p.B[1]) && al16(p.B[2]) && al16(p.C) &&
+         al16(p.C2) && al16(p.res);
+}
+// 128-row tiles where they fill three quarters of their last round (two workgroups per CU), or past two rounds: they read
+// an operand fragment less per product.  64-row tiles (three per CU) otherwise.  Measured in 128-row tiles, us at
+// 64 / 128 rows: 396 tiles 11.8 / 11.1, 432 15.3 / 13.8, 512 16.7 / 14.9, 1152 78 / 73; 324 9.0 / 9.9, 516 12.9 / 14.0, 628 19.1 / 19.9.
+static bool ring_rows128(const MGemm& p) {
+  const long t = (long)((p.M + 127) / 128) * ((p.N + GN - 1) / GN), slots = 2L * cu_count();
+  return t >= 2 * slots || 4 * t > 3 * ((t + slots - 1) / slots * slots);
 }
 template <bool AKM, bool BKM>
 static void launch_layout(const MGemm& p, bool dma, hipStream_t st) {
   const bool epi = p.gelu || p.res != nullptr;
-  if constexpr (!AKM && BKM) {
-    if (dma && use_dma12(p)) {
-      if (epi) launch_dma12<true>(p, st);
-      else launch_dma12<false>(p, st);
+  if constexpr (!AKM) {
+    if (ring_form(p) && !(BKM && dma && large_tiles_fill(p))) {
+      if (ring_rows128(p)) {
+        if (epi) launch_ring<BKM, true, 2>(p, st);
+        else launch_ring<BKM, false, 2>(p, st);
+      } else {
+        if (epi) launch_ring<BKM, true, 1>(p, st);
+        else launch_ring<BKM, false, 1>(p, st);
+      }
       return;
     }
   }
-  if (dma) {
-    if (epi) launch_dma<AKM, BKM, true>(p, st);
-    else launch_dma<AKM, BKM, false>(p, st);
-    return;
+  if constexpr (!AKM && BKM) {
+    if (dma && use_dma12(p)) return launch_dma12(p, st);
+  }
+  if constexpr (BKM) {
+    if (dma) return launch_dma<AKM, BKM>(p, st);
   }
   const long tiles = (long)((p.N + GN - 1) / GN) * ((p.M + GM - 1) / GM);
   if constexpr (!AKM) {
@@ -1584,9 +1785,14 @@ static void launch_layout(const MGemm& p, bool dma, hipStream_t st) {
 }
 
 // Data gradients C = G W^T multiply by a weight stored [n][k] (an m-major B operand).  The large-tile kernels want
-// k-major B, and a weight is tiny beside the activations: when they apply, the caller transposes the weights once
-// per call (2 MB at d = 512) and the data gradients run on the same kernel as the forward projections.
-bool mfma_dgrad_wants_transposed_weights(int M, int N, int K) { return use_dma(M, N, K, false, true) && M >= TM; }
+// k-major B, and a weight is tiny beside the activations: where their tiles fill the chip the caller transposes the
+// weights once per call (2 MB at d = 512) and the data gradients run on the same kernel as the forward projections
+// (36 864 rows, d = 512, training step: 792 us against 811 with the ring kernel on the weights as stored).
+bool mfma_dgrad_wants_transposed_weights(int M, int N, int K) {
+  MGemm p = {};
+  p.M = M; p.N = N; p.K = K; p.split_k = 1;
+  return use_dma(M, N, K, false, true) && M >= TM && large_tiles_fill(p);
+}
 // out[s][c][r] = w[s][r][c] for up to four square d x d matrices (d % 32 == 0); grid (d / 32, d / 32, count)
 __global__ __launch_bounds__(256) void transpose_square_kernel(const bf16_t* w0, const bf16_t* w1, const bf16_t* w2,
                                                                const bf16_t* w3, int d, bf16_t* out) {
@@ -1671,7 +1877,7 @@ void launch_mfma_gemm_pair(const MGemm& a, const MGemm& b, hipStream_t st) {
 void launch_mfma_gemm(const MGemm& p, hipStream_t st) {
   if (qkv_rows_shape(p)) return launch_qkv_rows(p, nullptr, st);
   const bool dma = use_dma(p.M, p.N, p.K, p.a_kmajor, p.b_kmajor) && (p.b_kper == 0 || p.b_kper % DK == 0) && !p.ln_g &&
-                   p.gelu <= 1;   // MGEMM_GELU_BOTH / _GRAD exist in the 128 x 128 kernel only
+                   !p.gelu && !p.res;   // the large tiles have the bias epilogue only
   if (p.a_kmajor && p.b_kmajor) launch_layout<true, true>(p, dma, st);
   else if (p.b_kmajor) launch_layout<false, true>(p, dma, st);
   else if (p.a_kmajor) launch_layout<true, false>(p, dma, st);

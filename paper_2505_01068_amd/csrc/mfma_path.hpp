@@ -6,7 +6,7 @@
 namespace imattn {
 
 // Descriptor of one bf16 MFMA GEMM  C[M,N] = sum_k A(m,k) B(n,k)  (see mfma_gemm.hip).
-// Epilogue modes of the 128 x 128 kernel beyond the plain GELU (gelu = 1), for a layer's training passes:
+// Epilogue modes of the ring and the 128 x 128 kernel beyond the plain GELU (gelu = 1), for a layer's training passes:
 //   BOTH: C = A B + bias (the pre-activation), C2 = GELU(C as rounded to bf16);
 //   GRAD: C = (A B) * GELU'(res), res = the saved pre-activation (not added).
 constexpr int MGEMM_GELU_BOTH = 2, MGEMM_GELU_GRAD = 3;
@@ -50,7 +50,7 @@ inline bool mfma_linear_ok(int is_bf16, long K, long N) { return is_bf16 && K % 
 // weights of k_per columns each (K = 3 k_per, k_per % 64 == 0), as in dx = dQ Wq^T + dK Wk^T + dV Wv^T
 void mfma_dgrad(const void* G, long ldg, const void* w0, const void* w1, const void* w2, long ldw, int k_per, void* C,
                 long ldc, int M, int N, int K, hipStream_t st, const void* gelu_grad_of = nullptr);
-// (gelu_grad_of != NULL, shapes with mfma_gemm_small_tile only: C = (G W^T) * GELU'(gelu_grad_of), same ld as C)
+// (gelu_grad_of != NULL: C = (G W^T) * GELU'(gelu_grad_of), same ld as C)
 // weight gradient  C[M,N] (fp32) = A[R,M]^T G[R,N]  (contraction over rows), split-K with a fixed-order
 // reduction; n_per > 0: column block s of n_per columns goes to the [M, n_per] output o<s> (NULL = dropped);
 // n_per = 0: one [M, N] output o0.  `partial`: mfma_wgrad_partial_bytes.  M % 8 == 0 and N % 8 == 0.
@@ -60,7 +60,7 @@ void mfma_wgrad(const void* A, long lda, const void* G, long ldg, float* o0, flo
 void mfma_linear(const void* A, long lda, const void* w0, const void* w1, const void* w2, long ldb, int n_per,
                  const void* b0, const void* b1, const void* b2, int gelu, const void* res, void* C, long ldc, int M,
                  int N, int K, hipStream_t st, LnArgs ln = {nullptr, nullptr, 0.f}, void* C2 = nullptr);
-// (gelu = MGEMM_GELU_BOTH, shapes with mfma_gemm_small_tile only: C = the pre-activation, C2 = GELU of it)
+// (gelu = MGEMM_GELU_BOTH: C = the pre-activation, C2 = GELU of it)
 // y = h + GELU(LayerNorm(h) W1 + b1) W2 + b2 in one kernel at model width 64 or 128 (bf16, d_ff % 64 == 0,
 // 16-byte aligned pointers; b1 / b2 may be NULL)
 bool mlp_tail_ok(int is_bf16, long d, long d_ff, const void* h, const void* ln_g, const void* ln_b, const void* w1,
@@ -77,7 +77,6 @@ struct MlpTailPairSide {
 };
 void launch_mlp_tail_pair(const MlpTailPairSide& a, const MlpTailPairSide& b, float ln_eps, int R, int d, int d_ff,
                           hipStream_t st);
-bool mfma_gemm_small_tile(int M, int N, int K, bool b_kmajor);
 int mfma_gemm_split(int M, int N, int K);
 void launch_splitk_reduce(const float* partial, int split_k, int M, int N, float* o0, float* o1, float* o2, int n_per,
                           hipStream_t st);
