@@ -723,7 +723,8 @@ struct LayerTrain {
   size_t u, v, dz, dv, dh, t, partial, partial1, cpart, cpart2, cpart3, attws, ws_total;   // backward workspace
   size_t fwd_ws_total;                                                   // forward workspace: u
   int split_w1, split_w2;
-  size_t aws_bytes;
+  bool ring;        // bf16: all weight gradients in one launch (WgradRing)
+  WgradPlan plan;
 };
 static LayerTrain layer_train_layout(const im_shape_t* s, int32_t d_ff) {
   LayerTrain L;
@@ -745,9 +746,14 @@ static LayerTrain layer_train_layout(const im_shape_t* s, int32_t d_ff) {
   L.t = off; off += align256(R * d * es);
   L.split_w1 = L.split_w2 = 1;
   size_t p1, p2;
+  L.ring = pick_path(s) == PATH_MFMA && mfma_linear_ok(1, d, d_ff);
+  if (L.ring) L.plan = wgrad_ring_plan_layer((int)d, d_ff, (int)R);
   if (s->dtype == IM_DTYPE_F32) {
     p1 = wgrad_split_bytes((int)d, d_ff, (int)R);
     p2 = wgrad_split_bytes(d_ff, (int)d, (int)R);
+  } else if (L.ring) {
+    p1 = wgrad_ring_bytes(L.plan, (int)d, d_ff);
+    p2 = wgrad_ring_bytes(L.plan, d_ff, (int)d);
   } else {
     p1 = gemm_alu_partial_bytes((int)d, d_ff, (int)R, &L.split_w1);
     p2 = gemm_alu_partial_bytes(d_ff, (int)d, (int)R, &L.split_w2);
@@ -763,8 +769,7 @@ static LayerTrain layer_train_layout(const im_shape_t* s, int32_t d_ff) {
   L.cpart = off; off += align256(colsum_partial_bytes((int)R, (int)f));         // db1
   L.cpart2 = off; off += align256(colsum_partial_bytes((int)R, (int)(3 * d)));  // second LayerNorm's two sums and db2
   L.cpart3 = off; off += align256(colsum_partial_bytes((int)R, (int)(2 * d)));  // first LayerNorm's two sums
-  L.aws_bytes = bwd_workspace_bytes(s);
-  L.attws = off; off += align256(L.aws_bytes);
+  L.attws = off; off += align256(L.ring ? mfma_bwd_workspace_bytes(s, &L.plan) : bwd_workspace_bytes(s));
   L.ws_total = off;
   return L;
 }
@@ -875,6 +880,8 @@ int gsit_layer_bwd(const im_shape_t* shape, int32_t d_ff, const void* x, const g
   float* cpart3 = (float*)(ws + L.cpart3);
   ReduceList later;   // second-stage sums postponed to one launch at the end (matrix-core path, small outputs)
   later.n = 0;
+  WgradRing wr;        // bf16 on the matrix-core path: the same
+  wr.n = wr.tiles = 0;
   WgradSplitList wl;   // fp32: all four weight gradients (and the bias gradients beside them) in one launch
   wl.n = wl.tiles = 0;
   GemmDesc g;
@@ -885,6 +892,9 @@ int gsit_layer_bwd(const im_shape_t* shape, int32_t d_ff, const void* x, const g
   if (!bf) {
     wgrad_split_push(&wl, &later, (const float*)a, d_ff, (const float*)dy, d, (int)R, d_ff, (int)d, partial, 0, (float*)gr->w2, nullptr,
                      nullptr, (float*)gr->b2, nullptr, nullptr);
+  } else if (L.ring) {
+    wgrad_ring_push(&wr, L.plan, &later, a, d_ff, dy, d, d_ff, (int)d, partial, 0, (float*)gr->w2, nullptr, nullptr, (float*)gr->b2,
+                    nullptr, nullptr);
   } else if (gr->w2 && mm) {
     mfma_wgrad(a, d_ff, dy, d, (float*)gr->w2, nullptr, nullptr, 0, d_ff, (int)d, (int)R, partial, st, &later);
   } else if (gr->w2) {  // dW2 = a^T dy
@@ -893,7 +903,7 @@ int gsit_layer_bwd(const im_shape_t* shape, int32_t d_ff, const void* x, const g
     g.C[0] = gr->w2; g.ldc = d; g.M = d_ff; g.N = (int)d; g.K = (int)R; g.split_k = L.split_w2; g.partial = partial;
     if ((rc = launch_gemm_alu(g, bf, bf, 0, st))) return rc;
   }
-  // (bf16: db2 = column sums of dy: taken further down, together with the second LayerNorm's parameter gradients)
+  // (bf16 off the list: db2 = column sums of dy: taken further down, together with the second LayerNorm's parameter gradients)
   // dz = (dy W2^T) * GELU'(z)
   if (mm) {   // GELU' in the GEMM's epilogue
     mfma_dgrad(dy, d, p->w2, nullptr, nullptr, d, 0, dz, d_ff, (int)R, d_ff, (int)d, st, zpre);
@@ -909,6 +919,9 @@ int gsit_layer_bwd(const im_shape_t* shape, int32_t d_ff, const void* x, const g
   if (!bf) {
     wgrad_split_push(&wl, &later, (const float*)v, d, (const float*)dz, d_ff, (int)R, (int)d, d_ff, partial1, 0, (float*)gr->w1, nullptr,
                      nullptr, (float*)gr->b1, nullptr, nullptr);
+  } else if (L.ring) {
+    wgrad_ring_push(&wr, L.plan, &later, v, d, dz, d_ff, (int)d, d_ff, partial1, 0, (float*)gr->w1, nullptr, nullptr, (float*)gr->b1,
+                    nullptr, nullptr);
   } else if (gr->w1 && mm) {
     mfma_wgrad(v, d, dz, d_ff, (float*)gr->w1, nullptr, nullptr, 0, (int)d, d_ff, (int)R, partial1, st, &later);
   } else if (gr->w1) {  // dW1 = v^T dz
@@ -917,7 +930,7 @@ int gsit_layer_bwd(const im_shape_t* shape, int32_t d_ff, const void* x, const g
     g.C[0] = gr->w1; g.ldc = d_ff; g.M = (int)d; g.N = d_ff; g.K = (int)R; g.split_k = L.split_w1; g.partial = partial1;
     if ((rc = launch_gemm_alu(g, bf, bf, 0, st))) return rc;
   }
-  if (gr->b1 && bf) {
+  if (gr->b1 && bf && !L.ring) {
     const void* src1[1] = {dz};
     const long ld1[1] = {d_ff};
     float* out1[1] = {(float*)gr->b1};
@@ -936,7 +949,7 @@ int gsit_layer_bwd(const im_shape_t* shape, int32_t d_ff, const void* x, const g
   {  // gradients of the LayerNorm gain and bias: column sums of dy * xhat and of dy; and db2 = column sums of dy
     const void* src[3] = {t, dv, dy};
     const long ld3[3] = {d, d, d};
-    float* out3[3] = {(float*)gr->ln2_g, (float*)gr->ln2_b, bf ? (float*)gr->b2 : nullptr};
+    float* out3[3] = {(float*)gr->ln2_g, (float*)gr->ln2_b, bf && !L.ring ? (float*)gr->b2 : nullptr};
     if ((rc = launch_colsum_multi(src, ld3, out3, 3, (int)R, (int)d, bf, cpart2, st, defer))) return rc;
   }
   // h = x + IMAttention(u), u = LN(x; ln1): attention backward with upstream gradient dh; its dx is du (into dv)
@@ -945,12 +958,13 @@ int gsit_layer_bwd(const im_shape_t* shape, int32_t d_ff, const void* x, const g
   if (pick_path(shape) == PATH_MFMA)
     rc = mfma_attention_bwd(shape, u, p->wq, p->wk, p->wv, p->wo, valid_len, key_pad, sv + L.att, A.qkv, A.o, A.lse, A.extra,
                             dh, dv, gr->wq, gr->wk, gr->wv, gr->wo, gr->bq, gr->bk, gr->bv, gr->bo, ws + L.attws, st,
-                            defer);
+                            defer, L.ring ? &wr : nullptr, L.ring ? &L.plan : nullptr);
   else
     rc = bwd_smallhead(shape, u, p->wq, p->wk, p->wv, p->wo, valid_len, key_pad, sv + L.att, dh, dv, gr->wq, gr->wk, gr->wv,
                      gr->wo, gr->bq, gr->bk, gr->bv, gr->bo, ws + L.attws, st, bf ? nullptr : &later, bf ? nullptr : &wl);
   if (rc) return rc;
   launch_wgrad_split(wl, st);
+  if (L.ring) launch_wgrad_ring(wr, L.plan, (int)R, st);
   // dx = dh + LN1 backward(du)
   if ((rc = launch_layernorm_bwd(x, p->ln1_g, dv, dh, dx, t, (int)R, (int)d, ln_eps, bf, st))) return rc;
   {

@@ -187,13 +187,13 @@ size_t gemm_alu_partial_bytes(int M, int N, int K, int* split_k);
 // Each is a few microseconds of launch latency on its own.  A postponed job's partial buffer must stay untouched
 // until launch_reduce_list.
 struct ReduceJob { const float* partial; int nparts, M, N, n_per; long stride; float* o[3]; };   // stride: of a partial result, % 4 == 0
-struct ReduceList { ReduceJob job[16]; int n; };
+struct ReduceList { ReduceJob job[16]; int n; int first[16], lanes[16]; };   // first (workgroup of a job), lanes (over the partials): set by launch_reduce_list
 // N % 4 == 0, at most 65536 output quads and at most 8 MB of partials (a larger set is read back faster right after
 // it was written, while it is still in the last-level cache): the job can go on a list
 bool reduce_deferrable(int M, int N, int nparts);
 void reduce_push(ReduceList* l, const float* partial, int nparts, int M, int N, float* o0, float* o1, float* o2, int n_per,
                  long stride = 0);   // 0: M * N
-void launch_reduce_list(const ReduceList& l, hipStream_t st);
+void launch_reduce_list(ReduceList& l, hipStream_t st);
 // column sums of a [R, n] matrix (bias gradients), deterministic two-stage
 int launch_colsum(const void* a, long lda, int R, int n, int a_bf16, float* out, float* partial, hipStream_t st);
 size_t colsum_partial_bytes(int R, int n);   // for one matrix; launch_colsum_multi (count <= 4) needs count times as much

@@ -444,18 +444,21 @@ __global__ __launch_bounds__(256) void colsum_stage2(const float* __restrict__ p
 // bytes of `partial` for ONE matrix; launch_colsum_multi needs count times as much
 size_t colsum_partial_bytes(int R, int n) { return (size_t)((R + CS_ROWS - 1) / CS_ROWS) * n * sizeof(float); }
 
-// One launch for a list of second-stage sums (blockIdx.y = job).  A block is 16 output quads x 16 lanes over the
+// One launch for a list of second-stage sums.  A block is 16 output quads x 16 lanes over the
 // partials: lane zl adds partials zl, zl + 16, ... in ascending order, then the 16 lane sums are added in a fixed
-// order through LDS -- the same order as colsum_stage2 and the parallel split-K reduction use on their own.
+// order through LDS -- the same order as colsum_stage2 and the parallel split-K reduction use on their own.  With at most
+// 8, 4 or 2 partials a block is 32, 64 or 128 quads x that many lanes: none would have more than one partial anyway.
 // ODD: some job's rows or column blocks are not whole quads.
 template <bool ODD>
 __global__ __launch_bounds__(256) void reduce_list_kernel(ReduceList l) {
-  __shared__ float4 red[16][16];
-  const ReduceJob& j = l.job[blockIdx.y];
+  __shared__ float4 red[256];
+  int ji = 0;   // the blocks of a job follow those of the one before it
+  for (int k = 1; k < l.n; ++k) ji += (int)blockIdx.x >= l.first[k];
+  const ReduceJob& j = l.job[ji];
   const long n_out = (long)j.M * j.N;
-  const int ql = threadIdx.x & 15, zl = threadIdx.x >> 4;
-  if ((long)blockIdx.x * 64 >= n_out) return;   // block-uniform
-  const long i = ((long)blockIdx.x * 16 + ql) * 4;
+  const int lanes = l.lanes[ji], quads = 256 / lanes;   // powers of two
+  const int ql = threadIdx.x & (quads - 1), zl = threadIdx.x / quads;
+  const long i = ((long)((int)blockIdx.x - l.first[ji]) * quads + ql) * 4;
   float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
   if (i < n_out) {
     int z = zl;
@@ -471,11 +474,11 @@ __global__ __launch_bounds__(256) void reduce_list_kernel(ReduceList l) {
       s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
     }
   }
-  red[zl][ql] = s;
+  red[threadIdx.x] = s;
   __syncthreads();
   if (zl != 0 || i >= n_out) return;
-  for (int k = 1; k < 16; ++k) {
-    const float4 v = red[k][ql];
+  for (int k = 1; k < lanes; ++k) {
+    const float4 v = red[k * quads + ql];
     s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
   }
   if (!ODD) {   // the quad lies in one row of one output
@@ -510,17 +513,20 @@ void reduce_push(ReduceList* l, const float* partial, int nparts, int M, int N, 
   j.partial = partial; j.nparts = nparts; j.M = M; j.N = N; j.n_per = n_per;
   j.o[0] = o0; j.o[1] = o1; j.o[2] = o2;
 }
-void launch_reduce_list(const ReduceList& l, hipStream_t st) {
+void launch_reduce_list(ReduceList& l, hipStream_t st) {
   if (l.n == 0) return;
-  long mx = 0;
+  int blocks = 0;
   bool odd = false;
   for (int i = 0; i < l.n; ++i) {
-    mx = std::max(mx, (long)l.job[i].M * l.job[i].N);
+    const int np = l.job[i].nparts;
+    l.lanes[i] = np > 8 ? 16 : np > 4 ? 8 : np > 2 ? 4 : 2;
+    l.first[i] = blocks;
+    const long per = 4 * 256 / l.lanes[i];
+    blocks += (int)(((long)l.job[i].M * l.job[i].N + per - 1) / per);
     odd = odd || l.job[i].N % 4 != 0 || l.job[i].n_per % 4 != 0;
   }
-  const dim3 grid((unsigned)((mx + 63) / 64), l.n);
-  if (odd) hipLaunchKernelGGL(reduce_list_kernel<true>, grid, dim3(256), 0, st, l);
-  else hipLaunchKernelGGL(reduce_list_kernel<false>, grid, dim3(256), 0, st, l);
+  if (odd) hipLaunchKernelGGL(reduce_list_kernel<true>, dim3(blocks), dim3(256), 0, st, l);
+  else hipLaunchKernelGGL(reduce_list_kernel<false>, dim3(blocks), dim3(256), 0, st, l);
 }
 
 int launch_colsum_multi(const void* const* a, const long* lda, float* const* out, int count, int R, int n, int a_bf16,

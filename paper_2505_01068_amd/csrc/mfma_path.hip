@@ -28,27 +28,25 @@ static Dims dims(const im_shape_t* s) {
 size_t mfma_saved_extra_bytes(const im_shape_t*) { return 0; }
 size_t mfma_fwd_workspace_bytes(int) { return 0; }
 
-struct BwdWs { size_t d_o, delta, dqkv, partial, partial_o, cpart, wt, total; int split_w, split_o; bool tw; };
-static BwdWs bwd_ws(const im_shape_t* s) {
+struct BwdWs { size_t d_o, delta, dqkv, partial, partial_o, wt, total; bool tw; };
+static BwdWs bwd_ws(const im_shape_t* s, const WgradPlan* plan) {
   const Dims x = dims(s);
   BwdWs w;
   size_t off = 0;
   w.d_o = off; off += al(x.R * x.d * 2);
   w.delta = off; off += al((size_t)s->n_heads * x.R * 4);
   w.dqkv = off; off += al(x.R * 3 * x.d * 2);
-  w.split_w = mfma_gemm_split((int)x.d, (int)(3 * x.d), (int)x.R);
-  w.split_o = mfma_gemm_split((int)x.d, (int)x.d, (int)x.R);
   // one region per weight gradient: a postponed reduction (ReduceList) reads its partials at the end of the pass
-  w.partial = off; off += al((size_t)w.split_w * x.d * 3 * x.d * 4);
-  w.partial_o = off; off += al((size_t)w.split_o * x.d * x.d * 4);
-  w.cpart = off; off += al(4 * colsum_partial_bytes((int)x.R, (int)x.d));   // dbo, dbq, dbk, dbv in one launch
+  const WgradPlan pl = plan ? *plan : wgrad_ring_plan_attention((int)x.d, (int)x.R);
+  w.partial = off; off += al(wgrad_ring_bytes(pl, (int)x.d, (int)(3 * x.d)));
+  w.partial_o = off; off += al(wgrad_ring_bytes(pl, (int)x.d, (int)x.d));
   // Wo^T and [Wq^T; Wk^T; Wv^T] for the data gradients, where the large-tile GEMM serves them
   w.tw = x.d % 32 == 0 && mfma_dgrad_wants_transposed_weights((int)x.R, (int)x.d, (int)x.d);
   w.wt = off; off += w.tw ? al(4 * x.d * x.d * 2) : 0;
   w.total = off;
   return w;
 }
-size_t mfma_bwd_workspace_bytes(const im_shape_t* s) { return bwd_ws(s).total; }
+size_t mfma_bwd_workspace_bytes(const im_shape_t* s, const WgradPlan* plan) { return bwd_ws(s, plan).total; }
 
 static void init_gemm(MGemm* p) {
   memset(p, 0, sizeof(*p));
@@ -189,12 +187,12 @@ int mfma_attention_bwd(const im_shape_t* s, const void* x, const void* wq, const
                        const void* wo, const int32_t* valid_len, const uint8_t* key_pad, const char* sv,
                        size_t off_qkv, size_t off_o, size_t off_lse, size_t, const void* dy, void* dx, void* dwq,
                        void* dwk, void* dwv, void* dwo, void* dbq, void* dbk, void* dbv, void* dbo, char* ws,
-                       hipStream_t st, ReduceList* defer) {
+                       hipStream_t st, ReduceList* defer, WgradRing* wring, const WgradPlan* plan) {
   Geo g;
   build_geo(s, mfma_dq_tile_rows(), mfma_dkv_tile_rows(), &g);
   const Dims dm = dims(s);
   const int d = (int)dm.d, R = (int)dm.R;
-  const BwdWs w = bwd_ws(s);
+  const BwdWs w = bwd_ws(s, plan);
   const bf16_t* qkv = (const bf16_t*)(sv + off_qkv);
   const bf16_t* o = (const bf16_t*)(sv + off_o);
   const float* lse2 = (const float*)(sv + off_lse);
@@ -203,7 +201,6 @@ int mfma_attention_bwd(const im_shape_t* s, const void* x, const void* wq, const
   bf16_t* dqkv = (bf16_t*)(ws + w.dqkv);
   float* partial = (float*)(ws + w.partial);
   float* partial_o = (float*)(ws + w.partial_o);
-  float* cpart = (float*)(ws + w.cpart);
 
   MGemm p;
   bf16_t* wt = (bf16_t*)(ws + w.wt);   // [Wo^T; Wq^T; Wk^T; Wv^T], each d x d
@@ -219,40 +216,22 @@ int mfma_attention_bwd(const im_shape_t* s, const void* x, const void* wq, const
     p.C = d_o; p.ldc = d;
     launch_mfma_gemm(p, st);
   }
-  if (dwo) {
-    // dWo = O^T dy : contraction over token rows, both operands k-major as stored
-    ProfScope ps(PF_WGRAD, st);
-    init_gemm(&p);
-    p.A = o; p.lda = d; p.a_kmajor = 1;
-    p.B[0] = (const bf16_t*)dy; p.ldb = d; p.b_kmajor = 1;
-    p.M = d; p.N = d; p.K = R;
-    p.split_k = w.split_o; p.partial = partial_o;
-    launch_mfma_gemm(p, st);
-    if (defer && reduce_deferrable(d, d, w.split_o) && defer->n < 16) reduce_push(defer, partial_o, w.split_o, d, d, (float*)dwo, nullptr, nullptr, 0);
-    else launch_splitk_reduce(partial_o, w.split_o, d, d, (float*)dwo, nullptr, nullptr, 0, st);
-  }
-
   launch_mfma_bwd(g, qkv, 3 * d, o, d_o, d, lse2, valid_len, key_pad, delta, dqkv, 3 * d, st);
 
-  if (dwq || dwk || dwv) {
-    // dWq | dWk | dWv = x^T [dQ | dK | dV]
+  {
+    // dWo = O^T dy with dbo, dWq | dWk | dWv = x^T [dQ | dK | dV] with dbq | dbk | dbv
+    const WgradPlan pl = plan ? *plan : wgrad_ring_plan_attention(d, R);
+    WgradRing own;
+    ReduceList own_red;
+    own.n = own.tiles = own_red.n = 0;
+    WgradRing* wl = wring ? wring : &own;
+    ReduceList* red = defer ? defer : &own_red;
+    wgrad_ring_push(wl, pl, red, x, d, dqkv, 3 * d, d, 3 * d, partial, d, (float*)dwq, (float*)dwk, (float*)dwv, (float*)dbq,
+                    (float*)dbk, (float*)dbv);
+    wgrad_ring_push(wl, pl, red, o, d, dy, d, d, d, partial_o, 0, (float*)dwo, nullptr, nullptr, (float*)dbo, nullptr, nullptr);
     ProfScope ps(PF_WGRAD, st);
-    init_gemm(&p);
-    p.A = (const bf16_t*)x; p.lda = d; p.a_kmajor = 1;
-    p.B[0] = dqkv; p.ldb = 3 * d; p.b_kmajor = 1;
-    p.M = d; p.N = 3 * d; p.K = R;
-    p.split_k = w.split_w; p.partial = partial;
-    launch_mfma_gemm(p, st);
-    if (defer && reduce_deferrable(d, 3 * d, w.split_w) && defer->n < 16)
-      reduce_push(defer, partial, w.split_w, d, 3 * d, (float*)dwq, (float*)dwk, (float*)dwv, d);
-    else launch_splitk_reduce(partial, w.split_w, d, 3 * d, (float*)dwq, (float*)dwk, (float*)dwv, d, st);
-  }
-  if (dbo || dbq || dbk || dbv) {  // column sums of dy and of the dQ | dK | dV column blocks, one pair of launches
-    const void* src[4] = {dy, dqkv, dqkv + d, dqkv + 2 * (size_t)d};
-    const long lds4[4] = {(long)d, 3 * (long)d, 3 * (long)d, 3 * (long)d};
-    float* dbs[4] = {(float*)dbo, (float*)dbq, (float*)dbk, (float*)dbv};
-    ProfScope ps(PF_WGRAD, st);
-    launch_colsum_multi(src, lds4, dbs, 4, R, d, 1, cpart, st, defer);
+    if (!wring) launch_wgrad_ring(own, pl, R, st);
+    if (!defer) launch_reduce_list(own_red, st);
   }
 
   if (dx) {

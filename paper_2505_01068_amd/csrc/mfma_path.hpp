@@ -57,6 +57,18 @@ void mfma_dgrad(const void* G, long ldg, const void* w0, const void* w1, const v
 size_t mfma_wgrad_partial_bytes(int M, int N, int R);
 void mfma_wgrad(const void* A, long lda, const void* G, long ldg, float* o0, float* o1, float* o2, int n_per, int M,
                 int N, int R, float* partial, hipStream_t st, ReduceList* defer = nullptr);
+// All weight gradients of a backward pass in one launch, bias gradients beside them (wgrad_ring.hip).  The plan (tile, row
+// ranges) comes from the (M, N) of ALL products that may be pushed, so that it does not depend on which gradients are
+// asked for; the operands and the partial results (wgrad_ring_bytes each) stay untouched until the caller's reduction.
+struct WgradRingItem { const bf16_t *A, *G; long lda, ldg; int M, N, tiles_n, sums; float* partial; long stride; };
+struct WgradRing { WgradRingItem item[4]; int first[4]; int n, tiles, R, per; };
+struct WgradPlan { int T, tiles, per, z; };
+WgradPlan wgrad_ring_plan_attention(int d, int R);
+WgradPlan wgrad_ring_plan_layer(int d, int d_ff, int R);
+size_t wgrad_ring_bytes(const WgradPlan& p, int M, int N);
+void wgrad_ring_push(WgradRing* l, const WgradPlan& p, ReduceList* red, const void* A, long lda, const void* G, long ldg, int M, int N,
+                     float* partial, int n_per, float* w0, float* w1, float* w2, float* b0, float* b1, float* b2);
+void launch_wgrad_ring(WgradRing& l, const WgradPlan& p, int R, hipStream_t st);
 void mfma_linear(const void* A, long lda, const void* w0, const void* w1, const void* w2, long ldb, int n_per,
                  const void* b0, const void* b1, const void* b2, int gelu, const void* res, void* C, long ldc, int M,
                  int N, int K, hipStream_t st, LnArgs ln = {nullptr, nullptr, 0.f}, void* C2 = nullptr);
@@ -99,7 +111,7 @@ void build_geo(const im_shape_t* s, int q_tile, int k_tile, Geo* g);
 bool mfma_supports(int d_model, int dh);
 size_t mfma_saved_extra_bytes(const im_shape_t* s);
 size_t mfma_fwd_workspace_bytes(int d);
-size_t mfma_bwd_workspace_bytes(const im_shape_t* s);
+size_t mfma_bwd_workspace_bytes(const im_shape_t* s, const WgradPlan* plan = nullptr);   // plan: as mfma_attention_bwd's
 
 // sv + off_* : Q|K|V rows [R,3d], O [R,d], lse [B,H,T], extra (transposed copies).
 int mfma_attention_fwd(const im_shape_t* s, const void* x, const void* wq, const void* wk, const void* wv,
@@ -115,6 +127,8 @@ int mfma_attention_bwd(const im_shape_t* s, const void* x, const void* wq, const
                        const void* wo, const int32_t* valid_len, const uint8_t* key_pad, const char* sv,
                        size_t off_qkv, size_t off_o, size_t off_lse, size_t off_extra, const void* dy, void* dx,
                        void* dwq, void* dwk, void* dwv, void* dwo, void* dbq, void* dbk, void* dbv, void* dbo, char* ws,
-                       hipStream_t st, ReduceList* defer = nullptr);   // defer: see ReduceList (small outputs only)
+                       hipStream_t st, ReduceList* defer = nullptr, WgradRing* wring = nullptr, const WgradPlan* plan = nullptr);
+// defer: see ReduceList.  wring, plan: the weight and bias gradients go onto the caller's list, which
+// has that plan and is launched before *defer; x, dy and the workspace stay as they are until then.
 
 }  // namespace imattn
