@@ -720,7 +720,7 @@ extern "C" {
 
 struct LayerTrain {
   size_t att, h, zpre, a, saved_total;                                   // saved
-  size_t u, v, dz, dv, dh, t, partial, partial1, cpart, cpart2, cpart3, attws, ws_total;   // backward workspace
+  size_t u, v, dz, dv, dh, t, partial, partial1, cpart, cpart_b2, cpart2, cpart3, attws, ws_total;   // backward workspace
   size_t fwd_ws_total;                                                   // forward workspace: u
   int split_w1, split_w2;
   bool ring;        // bf16: all weight gradients in one launch (WgradRing)
@@ -767,8 +767,9 @@ static LayerTrain layer_train_layout(const im_shape_t* s, int32_t d_ff) {
   L.partial = off; off += align256(p2);     // dW2
   L.partial1 = off; off += align256(p1);    // dW1
   L.cpart = off; off += align256(colsum_partial_bytes((int)R, (int)f));         // db1
-  L.cpart2 = off; off += align256(colsum_partial_bytes((int)R, (int)(3 * d)));  // second LayerNorm's two sums and db2
-  L.cpart3 = off; off += align256(colsum_partial_bytes((int)R, (int)(2 * d)));  // first LayerNorm's two sums
+  L.cpart_b2 = off; off += align256(colsum_partial_bytes((int)R, (int)d));      // db2
+  L.cpart2 = off; off += align256(layernorm_bwd_partial_bytes((int)R, (int)d, es == 2));   // second LayerNorm's two sums
+  L.cpart3 = off; off += align256(layernorm_bwd_partial_bytes((int)R, (int)d, es == 2));   // first LayerNorm's
   L.attws = off; off += align256(L.ring ? mfma_bwd_workspace_bytes(s, &L.plan) : bwd_workspace_bytes(s));
   L.ws_total = off;
   return L;
@@ -903,7 +904,7 @@ int gsit_layer_bwd(const im_shape_t* shape, int32_t d_ff, const void* x, const g
     g.C[0] = gr->w2; g.ldc = d; g.M = d_ff; g.N = (int)d; g.K = (int)R; g.split_k = L.split_w2; g.partial = partial;
     if ((rc = launch_gemm_alu(g, bf, bf, 0, st))) return rc;
   }
-  // (bf16 off the list: db2 = column sums of dy: taken further down, together with the second LayerNorm's parameter gradients)
+  // (bf16 off the list: db2 = column sums of dy: taken further down)
   // dz = (dy W2^T) * GELU'(z)
   if (mm) {   // GELU' in the GEMM's epilogue
     mfma_dgrad(dy, d, p->w2, nullptr, nullptr, d, 0, dz, d_ff, (int)R, d_ff, (int)d, st, zpre);
@@ -945,12 +946,14 @@ int gsit_layer_bwd(const im_shape_t* shape, int32_t d_ff, const void* x, const g
     if ((rc = launch_gemm_alu(g, bf, bf, bf, st))) return rc;
   }
   // dh = dy + LN2 backward(dv)
-  if ((rc = launch_layernorm_bwd(h, p->ln2_g, dv, dy, dh, t, (int)R, (int)d, ln_eps, bf, st))) return rc;
-  {  // gradients of the LayerNorm gain and bias: column sums of dy * xhat and of dy; and db2 = column sums of dy
-    const void* src[3] = {t, dv, dy};
-    const long ld3[3] = {d, d, d};
-    float* out3[3] = {(float*)gr->ln2_g, (float*)gr->ln2_b, bf && !L.ring ? (float*)gr->b2 : nullptr};
-    if ((rc = launch_colsum_multi(src, ld3, out3, 3, (int)R, (int)d, bf, cpart2, st, defer))) return rc;
+  if ((rc = launch_layernorm_bwd(h, p->ln2_g, dv, dy, dh, t, (int)R, (int)d, ln_eps, bf, (float*)gr->ln2_g, (float*)gr->ln2_b, cpart2,
+                                 defer, st)))
+    return rc;
+  if (gr->b2 && bf && !L.ring) {
+    const void* src[1] = {dy};
+    const long ld1[1] = {d};
+    float* out1[1] = {(float*)gr->b2};
+    if ((rc = launch_colsum_multi(src, ld1, out1, 1, (int)R, (int)d, bf, (float*)(ws + L.cpart_b2), st, defer))) return rc;
   }
   // h = x + IMAttention(u), u = LN(x; ln1): attention backward with upstream gradient dh; its dx is du (into dv)
   if ((rc = launch_layernorm(x, p->ln1_g, p->ln1_b, u, (int)R, (int)d, ln_eps, bf, st))) return rc;
@@ -966,13 +969,9 @@ int gsit_layer_bwd(const im_shape_t* shape, int32_t d_ff, const void* x, const g
   launch_wgrad_split(wl, st);
   if (L.ring) launch_wgrad_ring(wr, L.plan, (int)R, st);
   // dx = dh + LN1 backward(du)
-  if ((rc = launch_layernorm_bwd(x, p->ln1_g, dv, dh, dx, t, (int)R, (int)d, ln_eps, bf, st))) return rc;
-  {
-    const void* src[2] = {t, dv};
-    const long ld2[2] = {d, d};
-    float* out2[2] = {(float*)gr->ln1_g, (float*)gr->ln1_b};
-    if ((rc = launch_colsum_multi(src, ld2, out2, 2, (int)R, (int)d, bf, cpart3, st, defer))) return rc;
-  }
+  if ((rc = launch_layernorm_bwd(x, p->ln1_g, dv, dh, dx, t, (int)R, (int)d, ln_eps, bf, (float*)gr->ln1_g, (float*)gr->ln1_b, cpart3,
+                                 defer, st)))
+    return rc;
   launch_reduce_list(later, st);
   return check_hip("gsit_layer_bwd launch");
 }

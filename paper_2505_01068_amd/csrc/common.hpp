@@ -246,11 +246,13 @@ void wgrad_split_push(WgradSplitList* l, ReduceList* red, const float* A, long l
 void launch_wgrad_split(const WgradSplitList& l, hipStream_t st);
 
 // encoder-layer backward pieces: a = GELU(z); g <- g * GELU'(z) in place; LayerNorm backward of rows
-// (dx = input gradient + res (res may be NULL), t = dy * xhat for the gamma gradient)
+// (dx = input gradient + res (res may be NULL), t: scratch of the rows' size for dy * xhat)
 int launch_gelu_fwd(const void* z, void* a, long n, int bf16, hipStream_t st);
 int launch_gelu_bwd(const void* z, void* g, long n, int bf16, hipStream_t st);
+// gradients of gain and bias: from per-block sums in `partial` (layernorm_bwd_partial_bytes), onto the list `red` if given
+size_t layernorm_bwd_partial_bytes(int R, int d, int bf16);
 int launch_layernorm_bwd(const void* x, const void* gamma, const void* dy, const void* res, void* dx, void* t, int R,
-                         int d, float eps, int bf16, hipStream_t st);
+                         int d, float eps, int bf16, float* dgamma, float* dbeta, float* partial, ReduceList* red, hipStream_t st);
 
 void set_error(const char* fmt, ...);
 

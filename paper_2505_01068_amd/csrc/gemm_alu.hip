@@ -584,53 +584,66 @@ __global__ __launch_bounds__(256) void layernorm_kernel(const T* __restrict__ x,
   for (int e = lane; e < d; e += 64) stf(y + r * d + e, (ldf(xr + e) - mu) * rstd * ldf(gamma + e) + ldf(beta + e));
 }
 
-// bf16 rows of d = 8 LPR elements (LPR a power of two <= 32): LPR lanes share a row, each holds 8
-// consecutive elements (one 16-byte load), and a wave normalises 64 / LPR rows at once.  At d = 64 that is
-// 8 rows per wave and full-width loads and stores instead of one row and 2 bytes per lane.
+// eight bf16 (16 bytes) as fp32 and back
+__device__ __forceinline__ void unpack8(const uint4& r, float (&v)[8]) {
+  const unsigned w[4] = {r.x, r.y, r.z, r.w};
+#pragma unroll
+  for (int j = 0; j < 4; ++j) { v[2 * j] = __uint_as_float(w[j] << 16); v[2 * j + 1] = __uint_as_float(w[j] & 0xffff0000u); }
+}
+__device__ __forceinline__ uint4 pack8_rne(const float (&v)[8]) {
+  unsigned w[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) w[j] = (unsigned)f2bf(v[2 * j]) | ((unsigned)f2bf(v[2 * j + 1]) << 16);
+  return make_uint4(w[0], w[1], w[2], w[3]);
+}
+// Rows as 16-byte pieces: LPR lanes (a power of two) share a row, lane i < d / VW holds elements VW i .. VW i + VW - 1, and a
+// wave normalises 64 / LPR rows at once (d a multiple of VW = 4 fp32 or 8 bf16 elements, 16-byte aligned rows).  One row per
+// wave and one element per lane, the form above, left 24 of 64 lanes idle at d = 40 and asked for a memory round trip per
+// row: 33 600 x 40 fp32 9.8 us, 4.0 like this.
+template <typename T> struct LnVec { static constexpr int VW = 16 / sizeof(T); };
+__device__ __forceinline__ void ln_load(const float* p, float (&v)[4]) {
+  const float4 r = *(const float4*)p;
+  v[0] = r.x; v[1] = r.y; v[2] = r.z; v[3] = r.w;
+}
+__device__ __forceinline__ void ln_store(float* p, const float (&v)[4]) { *(float4*)p = make_float4(v[0], v[1], v[2], v[3]); }
+__device__ __forceinline__ void ln_load(const bf16_t* p, float (&v)[8]) { unpack8(*(const uint4*)p, v); }
+__device__ __forceinline__ void ln_store(bf16_t* p, const float (&v)[8]) { *(uint4*)p = pack8_rne(v); }
 template <int LPR>
-__global__ __launch_bounds__(256) void layernorm_rows_kernel(const bf16_t* __restrict__ x,
-                                                             const bf16_t* __restrict__ gamma,
-                                                             const bf16_t* __restrict__ beta,
-                                                             bf16_t* __restrict__ y, int R, float eps) {
-  typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-  constexpr int RPW = 64 / LPR, d = 8 * LPR;
+__device__ __forceinline__ float ln_rowsum(float v) {
+#pragma unroll
+  for (int o = LPR / 2; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+  return v;
+}
+template <typename T, int LPR>
+__global__ __launch_bounds__(256) void layernorm_rows_kernel(const T* __restrict__ x, const T* __restrict__ gamma,
+                                                             const T* __restrict__ beta, T* __restrict__ y, int R, int d, float eps) {
+  constexpr int VW = LnVec<T>::VW, RPW = 64 / LPR;
   const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
   const long r = ((long)blockIdx.x * 4 + wave) * RPW + lane / LPR;
-  const int c = (lane % LPR) * 8;
-  const bool live = r < R;
-  float v[8], gm[8], bt[8];
-  {
-    u32x4 raw = {0u, 0u, 0u, 0u};
-    if (live) raw = *(const u32x4*)(x + r * d + c);
-    const u32x4 gr = *(const u32x4*)(gamma + c), br = *(const u32x4*)(beta + c);
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      v[2 * j] = __uint_as_float(raw[j] << 16); v[2 * j + 1] = __uint_as_float(raw[j] & 0xffff0000u);
-      gm[2 * j] = __uint_as_float(gr[j] << 16); gm[2 * j + 1] = __uint_as_float(gr[j] & 0xffff0000u);
-      bt[2 * j] = __uint_as_float(br[j] << 16); bt[2 * j + 1] = __uint_as_float(br[j] & 0xffff0000u);
-    }
-  }
+  const bool in = (lane % LPR) * VW < d;
+  const int c = in ? (lane % LPR) * VW : 0;
+  const long at = min(r, (long)R - 1) * d + c;
+  float v[VW], gm[VW], bt[VW];
+  ln_load(x + at, v);
+  ln_load(gamma + c, gm);
+  ln_load(beta + c, bt);
   float s = 0.f;
 #pragma unroll
-  for (int j = 0; j < 8; ++j) s += v[j];
-#pragma unroll
-  for (int o = LPR / 2; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
-  const float mu = s * (1.f / d);
+  for (int j = 0; j < VW; ++j) s += v[j];
+  const float mu = ln_rowsum<LPR>(in ? s : 0.f) / d;
   float q = 0.f;
 #pragma unroll
-  for (int j = 0; j < 8; ++j) { const float t = v[j] - mu; q = fmaf(t, t, q); }
+  for (int j = 0; j < VW; ++j) { const float t = v[j] - mu; q = fmaf(t, t, q); }
+  const float rstd = rsqrtf(ln_rowsum<LPR>(in ? q : 0.f) / d + eps);
+  if (r >= R || !in) return;
 #pragma unroll
-  for (int o = LPR / 2; o > 0; o >>= 1) q += __shfl_xor(q, o, 64);
-  const float rstd = rsqrtf(q * (1.f / d) + eps);
-  if (!live) return;
-  u32x4 out;
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const float a = (v[2 * j] - mu) * rstd * gm[2 * j] + bt[2 * j], b = (v[2 * j + 1] - mu) * rstd * gm[2 * j + 1] + bt[2 * j + 1];
-    out[j] = (unsigned)f2bf(a) | ((unsigned)f2bf(b) << 16);
-  }
-  *(u32x4*)(y + r * d + c) = out;
+  for (int j = 0; j < VW; ++j) v[j] = (v[j] - mu) * rstd * gm[j] + bt[j];
+  ln_store(y + at, v);
 }
+// lanes per row for rows of n 16-byte pieces (0: more than a wave)
+static int ln_lanes(int n) { return n <= 8 ? 8 : n <= 16 ? 16 : n <= 32 ? 32 : n <= 64 ? 64 : 0; }
+#define LN_LANES(LPR, CALL) \
+  do { if (LPR == 8) { CALL(8); } else if (LPR == 16) { CALL(16); } else if (LPR == 32) { CALL(32); } else { CALL(64); } } while (0)
 
 // ---- pieces of the encoder-layer backward ----
 __device__ __forceinline__ float gelu_f(float z) { return 0.5f * z * (1.f + erff(z * 0.70710678118654752440f)); }
@@ -646,18 +659,6 @@ template <typename T>
 __global__ void gelu_bwd_kernel(const T* __restrict__ z, T* __restrict__ g, long n) {  // g: da in, dz out
   for (long i = blockIdx.x * (long)blockDim.x + threadIdx.x; i < n; i += (long)gridDim.x * blockDim.x)
     stf(g + i, ldf(g + i) * gelu_grad_f(ldf(z + i)));
-}
-// bf16, 8 elements (16 bytes) per thread and step
-__device__ __forceinline__ void unpack8(const uint4& r, float (&v)[8]) {
-  const unsigned w[4] = {r.x, r.y, r.z, r.w};
-#pragma unroll
-  for (int j = 0; j < 4; ++j) { v[2 * j] = __uint_as_float(w[j] << 16); v[2 * j + 1] = __uint_as_float(w[j] & 0xffff0000u); }
-}
-__device__ __forceinline__ uint4 pack8_rne(const float (&v)[8]) {
-  unsigned w[4];
-#pragma unroll
-  for (int j = 0; j < 4; ++j) w[j] = (unsigned)f2bf(v[2 * j]) | ((unsigned)f2bf(v[2 * j + 1]) << 16);
-  return make_uint4(w[0], w[1], w[2], w[3]);
 }
 // Phi(x), the standard normal CDF, with erf from Abramowitz & Stegun 7.1.26 (|error| <= 1.5e-7, far below the
 // bf16 rounding of the results): a reciprocal, an exp2 and six multiply-adds instead of the library erff.
@@ -756,67 +757,121 @@ __global__ __launch_bounds__(256) void layernorm_bwd_kernel(const T* __restrict_
     stf(t + r * d + e, g * xh);
   }
 }
-// The same for bf16 rows of d = 8 LPR elements, LPR lanes per row and 64 / LPR rows per wave (see layernorm_rows_kernel).
-template <int LPR>
-__global__ __launch_bounds__(256) void layernorm_bwd_rows_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ gamma,
-                                                                 const bf16_t* __restrict__ dy, const bf16_t* __restrict__ res,
-                                                                 bf16_t* __restrict__ dx, bf16_t* __restrict__ t, int R,
-                                                                 float eps) {
-  constexpr int RPW = 64 / LPR, d = 8 * LPR;
+// The same in 16-byte pieces (see layernorm_rows_kernel), and the column sums with it: a workgroup takes `rows` rows, a
+// lane adds g xhat and g of its columns over its rows in fp32, and the block's sums leave as one partial result
+// [2][d] (gain, bias).  The next rows are requested before the present ones are used.  Without it the gain's products went
+// to memory, rounded to the tensor type, and were read back with dy by two more launches: 33 600 x 40 fp32 15.5 + 4.8 us, 8.0 like this.
+template <typename T, int LPR>
+__global__ __launch_bounds__(256) void layernorm_bwd_rows_kernel(const T* __restrict__ x, const T* __restrict__ gamma,
+                                                                 const T* __restrict__ dy, const T* __restrict__ res,
+                                                                 T* __restrict__ dx, float* __restrict__ partial, int R, int d,
+                                                                 float eps, int rows) {
+  constexpr int VW = LnVec<T>::VW, RPW = 64 / LPR, STEP = 4 * RPW;
+  __shared__ float red[4][2][LPR * VW];
   const int wave = threadIdx.x / 64, lane = threadIdx.x % 64;
-  const long r = ((long)blockIdx.x * 4 + wave) * RPW + lane / LPR;
-  const int c = (lane % LPR) * 8;
-  const bool live = r < R;
-  const long at = (live ? r : 0) * d + c;
-  float xv[8], gv[8], gm[8], rs[8];
-  unpack8(*(const uint4*)(x + at), xv);
-  unpack8(*(const uint4*)(dy + at), gv);
-  unpack8(*(const uint4*)(gamma + c), gm);
-  if (res) unpack8(*(const uint4*)(res + at), rs);
-  auto rowsum = [&](float v) {
+  const bool in = (lane % LPR) * VW < d;
+  const int c = in ? (lane % LPR) * VW : 0;
+  const long r0 = (long)blockIdx.x * rows + wave * RPW + lane / LPR;   // rows % STEP == 0
+  float gm[VW], sg[VW], sb[VW], xn[VW], gn[VW], rn[VW];
+  ln_load(gamma + c, gm);
 #pragma unroll
-    for (int o = LPR / 2; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
+  for (int j = 0; j < VW; ++j) sg[j] = sb[j] = rn[j] = 0.f;
+  auto request = [&](long r) {
+    const long at = min(r, (long)R - 1) * d + c;
+    ln_load(x + at, xn);
+    ln_load(dy + at, gn);
+    if (res) ln_load(res + at, rn);
   };
-  float s = 0.f;
+  request(r0);
+  for (int k = 0; k < rows; k += STEP) {
+    const long r = r0 + k;
+    float xv[VW], g[VW], rs[VW];
 #pragma unroll
-  for (int j = 0; j < 8; ++j) s += xv[j];
-  const float mu = rowsum(s) * (1.f / d);
-  float q = 0.f;
+    for (int j = 0; j < VW; ++j) {
+      xv[j] = xn[j];
+      g[j] = gn[j];
+      rs[j] = rn[j];
+    }
+    if (k + STEP < rows) request(r + STEP);
+    float s = 0.f, q = 0.f, m1 = 0.f, m2 = 0.f, a[VW];
 #pragma unroll
-  for (int j = 0; j < 8; ++j) { const float w = xv[j] - mu; q = fmaf(w, w, q); }
-  const float rstd = rsqrtf(rowsum(q) * (1.f / d) + eps);
-  float m1 = 0.f, m2 = 0.f, xh[8], a[8];
+    for (int j = 0; j < VW; ++j) s += xv[j];
+    const float mu = ln_rowsum<LPR>(in ? s : 0.f) / d;
 #pragma unroll
-  for (int j = 0; j < 8; ++j) {
-    a[j] = gm[j] * gv[j];
-    xh[j] = (xv[j] - mu) * rstd;
-    m1 += a[j];
-    m2 = fmaf(a[j], xh[j], m2);
+    for (int j = 0; j < VW; ++j) {
+      xv[j] -= mu;
+      q = fmaf(xv[j], xv[j], q);
+    }
+    const float rstd = rsqrtf(ln_rowsum<LPR>(in ? q : 0.f) / d + eps);
+#pragma unroll
+    for (int j = 0; j < VW; ++j) {
+      xv[j] *= rstd;   // xhat
+      a[j] = gm[j] * g[j];
+      m1 += a[j];
+      m2 = fmaf(a[j], xv[j], m2);
+    }
+    m1 = ln_rowsum<LPR>(in ? m1 : 0.f) / d;
+    m2 = ln_rowsum<LPR>(in ? m2 : 0.f) / d;
+    if (r >= R || !in) continue;
+#pragma unroll
+    for (int j = 0; j < VW; ++j) {
+      sg[j] += g[j] * xv[j];
+      sb[j] += g[j];
+      a[j] = rstd * (a[j] - m1 - xv[j] * m2) + rs[j];
+    }
+    ln_store(dx + r * d + c, a);
   }
-  m1 = rowsum(m1) * (1.f / d);
-  m2 = rowsum(m2) * (1.f / d);
-  if (!live) return;
-  float o1[8], o2[8];
 #pragma unroll
-  for (int j = 0; j < 8; ++j) {
-    o1[j] = rstd * (a[j] - m1 - xh[j] * m2) + (res ? rs[j] : 0.f);
-    o2[j] = gv[j] * xh[j];
+  for (int j = 0; j < VW; ++j)
+#pragma unroll
+    for (int o = LPR; o < 64; o <<= 1) {
+      sg[j] += __shfl_xor(sg[j], o, 64);
+      sb[j] += __shfl_xor(sb[j], o, 64);
+    }
+  if (lane < LPR)
+#pragma unroll
+    for (int j = 0; j < VW; ++j) {
+      red[wave][0][lane * VW + j] = sg[j];
+      red[wave][1][lane * VW + j] = sb[j];
+    }
+  __syncthreads();
+  for (int i = threadIdx.x; i < 2 * d; i += 256) {
+    const int w = i >= d, e = i - (w ? d : 0);
+    partial[(long)blockIdx.x * 2 * d + i] = (red[0][w][e] + red[1][w][e]) + (red[2][w][e] + red[3][w][e]);
   }
-  *(uint4*)(dx + at) = pack8_rne(o1);
-  *(uint4*)(t + at) = pack8_rne(o2);
+}
+// Rows per workgroup: two workgroups per CU, one to sixteen passes of its waves each (layer step at 8 400 x 256 bf16: 245 us
+// with 132 workgroups of 64 rows, 227 with 525 of 16).
+static int lnb_rows(int R, int lpr) {
+  const int step = 4 * (64 / lpr);
+  return step * std::max(1, std::min(16, R / (512 * step)));
+}
+size_t layernorm_bwd_partial_bytes(int R, int d, int bf16) {
+  const int vw = bf16 ? 8 : 4, lpr = d % vw == 0 ? ln_lanes(d / vw) : 0;
+  size_t n = 2 * colsum_partial_bytes(R, d);   // where the kernel above does not serve the call
+  if (lpr) n = std::max(n, (size_t)((R + lnb_rows(R, lpr) - 1) / lnb_rows(R, lpr)) * 2 * d * sizeof(float));
+  return n;
 }
 int launch_layernorm_bwd(const void* x, const void* gamma, const void* dy, const void* res, void* dx, void* t, int R,
-                         int d, float eps, int bf16, hipStream_t st) {
+                         int d, float eps, int bf16, float* dgamma, float* dbeta, float* partial, ReduceList* red, hipStream_t st) {
   dim3 grid((R + 3) / 4), block(256);
-  const uintptr_t al = (uintptr_t)x | (uintptr_t)gamma | (uintptr_t)dy | (uintptr_t)res | (uintptr_t)dx | (uintptr_t)t;
-  if (bf16 && (al & 15) == 0 && (d == 64 || d == 128 || d == 256)) {
-    const int lpr = d / 8, rows_per_block = 4 * (64 / lpr);
-    const dim3 g2((R + rows_per_block - 1) / rows_per_block);
-#define LNB_ROWS(L) hipLaunchKernelGGL((layernorm_bwd_rows_kernel<L>), g2, block, 0, st, (const bf16_t*)x, (const bf16_t*)gamma, \
-                                       (const bf16_t*)dy, (const bf16_t*)res, (bf16_t*)dx, (bf16_t*)t, R, eps)
-    if (lpr == 8) LNB_ROWS(8); else if (lpr == 16) LNB_ROWS(16); else LNB_ROWS(32);
-#undef LNB_ROWS
+  const uintptr_t al = (uintptr_t)x | (uintptr_t)gamma | (uintptr_t)dy | (uintptr_t)res | (uintptr_t)dx;
+  const int vw = bf16 ? 8 : 4, lpr = d % vw == 0 ? ln_lanes(d / vw) : 0;
+  if (lpr && (al & 15) == 0) {
+    const int rows = lnb_rows(R, lpr), blocks = (R + rows - 1) / rows;
+#define LNB_BF16(N) hipLaunchKernelGGL((layernorm_bwd_rows_kernel<bf16_t, N>), dim3(blocks), block, 0, st, (const bf16_t*)x, \
+                    (const bf16_t*)gamma, (const bf16_t*)dy, (const bf16_t*)res, (bf16_t*)dx, partial, R, d, eps, rows)
+#define LNB_F32(N) hipLaunchKernelGGL((layernorm_bwd_rows_kernel<float, N>), dim3(blocks), block, 0, st, (const float*)x, \
+                   (const float*)gamma, (const float*)dy, (const float*)res, (float*)dx, partial, R, d, eps, rows)
+    if (bf16) LN_LANES(lpr, LNB_BF16); else LN_LANES(lpr, LNB_F32);
+#undef LNB_BF16
+#undef LNB_F32
+    ReduceList own;
+    own.n = 0;
+    ReduceList* l = red && red->n + 2 <= 16 ? red : &own;
+    if (dgamma) reduce_push(l, partial, blocks, 1, d, dgamma, nullptr, nullptr, 0, 2 * d);
+    if (dbeta) reduce_push(l, partial + d, blocks, 1, d, dbeta, nullptr, nullptr, 0, 2 * d);
+    launch_reduce_list(own, st);
     return IM_OK;
   }
   if (bf16)
@@ -825,20 +880,27 @@ int launch_layernorm_bwd(const void* x, const void* gamma, const void* dy, const
   else
     hipLaunchKernelGGL((layernorm_bwd_kernel<float>), grid, block, 0, st, (const float*)x, (const float*)gamma,
                        (const float*)dy, (const float*)res, (float*)dx, (float*)t, R, d, eps);
-  return IM_OK;
+  const void* src[2] = {t, dy};
+  const long ld2[2] = {d, d};
+  float* out[2] = {dgamma, dbeta};
+  return launch_colsum_multi(src, ld2, out, 2, R, d, bf16, partial, st, red);
 }
 
 int launch_layernorm(const void* x, const void* gamma, const void* beta, void* y, int R, int d, float eps, int bf16,
                      hipStream_t st) {
   dim3 grid((R + 3) / 4), block(256);
   const bool aligned = (((uintptr_t)x | (uintptr_t)y | (uintptr_t)gamma | (uintptr_t)beta) & 15) == 0;
-  if (bf16 && aligned && (d == 64 || d == 128 || d == 256)) {
-    const int lpr = d / 8, rows_per_block = 4 * (64 / lpr);
+  const int vw = bf16 ? 8 : 4, lpr = d % vw == 0 ? ln_lanes(d / vw) : 0;
+  if (lpr && aligned) {
+    const int rows_per_block = 4 * (64 / lpr);
     const dim3 g2((R + rows_per_block - 1) / rows_per_block);
-#define LN_ROWS(L) hipLaunchKernelGGL((layernorm_rows_kernel<L>), g2, block, 0, st, (const bf16_t*)x, (const bf16_t*)gamma, \
-                                      (const bf16_t*)beta, (bf16_t*)y, R, eps)
-    if (lpr == 8) LN_ROWS(8); else if (lpr == 16) LN_ROWS(16); else LN_ROWS(32);
-#undef LN_ROWS
+#define LN_BF16(N) hipLaunchKernelGGL((layernorm_rows_kernel<bf16_t, N>), g2, block, 0, st, (const bf16_t*)x, (const bf16_t*)gamma, \
+                                      (const bf16_t*)beta, (bf16_t*)y, R, d, eps)
+#define LN_F32(N) hipLaunchKernelGGL((layernorm_rows_kernel<float, N>), g2, block, 0, st, (const float*)x, (const float*)gamma, \
+                                     (const float*)beta, (float*)y, R, d, eps)
+    if (bf16) LN_LANES(lpr, LN_BF16); else LN_LANES(lpr, LN_F32);
+#undef LN_BF16
+#undef LN_F32
     return IM_OK;
   }
   if (bf16)
