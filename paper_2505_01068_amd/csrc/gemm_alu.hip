@@ -446,8 +446,9 @@ size_t colsum_partial_bytes(int R, int n) { return (size_t)((R + CS_ROWS - 1) / 
 
 // One launch for a list of second-stage sums.  A block is 16 output quads x 16 lanes over the
 // partials: lane zl adds partials zl, zl + 16, ... in ascending order, then the 16 lane sums are added in a fixed
-// order through LDS -- the same order as colsum_stage2 and the parallel split-K reduction use on their own.  With at most
-// 8, 4 or 2 partials a block is 32, 64 or 128 quads x that many lanes: none would have more than one partial anyway.
+// order through LDS -- the same order as colsum_stage2 and the parallel split-K reduction use on their own.  Fewer lanes share
+// a quad (8, 4 or 2, with as many times the quads per block) where no lane would have a second partial otherwise, or where the
+// output alone fills the chip: 786 432 sums of 10 partials took 19 us with 16 lanes, six of them idle.
 // ODD: some job's rows or column blocks are not whole quads.
 template <bool ODD>
 __global__ __launch_bounds__(256) void reduce_list_kernel(ReduceList l) {
@@ -461,17 +462,14 @@ __global__ __launch_bounds__(256) void reduce_list_kernel(ReduceList l) {
   const long i = ((long)((int)blockIdx.x - l.first[ji]) * quads + ql) * 4;
   float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
   if (i < n_out) {
-    int z = zl;
-    for (; z + 48 < j.nparts; z += 64) {   // four requests in flight; added in the same ascending order
+    const int np = j.nparts;
+    for (int z = zl; z < np; z += 4 * lanes) {   // four requests in flight; added in ascending order
       float4 v[4];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) v[u] = *(const float4*)(j.partial + (z + 16 * u) * j.stride + i);
+      for (int u = 0; u < 4; ++u) v[u] = *(const float4*)(j.partial + min(z + u * lanes, np - 1) * j.stride + i);
 #pragma unroll
-      for (int u = 0; u < 4; ++u) { s.x += v[u].x; s.y += v[u].y; s.z += v[u].z; s.w += v[u].w; }
-    }
-    for (; z < j.nparts; z += 16) {
-      const float4 v = *(const float4*)(j.partial + z * j.stride + i);
-      s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
+      for (int u = 0; u < 4; ++u)
+        if (z + u * lanes < np) { s.x += v[u].x; s.y += v[u].y; s.z += v[u].z; s.w += v[u].w; }
     }
   }
   red[threadIdx.x] = s;
@@ -519,7 +517,10 @@ void launch_reduce_list(ReduceList& l, hipStream_t st) {
   bool odd = false;
   for (int i = 0; i < l.n; ++i) {
     const int np = l.job[i].nparts;
-    l.lanes[i] = np > 8 ? 16 : np > 4 ? 8 : np > 2 ? 4 : 2;
+    const long quads = ((long)l.job[i].M * l.job[i].N + 3) / 4;
+    int lanes = 16;
+    while (lanes > 2 && (lanes / 2 >= np || quads * lanes > 131072)) lanes /= 2;   // 131 072 threads: eight waves per CU
+    l.lanes[i] = lanes;
     l.first[i] = blocks;
     const long per = 4 * 256 / l.lanes[i];
     blocks += (int)(((long)l.job[i].M * l.job[i].N + per - 1) / per);
