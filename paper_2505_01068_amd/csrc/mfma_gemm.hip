@@ -111,9 +111,7 @@ __device__ __forceinline__ void store_km(const Tile128& t, bf16_t* lds, int tid)
 // (K == 64): the 8 lanes that hold a row (8 elements each) share its mean and variance through three
 // shuffles; two-pass in fp32 and rounded to bf16 exactly as the stand-alone kernel does.
 template <int U>
-__device__ __forceinline__ void ln_tile_rows(TileRegs<U>& t, const bf16_t* gamma, const bf16_t* beta, float eps, int tid) {
-  const int c = (tid & 7) * 8;
-  const u32x4 gr = *(const u32x4*)(gamma + c), br = *(const u32x4*)(beta + c);
+__device__ __forceinline__ void ln_tile_rows(TileRegs<U>& t, u32x4 gr, u32x4 br, float eps) {   // gr, br: the lane's gain and bias
 #pragma unroll
   for (int u = 0; u < U; ++u) {
     float v[8];
@@ -244,7 +242,8 @@ __device__ __forceinline__ void mfma_gemm_tile(const MGemm& p, int bx, int by, i
     if constexpr (AKM) load_km(ta, amat, 0, p.lda, k0, p.K, m0, p.M, tid);
     else {
       load_mm(ta, pA, p.lda, m0, p.M - 1, k0, p.K, tid);
-      if (pln_g) ln_tile_rows(ta, pln_g, pln_b, p.ln_eps, tid);  // K == 64: this is the only k-tile
+      if (pln_g)   // K == 64: this is the only k-tile
+        ln_tile_rows(ta, *(const u32x4*)(pln_g + (tid & 7) * 8), *(const u32x4*)(pln_b + (tid & 7) * 8), p.ln_eps);
     }
     if (BKM) {
       load_km(tb, bmat, p.b_nper, p.ldb, k0, p.K, n0, p.N, tid);
@@ -408,7 +407,9 @@ __global__ __launch_bounds__(256, 3) void mfma_gemm_pair_kernel(MGemm p) {
 // output leaves through LDS as fp32 (GELU, GELU' and the residual act on unrounded sums), eight lanes to a
 // 128-byte row segment, and the residual is read in the same coalesced form.
 // Row-major tiles: 128-byte rows, chunk c of row r at c ^ sw_f(r); k-major tile [64][16 chunks]: chunk c of row k at
-// c ^ ((k & 3) << 2).  k order and rounding are those of the kernel above: results are bit for bit the same.
+// c ^ ((k & 3) << 2).  LN (K == 64): the rows of A are normalised in LDS before they are multiplied (first MLP product of a
+// width-64 layer with GELU_BOTH, 29 600 x 256: 18.9 us in the register-staged kernel, 15.2 here).
+// k order and rounding are those of the kernel above: results are bit for bit the same.
 // Measured against the better of the two kernels it replaced here: 8 400 x 256 x 1024 + residual 33.8 -> 13.6 us,
 // 8 400 x 256 x 256 + residual 18.7 -> 7.1, 8 400 x 1024 x 256 with GELU' 23.6 -> 15.7, 29 600 x 64 x 256 + residual
 // 10.3 -> 7.2, 4 000 x 512 x 2048 + residual 55 -> 21, 16 000 x 1536 x 512 41 -> 36.  Three, four or six stages (one or two
@@ -417,8 +418,9 @@ constexpr int RK = 64;
 constexpr int ring_stage_bytes(int mb) { return (64 * mb + GN) * RK * 2; }
 constexpr int ring_lds_bytes(int mb) { return 2 * ring_stage_bytes(mb); }
 
-template <bool BKM, bool EPI, int MB>
+template <bool BKM, bool EPI, int MB, bool LN = false>
 __global__ __launch_bounds__(256, 2) void mfma_gemm_ring_kernel(MGemm p) {
+  static_assert(!LN || MB == 1, "the LayerNorm form: 64 rows, two per thread");
   extern __shared__ __attribute__((aligned(1024))) bf16_t smem[];
   constexpr int ROWS = 64 * MB, STB = ring_stage_bytes(MB);
   constexpr int CA = 2 * MB, CB = 4;   // 16-byte chunks per thread, operand and stage
@@ -476,6 +478,11 @@ __global__ __launch_bounds__(256, 2) void mfma_gemm_ring_kernel(MGemm p) {
   };
 
   issue(0);
+  u32x4 lng, lnb;
+  if constexpr (LN) {
+    lng = *(const u32x4*)(p.ln_g + (tid & 7) * 8);
+    lnb = *(const u32x4*)(p.ln_b + (tid & 7) * 8);
+  }
   f32x16 acc[2][MB];   // [n block][m block], registers 4i..4i+3 = columns n = 8i + 4hi + 0..3; start at the bias
   {
     int nq[8];
@@ -505,8 +512,22 @@ __global__ __launch_bounds__(256, 2) void mfma_gemm_ring_kernel(MGemm p) {
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
     if (it + 1 < n_it) issue(it + 1);
-    const char* st = (const char*)smem + (it & 1) * STB;
+    char* st = (char*)smem + (it & 1) * STB;
     const bf16_t* sA = (const bf16_t*)st;
+    if constexpr (LN) {   // eight lanes per row, two rows per lane
+      TileRegs<2> t;
+      bf16_t* at[2];
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        const int r = (tid >> 3) + 32 * u;
+        at[u] = (bf16_t*)st + r * SW_LD + (((tid & 7) ^ sw_f(r)) << 3);
+        t.v[u] = *(const u32x4*)at[u];
+      }
+      ln_tile_rows(t, lng, lnb, p.ln_eps);
+#pragma unroll
+      for (int u = 0; u < 2; ++u) *(u32x4*)at[u] = t.v[u];
+      __syncthreads();
+    }
     const char* sB = st + ROWS * RK * 2;
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
@@ -1720,22 +1741,17 @@ static void launch_dma12(const MGemm& p, hipStream_t st) {
   dim3 grid((p.N + DN - 1) / DN, (p.M + TM - 1) / TM, 1);
   hipLaunchKernelGGL((mfma_gemm_dma12_kernel), grid, dim3(TWAVES * 64), T_LDS_BYTES, st, p);
 }
-template <bool BKM, bool EPI, int MB>
+template <bool BKM, bool EPI, int MB, bool LN = false>
 static void launch_ring(const MGemm& p, hipStream_t st) {
-  static bool configured = false;
-  if (!configured) {
-    (void)hipFuncSetAttribute((const void*)mfma_gemm_ring_kernel<BKM, EPI, MB>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                              ring_lds_bytes(MB));
-    configured = true;
-  }
+  static_assert(ring_lds_bytes(MB) <= 65536, "no attribute is needed up to 64 KB");
   dim3 grid((p.N + GN - 1) / GN, (p.M + 64 * MB - 1) / (64 * MB), 1);
-  hipLaunchKernelGGL((mfma_gemm_ring_kernel<BKM, EPI, MB>), grid, dim3(256), ring_lds_bytes(MB), st, p);
+  hipLaunchKernelGGL((mfma_gemm_ring_kernel<BKM, EPI, MB, LN>), grid, dim3(256), ring_lds_bytes(MB), st, p);
 }
 // Forms the ring kernel takes: row-major A, whole 64-deep k-tiles (per weight, where K is split over several) and
 // everything it copies or stores in 16-byte units aligned to that.
 static bool ring_form(const MGemm& p) {
   auto al16 = [](const void* q) { return (reinterpret_cast<uintptr_t>(q) & 15) == 0; };
-  return !p.a_kmajor && p.split_k == 1 && !p.partial && !p.ln_g && p.K >= RK && p.K % RK == 0 && p.M >= 1 && p.N >= 8 &&
+  return !p.a_kmajor && p.split_k == 1 && !p.partial && (!p.ln_g || (p.K == RK && al16(p.ln_g) && al16(p.ln_b))) && p.K >= RK && p.K % RK == 0 && p.M >= 1 && p.N >= 8 &&
          p.N % 8 == 0 && p.lda % 8 == 0 && p.ldb % 8 == 0 && p.ldc % 8 == 0 && p.b_kper % RK == 0 && p.b_nper % 8 == 0 &&
          (!p.scale0_on || p.n_per % 8 == 0) && al16(p.A) && al16(p.B[0]) && al16(p.B[1]) && al16(p.B[2]) && al16(p.C) &&
          al16(p.C2) && al16(p.res);
@@ -1751,7 +1767,14 @@ template <bool AKM, bool BKM>
 static void launch_layout(const MGemm& p, bool dma, hipStream_t st) {
   const bool epi = p.gelu || p.res != nullptr;
   if constexpr (!AKM) {
-    if (ring_form(p) && !(BKM && dma && large_tiles_fill(p))) {
+    if (ring_form(p) && (BKM || !p.ln_g) && !(BKM && dma && large_tiles_fill(p))) {
+      if constexpr (BKM) {
+        if (p.ln_g) {
+          if (epi) launch_ring<true, true, 1, true>(p, st);
+          else launch_ring<true, false, 1, true>(p, st);
+          return;
+        }
+      }
       if (ring_rows128(p)) {
         if (epi) launch_ring<BKM, true, 2>(p, st);
         else launch_ring<BKM, false, 2>(p, st);
