@@ -448,7 +448,8 @@ size_t colsum_partial_bytes(int R, int n) { return (size_t)((R + CS_ROWS - 1) / 
 // partials: lane zl adds partials zl, zl + 16, ... in ascending order, then the 16 lane sums are added in a fixed
 // order through LDS -- the same order as colsum_stage2 and the parallel split-K reduction use on their own.  Fewer lanes share
 // a quad (8, 4 or 2, with as many times the quads per block) where no lane would have a second partial otherwise, or where the
-// output alone fills the chip: 786 432 sums of 10 partials took 19 us with 16 lanes, six of them idle.
+// output alone fills the chip: 786 432 sums of 10 partials took 19 us with 16 lanes, six of them idle.  More than 256
+// partials are shared by 32 or 64 lanes: 925 of them are 15 trips to memory, one after the other, for 16 lanes.
 // ODD: some job's rows or column blocks are not whole quads.
 template <bool ODD>
 __global__ __launch_bounds__(256) void reduce_list_kernel(ReduceList l) {
@@ -519,6 +520,7 @@ void launch_reduce_list(ReduceList& l, hipStream_t st) {
     const int np = l.job[i].nparts;
     const long quads = ((long)l.job[i].M * l.job[i].N + 3) / 4;
     int lanes = 16;
+    while (lanes < 64 && np > 16 * lanes) lanes *= 2;
     while (lanes > 2 && (lanes / 2 >= np || quads * lanes > 131072)) lanes /= 2;   // 131 072 threads: eight waves per CU
     l.lanes[i] = lanes;
     l.first[i] = blocks;
