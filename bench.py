@@ -224,9 +224,9 @@ def roofline_of(dom, fr, bf16_mfma, peaks, traffic, traffic_src, dom_launches, s
                 "unit": "TFLOP/s", "frac": e["frac"], "frac_of_published_peak": e["frac_of_published_peak"],
                 "traffic": traffic, "traffic_source": traffic_src,
                 "avg_launch_ms": round(e["ms"] / max(dom_launches, 1.0), 4),
-                "note": "row-per-lane fp32 kernels: fused multiply-adds of the products counted, exp and softmax bookkeeping "
-                        "not; peak = fp32 vector rate without packed instructions (256 CU x 64 lanes x 2 flop x 2.4 GHz), "
-                        "the published 157.3 TFLOP/s assumes packed fp32, which the library is compiled without"}
+                "note": "fp32 operands as three bf16 parts on the matrix cores: fp32 multiply-adds of the products counted, exp and "
+                        "softmax bookkeeping not; peak = fp32 vector rate without packed instructions (256 CU x 64 lanes x 2 flop "
+                        "x 2.4 GHz), the vector ALU's issue being what bounds these kernels (exp2, splitting of the probabilities)"}
     return roof
 
 
