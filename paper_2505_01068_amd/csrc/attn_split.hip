@@ -12,7 +12,7 @@
 //            ONE instruction (dh <= 5; two for dh <= 10).
 //   P V:     the three parts of V's columns are rows of the A operand (3 dh <= 16 rows: one instruction for all three),
 //            and the probabilities' three parts are three B operands.
-// One slot of the score product is left for the key mask (1 on the query side, 0 or -1e30 on the key side), one row of
+// One slot of the score product is left for the key mask (1 on the query side, 0 or -inf on the key side), one row of
 // the P V product is all ones (the row sum).
 //
 // Bound: vector-instruction issue.  Per score the forward has one exp2, half a max and 5.5 instructions that split the
@@ -50,8 +50,7 @@ struct SplitCfg {
   static constexpr int BLK = NS * 64 + 8;               // 16-byte units of a 16-row score-operand block; the 8 spread
                                                         // the two blocks of a step over the banks (writer's side)
 };
-constexpr float SPLIT_MASKED = -1e30f;    // mask slot of a key that must not be attended
-constexpr float SPLIT_UNSET = -1e29f;     // "no valid key seen yet" threshold: above every masked score, below any other
+constexpr float SPLIT_MASKED = -__builtin_inff();   // mask slot of a key that must not be attended: whatever the key's row holds
 constexpr float SPLIT_LAZY = 8.f;         // the softmax reference moves when a score exceeds it by 2^8
 
 __device__ __forceinline__ f32x4 mfma16(bf16x8 a, bf16x8 b, f32x4 c) {
@@ -404,7 +403,7 @@ void split_fwd_kernel(SplitGeo g, int tile_base, const T* __restrict__ Q, const 
         for (int i = 1; i < 8; ++i) mx = fmaxf(mx, e[i]);
         mx = fmaxf(mx, __shfl_xor(mx, 16));
         mx = fmaxf(mx, __shfl_xor(mx, 32));
-        const bool unset = thr == INT_MIN, move = mx > (unset ? SPLIT_UNSET : SPLIT_LAZY);
+        const bool unset = thr == INT_MIN, move = mx > (unset ? IM_NEG_INF : SPLIT_LAZY);
         const float by = move ? mx : 0.f;
         const float alpha = __builtin_amdgcn_exp2f(unset ? 0.f : -by);
 #pragma unroll
