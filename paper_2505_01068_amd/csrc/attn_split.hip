@@ -378,7 +378,7 @@ void split_fwd_kernel(SplitGeo g, int tile_base, const T* __restrict__ Q, const 
 #pragma unroll
   for (int rb = 0; rb < NTB; ++rb) acc[rb] = f32x4{0.f, 0.f, 0.f, 0.f};
   float m = 0.f;
-  int thr = INT_MIN;   // bits of the exponent above which the reference moves; INT_MIN: the row has no reference yet
+  int thr = INT_MIN;   // bits of the exponent from which the reference moves; INT_MIN: the row has no reference yet
   auto steps = [&](const u32x4* sS, int nst) {
     const bf16_t* const sT = (const bf16_t*)(sS + S_UNITS);
     for (int st = 0; st < nst; ++st) {
@@ -397,7 +397,8 @@ void split_fwd_kernel(SplitGeo g, int tile_base, const T* __restrict__ Q, const 
       }
 #pragma unroll
       for (int i = 0; i < 8; ++i) big = max(big, __float_as_int(e[i]));
-      if (__builtin_amdgcn_ballot_w64(big > thr)) {   // rare: no reference yet, or a score 2^8 above it
+      // rare: no reference yet (>=: a score of -0.0 has the bits of INT_MIN), or a score 2^8 above it
+      if (__builtin_amdgcn_ballot_w64(big >= thr)) {
         float mx = e[0];
 #pragma unroll
         for (int i = 1; i < 8; ++i) mx = fmaxf(mx, e[i]);

@@ -74,3 +74,15 @@ def test_bias_gradients_collect_no_rounding():
         err = np.linalg.norm(grads[k].double().cpu().numpy() - r) / np.linalg.norm(r)
         say(f"    {k} {err:.1e}")
         assert err < 1.4e-6, (k, err)
+
+
+def test_zero_scores_before_the_first_large_one():
+    # Leading zero rows without a mask and without a key bias: the first 32 keys of every segment give exactly zero scores, of
+    # either sign of zero.  They enter the sum with weight one and must be rescaled when the large scores behind them arrive.
+    say("[case] split attention, leading zero keys")
+    g = synth.attention_inputs(2, (80, 100, 70), 40, 8, "fp32", "none", seed=771)
+    for s0 in (0, 80, 180):
+        g["x"][:, s0:s0 + 32] = 0
+        g["x"][:, s0 + 32:s0 + 70] *= 3
+    for name in ("ifm_forward", "ifm_backward", "dense"):
+        Problem(g, oracle.NAMED_PATTERNS[name]).check(what=f"split/zero-keys/{name}")
