@@ -13,7 +13,11 @@
 //   P V:     the three parts of V's columns are rows of the A operand (3 dh <= 16 rows: one instruction for all three),
 //            and the probabilities' three parts are three B operands.
 // One slot of the score product is left for the key mask (1 on the query side, 0 or -inf on the key side), one row of
-// the P V product is all ones (the row sum).
+// the P V product is all ones (the row sum).  The score has the same bits in all three kernels: the product starts from zero
+// (the reference or lse is subtracted from its result) and has the same terms in the same slots, whichever side is the A
+// operand.  So exp2(score - lse) is the forward's probability to a rounding of lse.  With -m and -lse as the accumulator's
+// start (eight subtractions less per step) each kernel rounded the score in its own way: at scores around 300 the
+// probability of a row's only key was off by 1e-5 and dWv with it (3.0e-6 like this, 1.1e-5 so), at 1e6 dWv by 20 %.
 //
 // Bound: vector-instruction issue.  Per score the forward has one exp2, half a max and 5.5 instructions that split the
 // probability (63 per 32 x 16 step and wave, five matrix instructions beside them), dQ two and dK/dV eight more; at 32 x
@@ -80,6 +84,15 @@ __device__ __forceinline__ void split_rows(const float (&x)[DH], float (&p)[3][D
         r[e + 1] -= p[k][e + 1];
       }
     }
+}
+
+// The query row as the score product takes it: one fp32 value per column in every kernel.  (Contracted with the subtraction
+// in split_rows, the product's own rounding error would enter the second part, in some kernels and not in others.)
+template <int DH>
+__device__ __forceinline__ void scale_row(float (&x)[DH], float by) {
+#pragma clang fp contract(off)
+#pragma unroll
+  for (int e = 0; e < DH; ++e) x[e] = x[e] * by;
 }
 
 // position of streamed row t of a chunk: 16-row score block, row inside it
@@ -362,8 +375,7 @@ void split_fwd_kernel(SplitGeo g, int tile_base, const T* __restrict__ Q, const 
   bool more = walk.next(g, t.b, t.h, valid_len);
   if (more) request();
   if (wave == 3) {
-#pragma unroll
-    for (int e = 0; e < DH; ++e) raw[e] *= g.scale_log2e;
+    scale_row<DH>(raw, g.scale_log2e);
     split_rows<DH>(raw, part);
     store_score_row<DH, true>(smem + CH, lane >> 4, lane & 15, part, 1.f);
   }
@@ -382,36 +394,39 @@ void split_fwd_kernel(SplitGeo g, int tile_base, const T* __restrict__ Q, const 
   auto steps = [&](const u32x4* sS, int nst) {
     const bf16_t* const sT = (const bf16_t*)(sS + S_UNITS);
     for (int st = 0; st < nst; ++st) {
-      f32x4 x0 = {-m, -m, -m, -m}, x1 = x0;
+      f32x4 x0 = {0.f, 0.f, 0.f, 0.f}, x1 = x0;
 #pragma unroll
       for (int s = 0; s < NS; ++s) {
         x0 = mfma16(score_frag<DH>(sS, 2 * st, s, lane), bq[s], x0);
         x1 = mfma16(score_frag<DH>(sS, 2 * st + 1, s, lane), bq[s], x1);
       }
-      float e[8];
+      float e[8];   // score - m
       int big = INT_MIN;   // as integers: exact above 0, where the threshold lies, and no NaN canonicalisation
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        e[i] = x0[i];
-        e[4 + i] = x1[i];
+        e[i] = x0[i] - m;
+        e[4 + i] = x1[i] - m;
       }
 #pragma unroll
       for (int i = 0; i < 8; ++i) big = max(big, __float_as_int(e[i]));
       // rare: no reference yet (>=: a score of -0.0 has the bits of INT_MIN), or a score 2^8 above it
       if (__builtin_amdgcn_ballot_w64(big >= thr)) {
-        float mx = e[0];
+        float mx = x0[0];
 #pragma unroll
-        for (int i = 1; i < 8; ++i) mx = fmaxf(mx, e[i]);
+        for (int i = 0; i < 4; ++i) mx = fmaxf(mx, fmaxf(x0[i], x1[i]));
         mx = fmaxf(mx, __shfl_xor(mx, 16));
         mx = fmaxf(mx, __shfl_xor(mx, 32));
-        const bool unset = thr == INT_MIN, move = mx > (unset ? IM_NEG_INF : SPLIT_LAZY);
-        const float by = move ? mx : 0.f;
-        const float alpha = __builtin_amdgcn_exp2f(unset ? 0.f : -by);
+        const bool unset = thr == INT_MIN, move = unset ? mx > IM_NEG_INF : mx - m > SPLIT_LAZY;
+        const float to = move ? mx : m;
+        const float alpha = __builtin_amdgcn_exp2f(unset ? 0.f : m - to);
 #pragma unroll
         for (int rb = 0; rb < NTB; ++rb) acc[rb] *= alpha;
+        m = to;
 #pragma unroll
-        for (int i = 0; i < 8; ++i) e[i] -= by;
-        m += by;
+        for (int i = 0; i < 4; ++i) {
+          e[i] = x0[i] - m;
+          e[4 + i] = x1[i] - m;
+        }
         thr = move ? __float_as_int(SPLIT_LAZY) : thr;
       }
       float p[8];
@@ -509,8 +524,7 @@ void split_dq_kernel(SplitGeo g, int tile_base, const T* __restrict__ Q, const T
   bool more = walk.next(g, t.b, t.h, valid_len);
   if (more) request();
   if (wave >= 2) {
-#pragma unroll
-    for (int e = 0; e < DH; ++e) raw[e] = wave == 2 ? raw[e] : raw[e] * g.scale_log2e;
+    if (wave == 3) scale_row<DH>(raw, g.scale_log2e);
     split_rows<DH>(raw, part);
     store_score_row<DH, true>(sOwn + (wave == 2 ? S_UNITS : 0), lane >> 4, lane & 15, part, wave == 2 ? 0.f : 1.f,
                               wave == 2 && (lane & 1));
@@ -544,7 +558,7 @@ void split_dq_kernel(SplitGeo g, int tile_base, const T* __restrict__ Q, const T
   const float diag = (n & 2) ? ((n & 1) ? x[3] : x[2]) : ((n & 1) ? x[1] : x[0]);
   const float dl = __shfl(diag, 16 * (n >> 2) + n);
   if (lane < 16 && row < t.nrows) delta[t.stat0 + row] = dl;
-  ls = ls == IM_NEG_INF ? IM_NEG_INF : -ls;   // row with no live valid key: every p becomes 0
+  ls = ls == IM_NEG_INF ? -IM_NEG_INF : ls;   // row with no live valid key: every p becomes 0
   f32x4 acc[NTB];
 #pragma unroll
   for (int rb = 0; rb < NTB; ++rb) acc[rb] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -552,7 +566,7 @@ void split_dq_kernel(SplitGeo g, int tile_base, const T* __restrict__ Q, const T
     const u32x4* const sV = sK + S_UNITS;
     const bf16_t* const sT = (const bf16_t*)(sK + 2 * S_UNITS);
     for (int st = 0; st < nst; ++st) {
-      f32x4 x0 = {ls, ls, ls, ls}, x1 = x0, y0 = {0.f, 0.f, 0.f, 0.f}, y1 = y0;
+      f32x4 x0 = {0.f, 0.f, 0.f, 0.f}, x1 = x0, y0 = x0, y1 = x0;
 #pragma unroll
       for (int s = 0; s < NS; ++s) {
         x0 = mfma16(score_frag<DH>(sK, 2 * st, s, lane), bq[s], x0);
@@ -563,8 +577,8 @@ void split_dq_kernel(SplitGeo g, int tile_base, const T* __restrict__ Q, const T
       float ds[8];
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        ds[i] = __builtin_amdgcn_exp2f(x0[i]) * (y0[i] - dl);
-        ds[4 + i] = __builtin_amdgcn_exp2f(x1[i]) * (y1[i] - dl);
+        ds[i] = __builtin_amdgcn_exp2f(x0[i] - ls) * (y0[i] - dl);
+        ds[4 + i] = __builtin_amdgcn_exp2f(x1[i] - ls) * (y1[i] - dl);
       }
       bf16x8 bd[3];
       split8(ds, bd);
@@ -608,7 +622,7 @@ void split_dkv_kernel(SplitGeo g, int tile_base, const T* __restrict__ Q, const 
   using F = SplitCfg<DH>;
   constexpr int NS = F::NS, NTB = F::NT;
   constexpr int S_UNITS = 4 * F::BLK, T_UNITS = 2 * NTB * 64;
-  // One chunk (Q, dO, both transposed, -lse, delta) and the own rows (K, V): with two chunk buffers, one barrier less
+  // One chunk (Q, dO, both transposed, lse, delta) and the own rows (K, V): with two chunk buffers, one barrier less
   // per chunk, the kernel took 44 instead of 41 us (101 registers).
   constexpr int CH = 2 * S_UNITS + 2 * T_UNITS + 2 * SPLIT_ROWS / 4, STAT_AT = 2 * S_UNITS + 2 * T_UNITS;
   __shared__ u32x4 smem[cmax(CH + 2 * S_UNITS, 2 * spill_units<NTB>())];
@@ -639,7 +653,8 @@ void split_dkv_kernel(SplitGeo g, int tile_base, const T* __restrict__ Q, const 
     if (wave < 2 && lane < ((n + 31) & ~31)) {
       const bool in = lane < n;
 #pragma unroll
-      for (int e = 0; e < DH; ++e) raw[e] = in ? (wave ? raw[e] : raw[e] * g.scale_log2e) : 0.f;
+      for (int e = 0; e < DH; ++e) raw[e] = in ? raw[e] : 0.f;
+      if (!wave) scale_row<DH>(raw, g.scale_log2e);
       split_rows<DH>(raw, part);
       int blk, mm;
       step_pos(lane, blk, mm);
@@ -647,7 +662,7 @@ void split_dkv_kernel(SplitGeo g, int tile_base, const T* __restrict__ Q, const 
       store_score_row<DH, true>(buf + (wave ? S_UNITS : 0), blk, mm, part, wave ? 0.f : 1.f, wave && (lane & 1));
       store_tr_row<DH, NTB, false>((bf16_t*)(buf + 2 * S_UNITS + (wave ? T_UNITS : 0)), blk, mm, part, !wave && (lane & 1));
       ((float*)(buf + STAT_AT))[(wave ? SPLIT_ROWS : 0) + blk * 16 + mm] =
-          wave ? (in ? stat : 0.f) : (in && stat != IM_NEG_INF) ? -stat : IM_NEG_INF;
+          wave ? (in ? stat : 0.f) : (in && stat != IM_NEG_INF) ? stat : -IM_NEG_INF;
     }
   };
   bool ok = true;
@@ -680,7 +695,7 @@ void split_dkv_kernel(SplitGeo g, int tile_base, const T* __restrict__ Q, const 
     const bf16_t *const sQT = (const bf16_t*)(sQ + 2 * S_UNITS), *const sGT = (const bf16_t*)(sQ + 2 * S_UNITS + T_UNITS);
     const f32x4 *const sL = (const f32x4*)(sQ + STAT_AT), *const sD = sL + SPLIT_ROWS / 4;
     for (int st = 0; st < nst; ++st) {
-      f32x4 x0 = sL[8 * st + g4], x1 = sL[8 * st + 4 + g4], y0 = {0.f, 0.f, 0.f, 0.f}, y1 = y0;
+      f32x4 x0 = {0.f, 0.f, 0.f, 0.f}, x1 = x0, y0 = x0, y1 = x0;
 #pragma unroll
       for (int s = 0; s < NS; ++s) {
         x0 = mfma16(score_frag<DH>(sQ, 2 * st, s, lane), bk[s], x0);
@@ -688,12 +703,12 @@ void split_dkv_kernel(SplitGeo g, int tile_base, const T* __restrict__ Q, const 
         y0 = mfma16(score_frag<DH>(sG, 2 * st, s, lane), bv[s], y0);
         y1 = mfma16(score_frag<DH>(sG, 2 * st + 1, s, lane), bv[s], y1);
       }
-      const f32x4 d0 = sD[8 * st + g4], d1 = sD[8 * st + 4 + g4];
+      const f32x4 l0 = sL[8 * st + g4], l1 = sL[8 * st + 4 + g4], d0 = sD[8 * st + g4], d1 = sD[8 * st + 4 + g4];
       float p[8], ds[8];
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        p[i] = __builtin_amdgcn_exp2f(x0[i]);
-        p[4 + i] = __builtin_amdgcn_exp2f(x1[i]);
+        p[i] = __builtin_amdgcn_exp2f(x0[i] - l0[i]);
+        p[4 + i] = __builtin_amdgcn_exp2f(x1[i] - l1[i]);
         ds[i] = p[i] * (y0[i] - d0[i]);
         ds[4 + i] = p[4 + i] * (y1[i] - d1[i]);
       }

@@ -10,6 +10,45 @@ from tests.gpu_util import TOL, Problem, assert_close
 pytestmark = pytest.mark.gpu
 
 
+@pytest.mark.parametrize("dh", [5, 8, 16])
+@pytest.mark.parametrize("size", [1e3, 1e5, 1e17])
+def test_scores_far_apart(dh, size):
+    # scores of 1e6, 1e10 and 1e34: a row attends one key.  exp2(score - lse) of that key is one, not the difference of two
+    # roundings of the score; dWq and dWk, rounding noise times such keys, are finite.
+    print(f"[case] scores far apart dh={dh} size={size}", flush=True)
+    d, H = 4 * dh, 4
+    g = synth.attention_inputs(2, (40, 100, 30), d, H, "fp32", "valid_len", seed=1005)
+    for w in ("wq", "wk"):
+        g[w] = (g[w] * np.float32(size)).astype(np.float32)
+    pr = Problem(g, oracle.IM_IFM_FORWARD)
+    y_ref, cache = pr.oracle_fwd(cache=True)
+    close = lambda got, ref, what: assert_close(got, ref, 5e-3, what)  # noqa: E731  (near ties: weights of single rows)
+    close(pr.fwd(), y_ref, "y")
+    grads, ref = pr.bwd(), oracle.backward(cache, g["dy"])
+    for name in ("dwo", "dwv"):
+        close(grads[name], ref[name], name)
+    assert all(grads[n].isfinite().all() for n in ("dwq", "dwk"))
+
+
+@pytest.mark.parametrize("size", [3, 10, 30])
+def test_probabilities_of_the_backward_are_those_of_the_forward(size):
+    # scores around 30, 300 and 3000 (in the exponent of 2).  A score s has an error of 2^-24 s from its own rounding, and so
+    # have single probabilities; but a row's probabilities sum to one, and where one key takes the row its weight is exactly
+    # one.  dWv over many rows is good to the rounding of lse: 1.6e-8 x 30 .. 3000, with the 4e-7 of an ordinary call
+    # (measured 7e-7, 3.0e-6 and 8e-6).  Two roundings of the score that differ: 1.2e-6, 1.1e-5, 9.5e-5.
+    print(f"[case] large scores size={size}", flush=True)
+    g = synth.attention_inputs(8, (50, 200, 150), 40, 8, "fp32", "valid_len", seed=1006)
+    for w in ("wq", "wk"):
+        g[w] = (g[w] * np.float32(size)).astype(np.float32)
+    pr = Problem(g, oracle.IM_IFM_FORWARD)
+    pr.fwd()
+    _, cache = pr.oracle_fwd(cache=True)
+    ref = oracle.backward(cache, g["dy"])["dwv"]
+    err = np.linalg.norm(pr.bwd()["dwv"].double().cpu().numpy() - ref) / np.linalg.norm(ref)
+    print(f"    {err:.1e}")
+    assert err <= {3: 1.0e-6, 10: 5e-6, 30: 2e-5}[size], err
+
+
 @pytest.mark.parametrize("dh", [4, 5, 7, 12, 16])
 def test_contents_of_masked_keys_do_not_matter(dh):
     # a masked key whose row holds 3e35 (left-over memory).  As a query the row is computed like any other; every other row's
