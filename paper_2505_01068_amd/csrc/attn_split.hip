@@ -330,6 +330,77 @@ __host__ __device__ constexpr int spill_units() { return 16 * (16 * NTB + 4); } 
 
 constexpr int cmax(int a, int b) { return a > b ? a : b; }
 
+// ---- rows that the three-part products cannot give ----
+// An infinity, or a finite value beyond bf16's largest (3.39e38), has NaN among its parts, and NaN is every result that it
+// reaches.  A row whose result is NaN or infinite is computed again from memory in plain fp32 multiply-adds, one row per wave
+// and one row of the streamed operand per lane (no row of any ordinary call).
+// Such rows of the wave (row = lane % 16), one bit each.  check: the sum of zero times every value of the lane's accumulators.
+__device__ __forceinline__ unsigned not_finite(float check, bool in) {
+  unsigned long long b = __builtin_amdgcn_ballot_w64(check != check && in);
+  if (__builtin_expect(b == 0, 1)) return 0u;
+  b |= b >> 32;
+  return (unsigned)((b | b >> 16) & 0xffffu);
+}
+template <int NTB>
+__device__ __forceinline__ float check_acc(const f32x4 (&acc)[NTB], float check) {
+#pragma unroll
+  for (int rb = 0; rb < NTB; ++rb)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) check = fmaf(0.f, acc[rb][i], check);
+  return check;
+}
+__device__ __forceinline__ float wave_sum(float v) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+  return v;
+}
+template <int DH>
+__device__ __forceinline__ float dot_from(float s, const float (&a)[DH], const float (&b)[DH]) {
+#pragma unroll
+  for (int e = 0; e < DH; ++e) s = fmaf(a[e], b[e], s);
+  return s;
+}
+
+// Output row `row` of the tile (wave-uniform).
+template <typename T, int DH, bool EXACT>
+__device__ __forceinline__ void plain_fwd_row(const SplitGeo& g, const SplitTile& t, int row, int dh, const T* Q, const T* K, const T* V,
+                                              long ld, const int32_t* valid_len, const uint8_t* key_pad, T* O, long ldo,
+                                              float* lse2) {
+  const int lane = threadIdx.x & 63, hc = t.h * dh;
+  float q[DH], acc[DH], m = IM_NEG_INF, l = 0.f;
+  load_head_row<T, DH, EXACT>(Q + (t.row0 + row) * ld + hc, dh, q);
+  scale_row<DH>(q, g.scale_log2e);
+#pragma unroll
+  for (int e = 0; e < DH; ++e) acc[e] = 0.f;
+  SplitWalk walk(t.live);
+  while (walk.next(g, t.b, t.h, valid_len)) {
+    if (lane >= walk.n) continue;
+    const long r = walk.row0 + lane;
+    float k[DH], v[DH];
+    load_head_row<T, DH, EXACT>(K + r * ld + hc, dh, k);
+    load_head_row<T, DH, EXACT>(V + r * ld + hc, dh, v);
+    const float s = dot_from<DH>(key_pad && key_pad[r] != 0 ? IM_NEG_INF : 0.f, q, k);
+    const float mn = fmaxf(s, m), ms = mn == IM_NEG_INF ? 0.f : mn;
+    const float alpha = __builtin_amdgcn_exp2f(m - ms), p = __builtin_amdgcn_exp2f(s - ms);
+    l = l * alpha + p;
+#pragma unroll
+    for (int e = 0; e < DH; ++e) acc[e] = fmaf(p, v[e], acc[e] * alpha);
+    m = mn;
+  }
+  float mw = m;
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) mw = fmaxf(mw, __shfl_xor(mw, o));
+  const float ms = mw == IM_NEG_INF ? 0.f : mw, alpha = __builtin_amdgcn_exp2f(m - ms);
+  l = wave_sum(l * alpha);
+  const float inv = l > 0.f ? 1.f / l : 0.f;
+#pragma unroll
+  for (int e = 0; e < DH; ++e) {
+    const float v = wave_sum(acc[e] * alpha) * inv;
+    if (lane == 0 && e < dh) stf(O + (t.row0 + row) * ldo + hc + e, v);
+  }
+  if (lse2 && lane == 0) lse2[t.stat0 + row] = l > 0.f ? mw + log2f(l) : IM_NEG_INF;
+}
+
 // A wave owns 16 rows of the tile.  Waves 0 and 1 stage a chunk (one matrix each), the others the tile's own rows, which
 // go to LDS beside the first chunk: one memory round trip and one barrier before the first product.  Two 16-row blocks
 // per wave (128-row tiles, 128-row chunks: half the staging per score) measured the same at 500-row segments and a
@@ -453,10 +524,11 @@ void split_fwd_kernel(SplitGeo g, int tile_base, const T* __restrict__ Q, const 
   float* X = (float*)(smem + wave * (spill_units<NTB>() / 4));
   const int n = lane & 15, e0 = lane >> 4, row = wave * 16 + n;
   spill_acc<NTB>(X, acc, lane);
+  unsigned bad = not_finite(check_acc<NTB>(acc, 0.f), row < t.nrows);
   __builtin_amdgcn_wave_barrier();
   const float l = X[n * (16 * NTB + 4) + 3 * DH];
   const float inv = l > 0.f ? 1.f / l : 0.f;
-  if (row < t.nrows) {
+  if (row < t.nrows && !((bad >> n) & 1)) {
     T* const o = O + t.row0 * ldo + hc + row * (int)ldo;
 #pragma unroll
     for (int i = 0; i < (DH + 3) / 4; ++i) {
@@ -465,6 +537,43 @@ void split_fwd_kernel(SplitGeo g, int tile_base, const T* __restrict__ Q, const 
     }
     if (lse2 && e0 == 0) lse2[t.stat0 + row] = l > 0.f ? m + __log2f(l) : IM_NEG_INF;
   }
+  for (; bad; bad &= bad - 1)
+    plain_fwd_row<T, DH, EXACT>(g, t, wave * 16 + __builtin_ctz(bad), dh, Q, K, V, ld, valid_len, key_pad, O, ldo, lse2);
+}
+
+template <typename T, int DH, bool EXACT>
+__device__ __forceinline__ void plain_dq_row(const SplitGeo& g, const SplitTile& t, int row, int dh, const T* Q, const T* K, const T* V,
+                                             long ld, const T* O, const T* dO, long ldo, const float* lse2,
+                                             const int32_t* valid_len, const uint8_t* key_pad, float* delta, T* dQ, long ldg) {
+  const int lane = threadIdx.x & 63, hc = t.h * dh;
+  float q[DH], go[DH], acc[DH];
+  load_head_row<T, DH, EXACT>(O + (t.row0 + row) * ldo + hc, dh, q);
+  load_head_row<T, DH, EXACT>(dO + (t.row0 + row) * ldo + hc, dh, go);
+  const float dl = dot_from<DH>(0.f, go, q);
+  load_head_row<T, DH, EXACT>(Q + (t.row0 + row) * ld + hc, dh, q);
+  scale_row<DH>(q, g.scale_log2e);
+#pragma unroll
+  for (int e = 0; e < DH; ++e) acc[e] = 0.f;
+  float ls = lse2[t.stat0 + row];
+  if (ls == IM_NEG_INF) ls = -IM_NEG_INF;
+  SplitWalk walk(t.live);
+  while (walk.next(g, t.b, t.h, valid_len)) {
+    if (lane >= walk.n) continue;
+    const long r = walk.row0 + lane;
+    float k[DH], v[DH];
+    load_head_row<T, DH, EXACT>(K + r * ld + hc, dh, k);
+    load_head_row<T, DH, EXACT>(V + r * ld + hc, dh, v);
+    const float s = dot_from<DH>(key_pad && key_pad[r] != 0 ? IM_NEG_INF : 0.f, q, k);
+    const float ds = __builtin_amdgcn_exp2f(s - ls) * (dot_from<DH>(0.f, go, v) - dl);
+#pragma unroll
+    for (int e = 0; e < DH; ++e) acc[e] = fmaf(ds, k[e], acc[e]);
+  }
+#pragma unroll
+  for (int e = 0; e < DH; ++e) {
+    const float v = wave_sum(acc[e]) * g.scale;
+    if (lane == 0 && e < dh) stf(dQ + (t.row0 + row) * ldg + hc + e, v);
+  }
+  if (lane == (row & 15)) delta[t.stat0 + row] = (row & 1) ? -dl : dl;   // the lane that has stored it before
 }
 
 // dQ (and delta = rowsum(dO * O)): own rows are queries, keys are streamed.
@@ -600,13 +709,57 @@ void split_dq_kernel(SplitGeo g, int tile_base, const T* __restrict__ Q, const T
   if (!active) return;
   float* X = (float*)(smem + wave * (spill_units<NTB>() / 4));
   spill_acc<NTB>(X, acc, lane);
+  unsigned bad = not_finite(check_acc<NTB>(acc, 0.f * dl), row < t.nrows);
   __builtin_amdgcn_wave_barrier();
-  if (row < t.nrows) {
+  if (row < t.nrows && !((bad >> n) & 1)) {
     T* const o = dQ + t.row0 * ldg + hc + row * (int)ldg;
 #pragma unroll
     for (int i = 0; i < (DH + 3) / 4; ++i) {
       const int e = (lane >> 4) + 4 * i;
       if (e < dh) stf(o + e, part_sum<DH, NTB>(X, n, e) * ((row & 1) ? -g.scale : g.scale));
+    }
+  }
+  for (; bad; bad &= bad - 1)
+    plain_dq_row<T, DH, EXACT>(g, t, wave * 16 + __builtin_ctz(bad), dh, Q, K, V, ld, O, dO, ldo, lse2, valid_len, key_pad, delta, dQ,
+                               ldg);
+}
+
+template <typename T, int DH, bool EXACT>
+__device__ __forceinline__ void plain_dkv_row(const SplitGeo& g, const SplitTile& t, int row, int dh, const T* Q, const T* K,
+                                              const T* V, long ld, const T* dO, long ldo, const float* lse2, const float* delta,
+                                              const uint8_t* key_pad, T* dK, T* dV, long ldg) {
+  const int lane = threadIdx.x & 63, hc = t.h * dh;
+  float k[DH], v[DH], ak[DH], av[DH];
+  load_head_row<T, DH, EXACT>(K + (t.row0 + row) * ld + hc, dh, k);
+  load_head_row<T, DH, EXACT>(V + (t.row0 + row) * ld + hc, dh, v);
+#pragma unroll
+  for (int e = 0; e < DH; ++e) ak[e] = av[e] = 0.f;
+  // a masked key's gradients are zero, whatever its row holds
+  if (row < t.vlen && !(key_pad && key_pad[t.row0 + row] != 0)) {
+    SplitWalk walk(t.live);
+    while (walk.next(g, t.b, t.h, nullptr)) {
+      if (lane >= walk.n) continue;
+      const long r = walk.row0 + lane;
+      float q[DH], go[DH];
+      load_head_row<T, DH, EXACT>(Q + r * ld + hc, dh, q);
+      load_head_row<T, DH, EXACT>(dO + r * ldo + hc, dh, go);
+      const float ls = lse2[walk.stat0 + lane], dl = (lane & 1) ? -delta[walk.stat0 + lane] : delta[walk.stat0 + lane];
+      scale_row<DH>(q, g.scale_log2e);
+      const float p = __builtin_amdgcn_exp2f(dot_from<DH>(0.f, q, k) - (ls == IM_NEG_INF ? -IM_NEG_INF : ls));
+      const float ds = p * (dot_from<DH>(0.f, go, v) - dl);
+#pragma unroll
+      for (int e = 0; e < DH; ++e) {
+        av[e] = fmaf(p, go[e], av[e]);
+        ak[e] = fmaf(ds, q[e], ak[e]);
+      }
+    }
+  }
+#pragma unroll
+  for (int e = 0; e < DH; ++e) {
+    const float a = wave_sum(ak[e]) * 0.69314718055994530942f, b = wave_sum(av[e]);
+    if (lane == 0 && e < dh) {
+      stf(dK + (t.row0 + row) * ldg + hc + e, a);
+      stf(dV + (t.row0 + row) * ldg + hc + e, b);
     }
   }
 }
@@ -738,8 +891,9 @@ void split_dkv_kernel(SplitGeo g, int tile_base, const T* __restrict__ Q, const 
   const float ln2 = 0.69314718055994530942f;   // the staged Q carries scale * log2(e); dK = scale * dS^T q
   spill_acc<NTB>(X, ak, lane);
   spill_acc<NTB>(X2, av, lane);
+  unsigned bad = not_finite(check_acc<NTB>(av, check_acc<NTB>(ak, 0.f)), row < t.nrows);
   __builtin_amdgcn_wave_barrier();
-  if (row < t.nrows) {
+  if (row < t.nrows && !((bad >> n) & 1)) {
     T *const pk = dK + t.row0 * ldg + hc + row * (int)ldg, *const pv = dV + t.row0 * ldg + hc + row * (int)ldg;
 #pragma unroll
     for (int i = 0; i < (DH + 3) / 4; ++i) {
@@ -750,6 +904,8 @@ void split_dkv_kernel(SplitGeo g, int tile_base, const T* __restrict__ Q, const 
       }
     }
   }
+  for (; bad; bad &= bad - 1)
+    plain_dkv_row<T, DH, EXACT>(g, t, wave * 16 + __builtin_ctz(bad), dh, Q, K, V, ld, dO, ldo, lse2, delta, key_pad, dK, dV, ldg);
 }
 
 // Zero columns col0 .. col0+ncols-1 of the rows of segment s (all batch elements): outputs of query

@@ -49,19 +49,48 @@ def test_probabilities_of_the_backward_are_those_of_the_forward(size):
     assert err <= {3: 1.0e-6, 10: 5e-6, 30: 2e-5}[size], err
 
 
+def test_scores_of_minus_infinity():
+    # head dimension 1: keys of -3.4e38 (beyond bf16's largest value) times a query overflow to -inf, a weight of zero
+    print("[case] scores of minus infinity", flush=True)
+    n, seg, d = 1, (70, 70, 33), 4
+    g = synth.attention_inputs(n, seg, d, d, "fp32", "none", seed=1003)
+    g["x"] = (1.5 + np.random.default_rng(3).random(g["x"].shape)).astype(np.float32)
+    g["x"][:, 5::9, 1] = -1.7e38                    # the key feature: K = 2 x_1
+    g["x"][:, 5::9, 0] = 2.0
+    for w, c, v in (("wq", 0, 1.0), ("wk", 1, 2.0), ("wv", 2, np.linspace(0.5, 1.5, d))):
+        g[w] = np.zeros((d, d), np.float32)
+        g[w][c] = v
+    g["dy"] = (g["dy"] * np.float32(1e-3)).astype(np.float32)
+    pr = Problem(g, oracle.NAMED_PATTERNS["self_only"])
+    y_ref, cache = pr.oracle_fwd(cache=True)        # fp64: the scores are -1e39, their weights zero
+    assert_close(pr.fwd(), y_ref, TOL["fp32"], "y")
+    grads, ref = pr.bwd(), oracle.backward(cache, g["dy"])
+    for name in ("dwo", "dwv"):
+        assert_close(grads[name], ref[name], TOL["fp32"], name)
+
+
 @pytest.mark.parametrize("dh", [4, 5, 7, 12, 16])
-def test_contents_of_masked_keys_do_not_matter(dh):
-    # a masked key whose row holds 3e35 (left-over memory).  As a query the row is computed like any other; every other row's
-    # y is that of a harmless row.
-    print(f"[case] masked keys dh={dh}", flush=True)
-    d, H, seg, rows = 3 * dh, 3, (20, 70, 40), [50]
+@pytest.mark.parametrize("rows", [(50,), (4, 50, 111)])
+def test_contents_of_masked_keys_do_not_matter(dh, rows):
+    # masked keys whose rows hold 3e35 (left-over memory); with several, the rows attend one another's products of 1e70.  As a
+    # query a masked row is computed like any other; every other row's y and dx, and what the rows give as keys (dV = dK = 0:
+    # dWv, dbv, dbk), are those of harmless rows.
+    print(f"[case] masked keys dh={dh} rows={rows}", flush=True)
+    d, H, seg, rows = 3 * dh, 3, (20, 70, 40), list(rows)
     g = synth.attention_inputs(2, seg, d, H, "fp32", "none", seed=1004, bias=True)
     g["key_pad"] = np.zeros((2, sum(seg)), np.uint8)
     g["key_pad"][:, rows] = 1
-    y = []
+    out = []
     for value in (0.0, 3e35):
         pr = Problem(g, oracle.NAMED_PATTERNS["self_only"])
         pr.t["x"][:, rows] = value
-        y.append(pr.fwd())
+        pr.t["dy"][:, rows] = 0     # as queries the rows have no part in any gradient
+        y = pr.fwd()
+        out.append((y, pr.bwd()))
     keep = [i for i in range(sum(seg)) if i not in rows]
-    assert_close(y[1][:, keep], y[0][:, keep].double().cpu().numpy(), TOL["fp32"], "y")
+    (y0, g0), (y1, g1) = out
+    assert_close(y1[:, keep], y0[:, keep].double().cpu().numpy(), TOL["fp32"], "y")
+    assert_close(g1["dx"][:, keep], g0["dx"][:, keep].double().cpu().numpy(), TOL["fp32"], "dx")
+    for n in ("dwv", "dbv", "dbk"):
+        scale = g0["dwv" if n == "dwv" else "dbv"].abs().max().item()
+        assert_close(g1[n], g0[n].double().cpu().numpy(), TOL["fp32"], n, scale)
