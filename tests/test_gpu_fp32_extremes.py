@@ -1,13 +1,77 @@
 """fp32 calls whose rows hold extreme values.  The products of these calls run on the bf16 matrix cores, each operand as three
-bf16 parts; the results are what fp32 multiply-adds give (a masked key has weight exactly zero, whatever its row holds)."""
+bf16 parts, which infinities and values beyond bf16's largest do not have; the results are what fp32 multiply-adds give (an
+infinity stays one; a masked key has weight exactly zero, whatever its row holds)."""
 import numpy as np
 import pytest
+import torch
 
 import oracle
 from paper_2505_01068_amd import synth
 from tests.gpu_util import TOL, Problem, assert_close
 
 pytestmark = pytest.mark.gpu
+TOP = 3.4e38   # finite in fp32, rounds to infinity in bf16
+
+
+def same(got, want, what):
+    """NaN, +inf and -inf where `want` (fp32, CPU) has them; elsewhere within the fp32 bar."""
+    got, want = got.cpu(), want.float()
+    assert torch.equal(got.isnan(), want.isnan()), what
+    assert torch.equal(got.isposinf(), want.isposinf()) and torch.equal(got.isneginf(), want.isneginf()), what
+    fin = want.isfinite()
+    assert (got[fin] - want[fin]).abs().max() <= TOL["fp32"] * want[fin].abs().max(), what
+
+
+@pytest.mark.parametrize("d,H", [(40, 8), (33, 3), (32, 2)])
+def test_infinities_in_weights_and_upstream_gradients(d, H):
+    # y = O Wo + bo, dWo = O^T dy, dbo = sum of dy rows: an infinite element of Wo or dy makes infinities of one sign per
+    # element of O, everything else stays finite.  dV, hence dbv, is infinite for the heads' columns that the row's keys feed.
+    print(f"[case] infinities d={d}", flush=True)
+    g = synth.attention_inputs(2, (20, 70, 40), d, H, "fp32", "none", seed=1001, bias=True)
+    ref_y, cache = oracle.forward(g["x"], g["wq"], g["wk"], g["wv"], g["wo"], g["seg_len"], oracle.IM_IFM_FORWARD, H, g["scale"],
+                                  bq=g["bq"], bk=g["bk"], bv=g["bv"], bo=g["bo"], return_cache=True)
+    o = torch.from_numpy(np.ascontiguousarray(cache["o"])).reshape(-1, d)
+    pr = Problem(g, oracle.IM_IFM_FORWARD)
+    pr.t["wo"][3, 5] = float("inf")
+    wo = pr.t["wo"].cpu().double()
+    same(pr.fwd().reshape(-1, d), (o @ torch.nan_to_num(wo, posinf=0.0)) + torch.from_numpy(g["bo"]).double()
+         + torch.where(torch.arange(d) == 5, o[:, 3:4] * float("inf"), torch.zeros(())), "y")
+    pr = Problem(g, oracle.IM_IFM_FORWARD)
+    pr.fwd()
+    dy = torch.from_numpy(g["dy"]).double().reshape(-1, d)
+    dy[90, 7], dy[11, 2] = float("-inf"), TOP
+    pr.t["dy"].copy_(dy.float().reshape(pr.t["dy"].shape))
+    grads = pr.bwd()
+    fin = dy.clone()
+    fin[90, 7] = 0
+    want = o.t() @ fin
+    want[:, 7] = -o[90] * float("inf")
+    same(grads["dwo"], want, "dwo")
+    want_b = fin.sum(0)
+    want_b[7] = float("-inf")
+    same(grads["dbo"], want_b, "dbo")
+    assert grads["dbv"].isinf().all()   # row 90 attends every key of its key segment with a positive weight
+
+
+@pytest.mark.parametrize("d,H", [(40, 8), (32, 2), (16, 16)])
+def test_finite_values_beyond_the_bf16_range(d, H):
+    # one element of x at the end of the fp32 range, weights small enough that every result is finite
+    print(f"[case] huge operands d={d}", flush=True)
+    g = synth.attention_inputs(2, (20, 70, 40), d, H, "fp32", "none", seed=1002, bias=True)
+    g["x"][1, 30, 3] = TOP
+    for n in ("wq", "wk", "wv"):
+        g[n] = (g[n] * np.float32(2e-38)).astype(np.float32)
+    g["dy"] = (g["dy"] * np.float32(1e-3)).astype(np.float32)
+    pr = Problem(g, oracle.NAMED_PATTERNS["self_only"])
+    y_ref, cache = pr.oracle_fwd(cache=True)
+    y = pr.fwd()
+    grads = pr.bwd()
+    ref = oracle.backward(cache, g["dy"])
+    assert_close(y, y_ref, TOL["fp32"], "y")
+    for n in ("dwv", "dwo", "dbv", "dbo"):   # (dWq and dWk multiply the rounding of a small dQ, dK by 3.4e38)
+        assert_close(grads[n], ref[n], TOL["fp32"], n)
+    for n in ("dwq", "dwk", "dx"):
+        assert grads[n].isfinite().all(), n
 
 
 @pytest.mark.parametrize("dh", [5, 8, 16])
