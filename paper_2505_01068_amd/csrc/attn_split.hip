@@ -225,7 +225,7 @@ __device__ __forceinline__ void load_head_row(const T* p, int dh, float (&out)[D
 // arguments indexed at run time is one scalar-memory round trip per access, and the short workgroups of these shapes
 // would spend most of their life in them.
 struct SplitGeo {
-  int H, dh, n_seg, T, pairs;          // pairs = batch elements x heads
+  int H, dh, n_seg, T, pair0, pairs;   // the launch's (batch element, head) pairs: first one, number
   unsigned h_magic;                    // pair / H = mulhi(pair, h_magic); 0: divide
   int tile0[IM_MAX_SEG], seg[IM_MAX_SEG];   // k-th segment of the tile order: its first tile (INT_MAX: none), its index
   unsigned live[IM_MAX_SEG];           // ... and the segments of the other side that it meets
@@ -265,7 +265,7 @@ constexpr int SPLIT_ROWS = 64;    // rows of a tile, and streamed rows of a chun
 struct SplitTile { int b, h, nrows, vlen; unsigned live; long row0, stat0; };   // vlen: valid rows from the tile's first one
 __device__ __forceinline__ bool find_tile(const SplitGeo& g, int tile_base, const int32_t* valid_len, SplitTile& t) {
   const int xcd = blockIdx.x & 7, idx = blockIdx.x >> 3, per = g.pairs >> 3, rem = g.pairs & 7;
-  const unsigned pair = xcd * per + min(xcd, rem) + idx;
+  const unsigned pair = g.pair0 + xcd * per + min(xcd, rem) + idx;
   t.b = g.h_magic ? __umulhi(pair, g.h_magic) : pair / g.H;
   t.h = pair - t.b * g.H;
   const int tile = blockIdx.y + tile_base;
@@ -946,8 +946,8 @@ static SplitGeo split_geo(const Geo& g, bool query_side) {
   SplitGeo s;
   s.H = g.H; s.dh = g.dh; s.n_seg = g.n_seg; s.T = g.T; s.R = g.R; s.cu = g.cu;
   s.scale = g.scale; s.scale_log2e = g.scale_log2e;
-  s.pairs = g.B * g.H;
-  s.h_magic = g.H > 1 && (uint64_t)s.pairs * g.H < (1ull << 32) ? (unsigned)((1ull << 32) / g.H + ((1ull << 32) % g.H != 0)) : 0u;
+  s.pair0 = s.pairs = 0;   // set per launch
+  s.h_magic = g.H > 1 && (uint64_t)g.B * g.H * g.H < (1ull << 32) ? (unsigned)((1ull << 32) / g.H + ((1ull << 32) % g.H != 0)) : 0u;
   const int nord = query_side ? g.q_nord : g.k_nord;
   for (int k = 0; k < IM_MAX_SEG; ++k) {
     const int seg = k < nord ? (query_side ? g.q_order[k] : g.k_order[k]) : 0;
@@ -974,19 +974,25 @@ static SplitGeo split_geo(const Geo& g, bool query_side) {
     else if ((dh) < 8) SPLIT_LAUNCH(KERNEL, 8, false, __VA_ARGS__);   \
     else SPLIT_LAUNCH(KERNEL, 16, false, __VA_ARGS__);                \
   } while (0)
-// grid (8 ceil(pairs / 8), tiles), at most 65535 tiles per launch
-#define SPLIT_LAUNCH(KERNEL, DHV, EX, ...)                                                                               \
-  do {                                                                                                                   \
-    for (int t0 = 0; t0 < ntiles; t0 += 65535)                                                                           \
-      hipLaunchKernelGGL((KERNEL<T, DHV, EX>), dim3((sg.pairs + 7) / 8 * 8, ntiles - t0 < 65535 ? ntiles - t0 : 65535),  \
-                         dim3(256), 0, st, sg, t0, __VA_ARGS__);                                                         \
+// grid (8 ceil(pairs / 8), tiles); a launch takes at most 2^22 pairs (a grid's x holds 2^32 - 1 threads) and 65535 tiles
+constexpr unsigned SPLIT_MAX_PAIRS = 1u << 22;
+#define SPLIT_LAUNCH(KERNEL, DHV, EX, ...)                                                                                  \
+  do {                                                                                                                      \
+    const unsigned npairs = (unsigned)g.B * g.H;                                                                            \
+    for (unsigned p0 = 0; p0 < npairs; p0 += SPLIT_MAX_PAIRS) {                                                             \
+      sg.pair0 = (int)p0;                                                                                                   \
+      sg.pairs = (int)(npairs - p0 < SPLIT_MAX_PAIRS ? npairs - p0 : SPLIT_MAX_PAIRS);                                      \
+      for (int t0 = 0; t0 < ntiles; t0 += 65535)                                                                            \
+        hipLaunchKernelGGL((KERNEL<T, DHV, EX>), dim3((sg.pairs + 7) / 8 * 8, ntiles - t0 < 65535 ? ntiles - t0 : 65535),   \
+                           dim3(256), 0, st, sg, t0, __VA_ARGS__);                                                          \
+    }                                                                                                                       \
   } while (0)
 
 template <typename T>
 static int fwd_dispatch(const Geo& g, const T* q, const T* k, const T* v, long ld, const int32_t* vl,
                         const uint8_t* kp, T* o, long ldo, float* lse2, hipStream_t st) {
   const int ntiles = g.q_tile_prefix[g.q_nord];
-  const SplitGeo sg = split_geo(g, true);
+  SplitGeo sg = split_geo(g, true);
   SPLIT_DISPATCH(g.dh, split_fwd_kernel, q, k, v, ld, vl, kp, o, ldo, lse2);
   return IM_OK;
 }
@@ -1029,13 +1035,13 @@ static int bwd_dispatch(const Geo& g, const T* q, const T* k, const T* v, long l
   {
     ProfScope ps(PF_ATTN_DQ, st);
     const int ntiles = g.q_tile_prefix[g.q_nord];
-    const SplitGeo sg = split_geo(g, true);
+    SplitGeo sg = split_geo(g, true);
     SPLIT_DISPATCH(g.dh, split_dq_kernel, q, k, v, ld, o, d_o, ldo, lse2, vl, kp, delta, dq, ldg);
   }
   {
     ProfScope ps(PF_ATTN_DKV, st);
     const int ntiles = g.k_tile_prefix[g.k_nord];
-    const SplitGeo sg = split_geo(g, false);
+    SplitGeo sg = split_geo(g, false);
     SPLIT_DISPATCH(g.dh, split_dkv_kernel, q, k, v, ld, d_o, ldo, lse2, delta, vl, kp, dk, dv, ldg);
   }
   return IM_OK;

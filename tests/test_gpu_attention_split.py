@@ -2,10 +2,11 @@
 padded for, the edges of the 16-row blocks, 32-row steps and 64-row tiles, and the moving softmax reference."""
 import numpy as np
 import pytest
+import torch
 
 import oracle
-from paper_2505_01068_amd import synth
-from tests.gpu_util import Problem
+from paper_2505_01068_amd import binding as B, synth
+from tests.gpu_util import TOL, Problem, assert_close
 
 pytestmark = pytest.mark.gpu
 
@@ -86,3 +87,22 @@ def test_zero_scores_before_the_first_large_one():
         g["x"][:, s0 + 32:s0 + 70] *= 3
     for name in ("ifm_forward", "ifm_backward", "dense"):
         Problem(g, oracle.NAMED_PATTERNS[name]).check(what=f"split/zero-keys/{name}")
+
+
+def test_more_pairs_than_one_grid_holds():
+    # 65 535 x 257 (batch element, head) pairs are 2^32 threads and more; the last batch elements in the last launch
+    say("[case] split attention, 16.8 million pairs")
+    batch, few, d, seg = 65535, 5, 257, (1, 1, 1)
+    g = synth.attention_inputs(few, seg, d, d, "fp32", "none", seed=781, with_dy=False)
+    w = {k: torch.from_numpy(g[k]).cuda() for k in ("wq", "wk", "wv", "wo")}
+    x = torch.from_numpy(g["x"]).cuda()
+    out = []
+    for n in (few, batch):
+        xs = x.repeat(n // few, 1, 1)
+        shape = B.make_shape(n, seg, d, d, oracle.IM_IFM_FORWARD, g["scale"], "fp32")
+        ws = torch.empty(B.im_attention_sizes(shape)[1], dtype=torch.uint8, device="cuda")
+        out.append(B.im_attention_fwd(shape, xs, **w, workspace=ws))
+    torch.cuda.synchronize()
+    assert_close(out[0], oracle.forward(g["x"], *(g[k] for k in ("wq", "wk", "wv", "wo")), seg, oracle.IM_IFM_FORWARD, d, g["scale"]),
+                 TOL["fp32"], "y")
+    assert torch.equal(out[1].view(batch // few, few, 3, d), out[0].expand(batch // few, few, 3, d))
