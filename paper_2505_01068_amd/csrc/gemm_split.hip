@@ -41,28 +41,8 @@ __device__ __forceinline__ void mfma32_split(const bf16x8 (&a)[3], const bf16x8 
 }
 
 // An infinity, or a finite value beyond bf16's largest (3.39e38), has infinities and NaN among its parts, and NaN is every
-// sum that it reaches.  A lane whose sums are not all finite takes those elements again from memory with fp32 multiply-adds
-// (one more comparison per element; no element of any ordinary call).
-__device__ __forceinline__ unsigned not_finite(const float (&v)[16]) {   // one bit per element
-  float check = 0.f;
-#pragma unroll
-  for (int r = 0; r < 16; ++r) check = fmaf(0.f, v[r], check);
-  unsigned bad = 0;
-  if (__builtin_expect(check != check, 0))
-#pragma unroll
-    for (int r = 0; r < 16; ++r) bad |= (__float_as_uint(v[r]) & 0x7fffffffu) >= 0x7f800000u ? 1u << r : 0u;
-  return bad;
-}
-// v[r] = again(r) where bit r of `bad` is set
-template <typename F>
-__device__ __forceinline__ void take_again(unsigned bad, float (&v)[16], F again) {
-  for (int r = 0; __builtin_amdgcn_ballot_w64(bad >> r != 0u); ++r)
-    if ((bad >> r) & 1u) {
-      const float x = again(r);
-#pragma unroll
-      for (int i = 0; i < 16; ++i) v[i] = i == r ? x : v[i];
-    }
-}
+// sum that it reaches.  A lane whose sums are not all finite takes its elements again from memory with fp32 multiply-adds
+// and stores them over the first ones (one instruction per element for the check; no lane of any ordinary call).
 
 // C[M, N] = A[M, K] B[K, N] (+ bias) (GELU) (+ res).  A row-major; B element (k, n) at k sbk + n sbn with one of the two
 // strides 1 (BT: sbk == 1), possibly in up to three buffers by columns or by rows of B.
@@ -192,34 +172,36 @@ __global__ __launch_bounds__(256, 3) void gemm_split_kernel(GemmDesc g) {
       const int m = m0 + 8 * (r >> 2) + (r & 3);
       rv[r] = all || m + 4 * h < g.M ? ((const float*)g.res + m * g.ldc)[off] : 0.f;
     }
-  float sum[16];
-#pragma unroll
-  for (int r = 0; r < 16; ++r) sum[r] = acc[r] + rest[r];
-  const unsigned bad = not_finite(sum);
-  if (__builtin_amdgcn_ballot_w64(bad != 0u))
-    take_again(bad, sum, [&](int r) {
-      const int m = min(m0 + 8 * (r >> 2) + (r & 3) + 4 * h, g.M - 1);
-      const float* const ap = (const float*)g.A + (long)m * g.sam;
-      int nn = n;
-      const float* const bp = g.bias_split ? gs_buffer((const float*)g.bias[0], (const float*)g.bias[1], (const float*)g.bias[2], nn, g.n_per)
-                                           : (const float*)g.bias[0];
-      float x = bp ? bp[nn] : 0.f;
-      nn = n;
-      const float* const wn = g.b_split == 1 ? gs_buffer(b0, b1, b2, nn, g.n_per) : b0;
-      for (int k = 0; k < K; ++k) {
-        int kk = k;
-        const float* const wp = g.b_split == 2 ? gs_buffer(b0, b1, b2, kk, g.k_per) : wn;
-        x = fmaf(ap[k], wp[BT ? nn * ldw + kk : kk * ldw + nn], x);
-      }
-      return x;
-    });
+  float check = 0.f;
 #pragma unroll
   for (int r = 0; r < 16; ++r) {
     const int m = m0 + 8 * (r >> 2) + (r & 3);
-    float v = sum[r];
+    float v = acc[r] + rest[r];
+    check = fmaf(0.f, v, check);
     if (GELU) v = 0.5f * v * (1.f + erff(v * 0.70710678118654752440f));
     if (g.res) v += rv[r];
     if (all || m + 4 * h < g.M) ((float*)g.C[0] + m * g.ldc)[off] = v;
+  }
+  if (__builtin_expect(check != check, 0)) {
+    int nn = n;
+    const float* bp = g.bias_split ? gs_buffer((const float*)g.bias[0], (const float*)g.bias[1], (const float*)g.bias[2], nn, g.n_per)
+                                   : (const float*)g.bias[0];
+    const float bv = bp ? bp[nn] : 0.f;
+    nn = n;
+    bp = g.b_split == 1 ? gs_buffer(b0, b1, b2, nn, g.n_per) : b0;
+    for (int r = 0; r < 16; ++r) {
+      const int m = m0 + 8 * (r >> 2) + 4 * h + (r & 3);
+      if (m >= g.M) continue;
+      float v = bv;
+      for (int k = 0; k < K; ++k) {
+        int kk = k;
+        const float* const q = g.b_split == 2 ? gs_buffer(b0, b1, b2, kk, g.k_per) : bp;
+        v = fmaf(((const float*)g.A + (long)m * g.sam)[k], q[BT ? nn * ldw + kk : kk * ldw + nn], v);
+      }
+      if (GELU) v = 0.5f * v * (1.f + erff(v * 0.70710678118654752440f));
+      if (g.res) v += ((const float*)g.res + m * g.ldc)[n];
+      ((float*)g.C[0] + m * g.ldc)[n] = v;
+    }
   }
 }
 
@@ -325,22 +307,23 @@ __global__ __launch_bounds__(256, 4) void wgrad_split_kernel(WgradSplitList l) {
   const int n = n0 + lo;
   if (!p.partial || m0 >= p.M || n >= p.N) return;
   float* const out = p.partial + (long)blockIdx.x * p.stride + n;
-  float sum[16];
-#pragma unroll
-  for (int r = 0; r < 16; ++r) sum[r] = big[r] + rest[r];
-  const unsigned bad = not_finite(sum);
-  if (__builtin_amdgcn_ballot_w64(bad != 0u))
-    take_again(bad, sum, [&](int r) {
-      const float* const a = p.A + (long)r0 * p.lda + min(m0 + 8 * (r >> 2) + 4 * h + (r & 3), p.M - 1);
-      const float* const gg = p.G + (long)r0 * p.ldg + n;
-      float x = 0.f;
-      for (int i = 0; i < nrows; ++i) x = fmaf(a[(long)i * p.lda], gg[(long)i * p.ldg], x);
-      return x;
-    });
+  float check = 0.f;
 #pragma unroll
   for (int r = 0; r < 16; ++r) {
     const int m = m0 + 8 * (r >> 2) + 4 * h + (r & 3);
-    if (m < p.M) out[m * p.N] = sum[r];
+    const float v = big[r] + rest[r];
+    check = fmaf(0.f, v, check);
+    if (m < p.M) out[m * p.N] = v;
+  }
+  if (__builtin_expect(check != check, 0)) {
+    const float *const A = p.A + (long)r0 * p.lda, *const G = p.G + (long)r0 * p.ldg;
+    for (int r = 0; r < 16; ++r) {
+      const int m = m0 + 8 * (r >> 2) + 4 * h + (r & 3);
+      if (m >= p.M) continue;
+      float v = 0.f;
+      for (int i = 0; i < nrows; ++i) v = fmaf(A[(long)i * p.lda + m], G[(long)i * p.ldg + n], v);
+      out[m * p.N] = v;
+    }
   }
 }
 
