@@ -190,7 +190,9 @@ __host__ __device__ constexpr bool tr_needed(int k, int rb, bool ones) {
 // measured), which a long accumulator would collect three times per step.  What the step's own products lose that way has
 // one sign too, and the bias gradients add it over all rows: odd steps multiply the operand with the other sign and are
 // subtracted, which turns the rounding around (the dQ and dK/dV kernels do the same to dP between odd and even query
-// rows).  Without, dbq was off by 2.4e-6 at 20 x 39/480/461 rows.
+// rows).  Without, dbq was off by 2.4e-6 at 20 x 39/480/461 rows.  Segments of up to 32 rows have one step each: the dK/dV
+// kernel, whose results no other sign turns around, sums them with the other sign in every second batch element and tile;
+// without, dbv was off by 3.2e-7 at 200 x 10/30/25 rows (1.9e-7 with, fp32 multiply-adds 2.4e-7).
 template <int DH, int NTB, bool ONES>
 __device__ __forceinline__ void accumulate_tr(const bf16_t* Tr, int st, const bf16x8 (&b)[3], f32x4 (&acc)[NTB], int lane) {
 #pragma unroll
@@ -794,6 +796,7 @@ void split_dkv_kernel(SplitGeo g, int tile_base, const T* __restrict__ Q, const 
   }
 
   float raw[DH], part[3][DH], stat = 0.f;
+  const bool turn = (t.b + blockIdx.y) & 1;   // the sums have the other sign
   SplitWalk walk(t.live);
   auto request = [&]() {
     if (wave < 2 && lane < ((walk.n + 31) & ~31)) {
@@ -813,7 +816,7 @@ void split_dkv_kernel(SplitGeo g, int tile_base, const T* __restrict__ Q, const 
       step_pos(lane, blk, mm);
       // odd query rows: -dO (and -delta from the dQ kernel) give -dS, which meets -Q; dV takes dO as it is
       store_score_row<DH, true>(buf + (wave ? S_UNITS : 0), blk, mm, part, wave ? 0.f : 1.f, wave && (lane & 1));
-      store_tr_row<DH, NTB, false>((bf16_t*)(buf + 2 * S_UNITS + (wave ? T_UNITS : 0)), blk, mm, part, !wave && (lane & 1));
+      store_tr_row<DH, NTB, false>((bf16_t*)(buf + 2 * S_UNITS + (wave ? T_UNITS : 0)), blk, mm, part, (!wave && (lane & 1)) != turn);
       ((float*)(buf + STAT_AT))[(wave ? SPLIT_ROWS : 0) + blk * 16 + mm] =
           wave ? (in ? stat : 0.f) : (in && stat != IM_NEG_INF) ? stat : -IM_NEG_INF;
     }
@@ -899,8 +902,8 @@ void split_dkv_kernel(SplitGeo g, int tile_base, const T* __restrict__ Q, const 
     for (int i = 0; i < (DH + 3) / 4; ++i) {
       const int e = g4 + 4 * i;
       if (e < dh) {
-        stf(pk + e, part_sum<DH, NTB>(X, n, e) * ln2);
-        stf(pv + e, part_sum<DH, NTB>(X2, n, e));
+        stf(pk + e, part_sum<DH, NTB>(X, n, e) * (turn ? -ln2 : ln2));
+        stf(pv + e, part_sum<DH, NTB>(X2, n, e) * (turn ? -1.f : 1.f));
       }
     }
   }

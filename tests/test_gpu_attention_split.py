@@ -77,6 +77,24 @@ def test_bias_gradients_collect_no_rounding():
         assert err < 1.4e-6, (k, err)
 
 
+def test_bias_gradients_collect_no_rounding_in_short_segments():
+    # segments of at most 32 rows: one step of the dV product per key, so that only other keys' steps can turn the rounding
+    # around.  fp32 multiply-adds give 2.4e-7 in the mean over inputs, a rounding with one sign 3.2e-7: over the 24 inputs of
+    # 64 columns the mean scatters by 2 per cent, and 2.8e-7 lies between.
+    say("[case] split attention, bias gradients of short segments")
+    seg, d, H, batch, total = (10, 30, 25), 64, 8, 200, 0.0
+    for seed in range(24):
+        g = synth.attention_inputs(batch, seg, d, H, "fp32", "valid_len", seed=1800 + seed, bias=True)
+        pr = Problem(g, oracle.NAMED_PATTERNS["structure2_b"])
+        pr.fwd()
+        _, cache = pr.oracle_fwd(cache=True)
+        ref = oracle.backward(cache, g["dy"])["dbv"]
+        total += (np.linalg.norm(pr.bwd()["dbv"].double().cpu().numpy() - ref) / np.linalg.norm(ref)) ** 2
+    err = (total / 24) ** 0.5
+    say(f"    dbv {err:.2e}")
+    assert err < 2.8e-7, err
+
+
 def test_zero_scores_before_the_first_large_one():
     # Leading zero rows without a mask and without a key bias: the first 32 keys of every segment give exactly zero scores, of
     # either sign of zero.  They enter the sum with weight one and must be rescaled when the large scores behind them arrive.
