@@ -181,7 +181,8 @@ static SavedLayout saved_layout(const im_shape_t* s) {
   return L;
 }
 
-static size_t bwd_workspace_bytes(const im_shape_t* s) {
+// wrows: rows per workgroup of the fp32 weight gradients (0: this attention's are all that the pass has)
+static size_t bwd_workspace_bytes(const im_shape_t* s, int wrows = 0) {
   const size_t es = s->dtype == IM_DTYPE_BF16 ? 2 : 4;
   const size_t R = (size_t)shape_rows(s), d = s->d_model;
   if (pick_path(s) == PATH_MFMA) return mfma_bwd_workspace_bytes(s);
@@ -189,8 +190,10 @@ static size_t bwd_workspace_bytes(const im_shape_t* s) {
   n += align256(R * d * es);                                          // dO
   n += align256(R * 3 * d * es);                                      // dQ | dK | dV
   n += align256((size_t)s->n_heads * R * sizeof(float));   // delta
-  if (s->dtype == IM_DTYPE_F32)   // both gradients' partial results and column sums stay until the reduction at the end
-    return n + align256(wgrad_split_bytes((int)d, (int)d, (int)R)) + align256(wgrad_split_bytes((int)d, (int)(3 * d), (int)R));
+  if (s->dtype == IM_DTYPE_F32) {   // both gradients' partial results and column sums stay until the reduction at the end
+    if (!wrows) wrows = wgrad_split_rows_attention((int)d, (int)R);
+    return n + align256(wgrad_split_bytes((int)d, (int)d, (int)R, wrows)) + align256(wgrad_split_bytes((int)d, (int)(3 * d), (int)R, wrows));
+  }
   size_t pb = std::max(gemm_alu_partial_bytes((int)d, (int)(3 * d), (int)R, nullptr),
                        gemm_alu_partial_bytes((int)d, (int)d, (int)R, nullptr));
   if (mfma_linear_ok(1, d, d))
@@ -275,12 +278,13 @@ static int fwd_smallhead(const im_shape_t* s, const void* x, const void* wq, con
 }
 
 // later / wlater: second-stage sums resp. fp32 weight gradients that the caller launches at the end of its own pass
-// (NULL: launched here); with wlater the operands (x, dy and the workspace) stay as they are until then.
+// (NULL: launched here); with wlater the operands (x, dy and the workspace) stay as they are until then, and wrows is the
+// caller's number of rows per workgroup.
 static int bwd_smallhead(const im_shape_t* s, const void* x, const void* wq, const void* wk, const void* wv,
                          const void* wo, const int32_t* valid_len, const uint8_t* key_pad, const char* sv,
                          const void* dy, void* dx, void* dwq, void* dwk, void* dwv, void* dwo, void* dbq, void* dbk,
                          void* dbv, void* dbo, char* ws, hipStream_t st, ReduceList* later = nullptr,
-                         WgradSplitList* wlater = nullptr) {
+                         WgradSplitList* wlater = nullptr, int wrows = 0) {
   const int bf = s->dtype == IM_DTYPE_BF16;
   const size_t es = bf ? 2 : 4;
   Geo g;
@@ -314,16 +318,17 @@ static int bwd_smallhead(const im_shape_t* s, const void* x, const void* wq, con
 
   if (!bf) {
     // dWo = O^T dy with dbo, dWq | dWk | dWv = x^T [dQ | dK | dV] with dbq | dbk | dbv: one launch, one reduction
-    float* po = (float*)b.take(wgrad_split_bytes((int)d, (int)d, (int)R));
-    float* pw = (float*)b.take(wgrad_split_bytes((int)d, (int)(3 * d), (int)R));
+    if (!wrows) wrows = wgrad_split_rows_attention((int)d, (int)R);
+    float* po = (float*)b.take(wgrad_split_bytes((int)d, (int)d, (int)R, wrows));
+    float* pw = (float*)b.take(wgrad_split_bytes((int)d, (int)(3 * d), (int)R, wrows));
     ReduceList red0;
     WgradSplitList wl0;
     red0.n = wl0.n = wl0.tiles = 0;
     ReduceList* red = later ? later : &red0;
     WgradSplitList* wl = wlater ? wlater : &wl0;
-    wgrad_split_push(wl, red, (const float*)x, d, (const float*)dqkv, 3 * d, (int)R, (int)d, (int)(3 * d), pw, (int)d,
+    wgrad_split_push(wl, wrows, red, (const float*)x, d, (const float*)dqkv, 3 * d, (int)R, (int)d, (int)(3 * d), pw, (int)d,
                      (float*)dwq, (float*)dwk, (float*)dwv, (float*)dbq, (float*)dbk, (float*)dbv);
-    wgrad_split_push(wl, red, (const float*)o, d, (const float*)dy, d, (int)R, (int)d, (int)d, po, 0, (float*)dwo, nullptr, nullptr,
+    wgrad_split_push(wl, wrows, red, (const float*)o, d, (const float*)dy, d, (int)R, (int)d, (int)d, po, 0, (float*)dwo, nullptr, nullptr,
                      (float*)dbo, nullptr, nullptr);
     ProfScope ps(PF_WGRAD, st);
     if (!wlater) launch_wgrad_split(*wl, st);
@@ -725,6 +730,7 @@ struct LayerTrain {
   int split_w1, split_w2;
   bool ring;        // bf16: all weight gradients in one launch (WgradRing)
   WgradPlan plan;
+  int wrows;        // fp32: rows per workgroup of the weight gradients
 };
 static LayerTrain layer_train_layout(const im_shape_t* s, int32_t d_ff) {
   LayerTrain L;
@@ -745,12 +751,14 @@ static LayerTrain layer_train_layout(const im_shape_t* s, int32_t d_ff) {
   L.dh = off; off += align256(R * d * es);
   L.t = off; off += align256(R * d * es);
   L.split_w1 = L.split_w2 = 1;
+  L.wrows = 0;
   size_t p1, p2;
   L.ring = pick_path(s) == PATH_MFMA && mfma_linear_ok(1, d, d_ff);
   if (L.ring) L.plan = wgrad_ring_plan_layer((int)d, d_ff, (int)R);
   if (s->dtype == IM_DTYPE_F32) {
-    p1 = wgrad_split_bytes((int)d, d_ff, (int)R);
-    p2 = wgrad_split_bytes(d_ff, (int)d, (int)R);
+    L.wrows = wgrad_split_rows_layer((int)d, d_ff, (int)R);
+    p1 = wgrad_split_bytes((int)d, d_ff, (int)R, L.wrows);
+    p2 = wgrad_split_bytes(d_ff, (int)d, (int)R, L.wrows);
   } else if (L.ring) {
     p1 = wgrad_ring_bytes(L.plan, (int)d, d_ff);
     p2 = wgrad_ring_bytes(L.plan, d_ff, (int)d);
@@ -770,7 +778,7 @@ static LayerTrain layer_train_layout(const im_shape_t* s, int32_t d_ff) {
   L.cpart_b2 = off; off += align256(colsum_partial_bytes((int)R, (int)d));      // db2
   L.cpart2 = off; off += align256(layernorm_bwd_partial_bytes((int)R, (int)d, es == 2));   // second LayerNorm's two sums
   L.cpart3 = off; off += align256(layernorm_bwd_partial_bytes((int)R, (int)d, es == 2));   // first LayerNorm's
-  L.attws = off; off += align256(L.ring ? mfma_bwd_workspace_bytes(s, &L.plan) : bwd_workspace_bytes(s));
+  L.attws = off; off += align256(L.ring ? mfma_bwd_workspace_bytes(s, &L.plan) : bwd_workspace_bytes(s, L.wrows));
   L.ws_total = off;
   return L;
 }
@@ -891,7 +899,7 @@ int gsit_layer_bwd(const im_shape_t* shape, int32_t d_ff, const void* x, const g
 
   // y = h + a W2 + b2
   if (!bf) {
-    wgrad_split_push(&wl, &later, (const float*)a, d_ff, (const float*)dy, d, (int)R, d_ff, (int)d, partial, 0, (float*)gr->w2, nullptr,
+    wgrad_split_push(&wl, L.wrows, &later, (const float*)a, d_ff, (const float*)dy, d, (int)R, d_ff, (int)d, partial, 0, (float*)gr->w2, nullptr,
                      nullptr, (float*)gr->b2, nullptr, nullptr);
   } else if (L.ring) {
     wgrad_ring_push(&wr, L.plan, &later, a, d_ff, dy, d, d_ff, (int)d, partial, 0, (float*)gr->w2, nullptr, nullptr, (float*)gr->b2,
@@ -918,7 +926,7 @@ int gsit_layer_bwd(const im_shape_t* shape, int32_t d_ff, const void* x, const g
   // z = v W1 + b1 with v = LN(h; ln2)
   if ((rc = launch_layernorm(h, p->ln2_g, p->ln2_b, v, (int)R, (int)d, ln_eps, bf, st))) return rc;
   if (!bf) {
-    wgrad_split_push(&wl, &later, (const float*)v, d, (const float*)dz, d_ff, (int)R, (int)d, d_ff, partial1, 0, (float*)gr->w1, nullptr,
+    wgrad_split_push(&wl, L.wrows, &later, (const float*)v, d, (const float*)dz, d_ff, (int)R, (int)d, d_ff, partial1, 0, (float*)gr->w1, nullptr,
                      nullptr, (float*)gr->b1, nullptr, nullptr);
   } else if (L.ring) {
     wgrad_ring_push(&wr, L.plan, &later, v, d, dz, d_ff, (int)d, d_ff, partial1, 0, (float*)gr->w1, nullptr, nullptr, (float*)gr->b1,
@@ -964,7 +972,7 @@ int gsit_layer_bwd(const im_shape_t* shape, int32_t d_ff, const void* x, const g
                             defer, L.ring ? &wr : nullptr, L.ring ? &L.plan : nullptr);
   else
     rc = bwd_smallhead(shape, u, p->wq, p->wk, p->wv, p->wo, valid_len, key_pad, sv + L.att, dh, dv, gr->wq, gr->wk, gr->wv,
-                     gr->wo, gr->bq, gr->bk, gr->bv, gr->bo, ws + L.attws, st, bf ? nullptr : &later, bf ? nullptr : &wl);
+                     gr->wo, gr->bq, gr->bk, gr->bv, gr->bo, ws + L.attws, st, bf ? nullptr : &later, bf ? nullptr : &wl, L.wrows);
   if (rc) return rc;
   launch_wgrad_split(wl, st);
   if (L.ring) launch_wgrad_ring(wr, L.plan, (int)R, st);

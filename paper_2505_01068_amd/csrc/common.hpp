@@ -226,7 +226,8 @@ size_t wgrad_small_partial_bytes(int M, int N, int R);
 void launch_wgrad_small_reduce(const float* partial, int nz, int M, int N, float* o0, float* o1, float* o2, int n_per,
                                hipStream_t st);
 int launch_wgrad_small(const void* A, long lda, const void* G, long ldg, int R, int M, int N, float* partial, hipStream_t st);
-// fp32 weight gradients over the same R rows in one launch (gemm_split.hip).  push: C[M,N] = A^T G into w0 (n_per == 0) or
+// fp32 weight gradients over the same R rows in one launch (gemm_split.hip), `rows` per workgroup: from the (M, N) of ALL
+// products that the pass may push, so that a gradient's bits do not depend on which others are asked for.  push: C[M,N] = A^T G into w0 (n_per == 0) or
 // column blocks of n_per columns into w0 | w1 | w2 (NULL = dropped), the column sums of G into b0 | b1 | b2 likewise;
 // partial: wgrad_split_bytes, untouched until the reduction list has run.
 struct WgradSplit {
@@ -240,9 +241,11 @@ struct WgradSplitList {
   WgradSplit p[4];
   int n, tiles, R, rows;   // tiles: of the largest problem
 };
-size_t wgrad_split_bytes(int M, int N, int R);
-void wgrad_split_push(WgradSplitList* l, ReduceList* red, const float* A, long lda, const float* G, long ldg, int R, int M, int N,
-                      float* partial, int n_per, float* w0, float* w1, float* w2, float* b0, float* b1, float* b2);
+int wgrad_split_rows_attention(int d, int R);
+int wgrad_split_rows_layer(int d, int d_ff, int R);
+size_t wgrad_split_bytes(int M, int N, int R, int rows);
+void wgrad_split_push(WgradSplitList* l, int rows, ReduceList* red, const float* A, long lda, const float* G, long ldg, int R, int M,
+                      int N, float* partial, int n_per, float* w0, float* w1, float* w2, float* b0, float* b1, float* b2);
 void launch_wgrad_split(const WgradSplitList& l, hipStream_t st);
 
 // encoder-layer backward pieces: a = GELU(z); g <- g * GELU'(z) in place; LayerNorm backward of rows

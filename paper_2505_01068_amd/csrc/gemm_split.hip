@@ -4,6 +4,8 @@
 // them is taken as x1 y1 + x1 y2 + x2 y1 + x2 y2 + x1 y3 + x3 y1, each exact in fp32 and accumulated in fp32.  The
 // dropped terms are below 2^-26 of the product, a quarter of an fp32 rounding.  Six 32x32x16 bf16 instructions (15.5 ns
 // each) replace eight 32x32x2 fp32 ones (27 ns each, and those take the vector ALU's issue slots).
+#include <algorithm>
+
 #include "mfma_common.hpp"
 
 namespace imattn {
@@ -327,21 +329,28 @@ __global__ __launch_bounds__(256, 4) void wgrad_split_kernel(WgradSplitList l) {
   }
 }
 
-// rows per workgroup: about 224 partial results, so that a reduction reads what a few hundred workgroups wrote
-static int wgrad_split_rows(int R) {
-  const int rows = ((R + 223) / 224 + 15) & ~15;
-  return rows < 32 ? 32 : rows;
+// Rows per workgroup.  At most 224 row ranges, so that a reduction reads what a few hundred workgroups wrote, and at most
+// 2048 workgroups over all the products of the pass, eight per CU: what they write and the reduction reads back is then 34 MB
+// at every width (224 ranges alone: 1 GB at d = 256, d_ff = 1024, 33 600 rows, 12 GB at d = 1024; layer step of 29 600 rows at
+// d = 256 2540 us with 224, 2310 like this, at d = 512 8500 / 7070, 3 700 rows at d = 1024 5420 / 3320).
+static int wgrad_split_rows(int R, long tiles) {
+  const int ranges = (int)std::max(1L, std::min(224L, 2048 / tiles));
+  return std::max(32, ((R + ranges - 1) / ranges + 15) & ~15);
 }
-static int wgrad_split_parts(int R) { const int rows = wgrad_split_rows(R); return (R + rows - 1) / rows; }
-size_t wgrad_split_bytes(int M, int N, int R) {
-  return (size_t)wgrad_split_parts(R) * (((long)M * N + 3) / 4 * 4 + (N + 3) / 4 * 4) * sizeof(float);
+static long wgrad_split_tiles(int M, int N) { return (long)((M + 63) / 64) * ((N + 63) / 64); }
+int wgrad_split_rows_attention(int d, int R) { return wgrad_split_rows(R, wgrad_split_tiles(d, d) + wgrad_split_tiles(d, 3 * d)); }
+int wgrad_split_rows_layer(int d, int d_ff, int R) {
+  return wgrad_split_rows(R, wgrad_split_tiles(d, d) + wgrad_split_tiles(d, 3 * d) + wgrad_split_tiles(d, d_ff) + wgrad_split_tiles(d_ff, d));
 }
-void wgrad_split_push(WgradSplitList* l, ReduceList* red, const float* A, long lda, const float* G, long ldg, int R, int M, int N,
-                      float* partial, int n_per, float* w0, float* w1, float* w2, float* b0, float* b1, float* b2) {
+size_t wgrad_split_bytes(int M, int N, int R, int rows) {
+  return (size_t)((R + rows - 1) / rows) * (((long)M * N + 3) / 4 * 4 + (N + 3) / 4 * 4) * sizeof(float);
+}
+void wgrad_split_push(WgradSplitList* l, int rows, ReduceList* red, const float* A, long lda, const float* G, long ldg, int R, int M,
+                      int N, float* partial, int n_per, float* w0, float* w1, float* w2, float* b0, float* b1, float* b2) {
   const bool w = w0 || w1 || w2, b = b0 || b1 || b2;
   if (!w && !b) return;
   WgradSplit& p = l->p[l->n++];
-  const int parts = wgrad_split_parts(R);
+  const int parts = (R + rows - 1) / rows;
   p.A = A; p.G = G; p.lda = lda; p.ldg = ldg; p.M = M; p.N = N;
   p.stride = (int)(((long)M * N + 3) / 4 * 4);
   p.partial = w ? partial : nullptr;
@@ -350,7 +359,7 @@ void wgrad_split_push(WgradSplitList* l, ReduceList* red, const float* A, long l
   p.tn_magic = tn == 1 ? 0u : (unsigned)(((1ull << 32) + tn - 1) / tn);   // t / tn = mulhi(t, magic) for t tn < 2^32; 0: tn is 1
   l->tiles = l->tiles > (int)tiles ? l->tiles : (int)tiles;
   l->R = R;
-  l->rows = wgrad_split_rows(R);
+  l->rows = rows;
   if (w) reduce_push(red, p.partial, parts, M, N, w0, w1, w2, n_per, p.stride);
   if (b) reduce_push(red, p.csum, parts, 1, N, b0, b1, b2, n_per, (N + 3) / 4 * 4);
 }

@@ -154,3 +154,20 @@ def test_schedule_covers_exactly_the_live_blocks(seg, name, tile):
     # heaviest segments first
     per_row = [it.pairs // it.q_rows for it in items]
     assert per_row == sorted(per_row, reverse=True)
+
+
+@pytest.mark.parametrize("d", [40, 64, 128, 256, 512, 1024])
+@pytest.mark.parametrize("batch", [1, 8, 32, 256])
+def test_fp32_workspace_does_not_grow_with_the_partial_results_of_wide_gradients(d, batch):
+    # the backward's workspace is its row tensors and, for the weight gradients, at most 2048 partial tiles of 64 x 64 (or one
+    # set of tiles, where a set is more), with as many sums of 64 columns, plus what whole tiles add at the edges
+    seg, d_ff = (50, 500, 375), 4 * d
+    R, H = batch * sum(seg), max(d // 16, 8)
+    s = shape(batch=batch, seg_len=seg, d_model=d, n_heads=H)
+    tiles = lambda m, n: -(-m // 64) * -(-n // 64)  # noqa: E731
+    partial = lambda t: max(t, 2048) * (64 * 64 + 64) * 4 + (1 << 16)  # noqa: E731
+    attention = R * (4 * d + H) * 4
+    assert B.im_attention_sizes(s)[1] <= attention + partial(tiles(d, d) + tiles(d, 3 * d))
+    layer = attention + R * (5 * d + d_ff) * 4
+    extra = 4 * (R // 256 + 1) * (d_ff + d) + 2 * 4 * 2 * d * (R // 64 + 600)      # column sums, two LayerNorms' sums
+    assert B.gsit_layer_train_sizes(s, d_ff)[1] <= layer + partial(tiles(d, d) + tiles(d, 3 * d) + 2 * tiles(d, d_ff)) + extra
