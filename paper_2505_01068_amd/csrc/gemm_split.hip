@@ -333,9 +333,14 @@ __global__ __launch_bounds__(256, 4) void wgrad_split_kernel(WgradSplitList l) {
 // 2048 workgroups over all the products of the pass, eight per CU: what they write and the reduction reads back is then 34 MB
 // at every width (224 ranges alone: 1 GB at d = 256, d_ff = 1024, 33 600 rows, 12 GB at d = 1024; layer step of 29 600 rows at
 // d = 256 2540 us with 224, 2310 like this, at d = 512 8500 / 7070, 3 700 rows at d = 1024 5420 / 3320).
+// Ranges of at most 2048 rows up to 12 tiles (d = 64, d_ff = 256; below 2 per cent of the tensors of those rows): a sum's
+// roundings, one per 16 rows, grow with the square root of its length, dWo of d = 8 over 1 048 560 rows 4.2e-7 with 224 ranges
+// of 4 688 rows, 3.0e-7 like this.  (The matrix instruction's rounding has no preferred sign here: with the sums of every
+// second range negated every error stays what it was.)
 static int wgrad_split_rows(int R, long tiles) {
   const int ranges = (int)std::max(1L, std::min(224L, 2048 / tiles));
-  return std::max(32, ((R + ranges - 1) / ranges + 15) & ~15);
+  const int rows = std::max(32, ((R + ranges - 1) / ranges + 15) & ~15);
+  return tiles <= 12 ? std::min(rows, 2048) : rows;
 }
 static long wgrad_split_tiles(int M, int N) { return (long)((M + 63) / 64) * ((N + 63) / 64); }
 int wgrad_split_rows_attention(int d, int R) { return wgrad_split_rows(R, wgrad_split_tiles(d, d) + wgrad_split_tiles(d, 3 * d)); }

@@ -54,3 +54,28 @@ def test_layer_weight_gradients(d, H, d_ff, batch, seg):
         B.gsit_layer_bwd(shape, d_ff, x, pd, saved, dy, some, workspace=ws)
         for k in want:
             assert torch.equal(some[k], grads[k]), k
+
+
+def test_weight_gradient_over_a_million_rows():
+    # dWo = O^T dy over 1 048 560 rows, each row of O good to 2e-7.  A partial sum of n rows is a random walk that is rounded
+    # once per 16 rows, by up to a few tenths of 2^-23 of its size: 2^-24 sqrt(n / 16), 4.2e-7 measured with ranges of 4 688
+    # rows; 2.9e-7 with fp32 multiply-adds in ranges of 1 024.
+    print("[case] fp32 weight gradient over 1 048 560 rows", flush=True)
+    batch, seg, d, H = 65535, (5, 5, 6), 8, 2
+    gen = torch.Generator(device="cuda").manual_seed(821)
+    x, dy = (torch.randn(batch, 16, d, device="cuda", generator=gen) for _ in range(2))
+    w = {k: torch.randn(d, d, device="cuda", generator=gen) * 0.4 for k in ("wq", "wk", "wv", "wo")}
+    shape = B.make_shape(batch, seg, d, H, oracle.IM_IFM_FORWARD, 0.5, "fp32")
+    saved, ws = (torch.empty(n, dtype=torch.uint8, device="cuda") for n in B.im_attention_sizes(shape))
+    B.im_attention_fwd(shape, x, **w, saved=saved, workspace=ws)
+    dwo, dx = torch.empty(d, d, device="cuda"), torch.empty_like(x)
+    B.im_attention_bwd(shape, x, **w, saved=saved, dy=dy, dx=dx, dwq=None, dwk=None, dwv=None, dwo=dwo, workspace=ws)
+    q, k, v = ((x.double() @ w[n].double()).view(batch, 16, H, d // H).transpose(1, 2).contiguous() for n in ("wq", "wk", "wv"))
+    segment = torch.tensor([0] * 5 + [1] * 5 + [2] * 6, device="cuda")
+    live = torch.tensor([[(oracle.IM_IFM_FORWARD >> (3 * i + j)) & 1 for j in range(3)] for i in range(3)], device="cuda")
+    p = (0.5 * (q @ k.transpose(2, 3).contiguous())).masked_fill(live[segment][:, segment] == 0, float("-inf")).softmax(-1)
+    o = (p @ v).transpose(1, 2).reshape(-1, d)
+    ref = o.t() @ dy.double().view(-1, d)
+    err = ((dwo - ref).norm() / ref.norm()).item()
+    print(f"    {err:.2e}")
+    assert err < 3.4e-7, err
