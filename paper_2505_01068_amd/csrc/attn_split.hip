@@ -963,7 +963,7 @@ static SplitGeo split_geo(const Geo& g, bool query_side) {
   return s;
 }
 
-// KERNEL for head dimension dh: exact instantiations, or the next larger of 4 / 8 / 16 with columns beyond dh zeroed.
+// KERNEL for head dimension dh: exact instantiations, or the next larger of 4 / 8 / 12 / 16 with columns beyond dh zeroed.
 #define SPLIT_DISPATCH(dh, KERNEL, ...)                               \
   do {                                                                \
     if ((dh) == 4) SPLIT_LAUNCH(KERNEL, 4, true, __VA_ARGS__);        \
@@ -975,6 +975,7 @@ static SplitGeo split_geo(const Geo& g, bool query_side) {
     else if ((dh) == 16) SPLIT_LAUNCH(KERNEL, 16, true, __VA_ARGS__); \
     else if ((dh) < 4) SPLIT_LAUNCH(KERNEL, 4, false, __VA_ARGS__);   \
     else if ((dh) < 8) SPLIT_LAUNCH(KERNEL, 8, false, __VA_ARGS__);   \
+    else if ((dh) < 12) SPLIT_LAUNCH(KERNEL, 12, false, __VA_ARGS__); \
     else SPLIT_LAUNCH(KERNEL, 16, false, __VA_ARGS__);                \
   } while (0)
 // grid (8 ceil(pairs / 8), tiles); a launch takes at most 2^22 pairs (a grid's x holds 2^32 - 1 threads) and 65535 tiles
