@@ -171,3 +171,11 @@ def test_fp32_workspace_does_not_grow_with_the_partial_results_of_wide_gradients
     layer = attention + R * (5 * d + d_ff) * 4
     extra = 4 * (R // 256 + 1) * (d_ff + d) + 2 * 4 * 2 * d * (R // 64 + 600)      # column sums, two LayerNorms' sums
     assert B.gsit_layer_train_sizes(s, d_ff)[1] <= layer + partial(tiles(d, d) + tiles(d, 3 * d) + 2 * tiles(d, d_ff)) + extra
+
+
+@pytest.mark.parametrize("d,H", [(256, 4), (512, 8), (1024, 16)])
+def test_bf16_workspace_of_tall_inputs_is_mostly_their_rows(d, H):
+    # 1 075 200 rows: dO, dQ | dK | dV and the row statistics, and less than a twentieth of that for partial results
+    s = shape(batch=1024, seg_len=(50, 500, 500), d_model=d, n_heads=H, dtype="bf16")
+    rows = 1024 * 1050 * (4 * d * 2 + H * 4)
+    assert rows <= B.im_attention_sizes(s)[1] <= 1.05 * rows

@@ -49,3 +49,26 @@ def test_layer_weight_gradients(d, H, d_ff, batch, seg):
         B.gsit_layer_bwd(shape, d_ff, x, pd, saved, dy, some, workspace=ws)
         for k in names:
             assert torch.equal(some[k], grads[k]), k
+
+
+@pytest.mark.parametrize("batch", [8750, 4501])   # 183 and 94 stages per range: two runs of 80 and a rest, one and a rest
+def test_ranges_of_more_than_80_stages(batch):
+    # Every segment one row that attends itself and Wv = I: O = x exactly, so dWo = x^T dy and dbo have exact references.
+    # A sum of 80 stages is rounded 320 times, by a few tenths of 2^-23 of its size: 5e-7 (measured 4.3e-7).
+    d, H, seg = 1024, 16, (1,) * 8
+    print(f"[case] bf16 weight gradients, tall d={d} rows={8 * batch}", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(931)
+    x, dy = (torch.randn(batch, 8, d, device="cuda", generator=gen).bfloat16() for _ in range(2))
+    w = {k: (torch.randn(d, d, device="cuda", generator=gen) / 32).bfloat16() for k in ("wq", "wk", "wo")}
+    w["wv"] = torch.eye(d, device="cuda").bfloat16()
+    shape = B.make_shape(batch, seg, d, H, sum(1 << (9 * i) for i in range(8)), 0.125, "bf16")
+    saved, ws = (torch.empty(n, dtype=torch.uint8, device="cuda") for n in B.im_attention_sizes(shape))
+    B.im_attention_fwd(shape, x, **w, saved=saved, workspace=ws)
+    dwo, dbo = torch.empty(d, d, device="cuda"), torch.empty(d, device="cuda")
+    B.im_attention_bwd(shape, x, **w, saved=saved, dy=dy, dx=torch.empty_like(x), dwq=None, dwk=None, dwv=None, dwo=dwo, dbo=dbo,
+                       workspace=ws)
+    a, g = x.view(-1, d).double(), dy.view(-1, d).double()
+    for got, ref, bar in ((dwo, a.t() @ g, 6e-7), (dbo, g.sum(0), 3e-7)):
+        err = ((got - ref).norm() / ref.norm()).item()
+        print(f"    {err:.1e}")
+        assert err < bar, err
