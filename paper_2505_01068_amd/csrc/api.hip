@@ -277,8 +277,8 @@ static int fwd_smallhead(const im_shape_t* s, const void* x, const void* wq, con
   return check_hip("im_attention_fwd launch");
 }
 
-// later / wlater: second-stage sums resp. fp32 weight gradients that the caller launches at the end of its own pass
-// (NULL: launched here); with wlater the operands (x, dy and the workspace) stay as they are until then, and wrows is the
+// later / wlater, both or neither: second-stage sums resp. fp32 weight gradients that the caller launches at the end of its
+// own pass (NULL: launched here); with wlater the operands (x, dy and the workspace) stay as they are until then, and wrows is the
 // caller's number of rows per workgroup.
 static int bwd_smallhead(const im_shape_t* s, const void* x, const void* wq, const void* wk, const void* wv,
                          const void* wo, const int32_t* valid_len, const uint8_t* key_pad, const char* sv,
@@ -324,15 +324,17 @@ static int bwd_smallhead(const im_shape_t* s, const void* x, const void* wq, con
     ReduceList red0;
     WgradSplitList wl0;
     red0.n = wl0.n = wl0.tiles = 0;
-    ReduceList* red = later ? later : &red0;
+    ReduceList* red = wlater ? later : &red0;
     WgradSplitList* wl = wlater ? wlater : &wl0;
     wgrad_split_push(wl, wrows, red, (const float*)x, d, (const float*)dqkv, 3 * d, (int)R, (int)d, (int)(3 * d), pw, (int)d,
                      (float*)dwq, (float*)dwk, (float*)dwv, (float*)dbq, (float*)dbk, (float*)dbv);
     wgrad_split_push(wl, wrows, red, (const float*)o, d, (const float*)dy, d, (int)R, (int)d, (int)d, po, 0, (float*)dwo, nullptr, nullptr,
                      (float*)dbo, nullptr, nullptr);
-    ProfScope ps(PF_WGRAD, st);
-    if (!wlater) launch_wgrad_split(*wl, st);
-    if (!later) launch_reduce_list(*red, st);
+    if (!wlater) {
+      ProfScope ps(PF_WGRAD, st);
+      launch_wgrad_split(*wl, st);
+      launch_reduce_list(*red, st);
+    }
   } else {
     int split = 1;
     size_t pbytes = std::max(gemm_alu_partial_bytes((int)d, (int)(3 * d), (int)R, &split),
@@ -974,8 +976,11 @@ int gsit_layer_bwd(const im_shape_t* shape, int32_t d_ff, const void* x, const g
     rc = bwd_smallhead(shape, u, p->wq, p->wk, p->wv, p->wo, valid_len, key_pad, sv + L.att, dh, dv, gr->wq, gr->wk, gr->wv,
                      gr->wo, gr->bq, gr->bk, gr->bv, gr->bo, ws + L.attws, st, bf ? nullptr : &later, bf ? nullptr : &wl, L.wrows);
   if (rc) return rc;
-  launch_wgrad_split(wl, st);
-  if (L.ring) launch_wgrad_ring(wr, L.plan, (int)R, st);
+  if (wl.n || wr.n) {
+    ProfScope ps(PF_WGRAD, st);
+    launch_wgrad_split(wl, st);
+    if (L.ring) launch_wgrad_ring(wr, L.plan, (int)R, st);
+  }
   // dx = dh + LN1 backward(du)
   if ((rc = launch_layernorm_bwd(x, p->ln1_g, dv, dh, dx, t, (int)R, (int)d, ln_eps, bf, (float*)gr->ln1_g, (float*)gr->ln1_b, cpart3,
                                  defer, st)))

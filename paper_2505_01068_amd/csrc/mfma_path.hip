@@ -229,9 +229,11 @@ int mfma_attention_bwd(const im_shape_t* s, const void* x, const void* wq, const
     wgrad_ring_push(wl, pl, red, x, d, dqkv, 3 * d, d, 3 * d, partial, d, (float*)dwq, (float*)dwk, (float*)dwv, (float*)dbq,
                     (float*)dbk, (float*)dbv);
     wgrad_ring_push(wl, pl, red, o, d, dy, d, d, d, partial_o, 0, (float*)dwo, nullptr, nullptr, (float*)dbo, nullptr, nullptr);
-    ProfScope ps(PF_WGRAD, st);
-    if (!wring) launch_wgrad_ring(own, pl, R, st);
-    if (!defer) launch_reduce_list(own_red, st);
+    if (!wring) {
+      ProfScope ps(PF_WGRAD, st);
+      launch_wgrad_ring(own, pl, R, st);
+      if (!defer) launch_reduce_list(own_red, st);
+    }
   }
 
   if (dx) {

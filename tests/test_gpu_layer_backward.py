@@ -154,3 +154,26 @@ def test_layer_backward_at_the_benchmark_shape():
     floor = 2.0 ** -8 * max(float(np.max(np.abs(v))) for v in acc.values())
     errs = {n: assert_close(v, acc[n], tol, f"c4train d{n}", grad_scale(n, acc[n], floor, np.max(dk_sum))) for n, v in grads.items()}
     say("    " + " ".join(f"d{k}={v:.1e}" for k, v in errs.items()))
+
+
+@pytest.mark.parametrize("dtype,d,H,d_ff,batch,seg", [("bf16", 512, 8, 2048, 16, (24, 500, 500)), ("fp32", 40, 8, 160, 32, (50, 500, 500))])
+def test_kernel_timing_covers_the_weight_gradients(dtype, d, H, d_ff, batch, seg):
+    # the family's time cannot be below its flops at 2.5 PFLOP/s (40 us), or its operands' bytes at 8 TB/s (11 us; an empty
+    # pair of events reads 4 to 5 us)
+    print(f"[case] kernel timing of a layer's weight gradients {dtype}", flush=True)
+    R = batch * sum(seg)
+    shape = B.make_shape(batch, seg, d, H, oracle.IM_IFM_FORWARD, 0.3, dtype)
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    x, dy = (torch.randn(batch, sum(seg), d, device="cuda").to(dt) for _ in range(2))
+    pd = {k: to_dev(v, dtype) for k, v in synth.layer_params(d, d_ff, 3, 0, dtype=dtype).items()}
+    saved, ws = (torch.empty(n, dtype=torch.uint8, device="cuda") for n in B.gsit_layer_train_sizes(shape, d_ff))
+    grads = {k: torch.empty(v.shape, dtype=torch.float32, device="cuda") for k, v in pd.items()}
+    B.gsit_layer_fwd_train(shape, d_ff, x, pd, saved, workspace=ws)
+    B.im_profile_enable(True)
+    B.gsit_layer_bwd(shape, d_ff, x, pd, saved, dy, grads, workspace=ws)
+    torch.cuda.synchronize()
+    ms, launches = B.im_profile_get()["wgrad"]
+    B.im_profile_enable(False)
+    flops, nbytes = 2 * R * (4 * d * d + 2 * d * d_ff), x.element_size() * R * (8 * d + 2 * d_ff)
+    print(f"    {ms * 1e3:.1f} us")
+    assert launches == 1 and ms * 1e-3 >= max(flops / 2.5e15, nbytes / 8e12)
