@@ -418,7 +418,10 @@ constexpr int RK = 64;
 constexpr int ring_stage_bytes(int mb) { return (64 * mb + GN) * RK * 2; }
 constexpr int ring_lds_bytes(int mb) { return 2 * ring_stage_bytes(mb); }
 
-template <bool BKM, bool EPI, int MB, bool LN = false>
+// TAIL: K % 64 == 32.  The last stage is half a stage: its second half is a copy of the first (any address inside the
+// operands will do) and is not multiplied.  Residual and GELU products only; 67 200 x 256 x 1056 + residual 74 us, 88 in the
+// register-staged kernel; the layer forward around it 297 us, 310 with that, 304 in the 256-row tiles of old.
+template <bool BKM, bool EPI, int MB, bool LN = false, bool TAIL = false>
 __global__ __launch_bounds__(256, 2) void mfma_gemm_ring_kernel(MGemm p) {
   static_assert(!LN || MB == 1, "the LayerNorm form: 64 rows, two per thread");
   extern __shared__ __attribute__((aligned(1024))) bf16_t smem[];
@@ -430,7 +433,8 @@ __global__ __launch_bounds__(256, 2) void mfma_gemm_ring_kernel(MGemm p) {
   int bx, by, bz;
   xcd_block_index(bx, by, bz);
   const int m0 = by * ROWS, n0 = bx * GN;
-  const int n_it = p.K / RK;   // K % 64 == 0 is required by the launcher
+  static_assert(!TAIL || (BKM && !LN), "k-major B, plain rows");
+  const int n_it = TAIL ? (p.K + 32) / RK : p.K / RK;   // K % 64 is required by the launcher to be 32 resp. 0
 
   const bf16_t* ga[CA];
   const bf16_t* gb[CB];   // k-major B: source pointer
@@ -463,6 +467,17 @@ __global__ __launch_bounds__(256, 2) void mfma_gemm_ring_kernel(MGemm p) {
   }
   auto issue = [&](int it) {
     char* base = (char*)smem + (it & 1) * STB;
+    if (TAIL && it == n_it - 1) {   // columns and rows of the second half: 32 back
+#pragma unroll
+      for (int j = 0; j < CA; ++j) {
+        const int slot = (wave * CA + j) * 64 + lane, c = (slot & 7) ^ sw_f(slot >> 3);
+        dma16(ga[j] + (long)it * RK - (c & 4) * 8, base + (wave * CA + j) * 1024);
+      }
+#pragma unroll
+      for (int j = 0; j < CB; ++j)   // k = 4 (4 wave + j) + lane / 16
+        dma16(gb[j] + ((long)it * RK - (wave >= 2 ? 32 : 0)) * p.ldb, base + ROWS * RK * 2 + (wave * CB + j) * 1024);
+      return;
+    }
 #pragma unroll
     for (int j = 0; j < CA; ++j) dma16(ga[j] + (long)it * RK, base + (wave * CA + j) * 1024);
     const bf16_t* mat = p.B[0];
@@ -531,6 +546,7 @@ __global__ __launch_bounds__(256, 2) void mfma_gemm_ring_kernel(MGemm p) {
     const char* sB = st + ROWS * RK * 2;
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
+      if (TAIL && s == 2 && it == n_it - 1) break;
       bf16x8 fa[MB], fb[2];
 #pragma unroll
       for (int x = 0; x < MB; ++x) fa[x] = lds_frag_sw(sA, wm * 32 * MB + x * 32, lo, s * 2 + hi);
@@ -1741,17 +1757,18 @@ static void launch_dma12(const MGemm& p, hipStream_t st) {
   dim3 grid((p.N + DN - 1) / DN, (p.M + TM - 1) / TM, 1);
   hipLaunchKernelGGL((mfma_gemm_dma12_kernel), grid, dim3(TWAVES * 64), T_LDS_BYTES, st, p);
 }
-template <bool BKM, bool EPI, int MB, bool LN = false>
+template <bool BKM, bool EPI, int MB, bool LN = false, bool TAIL = false>
 static void launch_ring(const MGemm& p, hipStream_t st) {
   static_assert(ring_lds_bytes(MB) <= 65536, "no attribute is needed up to 64 KB");
   dim3 grid((p.N + GN - 1) / GN, (p.M + 64 * MB - 1) / (64 * MB), 1);
-  hipLaunchKernelGGL((mfma_gemm_ring_kernel<BKM, EPI, MB, LN>), grid, dim3(256), ring_lds_bytes(MB), st, p);
+  hipLaunchKernelGGL((mfma_gemm_ring_kernel<BKM, EPI, MB, LN, TAIL>), grid, dim3(256), ring_lds_bytes(MB), st, p);
 }
-// Forms the ring kernel takes: row-major A, whole 64-deep k-tiles (per weight, where K is split over several) and
-// everything it copies or stores in 16-byte units aligned to that.
+// Forms the ring kernel takes: row-major A, whole 64-deep k-tiles (per weight, where K is split over several; half a last one
+// in residual and GELU products of k-major weights) and everything it copies or stores in 16-byte units aligned to that.
+static bool ring_tail(const MGemm& p) { return p.K % RK == 32 && p.b_kmajor && !p.ln_g && p.b_kper == 0 && (p.gelu || p.res); }
 static bool ring_form(const MGemm& p) {
   auto al16 = [](const void* q) { return (reinterpret_cast<uintptr_t>(q) & 15) == 0; };
-  return !p.a_kmajor && p.split_k == 1 && !p.partial && (!p.ln_g || (p.K == RK && al16(p.ln_g) && al16(p.ln_b))) && p.K >= RK && p.K % RK == 0 && p.M >= 1 && p.N >= 8 &&
+  return !p.a_kmajor && p.split_k == 1 && !p.partial && (!p.ln_g || (p.K == RK && al16(p.ln_g) && al16(p.ln_b))) && p.K >= RK && (p.K % RK == 0 || ring_tail(p)) && p.M >= 1 && p.N >= 8 &&
          p.N % 8 == 0 && p.lda % 8 == 0 && p.ldb % 8 == 0 && p.ldc % 8 == 0 && p.b_kper % RK == 0 && p.b_nper % 8 == 0 &&
          (!p.scale0_on || p.n_per % 8 == 0) && al16(p.A) && al16(p.B[0]) && al16(p.B[1]) && al16(p.B[2]) && al16(p.C) &&
          al16(p.C2) && al16(p.res);
@@ -1772,6 +1789,13 @@ static void launch_layout(const MGemm& p, bool dma, hipStream_t st) {
         if (p.ln_g) {
           if (epi) launch_ring<true, true, 1, true>(p, st);
           else launch_ring<true, false, 1, true>(p, st);
+          return;
+        }
+      }
+      if constexpr (BKM) {
+        if (ring_tail(p)) {
+          if (ring_rows128(p)) launch_ring<true, true, 2, false, true>(p, st);
+          else launch_ring<true, true, 1, false, true>(p, st);
           return;
         }
       }
