@@ -776,8 +776,11 @@ static LayerTrain layer_train_layout(const im_shape_t* s, int32_t d_ff) {
   // partials keeps a region of its own
   L.partial = off; off += align256(p2);     // dW2
   L.partial1 = off; off += align256(p1);    // dW1
-  L.cpart = off; off += align256(colsum_partial_bytes((int)R, (int)f));         // db1
-  L.cpart_b2 = off; off += align256(colsum_partial_bytes((int)R, (int)d));      // db2
+  L.cpart = L.cpart_b2 = off;
+  if (es == 2 && !L.ring) {   // bias gradients that no weight gradient brings along
+    off += align256(colsum_partial_bytes((int)R, (int)f));                      // db1
+    L.cpart_b2 = off; off += align256(colsum_partial_bytes((int)R, (int)d));    // db2
+  }
   L.cpart2 = off; off += align256(layernorm_bwd_partial_bytes((int)R, (int)d, es == 2));   // second LayerNorm's two sums
   L.cpart3 = off; off += align256(layernorm_bwd_partial_bytes((int)R, (int)d, es == 2));   // first LayerNorm's
   L.attws = off; off += align256(L.ring ? mfma_bwd_workspace_bytes(s, &L.plan) : bwd_workspace_bytes(s, L.wrows));

@@ -126,30 +126,6 @@ __device__ __forceinline__ void udivmod(unsigned n, unsigned d, unsigned& q, uns
     r = n % d;
   }
 }
-
-// Workgroup -> (tile, head, batch element) for a grid (tiles, heads, batch), segment-major: all
-// workgroups of the first segment of the tile order (the one with the most work per tile) come
-// first, for every (batch element, head) pair, then those of the next segment.  The workgroups
-// that run longest start first and the short ones fill the tail of the launch.  Inside a segment
-// the order is pair, then tile (the tiles of one pair read the same keys and start together) --
-// except with packed rows (tile_first), where the grid covers the longest sample and the later
-// tiles of most pairs find no rows: there tile, then pair, so the tiles that have work are not
-// queued behind the empty ones.
-__device__ __forceinline__ void segment_major_index(const int* prefix, int nord, bool tile_first, int& tile, int& h,
-                                                    int& b) {
-  const unsigned gx = gridDim.x, gy = gridDim.y, npair = gy * gridDim.z;
-  const unsigned lin = blockIdx.x + gx * (blockIdx.y + gy * blockIdx.z);
-  int k = 0;
-  while (k + 1 < nord && lin >= npair * (unsigned)prefix[k + 1]) ++k;
-  const unsigned nt = (unsigned)(prefix[k + 1] - prefix[k]), j = lin - npair * (unsigned)prefix[k];
-  unsigned pair, t, hh, bb;
-  if (tile_first) udivmod(j, npair, t, pair);
-  else udivmod(j, nt, pair, t);
-  udivmod(pair, gy, bb, hh);
-  tile = prefix[k] + (int)t;
-  h = (int)hh;
-  b = (int)bb;
-}
 #endif
 
 // ---- launchers implemented in the .hip files (all enqueue on `st`, none syncs) ----
@@ -188,14 +164,14 @@ size_t gemm_alu_partial_bytes(int M, int N, int K, int* split_k);
 // until launch_reduce_list.
 struct ReduceJob { const float* partial; int nparts, M, N, n_per; long stride; float* o[3]; };   // stride: of a partial result, % 4 == 0
 struct ReduceList { ReduceJob job[16]; int n; int first[16], lanes[16]; };   // first (workgroup of a job), lanes (over the partials): set by launch_reduce_list
-// N % 4 == 0, at most 65536 output quads and at most 8 MB of partials (a larger set is read back faster right after
-// it was written, while it is still in the last-level cache): the job can go on a list
+// A split-K product or column sum that is launched by itself may go on a list: N % 4 == 0, at most 65536 output quads and at
+// most 8 MB of partials (a larger set is read back faster right after it was written, while it is still in the last-level
+// cache).  The launches that hold all weight gradients of a pass put every job on it, whatever its size.
 bool reduce_deferrable(int M, int N, int nparts);
 void reduce_push(ReduceList* l, const float* partial, int nparts, int M, int N, float* o0, float* o1, float* o2, int n_per,
                  long stride = 0);   // 0: M * N
 void launch_reduce_list(ReduceList& l, hipStream_t st);
 // column sums of a [R, n] matrix (bias gradients), deterministic two-stage
-int launch_colsum(const void* a, long lda, int R, int n, int a_bf16, float* out, float* partial, hipStream_t st);
 size_t colsum_partial_bytes(int R, int n);   // for one matrix; launch_colsum_multi (count <= 4) needs count times as much
 // column sums of up to 3 [R, n] matrices (same element type) in one pair of launches; out[i] == nullptr skips matrix i
 int launch_colsum_multi(const void* const* a, const long* lda, float* const* out, int count, int R, int n, int a_bf16,

@@ -561,9 +561,6 @@ int launch_colsum_multi(const void* const* a, const long* lda, float* const* out
   hipLaunchKernelGGL(colsum_stage2, dim3((n + 15) / 16, 1, count), dim3(256), 0, st, partial, nblk, n, q);
   return IM_OK;
 }
-int launch_colsum(const void* a, long lda, int R, int n, int a_bf16, float* out, float* partial, hipStream_t st) {
-  return launch_colsum_multi(&a, &lda, &out, 1, R, n, a_bf16, partial, st);
-}
 
 // ---- LayerNorm over the feature axis: one wavefront per row, two-pass (mean, then variance) in fp32 ----
 template <typename T>

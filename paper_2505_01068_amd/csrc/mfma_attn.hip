@@ -54,7 +54,7 @@ __device__ __forceinline__ void xcd_tile_index(const int* prefix, int nord, bool
   while (k + 1 < nord && idx >= per * (unsigned)prefix[k + 1]) ++k;
   const unsigned nt = (unsigned)(prefix[k + 1] - prefix[k]), j = idx - per * (unsigned)prefix[k];
   unsigned pl, t, hh, bb;
-  if (tile_first) udivmod(j, per, t, pl);  // packed rows: see segment_major_index
+  if (tile_first) udivmod(j, per, t, pl);  // packed rows: the later tiles of most pairs find no rows
   else udivmod(j, nt, pl, t);
   udivmod(xcd * per + pl, gy, bb, hh);
   tile = prefix[k] + (int)t;

@@ -1685,8 +1685,8 @@ __global__ __launch_bounds__(256) void mfma_splitk_reduce_par_kernel(const float
 }
 
 // Where the 256 x 256 tiles apply: k-major B, whole 32-deep k-tiles, a contraction long enough to fill their ring.
-// Weight gradients (both operands k-major, contraction over token rows) take them whenever they do, at 1.5x the
-// 128 x 128 kernel; projections only under large_tiles_fill below.
+// Split-K weight gradients (both operands k-major, contraction over token rows: bf16 models off the matrix-core attention, or
+// of an odd hidden width) take them whenever they do, at 1.5x the 128 x 128 kernel; projections only under large_tiles_fill below.
 static bool use_dma(int M, int N, int K, bool akm = true, bool bkm = true) {
   if (!(bkm && M >= DM && N >= DN && K % DK == 0 && M % 8 == 0 && N % 8 == 0)) return false;
   return akm ? K >= 64 * DK : K >= 8 * DK;

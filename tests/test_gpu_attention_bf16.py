@@ -1,4 +1,4 @@
-"""GPU parity, bf16 paths (MFMA kernels at head dim 64; row-per-lane kernels at small head dims)
+"""GPU parity, bf16 paths (MFMA kernels at head dim 64; fp32-arithmetic kernels at other small head dims)
 vs the fp64 oracle evaluated on the same bf16-rounded inputs.  Bar: 2e-2 relative, per tensor."""
 import numpy as np
 import pytest
@@ -38,22 +38,47 @@ def test_mfma_shapes_and_segment_counts(seg, H):
 
 
 def test_mfma_wide_model_weight_gradient_kernel():
-    # d = 320 (5 heads), 2048 token rows: the weight gradients take the asynchronous 256 x 256 GEMM
-    # kernel with ragged row / column tiles (320 = 256 + 64, 960 = 3 * 256 + 192) and split-K
-    say("[case] mfma d=320 R=2048 (large-tile weight-gradient GEMM)")
+    # d = 320 (5 heads), 2048 token rows: the weight gradients in tiles of 128 with ragged row / column tiles
+    # (320 = 2 * 128 + 64, 960 = 7 * 128 + 64) and several row ranges
+    say("[case] mfma d=320 R=2048 (weight-gradient GEMM, ragged tiles)")
     g = synth.attention_inputs(2, (300, 420, 304), 320, 5, "bf16", "valid_len", seed=41, bias=True)
     errs = Problem(g, oracle.IM_IFM_BACKWARD).check(what="mfma d=320")
     say("    " + " ".join(f"{k}={v:.1e}" for k, v in errs.items()))
 
 
 def test_mfma_projection_large_tile_ragged_rows():
-    # d = 256, 2 x 1092 = 2184 token rows (a multiple of 8, not of 256): the QKV and output projections
-    # take the asynchronous 256 x 256 GEMM kernel with a ragged last row tile (2184 = 8 * 256 + 136) and,
-    # for N = 768 / 256, full column tiles; biases go through its staged epilogue
-    say("[case] mfma d=256 R=2184 (large-tile projection GEMM, ragged rows)")
+    # d = 256, 2 x 1092 = 2184 token rows: the QKV and output projections in 64-row tiles with a ragged last one
+    # (2184 = 34 * 64 + 8) and, for N = 768 / 256, full column tiles; biases go through the staged epilogue
+    say("[case] mfma d=256 R=2184 (projection GEMM, ragged rows)")
     g = synth.attention_inputs(2, (300, 488, 304), 256, 4, "bf16", "valid_len", seed=43, bias=True)
     errs = Problem(g, oracle.IM_IFM_FORWARD).check(what="mfma d=256")
     say("    " + " ".join(f"{k}={v:.1e}" for k, v in errs.items()))
+
+
+def test_mfma_projection_256_row_tiles_ragged():
+    """488 samples x (20 + 27 + 20) rows = 32 696 token rows, d = 512 (8 heads): 128 x 2 and 128 x 6 tiles of 256 x 256 are
+    one and three full rounds of the 256 CUs (288-row tiles: as many rounds, longer ones), so that all projections and, on
+    transposed weights, the data gradients take the asynchronous 256 x 256 kernel; the last row tile is ragged
+    (32 696 = 127 x 256 + 184), biases go through its staged epilogue.  The oracle sees the first and last elements."""
+    say("[case] mfma d=512 R=32696 (256-row projection tiles, ragged rows)")
+    g = synth.attention_inputs(488, (20, 27, 20), 512, 8, "bf16", "valid_len", seed=48, bias=True)
+    p = Problem(g, oracle.IM_IFM_FORWARD)
+    y, dx = p.fwd(), p.bwd()["dx"]
+    for sl in (slice(0, 3), slice(485, 488)):
+        y_ref, cache = oracle.forward(g["x"][sl], g["wq"], g["wk"], g["wv"], g["wo"], g["seg_len"], p.lm, 8, g["scale"],
+                                      bq=g["bq"], bk=g["bk"], bv=g["bv"], bo=g["bo"], valid_len=g["valid_len"][sl],
+                                      return_cache=True)
+        ref = oracle.backward(cache, g["dy"][sl])
+        assert rel_err(y[sl], y_ref) <= 2e-2 and rel_err(dx[sl], ref["dx"]) <= 2e-2
+
+
+@pytest.mark.parametrize("seg", [(300, 440, 300), (300, 428, 300)])   # 2 080 rows, a multiple of 32; 2 056, not
+def test_small_head_wide_model_weight_gradients(seg):
+    # 32 heads of dimension 10 at d = 320: bf16 off the matrix-core attention.  Its weight gradients are split-K products, of
+    # 2 080 rows in the 256 x 256 kernel with both operands k-major (ragged tiles: 320 = 256 + 64, 960 = 3 x 256 + 192).
+    say(f"[case] small-head bf16 d=320 R={2 * sum(seg)} (split-K weight gradients)")
+    g = synth.attention_inputs(2, seg, 320, 32, "bf16", "valid_len", seed=49, bias=True)
+    Problem(g, oracle.IM_IFM_BACKWARD).check(what=f"small-head d=320 R={2 * sum(seg)}")
 
 
 def test_mfma_projection_288_row_tiles_ragged():
@@ -125,8 +150,8 @@ def test_subhead_bf16_other_widths_fwd_bwd(d, H, name, padding):
 
 @pytest.mark.parametrize("d,H", [(48, 6), (40, 8), (96, 6)])
 def test_rowlane_bf16_widths_off_the_matrix_cores(d, H):
-    # bf16 storage with d % 64 != 0 (head dims 8, 5, 16): the row-per-lane kernels
-    say(f"[case] rowlane bf16 d={d} H={H}")
+    # bf16 storage with d % 64 != 0 (head dims 8, 5, 16): the small-head kernels in fp32 arithmetic
+    say(f"[case] small-head bf16 d={d} H={H}")
     g = synth.attention_inputs(3, (50, 200, 130), d, H, "bf16", "valid_len", seed=24, bias=True)
     errs = Problem(g, oracle.IM_IFM_FORWARD).check(what=f"rowlane-bf16/{d}")
     say("    " + " ".join(f"{k}={v:.1e}" for k, v in errs.items()))

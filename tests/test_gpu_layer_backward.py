@@ -86,7 +86,7 @@ def test_layer_backward_bf16_small_heads(bias):
 
 
 def test_layer_backward_bf16_narrow_widths():
-    # d = 40 (head dim 5: row-per-lane attention), d_ff = 104: multiples of 8 but not of 64, so the
+    # d = 40 (head dim 5: small-head attention), d_ff = 104: multiples of 8 but not of 64, so the
     # matrix-core GEMMs run with partial k-tiles and the split data gradient stays on the ALU GEMM
     say("[case] layer bwd bf16 d=40 d_ff=104")
     d, H, d_ff, seg = 40, 8, 104, (50, 200, 130)
@@ -118,9 +118,9 @@ def test_layer_backward_bitwise_reproducible():
 
 
 def test_layer_backward_bf16_wide_model_large_tile_epilogues():
-    # d = 256, d_ff = 512: the projections and both MLP GEMMs run on the 256 x 256 large-tile kernel, including its
-    # GELU and residual epilogues; 1136 rows = 4 row tiles + a ragged one
-    say("[case] layer fwd+bwd bf16 d=256 (large-tile GEMM with GELU / residual epilogues)")
+    # d = 256, d_ff = 512: the projections and both MLP GEMMs in 64-row tiles, with the GELU, GELU' and residual
+    # epilogues; 1136 rows = 17 row tiles + a ragged one
+    say("[case] layer fwd+bwd bf16 d=256 (ring GEMM with GELU / residual epilogues)")
     d, H, d_ff, seg = 256, 4, 512, (72, 296, 200)
     g = synth.attention_inputs(2, seg, d, H, "bf16", "valid_len", seed=506)
     p = synth.layer_params(d, d_ff, 506, 0, dtype="bf16")

@@ -42,7 +42,7 @@ def run_model(g, m, dtype, d_ff, d_ff_intra, H_intra, masks=None):
 @pytest.mark.parametrize("dtype,d,H,Hi", [("fp32", 40, 8, 8), ("bf16", 64, 8, 8)])
 @pytest.mark.parametrize("padding", ["valid_len", "none", "key_pad"])
 def test_model_small_heads(dtype, d, H, Hi, padding):
-    # row-per-lane path at both widths (head dims 5 / 10 and 8 / 16)
+    # small-head path at both widths (head dims 5 / 10 and 8 / 16)
     say(f"[case] model dtype={dtype} d={d} padding={padding}")
     seg, d_ff, L, Li, n_out = (37, 130, 75), 2 * d, 2, 2, 3
     g = synth.attention_inputs(3, seg, d, H, dtype, padding, seed=401, with_dy=False)

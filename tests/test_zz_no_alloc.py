@@ -1,7 +1,7 @@
 """The allocation-free forward (im_attention_fwd_noalloc) against im_attention_fwd with a caller
 workspace: same inputs, same output (the parity bar of the forward, and in fact bitwise), on two calls
 in a row of which the second is smaller -- the built-in scratch buffer then still holds the first
-call's tensors -- for the row-per-lane (fp32) and the matrix-core (bf16) paths.  Collected last."""
+call's tensors -- for the small-head (fp32) and the matrix-core (bf16) paths.  Collected last."""
 import ctypes as C
 
 import numpy as np
