@@ -12,7 +12,7 @@ and weight gradients included in the time, not in the flops).
 Prints ONE JSON line.  `roofline` is for the dominant attention kernel of the
 step, timed with HIP events recorded by the library on the call's stream over
 the timed steps (im_profile_enable); `kernel_frac` gives the same fraction for
-every attention kernel and `attn_core_frac` for the three together (separate
+every attention kernel and `attn_core_frac` for the three together (bf16; separate
 pass after the timed region); `cpu_baseline` is the fp64 CPU oracle timed on a
 bounded sample of the same workload.  `measured_peaks` are two micro-benchmarks
 run in the same process (register-resident MFMA loop, streaming copy);
@@ -36,9 +36,6 @@ sys.path.insert(0, ROOT)
 # MI355X published peaks
 PEAK_HBM_GBS = 8000.0
 PEAK_MFMA_BF16_TFLOPS = 2500.0
-PEAK_FP32_VALU_TFLOPS = 157.3        # published fp32 vector rate: counts packed (two-wide) fp32 instructions
-PEAK_FP32_VALU_UNPACKED_TFLOPS = 78.6  # 256 CU x 64 lanes x 2 flop x 2.4 GHz: the rate of code without packed fp32,
-                                       # which is what the library is compiled to (packed fp32 selection is switched off)
 
 # Maximum sequence lengths of the datasets (App. "Datasets"), reordered to text / vision / audio the way the
 # benchmark configuration's 50 / 500 / 375 reads the first row.
@@ -49,6 +46,17 @@ INFO_DISORDER_MASK = (1 << 1) | (1 << 2) | (1 << 5) | (1 << 6)
 # MFMA instructions (32x32x16 bf16, 32768 flops each) the kernels execute per 32 x 32 block of scores of one head
 MFMA_PER_BLOCK = {64: {"attn_fwd": 8, "attn_dq": 12, "attn_dkv": 16},     # head dim 64
                   0: {"attn_fwd": 3, "attn_dq": 4, "attn_dkv": 6}}        # sub-head mode (head dims 8 / 16)
+def split_flops_per_pair(dh):
+    """Matrix flops that the small-head kernels execute per (query, key) pair and head: 32 per 16x16x32 instruction of a step
+    of 32 x 16 pairs.  Operands are three bf16 parts; a score takes six products of parts, a transposed product up to three
+    instructions per 16 rows of the parts' columns (two less where they would only meet third parts)."""
+    D = next(n for n in ((4, 5, 6, 8, 10, 12, 16) if dh in (5, 6, 10) else (4, 8, 12, 16)) if n >= dh)
+    score = 2 * ((6 * D + 1 + 31) // 32)
+    tr = lambda blocks, ones: sum(3 if 16 * rb < 2 * D or (ones and rb == blocks - 1) else 1 for rb in range(blocks))  # noqa: E731
+    plain, summed = tr((3 * D + 15) // 16, False), tr((3 * D + 16) // 16, True)
+    return {"attn_fwd": 32 * (score + summed), "attn_dq": 32 * (2 * score + plain), "attn_dkv": 32 * (2 * score + 2 * plain)}
+
+
 ALG_COEF = {"attn_fwd": 4.0, "attn_dq": 2.0, "attn_dkv": 8.0}   # algorithmic flops per (pair x model column): forward 4 P d, dQ kernel 2 P d, dK/dV kernel 8 P d
 
 
@@ -181,7 +189,8 @@ def host_threads():
 
 def attention_fracs(per_step, launches, P_exec, d, dh, bf16_mfma, peaks):
     """Per attention kernel: algorithmic flops per launch / average launch time, against the roofline of the
-    path.  P_exec = pairs the kernels execute (query rows in memory x valid live keys)."""
+    path.  P_exec = pairs the kernels execute (query rows in memory x valid live keys).  fp32: no fraction of the algorithmic
+    flops is a limit of those kernels; the flops that the matrix cores execute are given against their peak."""
     out = {}
     sub = MFMA_PER_BLOCK[64 if dh == 64 else 0]
     for k in ("attn_fwd", "attn_dq", "attn_dkv"):
@@ -199,8 +208,9 @@ def attention_fracs(per_step, launches, P_exec, d, dh, bf16_mfma, peaks):
             if peaks:
                 e["frac_of_measured_peak"] = round(tf / peaks["mfma_bf16_tflops"], 4)
         else:
-            e["frac"] = round(tf / PEAK_FP32_VALU_UNPACKED_TFLOPS, 4)
-            e["frac_of_published_peak"] = round(tf / PEAK_FP32_VALU_TFLOPS, 4)
+            exe = split_flops_per_pair(dh)[k] * P_exec * (d // dh)
+            e["executed_mfma_tflops"] = round(exe / (per_step[k] * 1e-3) / 1e12, 2)
+            e["executed_frac"] = round(exe / (per_step[k] * 1e-3) / 1e12 / PEAK_MFMA_BF16_TFLOPS, 4)
         out[k] = e
     return out
 
@@ -220,13 +230,13 @@ def roofline_of(dom, fr, bf16_mfma, peaks, traffic, traffic_src, dom_launches, s
                             "so only useful_mfma_frac of every MFMA is algorithmic work; `achieved` counts algorithmic flops, "
                             "`executed_mfma_tflops` the flops the matrix cores execute")
     else:
-        roof = {"bound": "alu", "kernel": dom, "achieved": e["alg_tflops"], "peak": PEAK_FP32_VALU_UNPACKED_TFLOPS,
-                "unit": "TFLOP/s", "frac": e["frac"], "frac_of_published_peak": e["frac_of_published_peak"],
+        roof = {"bound": "mfma", "kernel": dom, "achieved": e["executed_mfma_tflops"], "peak": PEAK_MFMA_BF16_TFLOPS,
+                "unit": "TFLOP/s", "frac": e["executed_frac"], "alg_tflops": e["alg_tflops"],
                 "traffic": traffic, "traffic_source": traffic_src,
                 "avg_launch_ms": round(e["ms"] / max(dom_launches, 1.0), 4),
-                "note": "fp32 operands as three bf16 parts on the matrix cores: fp32 multiply-adds of the products counted, exp and "
-                        "softmax bookkeeping not; peak = fp32 vector rate without packed instructions (256 CU x 64 lanes x 2 flop "
-                        "x 2.4 GHz), the vector ALU's issue being what bounds these kernels (exp2, splitting of the probabilities)"}
+                "note": "fp32 operands as three bf16 parts on the matrix cores: `achieved` counts the bf16 flops that the matrix "
+                        "cores execute for whole 32 x 16 steps, `alg_tflops` the fp32 multiply-adds of the products; what bounds "
+                        "these kernels is the issue of vector instructions (exp2, splitting of the probabilities), not counted here"}
     return roof
 
 
@@ -583,7 +593,6 @@ def main():
     roof = roofline_of(dom, fr, mfma_path, peaks, traffic, traffic_src, launches[dom], dh != 64)
     core_ms = sum(per_step[k] for k in fr)
     core_tf = 14.0 * P_rows * d / (core_ms * 1e-3) / 1e12
-    peak_core = PEAK_MFMA_BF16_TFLOPS if mfma_path else PEAK_FP32_VALU_UNPACKED_TFLOPS
 
     out = {
         "metric": "IM-attention fwd+bwd TFLOP/s on live blocks; % of HBM/MFMA roofline",
@@ -604,7 +613,7 @@ def main():
         "kernel_ms_note": "dominant attention family: HIP events over the timed steps; the other families: a separate pass after them with every family bracketed",
         "kernel_frac": fr,
         "attn_core_tflops": round(core_tf, 3),
-        "attn_core_frac": round(core_tf / peak_core, 4),
+        "attn_core_frac": round(core_tf / PEAK_MFMA_BF16_TFLOPS, 4) if mfma_path else None,
         "roofline": roof,
     }
     if peaks:
