@@ -26,6 +26,13 @@
  *   - dtype IM_DTYPE_F32: every float array is fp32.
  *     dtype IM_DTYPE_BF16: activations, weights and biases are bfloat16; all
  *     accumulation is fp32; weight/bias GRADIENTS are written in fp32.
+ *   - fp32 products run on the bf16 matrix cores: an operand is the sum of three
+ *     bf16 parts, which hold its 24 bits, and of the nine partial products those
+ *     below 2^-24 of the product are left out; they are added in fp32.  Errors
+ *     against 64 bits are at or below those of fp32 multiply-adds.  A sum that comes
+ *     out infinite or NaN is taken again with fp32 multiply-adds, so that infinities
+ *     and values up to the largest fp32 number give what those give.  Operands below
+ *     2^-110 (8e-34) keep an absolute accuracy of 2^-134 instead of 24 bits.
  *   - Return value: IM_OK, or a negative error code.  Shape, pointer, alignment
  *     and workspace-size validation precedes any launch (a call rejected with
  *     IM_ERR_INVALID / UNSUPPORTED / WORKSPACE has enqueued nothing); IM_ERR_HIP

@@ -4,7 +4,7 @@
 // the vector ALU's rate and do not overlap with it (measured: 16x16x4 f32 13.5 ns, plus 1.25 ns for every vector
 // instruction beside it), so fp32 products gain nothing there; the bf16 instruction 16x16x32 takes 7.8 ns for 32 times
 // the products per k and runs beside the vector ALU.  Every operand is therefore written as the sum of THREE bf16
-// numbers, which holds all 24 bits of an fp32 significand exactly, and a product x y is the sum of the products of
+// numbers, which holds all 24 bits of an fp32 significand exactly (from 2^-110 up), and a product x y is the sum of the products of
 // parts, each exact in fp32, accumulated in fp32:
 //   scores:  x y = x1 y1 + x1 y2 + x1 y3 + x2 y1 + x2 y2 + x3 y1.  With round-to-nearest parts |x2| <= 2^-9 |x|,
 //            |x3| <= 2^-18 |x|: the three dropped terms are below 2^-26 |x y|, a quarter of an fp32 rounding.  The
@@ -19,12 +19,12 @@
 // start (eight subtractions less per step) each kernel rounded the score in its own way: at scores around 300 the
 // probability of a row's only key was off by 1e-5 and dWv with it (3.0e-6 like this, 1.1e-5 so), at 1e6 dWv by 20 %.
 //
-// Bound: vector-instruction issue.  Per score the forward has one exp2, half a max and 5.5 instructions that split the
-// probability (63 per 32 x 16 step and wave, five matrix instructions beside them), dQ two and dK/dV eight more; at 32 x
-// 50/500/375 rows, 8 heads of 5, the counters show the vector ALUs two thirds busy, the rest is the latency of a
+// Bound: vector-instruction issue.  Per score the forward has one subtraction, one exp2, half a max and 5.5 instructions that
+// split the probability (71 per 32 x 16 step and wave, five matrix instructions beside them), dQ two and dK/dV eight more;
+// at 32 x 50/500/375 rows, 8 heads of 5, the counters showed the vector ALUs two thirds busy, the rest is the latency of a
 // workgroup's own prologue.  The kernels before these (one query or key row per lane, fused multiply-adds, the other
 // operand broadcast from LDS) needed 10 to 20 multiply-adds and four LDS broadcasts per score: forward / dQ / dK/dV
-// 42 / 49 / 61 us at that shape against 28 / 32 / 41, 13 / 16 / 16 us at 64 x 50/50/50 rows against 8 / 9 / 11.
+// 42 / 49 / 61 us at that shape against 28 / 32 / 41, 13 / 16 / 16 us at 64 x 50/50/50 rows against 8 / 9 / 12.
 //
 // Lane layout of v_mfma_f32_16x16x32_bf16, lane l, g = l / 16: A row l % 16 / B column l % 16, k = 8 g .. 8 g + 7;
 // C/D column l % 16, register r = row 4 g + r.  A step is 32 rows of the streamed operand: row u of a step is row
@@ -186,8 +186,8 @@ __host__ __device__ constexpr bool tr_needed(int k, int rb, bool ones) {
   return k == 0 || ones || rb * 16 < 2 * DH;
 }
 // acc += the step's product.  The three parts' instructions start from zero and the step's sum is added with a rounding to
-// nearest: the instruction itself rounds towards minus infinity (by 0.7 of a unit of its largest addend on average,
-// measured), which a long accumulator would collect three times per step.  What the step's own products lose that way has
+// nearest: the instruction's own rounding, 0.6 to 0.9 units of its largest addend (rms), would be three per step at the
+// accumulator's size, and its mean is below zero (0.05 units where accumulator and products are of one size).  What the step's own products lose that way has
 // one sign too, and the bias gradients add it over all rows: odd steps multiply the operand with the other sign and are
 // subtracted, which turns the rounding around (the dQ and dK/dV kernels do the same to dP between odd and even query
 // rows).  Without, dbq was off by 2.4e-6 at 20 x 39/480/461 rows.  Segments of up to 32 rows have one step each: the dK/dV

@@ -1,8 +1,9 @@
 // fp32 GEMMs of the narrow models on the bf16 matrix cores.
 //
-// An fp32 number is the sum of three bf16 numbers (8 + 8 + 8 significand bits, rounded to nearest); a product of two of
-// them is taken as x1 y1 + x1 y2 + x2 y1 + x2 y2 + x1 y3 + x3 y1, each exact in fp32 and accumulated in fp32.  The
-// dropped terms are below 2^-26 of the product, a quarter of an fp32 rounding.  Six 32x32x16 bf16 instructions (15.5 ns
+// An fp32 number is the sum of three bf16 numbers (8 + 8 + 8 significand bits, rounded to nearest; from 2^-110 up: below,
+// the last part ends at bf16's smallest number, 2^-133); a product of two of them is taken as x1 y1 + x1 y2 + x2 y1 + x2 y2 +
+// x1 y3 + x3 y1, each exact in fp32 and accumulated in fp32.  The dropped terms are below 2^-26 of the product, a quarter of
+// an fp32 rounding.  Six 32x32x16 bf16 instructions (15.5 ns
 // each) replace eight 32x32x2 fp32 ones (27 ns each, and those take the vector ALU's issue slots).
 #include <algorithm>
 
@@ -29,10 +30,10 @@ __device__ __forceinline__ void split_parts8(const float (&x)[8], bf16x8 (&out)[
     out[k] = as_bf16x8(w);
   }
 }
-// The large term into `big`, the five small ones into `rest`.  The instruction rounds its sum towards minus infinity by a
-// tenth of a unit in the last place of its largest addend on average (measured; fp32 multiply-adds round to nearest): all
-// six terms in one accumulator would take that step six times at full size, a bias that a column sum over the rows of
-// the result (a LayerNorm or bias gradient) adds up -- 1.4e-6 instead of 4e-7 relative over 8400 rows.
+// The large term into `big`, the five small ones into `rest`.  The instruction's rounding is 0.4 to 0.9 units in the last place
+// of its largest addend (rms over random sums) and not quite without a sign: its mean is -0.05 units where accumulator and
+// products are of one size, -0.01 and less where the accumulator is ten times as large.  All six terms in one accumulator would
+// be rounded six times at full size, and a column sum over the rows of the result (a LayerNorm or bias gradient) adds the mean up -- 1.4e-6 instead of 4e-7 relative over 8400 rows.
 __device__ __forceinline__ void mfma32_split(const bf16x8 (&a)[3], const bf16x8 (&b)[3], f32x16& big, f32x16& rest) {
   rest = mfma32(a[2], b[0], rest);
   big = mfma32(a[0], b[0], big);

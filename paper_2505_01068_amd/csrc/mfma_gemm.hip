@@ -409,7 +409,8 @@ __global__ __launch_bounds__(256, 3) void mfma_gemm_pair_kernel(MGemm p) {
 // Row-major tiles: 128-byte rows, chunk c of row r at c ^ sw_f(r); k-major tile [64][16 chunks]: chunk c of row k at
 // c ^ ((k & 3) << 2).  LN (K == 64): the rows of A are normalised in LDS before they are multiplied (first MLP product of a
 // width-64 layer with GELU_BOTH, 29 600 x 256: 18.9 us in the register-staged kernel, 15.2 here).
-// k order and rounding are those of the kernel above: results are bit for bit the same.
+// k order and rounding are those of the kernel above.  (Wide layers' GELU was a kernel of its own with another erf: 8e-8 of
+// the activation before it is rounded to bf16, 3e-7 with the epilogue's; after the rounding both are off by 1.7302e-3.)
 // Measured against the better of the two kernels it replaced here: 8 400 x 256 x 1024 + residual 33.8 -> 13.6 us,
 // 8 400 x 256 x 256 + residual 18.7 -> 7.1, 8 400 x 1024 x 256 with GELU' 23.6 -> 15.7, 29 600 x 64 x 256 + residual
 // 10.3 -> 7.2, 4 000 x 512 x 2048 + residual 55 -> 21, 16 000 x 1536 x 512 41 -> 36.  Three, four or six stages (one or two

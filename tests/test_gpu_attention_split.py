@@ -56,7 +56,7 @@ def test_moving_reference():
 def test_bias_gradients_collect_no_rounding():
     # dbq and dbv add dQ and dV over 19 600 rows.  A rounding to nearest per row is 6e-8 times the square root of the number
     # of rows against a sum that grows the same way: the 2-norm error stays a few 1e-7.  A rounding with one sign grows with
-    # the number of rows itself; the bar of 1.4e-6 lies between (measured 9.1e-7 and 2.4e-6 at this shape).
+    # the number of rows itself; the bar of 1.4e-6 lies between (measured 4.7e-7 and 2.4e-6 at this shape).
     say("[case] split attention, bias gradients of many rows")
     seg, d, H, batch = (39, 480, 461), 32, 4, 20
     g = synth.attention_inputs(batch, seg, d, H, "fp32", "valid_len", seed=761, bias=True)
