@@ -7,7 +7,7 @@ import torch
 
 import oracle
 from paper_2505_01068_amd import synth
-from tests.gpu_util import TOL, Problem, assert_close
+from tests.gpu_util import TOL, PackedProblem, Problem, assert_close
 
 pytestmark = pytest.mark.gpu
 TOP = 3.4e38   # finite in fp32, rounds to infinity in bf16
@@ -158,3 +158,33 @@ def test_contents_of_masked_keys_do_not_matter(dh, rows):
     for n in ("dwv", "dbv", "dbk"):
         scale = g0["dwv" if n == "dwv" else "dbv"].abs().max().item()
         assert_close(g1[n], g0[n].double().cpu().numpy(), TOL["fp32"], n, scale)
+
+
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+@pytest.mark.parametrize("form", ["packed", "valid_len"])
+def test_contents_of_masked_keys_in_other_forms(dtype, form):
+    # the same for packed rows and for valid lengths beside key_pad (the masked keys' tiles end at other rows), and for bf16
+    # tensors whose heads (dimension 5) the small-head kernels serve.  A masked row of 3e35 as a query has scores of 1e70: its
+    # own y and every sum over queries that it enters are left out.
+    print(f"[case] masked keys {form} {dtype}", flush=True)
+    seg, rows = (20, 70, 40), [3, 22, 60, 95]
+    g = synth.attention_inputs(2, seg, 40, 8, dtype, "none", seed=1007)
+    lengths = np.array([[17, 70, 12], [20, 45, 40]], np.int32)
+    g["key_pad"] = np.zeros((2, sum(seg)), np.uint8)
+    g["key_pad"][:, rows] = 1
+    g["dy"][:, rows] = 0
+    inside = np.concatenate([np.arange(n)[None] < lengths[:, i:i + 1] for i, n in enumerate(seg)], axis=1)
+    g["x"][~inside], g["dy"][~inside] = 0, 0
+    if form == "valid_len":
+        g["valid_len"] = lengths
+    keep = inside.copy()
+    keep[:, rows] = False
+    y = []
+    for value in (0.0, 3e35):
+        g["x"][:, rows] = np.where(inside[:, rows, None], np.float32(value), 0)
+        pr = PackedProblem(g, oracle.NAMED_PATTERNS["self_only"], lengths) if form == "packed" else Problem(g, oracle.NAMED_PATTERNS["self_only"])
+        out, grads = pr.fwd(), pr.bwd()
+        at = torch.from_numpy(keep[inside] if form == "packed" else keep).cuda()
+        y.append((out[at], grads["dx"][at], grads["dwv"]))
+    for a, b, what in zip(y[1], y[0], ("y", "dx", "dwv")):
+        assert_close(a, b.double().cpu().numpy(), TOL[dtype], what)
