@@ -44,8 +44,17 @@ __device__ __forceinline__ void mfma32_split(const bf16x8 (&a)[3], const bf16x8 
 }
 
 // An infinity, or a finite value beyond bf16's largest (3.39e38), has infinities and NaN among its parts, and NaN is every
-// sum that it reaches.  A lane whose sums are not all finite takes its elements again from memory with fp32 multiply-adds
-// and stores them over the first ones (one instruction per element for the check; no lane of any ordinary call).
+// sum that it reaches.  A lane whose sums are not all finite takes those that are not again from memory with fp32
+// multiply-adds and stores them over the first ones (one instruction per element for the check; no lane of any ordinary call).
+__device__ __forceinline__ unsigned not_finite(const f32x16& a, const f32x16& b) {   // one bit each
+  unsigned bad = 0;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    const float v = a[r] + b[r];
+    bad |= v - v != 0.f ? 1u << r : 0u;
+  }
+  return bad;
+}
 
 // C[M, N] = A[M, K] B[K, N] (+ bias) (GELU) (+ res).  A row-major; B element (k, n) at k sbk + n sbn with one of the two
 // strides 1 (BT: sbk == 1), possibly in up to three buffers by columns or by rows of B.
@@ -192,11 +201,11 @@ __global__ __launch_bounds__(256, 3) void gemm_split_kernel(GemmDesc g) {
     const float bv = bp ? bp[nn] : 0.f;
     nn = n;
     bp = g.b_split == 1 ? gs_buffer(b0, b1, b2, nn, g.n_per) : b0;
-    for (int r = 0; r < 16; ++r) {
-      const int m = m0 + 8 * (r >> 2) + 4 * h + (r & 3);
-      if (m >= g.M) continue;
+    for (unsigned bad = not_finite(acc, rest); bad; bad &= bad - 1) {
+      const int r = __builtin_ctz(bad), m = m0 + 8 * (r >> 2) + 4 * h + (r & 3);
+      if (m >= g.M) break;
       float v = bv;
-      for (int k = 0; k < K; ++k) {
+      for (int k = 0; k < K && v == v; ++k) {   // (a NaN stays one)
         int kk = k;
         const float* const q = g.b_split == 2 ? gs_buffer(b0, b1, b2, kk, g.k_per) : bp;
         v = fmaf(((const float*)g.A + (long)m * g.sam)[k], q[BT ? nn * ldw + kk : kk * ldw + nn], v);
@@ -320,11 +329,11 @@ __global__ __launch_bounds__(256, 4) void wgrad_split_kernel(WgradSplitList l) {
   }
   if (__builtin_expect(check != check, 0)) {
     const float *const A = p.A + (long)r0 * p.lda, *const G = p.G + (long)r0 * p.ldg;
-    for (int r = 0; r < 16; ++r) {
-      const int m = m0 + 8 * (r >> 2) + 4 * h + (r & 3);
-      if (m >= p.M) continue;
+    for (unsigned bad = not_finite(big, rest); bad; bad &= bad - 1) {
+      const int r = __builtin_ctz(bad), m = m0 + 8 * (r >> 2) + 4 * h + (r & 3);
+      if (m >= p.M) break;
       float v = 0.f;
-      for (int i = 0; i < nrows; ++i) v = fmaf(A[(long)i * p.lda + m], G[(long)i * p.ldg + n], v);
+      for (int i = 0; i < nrows && v == v; ++i) v = fmaf(A[(long)i * p.lda + m], G[(long)i * p.ldg + n], v);
       out[m * p.N] = v;
     }
   }

@@ -188,3 +188,22 @@ def test_contents_of_masked_keys_in_other_forms(dtype, form):
         y.append((out[at], grads["dx"][at], grads["dwv"]))
     for a, b, what in zip(y[1], y[0], ("y", "dx", "dwv")):
         assert_close(a, b.double().cpu().numpy(), TOL[dtype], what)
+
+
+@pytest.mark.parametrize("d,H", [(40, 8), (33, 3), (32, 2)])
+def test_rows_of_nan(d, H):
+    # rows of x beyond the valid lengths hold NaN: as keys they are not read, as queries they give NaN, and every other row is
+    # bit for bit what it is without them.  The lengths split waves' 16 rows and the products' 32-row blocks, and leave some
+    # of both whole.
+    print(f"[case] rows of NaN d={d}", flush=True)
+    seg, lengths = (20, 70, 40), np.array([[17, 70, 12], [20, 9, 40]], np.int32)
+    g = synth.attention_inputs(2, seg, d, H, "fp32", "none", seed=1008, bias=True)
+    g["valid_len"] = lengths
+    pad = torch.from_numpy(np.concatenate([np.arange(n)[None] >= lengths[:, i:i + 1] for i, n in enumerate(seg)], axis=1))
+    y = []
+    for value in (0.0, float("nan")):
+        pr = Problem(g, oracle.IM_IFM_FORWARD)
+        pr.t["x"][pad.cuda()] = value
+        y.append(pr.fwd().cpu())
+    assert torch.equal(y[1][~pad], y[0][~pad])
+    assert y[0].isfinite().all() and y[1][pad].isnan().all()
