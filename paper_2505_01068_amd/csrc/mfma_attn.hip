@@ -19,9 +19,9 @@
 // epilogue does it before its one rounding to bf16), so Q K^T is the score in the exponent domain of
 // exp2 and no kernel multiplies scores; the per-row statistic saved by the forward is the NEGATED
 // log2-sum-exp (-inf for a row without any valid key), which the backward kernels add to the score --
-// every kernel by starting its score accumulator from it (the forward from its running reference),
-// as the dP accumulators start from -delta: the MFMA chains end as S - lse and dP - delta and the
-// softmax needs no add per element (dK/dV in sub-head mode still adds them per element).
+// by starting their score accumulators from it, as the dP accumulators start from -delta: the MFMA
+// chains end as S - lse and dP - delta and the softmax needs no add per element (dK/dV in sub-head
+// mode still adds them per element).  The forward exponentiates its scores as they are.
 //
 // Only live (query segment, key segment) blocks of the Interlaced Mask are
 // visited (Sec. 6 "Decomposition"); a row with several live segments carries
@@ -162,11 +162,13 @@ __device__ __forceinline__ void ring_feed_issue(const RingLane& rl, const RingLa
 // wait until at most `later` (0 or 1) stages of copies (4 per wave with 4 waves, 2 with 8) requested after the
 // wanted one are outstanding, then meet the other waves: the wanted stage is visible to all, and every wave
 // has finished reading the stage consumed before it.
+// `extra`: this wave issues one more copy per stage, ahead of the others.
 template <int NW = 4>
-__device__ __forceinline__ void ring_wait(int later) {
+__device__ __forceinline__ void ring_wait(int later, bool extra = false) {
   if (later > 0) {
-    if (NW == 4) asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
-    else asm volatile("s_waitcnt vmcnt(2)" ::: "memory");
+    if (NW != 4) asm volatile("s_waitcnt vmcnt(2)" ::: "memory");
+    else if (extra) asm volatile("s_waitcnt vmcnt(5)" ::: "memory");
+    else asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
   } else {
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   }
@@ -190,6 +192,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WGS * N
                                                        const uint8_t* __restrict__ key_pad, bf16_t* __restrict__ O,
                                                        long ldo, float* __restrict__ lse2) {
   __shared__ __attribute__((aligned(1024))) bf16_t sT[NST * RING_STAGE];  // per stage: K tile, V tile
+  __shared__ __attribute__((aligned(256))) unsigned sKP[NST * KT];        // per stage: key_pad bytes of the 64 keys, one per dword
+  __shared__ int sRedo[NW];
   const int tid = threadIdx.x, lane = tid & 63, lo = lane & 31, hi = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // scalar: branches on it are wave-uniform
   int tile, h, b;
@@ -245,19 +249,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WGS * N
     }
   }
 
-  f32x16 oacc[NDB][QB], nm[QB];
+  f32x16 oacc[NDB][QB];
   float m[QB], l[QB];
-#pragma unroll
-  for (int qb = 0; qb < QB; ++qb) {
-    m[qb] = IM_NEG_INF;
-    l[qb] = 0.f;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) nm[qb][r] = 0.f;
-#pragma unroll
-    for (int db = 0; db < NDB; ++db)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) oacc[db][qb][r] = 0.f;
-  }
 
   const int prow = perm32(lo);
   constexpr float tau = 8.f;  // scores are exponents of 2 (Q carries scale * log2(e))
@@ -271,93 +264,134 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WGS * N
   // key tiles of the live key segments; a segment contributes its first min(length, valid length) keys
   auto klen_of = [&](int j) {
     int n = useg_rows(g, b, j);
-    if (valid_len) n = min(n, max(0, valid_len[bm * g.n_seg + j]));
+    if (valid_len) n = min(n, max(0, __builtin_amdgcn_readfirstlane(valid_len[bm * g.n_seg + j])));
     return n;
   };
   const RingLane rl = ring_lane<NW>(wave, lane, cg);
   const unsigned ldb = (unsigned)ld * 2u;
-  TileCursor ic = {live, 0, 0, 0}, cc = ic;
-  cursor_next_seg(ic, klen_of);
-  cursor_next_seg(cc, klen_of);
-  int islot = 0, cslot = 0, inflight = 0;
   const RingLaneOff rlo = ring_lane_off(rl, ldb, ldb);
-  RingFeed feed = {nullptr, nullptr, 0};
-  // K and V rows of segment ic.seg; rows past the valid length but inside the segment are fetched and masked
-  auto seg_begin = [&]() {
-    feed.a = (const char*)(QKV + useg_row0(g, b, ic.seg) * ld + d);
-    feed.b = feed.a + (size_t)d * 2;
-    feed.rows = useg_rows(g, b, ic.seg);
-  };
-  if (ic.len > 0) seg_begin();
-  auto issue = [&]() {
-    ring_feed_issue<NW>(rl, rlo, feed, ldb, ldb, wave, sT + islot * RING_STAGE);
-    islot = (islot + 1 == NST) ? 0 : islot + 1;
-    ic.r0 += KT;
-    if (ic.r0 >= ic.len) {
-      cursor_next_seg(ic, klen_of);
-      if (ic.len > 0) seg_begin();
-    }
-  };
-  // NST - 1 stages are requested ahead: the slot refilled in an iteration is the one consumed in the one before
-  if (ic.len > 0) { issue(); ++inflight; }
-  if (NST > 2 && ic.len > 0) { issue(); ++inflight; }
-  // The ring loop, for NQB of the wave's QB query blocks (NQB < QB: a tile of half the height).
-  auto ring_loop = [&](auto nqb_tag) {
+  const bool kp_copy = wave == 0 && key_pad != nullptr;   // this wave fetches a stage's key_pad bytes
+
+  // One pass over the live key tiles, for NQB of the wave's QB query blocks (NQB < QB: a tile of half the height).
+  //
+  // GUARD = false: the scores are exponentiated as they leave the matrix cores, with no reference subtracted.  fp32 and
+  // bf16 share their exponent range, so the probabilities 2^s have full precision at any size; only the sum has to stay in
+  // range, which is checked once, behind the loop.  No maximum, no rescaling, no accumulator seed, no branch per block.
+  // (Four layers' attention at 32 x 50/500/375 rows, 8 heads of 8, valid lengths: 80 -> 70 us against the pass with a reference
+  // in every block; 3 x 333/1501/1290 rows, 4 heads of 64, single masked keys: 72 -> 55 us, of which the key_pad bytes in the
+  // ring are the larger part.)
+  // GUARD = true: the same with a running reference m per query row; the pass that rows whose sum left the range take.
+  auto stream = [&](auto nqb_tag, auto guard_tag) __attribute__((always_inline)) {
     constexpr int NQB = decltype(nqb_tag)::value;
+    constexpr bool GUARD = decltype(guard_tag)::value;
+    f32x16 nm[QB];   // GUARD: -m of the lane's query row in all 16 registers, where the score accumulators start
+#pragma unroll
+    for (int qb = 0; qb < QB; ++qb) {
+      m[qb] = GUARD ? IM_NEG_INF : 0.f;
+      l[qb] = 0.f;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) nm[qb][r] = 0.f;
+#pragma unroll
+      for (int db = 0; db < NDB; ++db)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) oacc[db][qb][r] = 0.f;
+    }
+    TileCursor ic = {live, 0, 0, 0}, cc = ic;
+    cursor_next_seg(ic, klen_of);
+    cursor_next_seg(cc, klen_of);
+    int islot = 0, cslot = 0, inflight = 0;
+    RingFeed feed = {nullptr, nullptr, 0};
+    const uint8_t* feed_kp = nullptr;
+    // K and V rows of segment ic.seg; rows past the valid length but inside the segment are fetched and masked
+    auto seg_begin = [&]() {
+      const long row0 = useg_row0(g, b, ic.seg);
+      feed.a = (const char*)(QKV + row0 * ld + d);
+      feed.b = feed.a + (size_t)d * 2;
+      feed.rows = useg_rows(g, b, ic.seg);
+      if (key_pad) feed_kp = key_pad + useg_row0(g, bm, ic.seg);
+    };
+    if (ic.len > 0) seg_begin();
+    auto issue = [&]() {
+      // The key_pad bytes travel with the stage: an ordinary load inside the loop would wait for every copy before it.
+      if (kp_copy) dma1_off(feed_kp, (unsigned)min(lane, feed.rows - 1), sKP + islot * KT);
+      feed_kp += KT;
+      ring_feed_issue<NW>(rl, rlo, feed, ldb, ldb, wave, sT + islot * RING_STAGE);
+      islot = (islot + 1 == NST) ? 0 : islot + 1;
+      ic.r0 += KT;
+      if (ic.r0 >= ic.len) {
+        cursor_next_seg(ic, klen_of);
+        if (ic.len > 0) seg_begin();
+      }
+    };
+    // NST - 1 stages are requested ahead: the slot refilled in an iteration is the one consumed in the one before
+    if (ic.len > 0) { issue(); ++inflight; }
+    if (NST > 2 && ic.len > 0) { issue(); ++inflight; }
     while (cc.len > 0) {
-      ring_wait<NW>(inflight - 1);
+      ring_wait<NW>(inflight - 1, kp_copy);
       if (ic.len > 0) issue(); else --inflight;
       const bf16_t* sK = sT + cslot * RING_STAGE;
       const bf16_t* sV = sK + KT * SW_LD;
+      const unsigned* kp = sKP + cslot * KT;
       cslot = (cslot + 1 == NST) ? 0 : cslot + 1;
-      const int k0 = cc.r0, klen = cc.len;
-      const uint8_t* kp_row = key_pad ? key_pad + useg_row0(g, bm, cc.seg) : nullptr;
+      const int keys = cc.len - cc.r0;   // valid keys from the tile's first one on (key_pad aside)
       cursor_step(cc, klen_of);
-      const bool need_mask = (k0 + KT > klen) || (kp_row != nullptr);  // tail tile or key_pad present (wave-uniform)
-      unsigned long long km = ~0ull;
-      if (need_mask) km = tile_key_mask(kp_row, k0, klen, lane) >> (8 * hi);
-      // The tile is processed as two blocks of 32 keys, each S^T -> softmax -> O^T, so that only one block of
-      // scores and of probabilities is live at a time.
+      const bool need_mask = keys < KT || key_pad != nullptr;  // tail tile or key_pad present (wave-uniform)
+      unsigned long long km = ~0ull;   // bit k <=> key k of the tile is a valid key
+      if (need_mask) km = __ballot(lane < keys && !(key_pad && kp[lane] != 0));
+      // The tile is processed as two blocks of 32 keys, each S^T -> softmax -> O^T.
 #pragma unroll
       for (int kb = 0; kb < 2; ++kb) {
+        if (kb == 1 && keys <= 32) break;
+        const unsigned kw = (unsigned)(km >> (32 * kb)) >> (8 * hi);   // bit 16 (r / 8) + r % 8: key of accumulator register r
         // ---- S^T = K Q^T ----
-        // The accumulator chain starts from -m (nm: the running reference of the lane's query row in all 16
-        // registers), so the scores leave the matrix cores already relative to it.
         f32x16 sacc[QB];
 #pragma unroll
         for (int s = 0; s < NS; ++s) {
           const bf16x8 a = lds_frag_sw(sK, kb * 32, prow, 2 * (s0 + s) + hi);
 #pragma unroll
-          for (int qb = 0; qb < NQB; ++qb) sacc[qb] = mfma32(a, qreg[qb][s], s == 0 ? nm[qb] : sacc[qb]);
+          for (int qb = 0; qb < NQB; ++qb) sacc[qb] = mfma32(a, qreg[qb][s], s == 0 ? (GUARD ? nm[qb] : f32x16{}) : sacc[qb]);
         }
+        // ---- softmax ----
+        bf16x8 pb[QB][2];
+        unsigned pmask[8];   // the validity of the keys of a packed pair of probabilities
         if (need_mask) {
 #pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            // register r of block kb on this lane half is key kb*32 + 16*(r/8) + 8*hi + r%8
-            const bool ok = (km >> (kb * 32 + 16 * (r >> 3) + (r & 7))) & 1ull;
+          for (int e = 0; e < 8; ++e) {
+            const int bit = 16 * (e >> 2) + 2 * (e & 3);
+            const unsigned v0 = (unsigned)((int)(kw << (31 - bit)) >> 31), v1 = (unsigned)((int)(kw << (30 - bit)) >> 31);
+            pmask[e] = __builtin_amdgcn_perm(v1, v0, 0x05040100);
+          }
+          if (GUARD) {   // the maximum must not see masked keys
 #pragma unroll
-            for (int qb = 0; qb < NQB; ++qb) sacc[qb][r] = ok ? sacc[qb][r] : IM_NEG_INF;
+            for (int r = 0; r < 16; ++r)
+#pragma unroll
+              for (int qb = 0; qb < NQB; ++qb) sacc[qb][r] = ((kw >> (16 * (r >> 3) + (r & 7))) & 1u) ? sacc[qb][r] : IM_NEG_INF;
           }
         }
-        // ---- online softmax, one running (reference, sum) per query row ----
-        bf16x8 pb[QB][2];
 #pragma unroll
         for (int qb = 0; qb < NQB; ++qb) {
-          // P^T operands of the block from its scores; returns the lane's part of the row sum, taken over the
-          // bf16-rounded probabilities (the values that multiply V) with two-element dot products against (1, 1)
-          auto exponentiate = [&]() {
+          // P^T operands of the block from its scores, 0 for a masked key whatever its row holds; the lane's part of the row
+          // sum is taken over the bf16-rounded probabilities (the values that multiply V) with two-element dot products
+          // against (1, 1)
+          auto exponentiate = [&](float sum) {
             float p[16];
 #pragma unroll
             for (int r = 0; r < 16; ++r) p[r] = fast_exp2(sacc[qb][r]);
             pb[qb][0] = pack8(p);
             pb[qb][1] = pack8(p + 8);
-            return sum_bf16x8(pb[qb][1], sum_bf16x8(pb[qb][0], 0.f));
+            if (!GUARD && need_mask) {
+              pb[qb][0] = and_bf16x8(pb[qb][0], pmask);
+              pb[qb][1] = and_bf16x8(pb[qb][1], pmask + 4);
+            }
+            return sum_bf16x8(pb[qb][1], sum_bf16x8(pb[qb][0], sum));
           };
-          // Almost every block: every row of the wave has a reference already and the scores are exponentiated
-          // as they left the matrix cores -- no maximum is taken at all.  fp32 and bf16 share their exponent
-          // range, so probabilities far above 1 lose nothing; only a row without a reference yet, or a row sum
-          // beyond 2^24 (or inf / NaN), sends the block through the rescaling branch, which recomputes it.
-          float rs = exponentiate();
+          if (!GUARD) {
+            l[qb] = exponentiate(l[qb]);
+            continue;
+          }
+          // A row without a reference yet, or a row sum of the block beyond 2^24 (or inf / NaN), sends the block
+          // through the rescaling branch, which recomputes it.
+          float rs = exponentiate(0.f);
           if (__builtin_expect(__any(m[qb] == IM_NEG_INF || !(rs <= 16777216.f)), 0)) {
             asm volatile("" ::: "memory");  // a real branch: nothing of it is to be executed speculatively
             float mx = sacc[qb][0];
@@ -382,7 +416,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WGS * N
             const float nmv = (m[qb] == IM_NEG_INF) ? 0.f : -m[qb];
 #pragma unroll
             for (int r = 0; r < 16; ++r) nm[qb][r] = nmv;
-            rs = exponentiate();
+            rs = exponentiate(0.f);
           }
           l[qb] += rs;
         }
@@ -398,30 +432,59 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WGS * N
       }
     }
   };
-  if (HALF && half_tile) ring_loop(std::integral_constant<int, 1>{});
-  else ring_loop(std::integral_constant<int, QB>{});
 
   // ---- epilogue: normalise, write O rows, O^T columns and the log-sum-exp ----
+  // Returns whether a row's results are out of the range of the pass without a reference: its sum not within 2^-80 .. 2^100
+  // (probabilities below 2^-126 are flushed: 2^-46 of such a sum), or an output that is not finite (a NaN sum stays one).
+  bool redo[QB];
+  auto finish = [&](bool again) __attribute__((always_inline)) {
+    bool any = false;
 #pragma unroll
-  for (int qb = 0; qb < QB; ++qb) {
-    const float lt = l[qb] + __shfl_xor(l[qb], 32, 64);
-    const float inv = lt > 0.f ? 1.f / lt : 0.f;
-    const int row = qrow[qb];
-    if (row >= qlen) continue;
-    const long t = useg_row0(g, b, qs) + row;
-    if (hi == 0 && lse2) lse2[useg_stat0(g, b, h, qs) + row] = lt > 0.f ? -(m[qb] + log2f(lt)) : IM_NEG_INF;  // negated
+    for (int qb = 0; qb < QB; ++qb) {
+      const float lt = l[qb] + __shfl_xor(l[qb], 32, 64);
+      const float inv = lt > 0.f ? 1.f / lt : 0.f;
+      const int row = qrow[qb];
+      if (row >= qlen || (again && !redo[qb])) continue;
+      const long t = useg_row0(g, b, qs) + row;
+      if (hi == 0 && lse2) lse2[useg_stat0(g, b, h, qs) + row] = lt > 0.f ? -(m[qb] + log2f(lt)) : IM_NEG_INF;  // negated
+      float nf = 0.f;
 #pragma unroll
-    for (int db = 0; db < NDB; ++db)
+      for (int db = 0; db < NDB; ++db)
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int dh0 = (db0 + db) * 32 + 8 * i + 4 * hi;  // column inside the 64-column group
-        if (DH < 64 && (dh0 < wo || dh0 >= wo + DH)) continue;
-        float v[4];
+        for (int i = 0; i < 4; ++i) {
+          const int dh0 = (db0 + db) * 32 + 8 * i + 4 * hi;  // column inside the 64-column group
+          if (DH < 64 && (dh0 < wo || dh0 >= wo + DH)) continue;
+          float v[4];
 #pragma unroll
-        for (int jj = 0; jj < 4; ++jj) v[jj] = oacc[db][qb][4 * i + jj] * inv;
-        const u32x2 pk = {pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3])};
-        *(u32x2*)(O + t * ldo + cg * 64 + dh0) = pk;
-      }
+          for (int jj = 0; jj < 4; ++jj) {
+            v[jj] = oacc[db][qb][4 * i + jj] * inv;
+            nf = fmaf(v[jj], 0.f, nf);   // 0, or NaN as soon as one value is not finite
+          }
+          const u32x2 pk = {pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3])};
+          *(u32x2*)(O + t * ldo + cg * 64 + dh0) = pk;
+        }
+      redo[qb] = lt < 0x1p-80f || lt > 0x1p100f || (nf != nf && lt == lt);
+      any |= redo[qb];
+    }
+    return any;
+  };
+  auto run = [&](auto guard_tag) __attribute__((always_inline)) {
+    if (HALF && half_tile) stream(std::integral_constant<int, 1>{}, guard_tag);
+    else stream(std::integral_constant<int, QB>{}, guard_tag);
+  };
+  run(std::integral_constant<bool, false>{});
+  // The rows of a workgroup that ask for it are taken again, together because the ring is the workgroup's; the other rows
+  // keep what they have.
+  const bool any = finish(false);
+  const bool wave_any = __any(any);
+  if (lane == 0) sRedo[wave] = wave_any;
+  __syncthreads();
+  int again = 0;
+#pragma unroll
+  for (int w = 0; w < NW; ++w) again |= sRedo[w];
+  if (__builtin_expect(__builtin_amdgcn_readfirstlane(again), 0)) {
+    run(std::integral_constant<bool, true>{});
+    finish(true);
   }
 }
 

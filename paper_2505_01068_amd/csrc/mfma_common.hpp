@@ -74,6 +74,14 @@ __device__ __forceinline__ float sum_bf16x8(bf16x8 v, float acc) {
   return acc;
 }
 
+__device__ __forceinline__ bf16x8 and_bf16x8(bf16x8 v, const unsigned* m) {
+  union { bf16x8 v; u32x4 u; } x;
+  x.v = v;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) x.u[i] &= m[i];
+  return x.v;
+}
+
 // Transposed fragment from a K-MAJOR tile (row = contraction index k, columns = m) using the
 // gfx950 LDS transpose read.  ds_read_b64_tr_b16 exchanges data inside each group of 16 lanes:
 // result[lane i][e] = data[lane 4e + i/4][i % 4] (checked on hardware), where data[lane j] are the
@@ -135,6 +143,11 @@ __device__ __forceinline__ void dma16_off(const void* gbase, unsigned byte_off, 
 }
 __device__ __forceinline__ void dma4_off(const void* gbase, unsigned byte_off, const void* lds_wave_base) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2"
+               :: "s"(lds_offset(lds_wave_base)), "v"(byte_off), "s"(gbase) : "memory");
+}
+// one byte per lane, zero-extended to the lane's dword in LDS
+__device__ __forceinline__ void dma1_off(const void* gbase, unsigned byte_off, const void* lds_wave_base) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_ubyte %1, %2"
                :: "s"(lds_offset(lds_wave_base)), "v"(byte_off), "s"(gbase) : "memory");
 }
 __device__ __forceinline__ void dma4(const void* gptr, const void* lds_wave_base) {

@@ -1,0 +1,59 @@
+"""bf16 matrix-core forward: rows whose sum of exponentials leaves the range of the pass without a reference are taken
+again with a running one, whatever the other rows of their workgroup hold, and change no bit of those."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2505_01068_amd import synth
+from tests.gpu_util import Problem, assert_close, TOL
+
+pytestmark = pytest.mark.gpu
+
+# t reads v, v reads v, a reads a: no row of t is a key
+LIVE = (1 << 1) | (1 << 4) | (1 << 8)
+
+
+def shifted(d, H, seg, padding, shift_bits):
+    """Every score of query row r of t is off by shift_bits[r] in the exponent of 2, by the first channel of each head: 8 in
+    every key, the shift in the query.  Softmax does not see it; 2^s overflows or vanishes."""
+    g = synth.attention_inputs(2, seg, d, H, "bf16", padding, seed=31)
+    dh = d // H
+    eye = np.eye(d, dtype=np.float32)
+    g["wq"], g["wk"] = eye, eye
+    x = g["x"].copy()
+    x[:, :, ::dh] = 8.0
+    a = np.zeros(seg[0], np.float32)
+    a[:len(shift_bits)] = np.asarray(shift_bits, np.float32) / (8.0 * g["scale"] * np.log2(np.e))
+    x[:, :seg[0], ::dh] = np.asarray(torch.from_numpy(a).to(torch.bfloat16).float())[None, :, None]
+    g["x"] = x
+    return g
+
+
+@pytest.mark.parametrize("padding", ["none", "valid_len", "key_pad"])
+@pytest.mark.parametrize("d,H,seg", [(64, 8, (70, 150, 33)), (64, 4, (33, 97, 20)), (192, 24, (65, 64, 65)), (128, 2, (140, 200, 50))])
+def test_shifted_rows(d, H, seg, padding):
+    n = seg[0]
+    bits = [0.0] * n
+    for r, v in ((1, 180.0), (2, -180.0), (5, 110.0), (6, -95.0), (n - 1, 300.0), (n // 2, -300.0)):
+        bits[r] = v
+    print(f"[case] shifted rows d={d} H={H} seg={seg} {padding}", flush=True)
+    g = shifted(d, H, seg, padding, bits)
+    p = Problem(g, LIVE)
+    y = p.fwd(save=True).clone()
+    grads = p.bwd()
+    torch.cuda.synchronize()
+    y_ref, cache = p.oracle_fwd(cache=True)
+    ref = oracle.backward(cache, g["dy"])
+    assert_close(y, y_ref, TOL["bf16"], "y")
+    # dV, dO and P from the saved log-sum-exp; the first channels of dQ and dK are differences of large numbers here
+    for name in ("dwv", "dwo"):
+        assert_close(grads[name], ref[name], TOL["bf16"], name)
+    assert torch.equal(p.fwd(save=False), y)
+    q = Problem(shifted(d, H, seg, padding, [0.0] * n), LIVE)
+    y0 = q.fwd(save=False)
+    torch.cuda.synchronize()
+    same = np.ones(sum(seg), bool)
+    same[[r for r in range(n) if bits[r] != 0.0]] = False
+    same = torch.from_numpy(same).cuda()
+    assert torch.equal(y[:, same], y0[:, same])
