@@ -26,6 +26,7 @@ struct Geo {
   // Sub-head forward only: bit k set = the query tiles of the k-th segment of q_order are half as tall
   // (q_tile_prefix counts them so); see launch_mfma_fwd.
   unsigned q_half;
+  unsigned even_cus;  // matrix-core attention kernels: CUs per XCD to deal the workgroups to, or 0 (see xcd_tile_index)
   float scale, scale_log2e;
   // Packed rows (im_shape_t::cu_rows): row offsets [B * n_seg + 1] on the device, and the row count.
   // cu == nullptr: padded rows, batch element b owns rows b*T .. b*T + T - 1.

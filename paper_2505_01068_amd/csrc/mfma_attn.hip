@@ -35,39 +35,135 @@ namespace imattn {
 
 constexpr int KT = 64;  // keys (or query rows) per staged tile
 
-// Workgroup -> (tile, head, batch element).  As with xcd_block_index every XCD owns a contiguous
-// range of (batch element, head) pairs, but inside that range the workgroups are ordered by segment
-// first (the tile order lists the segments by decreasing work per tile), then pair, then tile.  A
-// workgroup of a long live range runs several times longer than one of a short range; started pair
-// by pair, the long workgroups of the last pairs begin late and the XCD drains with most of its CUs
-// idle.  Started first, they leave the short ones to fill the tail.  The plain order is kept when
-// the pairs do not divide evenly over the 8 XCDs.
-__device__ __forceinline__ void xcd_tile_index(const int* prefix, int nord, bool tile_first, int& tile, int& h, int& b) {
-  const unsigned gx = gridDim.x, gy = gridDim.y, npair = gy * gridDim.z;
-  if (npair & 7u) {
-    xcd_block_index(tile, h, b);
-    return;
-  }
+// the lane's index from the hardware, where keeping it over a loop would cost a register that the loop does not have
+__device__ __forceinline__ int lane_id() { return __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)); }
+
+// Workgroup -> (tile, head, batch element).  As with xcd_block_index every XCD owns a contiguous range of (batch element,
+// head, tile), but inside that range the workgroups are ordered by segment first (the tile order lists the segments by
+// decreasing work per tile), then pair, then tile.  A workgroup of a long live range runs several times longer than one of
+// a short range; started pair by pair, the long workgroups of the last pairs begin late and the XCD drains with most of its
+// CUs idle.  Started first, they leave the short ones to fill the tail.
+//
+// cus != 0: the whole launch is resident at once and its tiles differ in length, so that nothing is left to fill a tail.  The
+// dispatcher deals the workgroups of an XCD to its `cus` CUs in turn (measured: workgroups i, i + cus, i + 2 cus share
+// a CU), and in plain order the CUs that get one workgroup more are those with the longest ones.  Here the CUs with one less
+// take the longest, and each group of CUs is dealt to and fro.  3 x 333/1501/1290 rows, 4 heads of 64 (12 pairs), forward + dQ +
+// dK/dV: in pair order 52 + 59 + 61 us, segment first and dealt like this 44 + 51 + 52.
+__device__ __forceinline__ unsigned even_rank(unsigned pos, unsigned n, unsigned cus) {
+  const unsigned full = n / cus, more = n % cus, round = pos / cus, cu = pos % cus;
+  const bool a = cu >= more;
+  const unsigned w = a ? cus - more : more, c = a ? cu - more : cu;
+  return (a ? 0u : (cus - more) * full) + round * w + ((round & 1u) ? w - 1u - c : c);
+}
+__device__ __forceinline__ void xcd_tile_index(const int (&prefix)[IM_MAX_SEG + 1], int nord, bool tile_first, unsigned cus, int& tile, int& h,
+                                               int& b) {
+  const unsigned gx = gridDim.x, gy = gridDim.y, npair = gy * gridDim.z, total = gx * npair;
   const unsigned lin = blockIdx.x + gx * (blockIdx.y + gy * blockIdx.z);
-  const unsigned xcd = lin & 7u, idx = lin >> 3, per = npair >> 3;  // pairs per XCD
-  int k = 0;
-  while (k + 1 < nord && idx >= per * (unsigned)prefix[k + 1]) ++k;
-  const unsigned nt = (unsigned)(prefix[k + 1] - prefix[k]), j = idx - per * (unsigned)prefix[k];
-  unsigned pl, t, hh, bb;
-  if (tile_first) udivmod(j, per, t, pl);  // packed rows: the later tiles of most pairs find no rows
-  else udivmod(j, nt, pl, t);
-  udivmod(xcd * per + pl, gy, bb, hh);
-  tile = prefix[k] + (int)t;
+  const unsigned xcd = lin & 7u, q = total >> 3, r = total & 7u, n = q + (xcd < r ? 1u : 0u);
+  unsigned idx = lin >> 3, pair, t;
+  if (cus) idx = even_rank(idx, n, cus);
+  if ((npair & 7u) == 0u) {   // whole pairs
+    const unsigned per = npair >> 3;  // pairs per XCD
+    int first = 0, last = prefix[1];
+#pragma unroll
+    for (int k = 1; k < IM_MAX_SEG; ++k)
+      if ((k < nord) & (idx >= per * (unsigned)prefix[k])) { first = prefix[k]; last = prefix[k + 1]; }
+    const unsigned nt = (unsigned)(last - first), j = idx - per * (unsigned)first;
+    if (tile_first) udivmod(j, per, t, pair);  // packed rows: the later tiles of most pairs find no rows
+    else udivmod(j, nt, pair, t);
+    pair += xcd * per;
+    t += (unsigned)first;
+  } else {
+    // tiles a .. of pair p0, all tiles of the pairs between, tiles .. c - 1 of pair p1
+    const unsigned start = xcd * q + (xcd < r ? xcd : r);
+    unsigned p0, a, p1, c;
+    udivmod(start, gx, p0, a);
+    udivmod(start + n, gx, p1, c);
+    const bool one = p0 == p1;
+    const unsigned e0 = one ? c : gx, mid = one ? 0u : p1 - p0 - 1u, e1 = one ? 0u : c;
+    pair = p0;
+    t = a;
+#pragma unroll 1
+    for (int k = 0; k < nord; ++k) {
+      const unsigned lo = (unsigned)prefix[k], nt = (unsigned)prefix[k + 1] - lo;
+      const unsigned f0 = max(lo, a), f1 = min(lo + nt, e0), nf = f1 > f0 ? f1 - f0 : 0u;
+      const unsigned l1 = min(lo + nt, e1), nl = l1 > lo ? l1 - lo : 0u;
+      if (idx < nf) { t = f0 + idx; break; }
+      idx -= nf;
+      if (idx < mid * nt) {
+        unsigned pl;
+        udivmod(idx, nt, pl, t);
+        pair = p0 + 1u + pl;
+        t += lo;
+        break;
+      }
+      idx -= mid * nt;
+      if (idx < nl) { pair = p1; t = lo + idx; break; }
+      idx -= nl;
+    }
+  }
+  unsigned bb, hh;
+  udivmod(pair, gy, bb, hh);
+  tile = (int)t;
   h = (int)hh;
   b = (int)bb;
 }
 
-// key-validity bit mask of one 64-key tile (bit k <=> key k0+k is a valid key)
-__device__ __forceinline__ unsigned long long tile_key_mask(const uint8_t* key_pad_row, int k0, int klen, int lane) {
-  const int k = k0 + lane;
-  bool ok = k < klen;
-  if (ok && key_pad_row) ok = key_pad_row[k] == 0;
-  return __ballot(ok);
+// decode_tile with constant indexes: the tables come in one scalar load each, where a loop over them is a chain of loads.
+// k: position of the segment in `order`.
+__device__ __forceinline__ void tile_segment(const int (&order)[IM_MAX_SEG], const int (&prefix)[IM_MAX_SEG + 1], int nord,
+                                             int tile, int& seg, int& in_seg, int& k) {
+  int first = 0;
+  k = 0;
+  seg = order[0];
+#pragma unroll
+  for (int i = 1; i < IM_MAX_SEG; ++i)
+    if ((i < nord) & (tile >= prefix[i])) { k = i; seg = order[i]; first = prefix[i]; }
+  in_seg = tile - first;
+}
+
+// The segments of one batch element: first row inside the batch element (packed rows: in the tensor), rows, and the rows
+// that are streamed (rows, or a key segment's valid length if that is less).  Read by lane s for segment s, in one memory
+// round trip at most and beside the loads of the workgroup's own rows, and kept in LDS, a copy per wave; reading valid_len
+// segment by segment put a chain of loads in front of the first tile and one into the loop at every segment's end.
+struct SegTable { int off[IM_MAX_SEG], rows[IM_MAX_SEG], len[IM_MAX_SEG]; };
+__device__ __forceinline__ int seg_get(const int (&v)[IM_MAX_SEG], int s) { return __builtin_amdgcn_readfirstlane(v[s]); }
+// fills the wave's table; qs_off, qs_rows: of segment qs; returns the set of segments of `live` with rows to stream
+__device__ __forceinline__ unsigned seg_table(SegTable& t, const Geo& g, int b, const int32_t* valid_row, unsigned live, int lane, int qs,
+                                              int& qs_off, int& qs_rows) {
+  int off = 0, rows = 0;
+  if (g.cu) {
+    const int32_t* c = g.cu + b * g.n_seg + min(lane, g.n_seg - 1);
+    off = c[0];
+    rows = c[1] - c[0];
+  } else {
+#pragma unroll
+    for (int s = 0; s < IM_MAX_SEG; ++s)
+      if (lane == s) { off = g.seg_off[s]; rows = g.seg_len[s]; }
+  }
+  int len = rows;
+  if (valid_row) len = min(len, max(0, valid_row[min(lane, g.n_seg - 1)]));
+  if (lane < IM_MAX_SEG) { t.off[lane] = off; t.rows[lane] = rows; t.len[lane] = len; }
+  qs_off = __builtin_amdgcn_readlane(off, qs);
+  qs_rows = __builtin_amdgcn_readlane(rows, qs);
+  return (unsigned)__ballot(lane < g.n_seg && ((live >> (lane & 31)) & 1u) && len > 0);
+}
+
+// Validity of the 64 keys of a staged tile as masks for packed bf16 pairs, 0xffff per valid key: keys from `keys` on and
+// those with a key_pad byte (kp: one per dword, or NULL) are not valid.  A lane makes one pair's mask and reads the eight of
+// its registers of a 32-key block back (block_masks): 10 vector instructions for a block where testing a bit per register
+// took 32 (forward) and 48 (dQ).  The table is the wave's own, so no barrier stands between.
+__device__ __forceinline__ void tile_masks(unsigned* pm, const unsigned* kp, int keys) {
+  const int i = lane_id() & 31;
+  u32x2 pad = {0u, 0u};
+  if (kp) pad = *(const u32x2*)(kp + 2 * i);
+  pm[i] = (2 * i < keys && pad[0] == 0u ? 0xffffu : 0u) | (2 * i + 1 < keys && pad[1] == 0u ? 0xffff0000u : 0u);
+}
+// register r of block kb on lane half hi is key kb*32 + 16*(r/8) + 8*hi + r%8
+__device__ __forceinline__ void block_masks(const unsigned* pm, int kb, int hi, unsigned (&m)[8]) {
+  const u32x4 a = *(const u32x4*)(pm + 16 * kb + 4 * hi), b = *(const u32x4*)(pm + 16 * kb + 8 + 4 * hi);
+#pragma unroll
+  for (int e = 0; e < 4; ++e) { m[e] = a[e]; m[4 + e] = b[e]; }
 }
 
 // Streamed operands (K and V tiles in the forward and dQ kernels, Q and dO tiles in the dK/dV
@@ -80,26 +176,18 @@ __device__ __forceinline__ unsigned long long tile_key_mask(const uint8_t* key_p
 constexpr int RING_NST = 3;
 constexpr int RING_STAGE = 2 * KT * SW_LD;  // bf16 elements per stage: two 64 x 64 tiles
 
-// Cursor over the 64-row tiles of the live segments, ascending segment order; segments whose
-// length (as given by len_of) is <= 0 are skipped.  len <= 0 <=> exhausted.  All scalar.
+// Cursor over the 64-row tiles of the live segments, ascending segment order; segments of length <= 0 are not in `rest`.
+// left: rows from the next tile's first one to the end of its segment; <= 0 <=> exhausted.  All scalar.
 struct TileCursor {
   unsigned rest;  // live segments not started yet
-  int seg, r0, len;
+  int seg, left;
 };
-template <class LenFn>
-__device__ __forceinline__ void cursor_next_seg(TileCursor& c, LenFn len_of) {
-  c.r0 = 0;
-  c.len = 0;
-  while (c.rest && c.len <= 0) {
-    c.seg = __builtin_ctz(c.rest);
-    c.rest &= c.rest - 1;
-    c.len = len_of(c.seg);
-  }
-}
-template <class LenFn>
-__device__ __forceinline__ void cursor_step(TileCursor& c, LenFn len_of) {
-  c.r0 += KT;
-  if (c.r0 >= c.len) cursor_next_seg(c, len_of);
+__device__ __forceinline__ bool cursor_next_seg(TileCursor& c, const SegTable& t) {
+  if (!c.rest) { c.left = 0; return false; }
+  c.seg = __builtin_ctz(c.rest);
+  c.rest &= c.rest - 1;
+  c.left = seg_get(t.len, c.seg);
+  return true;
 }
 
 // Per-lane constants of the ring copies: the two tile rows whose chunk positions this lane fills
@@ -159,13 +247,13 @@ __device__ __forceinline__ void ring_feed_issue(const RingLane& rl, const RingLa
   f.b += (size_t)KT * pitch_b;
   f.rows -= KT;
 }
-// wait until at most `later` (0 or 1) stages of copies (4 per wave with 4 waves, 2 with 8) requested after the
-// wanted one are outstanding, then meet the other waves: the wanted stage is visible to all, and every wave
+// wait for the oldest stage requested (later: one more stage has been requested after it; 4 copies per wave and stage with
+// 4 waves, 2 with 8), then meet the other waves: the wanted stage is visible to all, and every wave
 // has finished reading the stage consumed before it.
 // `extra`: this wave issues one more copy per stage, ahead of the others.
 template <int NW = 4>
-__device__ __forceinline__ void ring_wait(int later, bool extra = false) {
-  if (later > 0) {
+__device__ __forceinline__ void ring_wait(bool later, bool extra = false) {
+  if (later) {
     if (NW != 4) asm volatile("s_waitcnt vmcnt(2)" ::: "memory");
     else if (extra) asm volatile("s_waitcnt vmcnt(5)" ::: "memory");
     else asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
@@ -185,45 +273,46 @@ __device__ __forceinline__ void ring_wait(int later, bool extra = false) {
 // O^T only the one 32-row block of V^T that holds them.  Per 64-key tile that is 2 + 4 MFMAs per
 // query block instead of 8 + 8, and the softmax stays on 32 x 32 accumulator tiles -- about a
 // quarter of the VALU instructions of the row-per-lane kernel at these head sizes.
+// KS = 2: tiles of half the height, see split_rows.
 // PAIR: two problems of the same shape in one launch (two encoders side by side; see Geo::pair_B): grid z = 2 B.
-template <int QB, int DH, int NST, int WGS, int NW, bool PAIR, bool HEADW = false>
+template <int QB, int DH, int NST, int WGS, int NW, bool PAIR, bool HEADW = false, int KS = 1>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WGS * NW / 4, WGS * NW / 4))) void mfma_fwd_kernel(Geo g, const bf16_t* __restrict__ QKV, long ld,
                                                        const int32_t* __restrict__ valid_len,
                                                        const uint8_t* __restrict__ key_pad, bf16_t* __restrict__ O,
                                                        long ldo, float* __restrict__ lse2) {
   __shared__ __attribute__((aligned(1024))) bf16_t sT[NST * RING_STAGE];  // per stage: K tile, V tile
   __shared__ __attribute__((aligned(256))) unsigned sKP[NST * KT];        // per stage: key_pad bytes of the 64 keys, one per dword
+  __shared__ __attribute__((aligned(16))) unsigned sPM[NW][KT / 2];       // key masks of the wave's tile
+  __shared__ SegTable sSeg[NW];
   __shared__ int sRedo[NW];
   const int tid = threadIdx.x, lane = tid & 63, lo = lane & 31, hi = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // scalar: branches on it are wave-uniform
   int tile, h, b;
-  xcd_tile_index(g.q_tile_prefix, g.q_nord, g.cu != nullptr, tile, h, b);
+  xcd_tile_index(g.q_tile_prefix, g.q_nord, g.cu != nullptr, g.even_cus, tile, h, b);
   // HEADW (sub-head mode): the NW waves of a workgroup are NW heads of one 64-column group over the SAME 32 QB query
   // rows (grid.y counts groups of NW heads) -- the K/V stream is shared as before, but a tile is 64 rows instead of
   // 256, which at segment lengths like 50 / 500 / 375 leaves 4 % of the rows of the tiles empty instead of 28 %.
   if (HEADW) h = h * NW + wave;
   const bool second = PAIR && b >= g.pair_B;
   const int bm = second ? b - g.pair_B : b;   // batch element of the masks (valid_len, key_pad)
-  constexpr int WG_ROWS = HEADW ? 32 * QB : 32 * NW * QB;
-  int qs, q0;
+  constexpr int WG_ROWS = HEADW ? 32 * QB : 32 * NW * QB / KS;
+  static_assert(KS == 1 || (DH == 64 && QB == 1 && !PAIR && !HEADW), "");
+  const int rb = wave / KS, kg = wave % KS;   // row block of the tile, key block of a stage (KS = 2)
   // HALF: the launch may give the query segment with the longest key range tiles of half the height (one query
   // block per wave instead of two), see launch_mfma_fwd; such a workgroup runs the loop below for one block.
   constexpr bool HALF = HEADW && !PAIR && QB == 2;
-  bool half_tile = false;
-  if (HALF) {
-    int k = 0;
-    while (k + 1 < g.q_nord && tile >= g.q_tile_prefix[k + 1]) ++k;
-    qs = g.q_order[k];
-    half_tile = (g.q_half >> k) & 1u;
-    q0 = (tile - g.q_tile_prefix[k]) * (half_tile ? WG_ROWS / 2 : WG_ROWS);
-  } else {
-    decode_tile(second ? g.q_order2 : g.q_order, second ? g.q_tile_prefix2 : g.q_tile_prefix, second ? g.q_nord2 : g.q_nord,
-                WG_ROWS, tile, qs, q0);
-  }
+  int qs, q0, ord;
+  if (second) tile_segment(g.q_order2, g.q_tile_prefix2, g.q_nord2, tile, qs, q0, ord);
+  else tile_segment(g.q_order, g.q_tile_prefix, g.q_nord, tile, qs, q0, ord);
+  const bool half_tile = HALF && ((g.q_half >> ord) & 1u);
+  q0 *= half_tile ? WG_ROWS / 2 : WG_ROWS;
   const unsigned live = second ? g.q_live2[qs] : g.q_live[qs];   // live key segments of the tile's query segment
-  const int qlen = useg_rows(g, b, qs);
+  int qoff, qlen;
+  SegTable& sg = sSeg[wave];
+  const unsigned stream_set = seg_table(sg, g, b, valid_len ? valid_len + bm * g.n_seg : nullptr, live, lane, qs, qoff, qlen);
   if (q0 >= qlen) return;  // packed rows: this batch element's segment ends before the tile
   const int d = g.d;
+  const long row_b = g.cu ? 0 : (long)b * g.T, qrow0 = row_b + qoff;   // rows of the batch element, of segment qs
 
   constexpr int NS = DH == 64 ? 4 : 1;    // k-steps of S^T
   constexpr int NDB = DH == 64 ? 2 : 1;   // 32-row blocks of O^T
@@ -237,10 +326,10 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WGS * N
   int qrow[QB];
 #pragma unroll
   for (int qb = 0; qb < QB; ++qb) {
-    qrow[qb] = q0 + ((HEADW ? 0 : wave * QB) + qb) * 32 + lo;
+    qrow[qb] = q0 + ((HEADW ? 0 : rb * QB) + qb) * 32 + lo;
     if (HALF && half_tile && qb > 0) qrow[qb] = qlen;   // the next tile's rows: not computed, not stored
     const int rc = min(qrow[qb], qlen - 1);
-    const bf16_t* p = QKV + (useg_row0(g, b, qs) + rc) * ld + cg * 64 + hi * 8;
+    const bf16_t* p = QKV + (qrow0 + rc) * ld + cg * 64 + hi * 8;
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
       u32x4 v = *(const u32x4*)(p + (s0 + s) * 16);
@@ -261,12 +350,6 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WGS * N
 #pragma unroll
     for (int s = 0; s < NS; ++s) asm volatile("" :: "v"(qreg[qb][s]));
 
-  // key tiles of the live key segments; a segment contributes its first min(length, valid length) keys
-  auto klen_of = [&](int j) {
-    int n = useg_rows(g, b, j);
-    if (valid_len) n = min(n, max(0, __builtin_amdgcn_readfirstlane(valid_len[bm * g.n_seg + j])));
-    return n;
-  };
   const RingLane rl = ring_lane<NW>(wave, lane, cg);
   const unsigned ldb = (unsigned)ld * 2u;
   const RingLaneOff rlo = ring_lane_off(rl, ldb, ldb);
@@ -296,53 +379,51 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WGS * N
 #pragma unroll
         for (int r = 0; r < 16; ++r) oacc[db][qb][r] = 0.f;
     }
-    TileCursor ic = {live, 0, 0, 0}, cc = ic;
-    cursor_next_seg(ic, klen_of);
-    cursor_next_seg(cc, klen_of);
-    int islot = 0, cslot = 0, inflight = 0;
+    TileCursor ic = {stream_set, 0, 0};
+    int islot = 0, cslot = 0;
     RingFeed feed = {nullptr, nullptr, 0};
     const uint8_t* feed_kp = nullptr;
-    // K and V rows of segment ic.seg; rows past the valid length but inside the segment are fetched and masked
-    auto seg_begin = [&]() {
-      const long row0 = useg_row0(g, b, ic.seg);
-      feed.a = (const char*)(QKV + row0 * ld + d);
+    // K and V rows of the next segment; rows past the valid length but inside the segment are fetched and masked
+    auto next_seg = [&]() {
+      if (!cursor_next_seg(ic, sg)) return;
+      const int off = seg_get(sg.off, ic.seg);
+      feed.a = (const char*)(QKV + (row_b + off) * ld + d);
       feed.b = feed.a + (size_t)d * 2;
-      feed.rows = useg_rows(g, b, ic.seg);
-      if (key_pad) feed_kp = key_pad + useg_row0(g, bm, ic.seg);
+      feed.rows = seg_get(sg.rows, ic.seg);
+      if (key_pad) feed_kp = key_pad + ((g.cu ? 0 : (long)bm * g.T) + off);
     };
-    if (ic.len > 0) seg_begin();
+    next_seg();
+    // requests the next stage; returns its number of valid keys (key_pad aside), 0 if there is none
     auto issue = [&]() {
+      if (ic.left <= 0) return 0;
+      const int keys = ic.left;
       // The key_pad bytes travel with the stage: an ordinary load inside the loop would wait for every copy before it.
-      if (kp_copy) dma1_off(feed_kp, (unsigned)min(lane, feed.rows - 1), sKP + islot * KT);
+      if (kp_copy) dma1_off(feed_kp, (unsigned)min(lane_id(), feed.rows - 1), sKP + islot * KT);
       feed_kp += KT;
       ring_feed_issue<NW>(rl, rlo, feed, ldb, ldb, wave, sT + islot * RING_STAGE);
       islot = (islot + 1 == NST) ? 0 : islot + 1;
-      ic.r0 += KT;
-      if (ic.r0 >= ic.len) {
-        cursor_next_seg(ic, klen_of);
-        if (ic.len > 0) seg_begin();
-      }
+      ic.left -= KT;
+      if (ic.left <= 0) next_seg();
+      return keys;
     };
     // NST - 1 stages are requested ahead: the slot refilled in an iteration is the one consumed in the one before
-    if (ic.len > 0) { issue(); ++inflight; }
-    if (NST > 2 && ic.len > 0) { issue(); ++inflight; }
-    while (cc.len > 0) {
-      ring_wait<NW>(inflight - 1, kp_copy);
-      if (ic.len > 0) issue(); else --inflight;
+    int keys1 = issue(), keys2 = NST > 2 ? issue() : 0;   // of the next stage, of the one after it
+    while (keys1 > 0) {
+      ring_wait<NW>(keys2 > 0, kp_copy);
+      const int keys = keys1;   // valid keys from the tile's first one on
+      keys1 = keys2;
+      (NST > 2 ? keys2 : keys1) = issue();
       const bf16_t* sK = sT + cslot * RING_STAGE;
       const bf16_t* sV = sK + KT * SW_LD;
       const unsigned* kp = sKP + cslot * KT;
       cslot = (cslot + 1 == NST) ? 0 : cslot + 1;
-      const int keys = cc.len - cc.r0;   // valid keys from the tile's first one on (key_pad aside)
-      cursor_step(cc, klen_of);
       const bool need_mask = keys < KT || key_pad != nullptr;  // tail tile or key_pad present (wave-uniform)
-      unsigned long long km = ~0ull;   // bit k <=> key k of the tile is a valid key
-      if (need_mask) km = __ballot(lane < keys && !(key_pad && kp[lane] != 0));
-      // The tile is processed as two blocks of 32 keys, each S^T -> softmax -> O^T.
-#pragma unroll
-      for (int kb = 0; kb < 2; ++kb) {
+      if (need_mask) tile_masks(sPM[wave], key_pad ? kp : nullptr, keys);
+      // The tile is processed as two blocks of 32 keys, each S^T -> softmax -> O^T (KS = 2: one by each of two waves).
+#pragma unroll(GUARD ? 1 : 2)
+      for (int kk = 0; kk < 2 / KS; ++kk) {
+        const int kb = KS == 1 ? kk : kg;
         if (kb == 1 && keys <= 32) break;
-        const unsigned kw = (unsigned)(km >> (32 * kb)) >> (8 * hi);   // bit 16 (r / 8) + r % 8: key of accumulator register r
         // ---- S^T = K Q^T ----
         f32x16 sacc[QB];
 #pragma unroll
@@ -355,17 +436,12 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WGS * N
         bf16x8 pb[QB][2];
         unsigned pmask[8];   // the validity of the keys of a packed pair of probabilities
         if (need_mask) {
-#pragma unroll
-          for (int e = 0; e < 8; ++e) {
-            const int bit = 16 * (e >> 2) + 2 * (e & 3);
-            const unsigned v0 = (unsigned)((int)(kw << (31 - bit)) >> 31), v1 = (unsigned)((int)(kw << (30 - bit)) >> 31);
-            pmask[e] = __builtin_amdgcn_perm(v1, v0, 0x05040100);
-          }
+          block_masks(sPM[wave], kb, hi, pmask);
           if (GUARD) {   // the maximum must not see masked keys
 #pragma unroll
             for (int r = 0; r < 16; ++r)
 #pragma unroll
-              for (int qb = 0; qb < NQB; ++qb) sacc[qb][r] = ((kw >> (16 * (r >> 3) + (r & 7))) & 1u) ? sacc[qb][r] : IM_NEG_INF;
+              for (int qb = 0; qb < NQB; ++qb) sacc[qb][r] = (pmask[r >> 1] >> (16 * (r & 1)) & 1u) ? sacc[qb][r] : IM_NEG_INF;
           }
         }
 #pragma unroll
@@ -439,20 +515,39 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WGS * N
   bool redo[QB];
   auto finish = [&](bool again) __attribute__((always_inline)) {
     bool any = false;
+    if (KS == 2) {
+      // The two waves of a row block have every other key block each: a wave gives the other one 32 of the 64 columns,
+      // and both sums go together with their references (without one both are 0).
+      __syncthreads();   // the ring is read no more
+      float* ex = (float*)sT;   // per wave: 16 x 64 of the accumulator, then l and m
+      constexpr int EX = 18 * 64;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) ex[wave * EX + r * 64 + lane] = kg ? oacc[0][0][r] : oacc[NDB - 1][0][r];
+      ex[wave * EX + 16 * 64 + lane] = l[0];
+      ex[wave * EX + 17 * 64 + lane] = m[0];
+      __syncthreads();
+      const float* in = ex + (wave ^ 1) * EX;
+      const float m1 = in[17 * 64 + lane], l1 = in[16 * 64 + lane], mm = fmaxf(m[0], m1);
+      const float a0 = m[0] == IM_NEG_INF ? 0.f : fast_exp2(m[0] - mm), a1 = m1 == IM_NEG_INF ? 0.f : fast_exp2(m1 - mm);
+      m[0] = mm;
+      l[0] = a0 * l[0] + a1 * l1;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) oacc[0][0][r] = a0 * (kg ? oacc[NDB - 1][0][r] : oacc[0][0][r]) + a1 * in[r * 64 + lane];
+    }
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb) {
       const float lt = l[qb] + __shfl_xor(l[qb], 32, 64);
       const float inv = lt > 0.f ? 1.f / lt : 0.f;
       const int row = qrow[qb];
       if (row >= qlen || (again && !redo[qb])) continue;
-      const long t = useg_row0(g, b, qs) + row;
-      if (hi == 0 && lse2) lse2[useg_stat0(g, b, h, qs) + row] = lt > 0.f ? -(m[qb] + log2f(lt)) : IM_NEG_INF;  // negated
+      const long t = qrow0 + row;
+      if (hi == 0 && kg == 0 && lse2) lse2[(g.cu ? (long)h * g.R : ((long)b * g.H + h) * g.T) + qoff + row] = lt > 0.f ? -(m[qb] + log2f(lt)) : IM_NEG_INF;  // negated
       float nf = 0.f;
 #pragma unroll
-      for (int db = 0; db < NDB; ++db)
+      for (int db = 0; db < NDB / KS; ++db)
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-          const int dh0 = (db0 + db) * 32 + 8 * i + 4 * hi;  // column inside the 64-column group
+          const int dh0 = (KS == 2 ? kg : db0 + db) * 32 + 8 * i + 4 * hi;  // column inside the 64-column group
           if (DH < 64 && (dh0 < wo || dh0 >= wo + DH)) continue;
           float v[4];
 #pragma unroll
@@ -493,7 +588,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WGS * N
 // The two constant accumulator seeds (negated lse, -delta: 32 registers) put the kernel at 194 registers
 // and two workgroups per CU; with them the softmax is exp2, one multiply and the bf16 pack per score, and
 // that was measured faster than three workgroups per CU with two more vector instructions per score.
-template <int QB, int DH, int NST, int WGS, bool SEED>
+template <int QB, int DH, int NST, int WGS, bool SEED, int KS = 1>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WGS, WGS))) void mfma_dq_kernel(Geo g, const bf16_t* __restrict__ QKV, long ld,
                                                       const bf16_t* __restrict__ O,
                                                       const bf16_t* __restrict__ dO, long ldo,
@@ -502,16 +597,26 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WGS, WGS)))
                                                       const uint8_t* __restrict__ key_pad, float* __restrict__ delta,
                                                       bf16_t* __restrict__ dQKV, long ldg) {
   __shared__ __attribute__((aligned(1024))) bf16_t sT[NST * RING_STAGE];  // per stage: K tile, V tile
+  __shared__ __attribute__((aligned(256))) unsigned sKP[NST * KT];        // per stage: key_pad bytes of the 64 keys, one per dword
+  __shared__ __attribute__((aligned(16))) unsigned sPM[4][KT / 2];        // key masks of the wave's tile
+  __shared__ SegTable sSeg[4];
   const int tid = threadIdx.x, lane = tid & 63, lo = lane & 31, hi = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // scalar: branches on it are wave-uniform
   int tile, h, b;
-  xcd_tile_index(g.q_tile_prefix, g.q_nord, g.cu != nullptr, tile, h, b);
-  constexpr int WG_ROWS = 128 * QB;
-  int qs, q0;
-  decode_tile(g.q_order, g.q_tile_prefix, g.q_nord, WG_ROWS, tile, qs, q0);
-  const int qlen = useg_rows(g, b, qs);
+  xcd_tile_index(g.q_tile_prefix, g.q_nord, g.cu != nullptr, g.even_cus, tile, h, b);
+  constexpr int WG_ROWS = 128 * QB / KS;
+  static_assert(KS == 1 || (DH == 64 && QB == 1), "");
+  const int rb = wave / KS, kg = wave % KS;   // row block of the tile, key block of a stage (KS = 2)
+  int qs, q0, ord;
+  tile_segment(g.q_order, g.q_tile_prefix, g.q_nord, tile, qs, q0, ord);
+  q0 *= WG_ROWS;
+  int qoff, qlen;
+  SegTable& sg = sSeg[wave];
+  const unsigned stream_set = seg_table(sg, g, b, valid_len ? valid_len + b * g.n_seg : nullptr, g.q_live[qs], lane, qs, qoff, qlen);
   if (q0 >= qlen) return;  // packed rows: this batch element's segment ends before the tile
   const int d = g.d;
+  const long row_b = g.cu ? 0 : (long)b * g.T, qrow0 = row_b + qoff;   // rows of the batch element, of segment qs
+  const long stat0 = (g.cu ? (long)h * g.R : ((long)b * g.H + h) * g.T) + qoff;
 
   // sub-head mode (DH = 8 / 16) as in the forward: one k-step for S^T and dP^T, one 32-row block of dQ^T
   constexpr int NS = DH == 64 ? 4 : 1;
@@ -525,9 +630,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WGS, WGS)))
   float ls[QB], dl[QB];
 #pragma unroll
   for (int qb = 0; qb < QB; ++qb) {
-    qrow[qb] = q0 + (wave * QB + qb) * 32 + lo;
+    qrow[qb] = q0 + (rb * QB + qb) * 32 + lo;
     const int rc = min(qrow[qb], qlen - 1);
-    const long t = useg_row0(g, b, qs) + rc;
+    const long t = qrow0 + rc;
     const bf16_t* p = QKV + t * ld + cg * 64 + hi * 8;
     const bf16_t* pg = dO + t * ldo + cg * 64 + hi * 8;
     const bf16_t* po = O + t * ldo + cg * 64 + hi * 8;
@@ -548,10 +653,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WGS, WGS)))
     }
     acc += __shfl_xor(acc, 32, 64);
     dl[qb] = acc;
-    const long li = useg_stat0(g, b, h, qs) + rc;
+    const long li = stat0 + rc;
     const float lv = lse2[li];
     ls[qb] = lv;  // negated log2-sum-exp; -inf for a row without valid keys: every probability is exactly zero
-    if (hi == 0 && qrow[qb] < qlen) delta[li] = DH == 64 ? -acc : acc;  // see the dK/dV kernel
+    if (hi == 0 && kg == 0 && qrow[qb] < qlen) delta[li] = DH == 64 ? -acc : acc;  // see the dK/dV kernel
   }
 
   f32x16 dqacc[NDB][QB], nlb[QB], ndb[QB];
@@ -575,53 +680,53 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WGS, WGS)))
     asm volatile("" :: "v"(ls[qb]), "v"(dl[qb]));
   }
 
-  auto klen_of = [&](int j) {
-    int n = useg_rows(g, b, j);
-    if (valid_len) n = min(n, max(0, valid_len[b * g.n_seg + j]));
-    return n;
-  };
   const RingLane rl = ring_lane(wave, lane, cg);
   const unsigned ldb = (unsigned)ld * 2u;
-  TileCursor ic = {g.q_live[qs], 0, 0, 0}, cc = ic;
-  cursor_next_seg(ic, klen_of);
-  cursor_next_seg(cc, klen_of);
-  int islot = 0, cslot = 0, inflight = 0;
   const RingLaneOff rlo = ring_lane_off(rl, ldb, ldb);
+  const bool kp_copy = wave == 0 && key_pad != nullptr;   // this wave fetches a stage's key_pad bytes
+  TileCursor ic = {stream_set, 0, 0};
+  int islot = 0, cslot = 0;
   RingFeed feed = {nullptr, nullptr, 0};
-  // K and V rows of segment ic.seg; rows past the valid length but inside the segment are fetched and masked
-  auto seg_begin = [&]() {
-    feed.a = (const char*)(QKV + useg_row0(g, b, ic.seg) * ld + d);
+  const uint8_t* feed_kp = nullptr;
+  // K and V rows of the next segment; rows past the valid length but inside the segment are fetched and masked
+  auto next_seg = [&]() {
+    if (!cursor_next_seg(ic, sg)) return;
+    const long row0 = row_b + seg_get(sg.off, ic.seg);
+    feed.a = (const char*)(QKV + row0 * ld + d);
     feed.b = feed.a + (size_t)d * 2;
-    feed.rows = useg_rows(g, b, ic.seg);
+    feed.rows = seg_get(sg.rows, ic.seg);
+    if (key_pad) feed_kp = key_pad + row0;
   };
-  if (ic.len > 0) seg_begin();
-  auto issue = [&]() {
+  next_seg();
+  auto issue = [&]() {   // as in the forward
+    if (ic.left <= 0) return 0;
+    const int keys = ic.left;
+    if (kp_copy) dma1_off(feed_kp, (unsigned)min(lane_id(), feed.rows - 1), sKP + islot * KT);
+    feed_kp += KT;
     ring_feed_issue(rl, rlo, feed, ldb, ldb, wave, sT + islot * RING_STAGE);
     islot = (islot + 1 == NST) ? 0 : islot + 1;
-    ic.r0 += KT;
-    if (ic.r0 >= ic.len) {
-      cursor_next_seg(ic, klen_of);
-      if (ic.len > 0) seg_begin();
-    }
+    ic.left -= KT;
+    if (ic.left <= 0) next_seg();
+    return keys;
   };
-  if (ic.len > 0) { issue(); ++inflight; }
-  if (NST > 2 && ic.len > 0) { issue(); ++inflight; }
-  while (cc.len > 0) {
-    ring_wait(inflight - 1);
-    if (ic.len > 0) issue(); else --inflight;
+  int keys1 = issue(), keys2 = NST > 2 ? issue() : 0;
+  while (keys1 > 0) {
+    ring_wait(keys2 > 0, kp_copy);
+    const int keys = keys1;
+    keys1 = keys2;
+    (NST > 2 ? keys2 : keys1) = issue();
     const bf16_t* sK = sT + cslot * RING_STAGE;
     const bf16_t* sV = sK + KT * SW_LD;
     cslot = (cslot + 1 == NST) ? 0 : cslot + 1;
-    const int k0 = cc.r0, klen = cc.len;
-    const uint8_t* kp_row = key_pad ? key_pad + useg_row0(g, b, cc.seg) : nullptr;
-    cursor_step(cc, klen_of);
+    const unsigned* kp = sKP + (sK - sT) / RING_STAGE * KT;
     {
-      const bool need_mask = (k0 + KT > klen) || (kp_row != nullptr);
-      unsigned long long km = ~0ull;
-      if (need_mask) km = tile_key_mask(kp_row, k0, klen, lane) >> (8 * hi);
+      const bool need_mask = keys < KT || key_pad != nullptr;
+      if (need_mask) tile_masks(sPM[wave], key_pad ? kp : nullptr, keys);
       // two blocks of 32 keys, each S^T, dP^T -> dS^T -> dQ^T, so that one block of dS^T is live at a time
 #pragma unroll
-      for (int kb = 0; kb < 2; ++kb) {
+      for (int kk = 0; kk < 2 / KS; ++kk) {
+        const int kb = KS == 1 ? kk : kg;
+        if (kb == 1 && keys <= 32) break;
         bf16x8 dsb[QB][2];
         // The chains start from the row's negated lse resp. -delta (nlb, ndb: the lane's value in all 16
         // registers), so they end as S^T - lse and dP^T - delta.
@@ -636,13 +741,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WGS, WGS)))
             pacc[qb] = mfma32(av, greg[qb][s], s == 0 ? ndb[qb] : pacc[qb]);   // dP^T = V dO^T
           }
         }
-        if (need_mask) {  // wave-uniform: tail tile or key_pad present
-#pragma unroll
-          for (int qb = 0; qb < QB; ++qb)
-#pragma unroll
-            for (int r = 0; r < 16; ++r)
-              sacc[qb][r] = ((km >> (kb * 32 + 16 * (r >> 3) + (r & 7))) & 1ull) ? sacc[qb][r] : IM_NEG_INF;
-        }
 #pragma unroll
         for (int qb = 0; qb < QB; ++qb) {
           float ds[16];
@@ -653,6 +751,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WGS, WGS)))
           }
           dsb[qb][0] = pack8(ds);
           dsb[qb][1] = pack8(ds + 8);
+          if (need_mask) {  // wave-uniform: tail tile or key_pad present; a masked key's dS is 0 whatever its row holds
+            unsigned pmask[8];
+            block_masks(sPM[wave], kb, hi, pmask);
+            dsb[qb][0] = and_bf16x8(dsb[qb][0], pmask);
+            dsb[qb][1] = and_bf16x8(dsb[qb][1], pmask + 4);
+          }
         }
         // dQ^T += K^T dS^T over the 32 keys of the block
 #pragma unroll
@@ -667,16 +771,26 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WGS, WGS)))
     }
   }
 
+  if (KS == 2) {   // as in the forward: a wave gives the other one of its row block 32 of the 64 columns
+    __syncthreads();
+    float* ex = (float*)sT;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) ex[wave * 1024 + r * 64 + lane] = kg ? dqacc[0][0][r] : dqacc[NDB - 1][0][r];
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < 16; ++r)
+      dqacc[0][0][r] = (kg ? dqacc[NDB - 1][0][r] : dqacc[0][0][r]) + ex[(wave ^ 1) * 1024 + r * 64 + lane];
+  }
 #pragma unroll
   for (int qb = 0; qb < QB; ++qb) {
     const int row = qrow[qb];
     if (row >= qlen) continue;
-    const long t = useg_row0(g, b, qs) + row;
+    const long t = qrow0 + row;
 #pragma unroll
-    for (int db = 0; db < NDB; ++db)
+    for (int db = 0; db < NDB / KS; ++db)
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const int dh0 = (db0 + db) * 32 + 8 * i + 4 * hi;  // column inside the 64-column group
+        const int dh0 = (KS == 2 ? kg : db0 + db) * 32 + 8 * i + 4 * hi;  // column inside the 64-column group
         if (DH < 64 && (dh0 < wo || dh0 >= wo + DH)) continue;
         float v[4];
 #pragma unroll
@@ -697,7 +811,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WGS, WGS)))
 // starts from it, so the MFMA chain ends as dP - delta and no separate subtraction is needed.
 __device__ const float k_neg_inf = -__builtin_inff();
 
-template <int KB, int DH>
+template <int KB, int DH, int KS = 1>
 __global__ __launch_bounds__(256, DH == 64 ? 3 : 2) void mfma_dkv_kernel(Geo g, const bf16_t* __restrict__ QKV, long ld,
                                                        const bf16_t* __restrict__ dO, long ldo,
                                                        const float* __restrict__ lse2, const float* __restrict__ delta,
@@ -706,16 +820,24 @@ __global__ __launch_bounds__(256, DH == 64 ? 3 : 2) void mfma_dkv_kernel(Geo g, 
                                                        long ldg) {
   __shared__ __attribute__((aligned(1024))) bf16_t sT[RING_NST * RING_STAGE];
   __shared__ __attribute__((aligned(256))) float sLD[RING_NST * 2 * KT];  // per stage: lse[64], delta[64]
+  __shared__ SegTable sSeg[4];
   const int tid = threadIdx.x, lane = tid & 63, lo = lane & 31, hi = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // scalar: branches on it are wave-uniform
   int tile, h, b;
-  xcd_tile_index(g.k_tile_prefix, g.k_nord, g.cu != nullptr, tile, h, b);
-  constexpr int WG_ROWS = 128 * KB;
-  int ks, k0;
-  decode_tile(g.k_order, g.k_tile_prefix, g.k_nord, WG_ROWS, tile, ks, k0);
-  const int klen_seg = useg_rows(g, b, ks);
+  xcd_tile_index(g.k_tile_prefix, g.k_nord, g.cu != nullptr, g.even_cus, tile, h, b);
+  constexpr int WG_ROWS = 128 * KB / KS;
+  static_assert(KS == 1 || (DH == 64 && KB == 1), "");
+  const int rb = wave / KS, rg = wave % KS;   // key block of the tile, row block of a stage (KS = 2)
+  int ks, k0, ord;
+  tile_segment(g.k_order, g.k_tile_prefix, g.k_nord, tile, ks, k0, ord);
+  k0 *= WG_ROWS;
+  int koff, klen_seg;
+  SegTable& sg = sSeg[wave];
+  const unsigned stream_set = seg_table(sg, g, b, nullptr, g.k_live[ks], lane, ks, koff, klen_seg);
   if (k0 >= klen_seg) return;  // packed rows: this batch element's segment ends before the tile
   const int d = g.d;
+  const long row_b = g.cu ? 0 : (long)b * g.T, krow0 = row_b + koff;   // rows of the batch element, of segment ks
+  const long stat_b = g.cu ? (long)h * g.R : ((long)b * g.H + h) * g.T;
 
   // sub-head mode (DH = 8 / 16): one k-step for S and dP, one 32-row block of dV^T and dK^T
   constexpr int NS = DH == 64 ? 4 : 1;
@@ -724,28 +846,27 @@ __global__ __launch_bounds__(256, DH == 64 ? 3 : 2) void mfma_dkv_kernel(Geo g, 
   const int s0 = DH == 64 ? 0 : wo >> 4, db0 = DH == 64 ? 0 : wo >> 5;
   const bool other_half = DH == 8 && hi != ((wo >> 3) & 1);  // this lane half holds another head's columns
 
-  auto qlen_of = [&](int i) { return useg_rows(g, b, i); };
   const RingLane rl = ring_lane(wave, lane, cg);
   const unsigned ldb = (unsigned)ld * 2u, ldob = (unsigned)ldo * 2u;  // row pitches in bytes
-  TileCursor ic = {g.k_live[ks], 0, 0, 0}, cc = ic;
-  cursor_next_seg(ic, qlen_of);
-  cursor_next_seg(cc, qlen_of);
-  int islot = 0, cslot = 0, inflight = 0;
   const RingLaneOff rlo = ring_lane_off(rl, ldb, ldob);
+  TileCursor ic = {stream_set, 0, 0};
+  int islot = 0, cslot = 0;
   RingFeed feed = {nullptr, nullptr, 0};
   const float* feed_l = nullptr;  // lse and delta of the next tile's first row
   const float* feed_d = nullptr;
-  auto seg_begin = [&]() {  // Q and dO rows, lse and delta of segment ic.seg
-    const long row0 = useg_row0(g, b, ic.seg);
-    const long lb = useg_stat0(g, b, h, ic.seg);
-    feed.a = (const char*)(QKV + row0 * ld);
-    feed.b = (const char*)(dO + row0 * ldo);
-    feed.rows = ic.len;
-    feed_l = lse2 + lb;
-    feed_d = delta + lb;
+  auto next_seg = [&]() {  // Q and dO rows, lse and delta of the next segment
+    if (!cursor_next_seg(ic, sg)) return;
+    const int off = seg_get(sg.off, ic.seg);
+    feed.a = (const char*)(QKV + (row_b + off) * ld);
+    feed.b = (const char*)(dO + (row_b + off) * ldo);
+    feed.rows = ic.left;
+    feed_l = lse2 + stat_b + off;
+    feed_d = delta + stat_b + off;
   };
-  if (ic.len > 0) seg_begin();
-  auto issue = [&]() {
+  next_seg();
+  auto issue = [&]() {   // requests the next stage; returns the rows left of its segment, 0 if there is none
+    if (ic.left <= 0) return 0;
+    const int rows = ic.left;
     // negated lse (wave 0) and delta (wave 1), one float per lane.  Rows past the segment read -inf
     // as negated lse, so their probabilities are exactly zero.
     if (wave < 2) {
@@ -761,11 +882,9 @@ __global__ __launch_bounds__(256, DH == 64 ? 3 : 2) void mfma_dkv_kernel(Geo g, 
     feed_d += KT;
     ring_feed_issue(rl, rlo, feed, ldb, ldob, wave, sT + islot * RING_STAGE);
     islot = (islot + 1 == RING_NST) ? 0 : islot + 1;
-    ic.r0 += KT;
-    if (ic.r0 >= ic.len) {
-      cursor_next_seg(ic, qlen_of);
-      if (ic.len > 0) seg_begin();
-    }
+    ic.left -= KT;
+    if (ic.left <= 0) next_seg();
+    return rows;
   };
 
   bf16x8 kreg[KB][NS], vreg[KB][NS];
@@ -773,9 +892,9 @@ __global__ __launch_bounds__(256, DH == 64 ? 3 : 2) void mfma_dkv_kernel(Geo g, 
   bool kvalid[KB];
 #pragma unroll
   for (int kb = 0; kb < KB; ++kb) {
-    krow[kb] = k0 + (wave * KB + kb) * 32 + lo;
+    krow[kb] = k0 + (rb * KB + kb) * 32 + lo;
     const int rc = min(krow[kb], klen_seg - 1);
-    const long t = useg_row0(g, b, ks) + rc;
+    const long t = krow0 + rc;
     const bf16_t* p = QKV + t * ld + d + cg * 64 + hi * 8;
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
@@ -806,30 +925,25 @@ __global__ __launch_bounds__(256, DH == 64 ? 3 : 2) void mfma_dkv_kernel(Geo g, 
 #pragma unroll
     for (int s = 0; s < NS; ++s) asm volatile("" :: "v"(kreg[kb][s]), "v"(vreg[kb][s]));
 
-  if (ic.len > 0) { issue(); ++inflight; }
-  if (ic.len > 0) { issue(); ++inflight; }
-
+  int rows1 = issue(), rows2 = issue();
   const int prow = perm32(lo);
-  while (cc.len > 0) {
+  while (rows1 > 0) {
     // Copies complete in issue order.  The wanted stage is complete once at most the copies of the
     // stage requested after it (4 tile chunks, plus 1 on the waves that fetch lse / delta) are
-    // outstanding.
-    if (inflight > 1) {
-      if (wave < 2) asm volatile("s_waitcnt vmcnt(5)" ::: "memory");
-      else asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
-    } else {
-      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    }
-    __builtin_amdgcn_s_barrier();  // stage visible to all waves; everyone is done with the one before
-    if (ic.len > 0) issue(); else --inflight;  // refills the slot of the stage consumed before
+    // outstanding.  Behind the barrier the stage is visible to all waves, and everyone is done with the one before.
+    ring_wait(rows2 > 0, wave < 2);
+    const int rows = rows1;
+    rows1 = rows2;
+    rows2 = issue();  // refills the slot of the stage consumed before
     const bf16_t* sQ = sT + cslot * RING_STAGE;
     const bf16_t* sG = sQ + KT * SW_LD;
     const float* sL = sLD + cslot * 2 * KT;
     const float* sD = sL + KT;
     cslot = (cslot + 1 == RING_NST) ? 0 : cslot + 1;
-    cursor_step(cc, qlen_of);
 #pragma unroll
-    for (int qb = 0; qb < 2; ++qb) {
+    for (int qq = 0; qq < 2 / KS; ++qq) {
+      const int qb = KS == 1 ? qq : rg;
+      if (qb == 1 && rows <= 32) break;
       // negated lse / delta of the query rows of the block: register r of an accumulator holds row
       // (r / 8) * 16 + hi * 8 + r % 8.  At head dim 64 both go straight into the accumulators (the delta buffer
       // holds -delta): the MFMA chains then end as S - lse and dP - delta, and neither needs a vector
@@ -899,18 +1013,45 @@ __global__ __launch_bounds__(256, DH == 64 ? 3 : 2) void mfma_dkv_kernel(Geo g, 
     }
   }
 
+  const int lane_e = lane_id(), hi_e = lane_e >> 5;
+  if (KS == 2) {   // the two waves of a key block have every other row block each: one finishes dK, the other dV
+    __syncthreads();
+    float* ex = (float*)sT;
+    f32x16 sum[NDB];
+#pragma unroll
+    for (int db = 0; db < NDB; ++db)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) ex[(wave * NDB + db) * 1024 + r * 64 + lane_e] = rg ? dkacc[db][0][r] : dvacc[db][0][r];
+    __syncthreads();
+#pragma unroll
+    for (int db = 0; db < NDB; ++db)
+#pragma unroll
+      for (int r = 0; r < 16; ++r)
+        sum[db][r] = (rg ? dvacc[db][0][r] : dkacc[db][0][r]) + ex[((wave ^ 1) * NDB + db) * 1024 + r * 64 + lane_e];
+    const int krow_e = k0 + rb * 32 + (lane_e & 31);
+    if (krow_e >= klen_seg) return;
+    const float z = kvalid[0] ? (rg ? 1.f : 0.69314718055994530942f) : 0.f;   // see below
+    bf16_t* p = dQKV + (krow0 + krow_e) * ldg + (rg ? 2 * d : d) + cg * 64;
+#pragma unroll
+    for (int db = 0; db < NDB; ++db)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        *(u32x2*)(p + db * 32 + 8 * i + 4 * hi_e) = u32x2{pack_bf16(sum[db][4 * i] * z, sum[db][4 * i + 1] * z),
+                                                        pack_bf16(sum[db][4 * i + 2] * z, sum[db][4 * i + 3] * z)};
+    return;
+  }
 #pragma unroll
   for (int kb = 0; kb < KB; ++kb) {
-    const int row = krow[kb];
+    const int row = k0 + (rb * KB + kb) * 32 + (lane_e & 31);
     if (row >= klen_seg) continue;
-    const long t = useg_row0(g, b, ks) + row;
+    const long t = krow0 + row;
     // dK = scale dS^T Q, and the staged Q rows are scale log2(e) Q: the accumulator needs a factor ln 2
     const float zk = kvalid[kb] ? 0.69314718055994530942f : 0.f, zv = kvalid[kb] ? 1.f : 0.f;
 #pragma unroll
     for (int db = 0; db < NDB; ++db)
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const int dh0 = (db0 + db) * 32 + 8 * i + 4 * hi;  // column inside the 64-column group
+        const int dh0 = (db0 + db) * 32 + 8 * i + 4 * hi_e;  // column inside the 64-column group
         if (DH < 64 && (dh0 < wo || dh0 >= wo + DH)) continue;
         const u32x2 pk = {pack_bf16(dkacc[db][kb][4 * i] * zk, dkacc[db][kb][4 * i + 1] * zk),
                           pack_bf16(dkacc[db][kb][4 * i + 2] * zk, dkacc[db][kb][4 * i + 3] * zk)};
@@ -937,6 +1078,29 @@ constexpr int FWD_QB = 1, FWD_QB_SUB = 2, DQ_QB = 1, DKV_KB = 1;
 constexpr int FWD_NST = 2, FWD_WGS = 4, FWD_NW = 4;   // ring stages, workgroups per CU, waves per workgroup (head dim 64)
 constexpr int FWD_SUB_NST = 3, FWD_SUB_WGS = 3;       // the same in sub-head mode (4 waves)
 constexpr int DQ_NST = 3, DQ_WGS = 3;                 // dQ at head dim 64
+static int device_cus();
+// CUs per XCD if a launch of `wgs` workgroups is dealt out evenly (see xcd_tile_index), else 0: all resident with `per_cu`
+// workgroups on a CU, of different lengths.  Lengths of packed rows are not known here.
+static unsigned even_cus(const Geo& g, int nord, long wgs, int per_cu) {
+  const int cus = device_cus();
+  return !g.cu && nord > 1 && cus % 8 == 0 && wgs > cus && wgs <= (long)per_cu * cus ? (unsigned)cus / 8u : 0u;
+}
+// Head dimension 64, few workgroups: tiles of 64 rows instead of 128, the two 32-row blocks of a stage going to two waves of
+// a row block, which add their accumulators at the end (KS = 2).  With about one workgroup per CU a stage is a chain of
+// latencies (barrier, LDS reads, dependent matrix instructions, exponentials) with one wave per SIMD: 1.1 us for a forward
+// stage, 1.4 for dK/dV, 0.8 and 0.9 for half of it.  The copies per score double, and so the line is where the chip is full
+// without it; us for a training step, 128 / 64 rows, at 256 CUs:
+//   workgroups of 128 rows   104 (333/1501/1290 x 4 heads)  204 / 155      288 (512/2048/2048 x 8)  193 / 178
+//                            312                            227 / 192      320 (40/120/300 x 4)      85 / 82
+//                            416                            238 / 239      432 (50/500/500 x 4, layer) 255 / 257
+//                            624                            286 / 319      576 (512/2048/2048 x 8)  269 / 264
+static bool split_rows(const Geo& g, const int* prefix, int nord) {
+  return g.dh == 64 && 2 * (long)prefix[nord] * g.H * g.B <= 3L * device_cus();
+}
+// Tables of a schedule for tiles of `rows` rows (build_geo's for another height)
+static void retile(const Geo& g, const int* order, int nord, int rows, int* prefix) {
+  for (int k = 0; k < nord; ++k) prefix[k + 1] = prefix[k] + (g.seg_len[order[k]] + rows - 1) / rows;
+}
 // sub-head mode with a multiple of 4 heads: four heads of a 64-column group per workgroup, 64-row tiles
 static bool fwd_headw(int dh, int H) { return dh != 64 && H % 4 == 0; }
 int mfma_fwd_tile_rows(int dh, int H) { return dh == 64 ? 32 * FWD_NW * FWD_QB : fwd_headw(dh, H) ? 32 * FWD_QB_SUB : 128 * FWD_QB_SUB; }
@@ -989,6 +1153,8 @@ void launch_mfma_fwd(const Geo& g_in, const bf16_t* qkv, long ld, const int32_t*
   Geo g = g_in;
   g.q_half = 0;
   if (fwd_headw(g.dh, g.H)) fwd_half_tiles(g);
+  const bool split = split_rows(g, g.q_tile_prefix, g.q_nord);
+  if (split) retile(g, g.q_order, g.q_nord, 64 * FWD_QB, g.q_tile_prefix);
   // query segments with no live block: output 0, lse -inf
   for (int s = 0; s < g.n_seg; ++s) {
     if (g.q_live[s]) continue;
@@ -997,10 +1163,12 @@ void launch_mfma_fwd(const Geo& g_in, const bf16_t* qkv, long ld, const int32_t*
   }
   const int nt = g.q_tile_prefix[g.q_nord];
   if (nt == 0) return;
+  g.even_cus = g.dh == 64 ? even_cus(g, g.q_nord, (long)nt * g.H * g.B, FWD_WGS) : 0u;
   ProfScope ps(PF_ATTN_FWD, st);
   const dim3 grid(nt, g.H, g.B), gridw(nt, g.H / 4, g.B);
   const bool hw = fwd_headw(g.dh, g.H);
-  if (g.dh == 64) hipLaunchKernelGGL((mfma_fwd_kernel<FWD_QB, 64, FWD_NST, FWD_WGS, FWD_NW, false>), grid, dim3(64 * FWD_NW), 0, st, g, qkv, ld, valid_len, key_pad, o, ldo, lse2);
+  if (split) hipLaunchKernelGGL((mfma_fwd_kernel<FWD_QB, 64, FWD_NST, FWD_WGS, FWD_NW, false, false, 2>), grid, dim3(64 * FWD_NW), 0, st, g, qkv, ld, valid_len, key_pad, o, ldo, lse2);
+  else if (g.dh == 64) hipLaunchKernelGGL((mfma_fwd_kernel<FWD_QB, 64, FWD_NST, FWD_WGS, FWD_NW, false>), grid, dim3(64 * FWD_NW), 0, st, g, qkv, ld, valid_len, key_pad, o, ldo, lse2);
   else if (g.dh == 16 && hw) hipLaunchKernelGGL((mfma_fwd_kernel<FWD_QB_SUB, 16, FWD_SUB_NST, FWD_SUB_WGS, 4, false, true>), gridw, dim3(256), 0, st, g, qkv, ld, valid_len, key_pad, o, ldo, lse2);
   else if (hw) hipLaunchKernelGGL((mfma_fwd_kernel<FWD_QB_SUB, 8, FWD_SUB_NST, FWD_SUB_WGS, 4, false, true>), gridw, dim3(256), 0, st, g, qkv, ld, valid_len, key_pad, o, ldo, lse2);
   else if (g.dh == 16) hipLaunchKernelGGL((mfma_fwd_kernel<FWD_QB_SUB, 16, FWD_SUB_NST, FWD_SUB_WGS, 4, false>), grid, dim3(256), 0, st, g, qkv, ld, valid_len, key_pad, o, ldo, lse2);
@@ -1032,9 +1200,13 @@ void launch_mfma_fwd_pair(const Geo& g0, const Geo& g1, const bf16_t* qkv, long 
   else hipLaunchKernelGGL((mfma_fwd_kernel<FWD_QB_SUB, 8, FWD_SUB_NST, FWD_SUB_WGS, 4, true>), grid, dim3(256), 0, st, g, qkv, ld, valid_len, key_pad, o, ldo, lse2);
 }
 
-void launch_mfma_bwd(const Geo& g, const bf16_t* qkv, long ld, const bf16_t* o, const bf16_t* d_o, long ldo,
+void launch_mfma_bwd(const Geo& g_in, const bf16_t* qkv, long ld, const bf16_t* o, const bf16_t* d_o, long ldo,
                      const float* lse2, const int32_t* valid_len, const uint8_t* key_pad, float* delta, bf16_t* dqkv,
                      long ldg, hipStream_t st) {
+  Geo g = g_in;
+  const bool split_q = split_rows(g, g.q_tile_prefix, g.q_nord), split_k = split_rows(g, g.k_tile_prefix, g.k_nord);
+  if (split_q) retile(g, g.q_order, g.q_nord, 64 * DQ_QB, g.q_tile_prefix);
+  if (split_k) retile(g, g.k_order, g.k_nord, 64 * DKV_KB, g.k_tile_prefix);
   for (int s = 0; s < g.n_seg; ++s) {
     if (!g.q_live[s])
       launch_zero_seg_rows(g, s, 1, dqkv, ldg, 0, g.d, st);
@@ -1045,12 +1217,16 @@ void launch_mfma_bwd(const Geo& g, const bf16_t* qkv, long ld, const bf16_t* o, 
   if (nq == 0) return;
   { ProfScope ps(PF_ATTN_DQ, st);
     const dim3 grid(nq, g.H, g.B);
-    if (g.dh == 64) hipLaunchKernelGGL((mfma_dq_kernel<DQ_QB, 64, DQ_NST, DQ_WGS, true>), grid, dim3(256), 0, st, g, qkv, ld, o, d_o, ldo, lse2, valid_len, key_pad, delta, dqkv, ldg);
+    g.even_cus = g.dh == 64 ? even_cus(g, g.q_nord, (long)nq * g.H * g.B, 3) : 0u;
+    if (split_q) hipLaunchKernelGGL((mfma_dq_kernel<DQ_QB, 64, DQ_NST, DQ_WGS, true, 2>), grid, dim3(256), 0, st, g, qkv, ld, o, d_o, ldo, lse2, valid_len, key_pad, delta, dqkv, ldg);
+    else if (g.dh == 64) hipLaunchKernelGGL((mfma_dq_kernel<DQ_QB, 64, DQ_NST, DQ_WGS, true>), grid, dim3(256), 0, st, g, qkv, ld, o, d_o, ldo, lse2, valid_len, key_pad, delta, dqkv, ldg);
     else if (g.dh == 16) hipLaunchKernelGGL((mfma_dq_kernel<DQ_QB, 16, 3, 3, true>), grid, dim3(256), 0, st, g, qkv, ld, o, d_o, ldo, lse2, valid_len, key_pad, delta, dqkv, ldg);
     else hipLaunchKernelGGL((mfma_dq_kernel<DQ_QB, 8, 3, 3, true>), grid, dim3(256), 0, st, g, qkv, ld, o, d_o, ldo, lse2, valid_len, key_pad, delta, dqkv, ldg); }
   { ProfScope ps(PF_ATTN_DKV, st);
     const dim3 grid(nk, g.H, g.B);
-    if (g.dh == 64) hipLaunchKernelGGL((mfma_dkv_kernel<DKV_KB, 64>), grid, dim3(256), 0, st, g, qkv, ld, d_o, ldo, lse2, delta, valid_len, key_pad, dqkv, ldg);
+    g.even_cus = g.dh == 64 ? even_cus(g, g.k_nord, (long)nk * g.H * g.B, 3) : 0u;
+    if (split_k) hipLaunchKernelGGL((mfma_dkv_kernel<DKV_KB, 64, 2>), grid, dim3(256), 0, st, g, qkv, ld, d_o, ldo, lse2, delta, valid_len, key_pad, dqkv, ldg);
+    else if (g.dh == 64) hipLaunchKernelGGL((mfma_dkv_kernel<DKV_KB, 64>), grid, dim3(256), 0, st, g, qkv, ld, d_o, ldo, lse2, delta, valid_len, key_pad, dqkv, ldg);
     else if (g.dh == 16) hipLaunchKernelGGL((mfma_dkv_kernel<DKV_KB, 16>), grid, dim3(256), 0, st, g, qkv, ld, d_o, ldo, lse2, delta, valid_len, key_pad, dqkv, ldg);
     else hipLaunchKernelGGL((mfma_dkv_kernel<DKV_KB, 8>), grid, dim3(256), 0, st, g, qkv, ld, d_o, ldo, lse2, delta, valid_len, key_pad, dqkv, ldg); }
 }
