@@ -492,7 +492,7 @@ int im_attention_fwd(const im_shape_t* shape, const void* x, const void* wq, con
   char* ws = saved ? (char*)workspace : (char*)workspace + L.total;
   if (path == PATH_MFMA)
     return mfma_attention_fwd(shape, x, wq, wk, wv, wo, bq, bk, bv, bo, valid_len, key_pad, y, nullptr, sv, L.qkv,
-                              L.o, L.lse, L.extra, ws, as_stream(hip_stream));
+                              L.o, saved ? L.lse : NO_LSE, L.extra, ws, as_stream(hip_stream));
   return fwd_smallhead(shape, x, wq, wk, wv, wo, bq, bk, bv, bo, valid_len, key_pad, y, nullptr, sv,
                      as_stream(hip_stream));
 }
@@ -555,7 +555,7 @@ int im_attention_fwd_noalloc(const im_shape_t* shape, const void* x, const void*
   // block are zero-filled by a kernel), so nothing left in the buffer by an earlier call matters.
   if (path == PATH_MFMA)
     return mfma_attention_fwd(shape, x, wq, wk, wv, wo, bq, bk, bv, bo, valid_len, key_pad, y, nullptr, sv, L.qkv,
-                              L.o, L.lse, L.extra, sv + L.total, as_stream(hip_stream));
+                              L.o, NO_LSE, L.extra, sv + L.total, as_stream(hip_stream));
   return fwd_smallhead(shape, x, wq, wk, wv, wo, bq, bk, bv, bo, valid_len, key_pad, y, nullptr, sv,
                      as_stream(hip_stream));
 }
@@ -626,7 +626,7 @@ int gsit_layer_fwd(const im_shape_t* shape, int32_t d_ff, const void* x, const v
   const bool tail_fused = mfma && mlp_tail_ok(bf, d, d_ff, x, ln2_g, ln2_b, w1, w2, y) && (((uintptr_t)wo | (uintptr_t)aw) & 15) == 0;
   if (mfma)
     rc = mfma_attention_fwd(shape, ln1_fused ? x : u, wq, wk, wv, wo, bq, bk, bv, bo, valid_len, key_pad,
-                            tail_fused ? nullptr : h, x, aw, L.qkv, L.o, L.lse, L.extra, aw + L.total, st,
+                            tail_fused ? nullptr : h, x, aw, L.qkv, L.o, NO_LSE, L.extra, aw + L.total, st,
                             ln1_fused ? LnArgs{ln1_g, ln1_b, ln_eps} : LnArgs{nullptr, nullptr, 0.f});
   else
     rc = fwd_smallhead(shape, u, wq, wk, wv, wo, bq, bk, bv, bo, valid_len, key_pad, h, x, aw, st);
@@ -706,7 +706,7 @@ int gsit_layer_fwd_pair(const im_shape_t* s0, uint64_t mask1, int32_t d_ff, cons
   const SavedLayout L = saved_layout(&s2);
   char* sv = (char*)workspace;
   if (!mfma_attention_fwd_pair(s0, mask1, x0, x1, p0, p1, LnArgs{p0.ln1_g, p0.ln1_b, ln_eps}, LnArgs{p1.ln1_g, p1.ln1_b, ln_eps},
-                               valid_len, key_pad, sv, L.qkv, L.o, L.lse, st))
+                               valid_len, key_pad, sv, L.qkv, L.o, NO_LSE, st))
     return IM_OK;
   {
     ProfScope ps(PF_MISC, st);

@@ -285,6 +285,12 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WGS * N
   __shared__ __attribute__((aligned(16))) unsigned sPM[NW][KT / 2];       // key masks of the wave's tile
   __shared__ SegTable sSeg[NW];
   __shared__ int sRedo[NW];
+  // Sub-head mode: ones, four to each of the 16-key steps of a tile, where the step's V^T fragment has its rows in the tile.
+  // The lanes whose four rows of the fragment are not the head's read them: those rows of O^T are then the row sum of P,
+  // which the matrix cores take beside the product (a dot product per pair of probabilities otherwise, 8 of 40 vector
+  // instructions per 32 x 32 scores).
+  constexpr bool ONES = DH != 64;
+  __shared__ __attribute__((aligned(16))) bf16_t sOnes[ONES ? 3 * 16 * SW_LD + 4 : 4];
   const int tid = threadIdx.x, lane = tid & 63, lo = lane & 31, hi = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // scalar: branches on it are wave-uniform
   int tile, h, b;
@@ -341,6 +347,19 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WGS * N
   f32x16 oacc[NDB][QB];
   float m[QB], l[QB];
 
+  // V^T fragments in sub-head mode: the lane's two addresses (lds_frag_tr_sw) from the V tile on, or the ones
+  unsigned vt0 = 0, vt1 = 0, vt_tile = 0;   // vt_tile: all bits set where the tile's address is to be added
+  if (ONES) {
+    const int j = lane & 15, gg = lane >> 4, lrow = 8 * (gg >> 1) + (j >> 2), lchunk = 2 * (gg & 1) + ((j & 3) >> 1);
+    const int chunk = (db0 * 4) | lchunk, f = sw_f(lrow);
+    const unsigned ones = (unsigned)(uintptr_t)sOnes;
+    const bool own = chunk >= (wo >> 3) && chunk < (wo + DH) >> 3;
+    vt0 = own ? (unsigned)(lrow * SW_LD + ((chunk ^ f) << 3) + 4 * (j & 1)) * 2u : ones;
+    vt1 = own ? (unsigned)((lrow + 4) * SW_LD + ((chunk ^ f ^ 1) << 3) + 4 * (j & 1)) * 2u : ones;
+    vt_tile = own ? ~0u : 0u;
+    if (lane < 16) sOnes[(lane >> 2) * 16 * SW_LD + (lane & 3)] = 0x3f80;   // every wave, so that none waits for another
+  }
+
   const int prow = perm32(lo);
   constexpr float tau = 8.f;  // scores are exponents of 2 (Q carries scale * log2(e))
   // The compiler does not see the asynchronous copies in its vmcnt bookkeeping: consuming the Q
@@ -367,13 +386,10 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WGS * N
   auto stream = [&](auto nqb_tag, auto guard_tag) __attribute__((always_inline)) {
     constexpr int NQB = decltype(nqb_tag)::value;
     constexpr bool GUARD = decltype(guard_tag)::value;
-    f32x16 nm[QB];   // GUARD: -m of the lane's query row in all 16 registers, where the score accumulators start
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb) {
       m[qb] = GUARD ? IM_NEG_INF : 0.f;
       l[qb] = 0.f;
-#pragma unroll
-      for (int r = 0; r < 16; ++r) nm[qb][r] = 0.f;
 #pragma unroll
       for (int db = 0; db < NDB; ++db)
 #pragma unroll
@@ -417,6 +433,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WGS * N
       const bf16_t* sV = sK + KT * SW_LD;
       const unsigned* kp = sKP + cslot * KT;
       cslot = (cslot + 1 == NST) ? 0 : cslot + 1;
+      const unsigned vta = (vt_tile & (unsigned)(uintptr_t)sV) + vt0, vtb = (vt_tile & (unsigned)(uintptr_t)sV) + vt1;
       const bool need_mask = keys < KT || key_pad != nullptr;  // tail tile or key_pad present (wave-uniform)
       if (need_mask) tile_masks(sPM[wave], key_pad ? kp : nullptr, keys);
       // The tile is processed as two blocks of 32 keys, each S^T -> softmax -> O^T (KS = 2: one by each of two waves).
@@ -430,7 +447,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WGS * N
         for (int s = 0; s < NS; ++s) {
           const bf16x8 a = lds_frag_sw(sK, kb * 32, prow, 2 * (s0 + s) + hi);
 #pragma unroll
-          for (int qb = 0; qb < NQB; ++qb) sacc[qb] = mfma32(a, qreg[qb][s], s == 0 ? (GUARD ? nm[qb] : f32x16{}) : sacc[qb]);
+          for (int qb = 0; qb < NQB; ++qb) sacc[qb] = mfma32(a, qreg[qb][s], s == 0 ? f32x16{} : sacc[qb]);
         }
         // ---- softmax ----
         bf16x8 pb[QB][2];
@@ -459,6 +476,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WGS * N
               pb[qb][0] = and_bf16x8(pb[qb][0], pmask);
               pb[qb][1] = and_bf16x8(pb[qb][1], pmask + 4);
             }
+            if (ONES && !GUARD) return 0.f;
             return sum_bf16x8(pb[qb][1], sum_bf16x8(pb[qb][0], sum));
           };
           if (!GUARD) {
@@ -467,6 +485,9 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WGS * N
           }
           // A row without a reference yet, or a row sum of the block beyond 2^24 (or inf / NaN), sends the block
           // through the rescaling branch, which recomputes it.
+          const float m0 = m[qb] == IM_NEG_INF ? 0.f : m[qb];
+#pragma unroll
+          for (int r = 0; r < 16; ++r) sacc[qb][r] -= m0;
           float rs = exponentiate(0.f);
           if (__builtin_expect(__any(m[qb] == IM_NEG_INF || !(rs <= 16777216.f)), 0)) {
             asm volatile("" ::: "memory");  // a real branch: nothing of it is to be executed speculatively
@@ -475,8 +496,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WGS * N
             for (int r = 1; r < 16; ++r) mx = fmaxf(mx, sacc[qb][r]);
             mx = fmaxf(mx, __shfl_xor(mx, 32, 64));  // block maximum relative to m (the raw maximum while m = -inf)
             // The reference moves when a row has none yet, or when the block maximum exceeds it by more than
-            // 2^8 in the exponent domain: accumulator rescale, shifting the block's scores to the new reference
-            // and rebuilding nm.
+            // 2^8 in the exponent domain: accumulator rescale, shifting the block's scores to the new reference.
             const bool first = m[qb] == IM_NEG_INF;
             const bool upd = first ? mx > IM_NEG_INF : mx > tau;
             const float shift = upd ? mx : 0.f;
@@ -489,9 +509,6 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WGS * N
             if (upd) m[qb] = first ? mx : m[qb] + mx;
 #pragma unroll
             for (int r = 0; r < 16; ++r) sacc[qb][r] -= shift;
-            const float nmv = (m[qb] == IM_NEG_INF) ? 0.f : -m[qb];
-#pragma unroll
-            for (int r = 0; r < 16; ++r) nm[qb][r] = nmv;
             rs = exponentiate(0.f);
           }
           l[qb] += rs;
@@ -501,11 +518,16 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WGS * N
         for (int db = 0; db < NDB; ++db)
 #pragma unroll
           for (int half = 0; half < 2; ++half) {
-            const bf16x8 a = lds_frag_tr_sw(sV, kb * 32 + half * 16, (db0 + db) * 32, lane);
+            const bf16x8 a = ONES ? lds_frag_tr_at(vta, vtb, (kb * 32 + half * 16) * SW_LD * 2)
+                                  : lds_frag_tr_sw(sV, kb * 32 + half * 16, (db0 + db) * 32, lane);
 #pragma unroll
             for (int qb = 0; qb < NQB; ++qb) oacc[db][qb] = mfma32(a, pb[qb][half], oacc[db][qb]);
           }
       }
+    }
+    if (ONES) {
+#pragma unroll
+      for (int qb = 0; qb < QB; ++qb) l[qb] = (wo & 31) == 0 ? oacc[0][qb][8] : oacc[0][qb][0];   // rows 16.. / 0.. of O^T: not the head's
     }
   };
 
@@ -536,7 +558,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WGS * N
     }
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb) {
-      const float lt = l[qb] + __shfl_xor(l[qb], 32, 64);
+      const float lt = ONES ? l[qb] : l[qb] + __shfl_xor(l[qb], 32, 64);
       const float inv = lt > 0.f ? 1.f / lt : 0.f;
       const int row = qrow[qb];
       if (row >= qlen || (again && !redo[qb])) continue;
@@ -1068,7 +1090,9 @@ __global__ __launch_bounds__(256, DH == 64 ? 3 : 2) void mfma_dkv_kernel(Geo g, 
 //   forward, head dim 64: 1 query block per wave, 4 waves, a 2-stage ring and 128 registers, so that four
 //     workgroups (16 waves) share a CU -- 10 % faster than 3 stages at three workgroups; 8-wave workgroups
 //     (256 query rows) were slower;
-//   forward, sub-head mode: 2 query blocks per wave (half the K/V tile traffic per score), 3 stages, 3 workgroups;
+//   forward, sub-head mode: 2 query blocks per wave (half the K/V tile traffic per score), 2 stages, 4 workgroups (115
+//     registers; four layers of 32 x 50/500/375 rows, no padding, intra-modal mask: 169 us with 3 stages and 3 workgroups, 160
+//     with 2 and 4, 150 with the row sums on the matrix cores);
 //   dQ, head dim 64: 3 stages, 3 workgroups per CU, accumulators seeded with -lse and -delta (unseeded: 7 % slower;
 //     4 workgroups need spills);
 //   dQ, sub-head mode: 3 workgroups per CU as well (114 registers; 27 against 33 us with two at B = 32, 50 / 500 / 375
@@ -1076,7 +1100,7 @@ __global__ __launch_bounds__(256, DH == 64 ? 3 : 2) void mfma_dkv_kernel(Geo g, 
 //   dK/dV: 1 key block per wave, 3 workgroups per CU at head dim 64, 2 in sub-head mode (3 measured the same).
 constexpr int FWD_QB = 1, FWD_QB_SUB = 2, DQ_QB = 1, DKV_KB = 1;
 constexpr int FWD_NST = 2, FWD_WGS = 4, FWD_NW = 4;   // ring stages, workgroups per CU, waves per workgroup (head dim 64)
-constexpr int FWD_SUB_NST = 3, FWD_SUB_WGS = 3;       // the same in sub-head mode (4 waves)
+constexpr int FWD_SUB_NST = 2, FWD_SUB_WGS = 4;       // the same in sub-head mode (4 waves)
 constexpr int DQ_NST = 3, DQ_WGS = 3;                 // dQ at head dim 64
 static int device_cus();
 // CUs per XCD if a launch of `wgs` workgroups is dealt out evenly (see xcd_tile_index), else 0: all resident with `per_cu`

@@ -190,6 +190,18 @@ __device__ __forceinline__ bf16x8 lds_frag_tr_sw(const bf16_t* lds, int k_base, 
   return x.v;
 }
 
+// transposed fragment from the LDS byte addresses of its two reads, `off` bytes further on (a constant)
+__device__ __forceinline__ bf16x8 lds_frag_tr_at(unsigned a0, unsigned a1, int off) {
+  typedef v4i16 __attribute__((address_space(3))) * lds_v4_ptr;
+  typedef char __attribute__((address_space(3))) * lds_char_ptr;
+  const v4i16 a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4_ptr)((lds_char_ptr)a0 + off));
+  const v4i16 b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4_ptr)((lds_char_ptr)a1 + off));
+  union { v4i16 h[2]; bf16x8 v; } x;
+  x.h[0] = a;
+  x.h[1] = b;
+  return x.v;
+}
+
 __device__ __forceinline__ bf16x8 lds_frag(const bf16_t* lds, int row, int col) {
   return as_bf16x8(*(const u32x4*)(lds + row * LDS_LD + col));
 }

@@ -135,7 +135,7 @@ bool mfma_attention_fwd_pair(const im_shape_t* s0, uint64_t mask1, const void* x
   const int d = (int)dm.d, R = (int)dm.R;
   bf16_t* qkv = (bf16_t*)(sv + off_qkv);
   bf16_t* o = (bf16_t*)(sv + off_o);
-  float* lse2 = (float*)(sv + off_lse);
+  float* lse2 = off_lse == NO_LSE ? nullptr : (float*)(sv + off_lse);
   MGemm a, b;
   qkv_gemm(&a, x0, p0.wq, p0.wk, p0.wv, p0.bq, p0.bk, p0.bv, ln0, g0.scale_log2e, qkv, R, d);
   qkv_gemm(&b, x1, p1.wq, p1.wk, p1.wv, p1.bq, p1.bk, p1.bv, ln1, g1.scale_log2e, qkv + (size_t)R * 3 * d, R, d);
@@ -156,7 +156,7 @@ int mfma_attention_fwd(const im_shape_t* s, const void* x, const void* wq, const
   const int d = (int)dm.d;
   bf16_t* qkv = (bf16_t*)(sv + off_qkv);
   bf16_t* o = (bf16_t*)(sv + off_o);
-  float* lse2 = (float*)(sv + off_lse);
+  float* lse2 = off_lse == NO_LSE ? nullptr : (float*)(sv + off_lse);
 
   MGemm p;
   {

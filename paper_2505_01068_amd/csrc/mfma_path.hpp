@@ -113,7 +113,8 @@ size_t mfma_saved_extra_bytes(const im_shape_t* s);
 size_t mfma_fwd_workspace_bytes(int d);
 size_t mfma_bwd_workspace_bytes(const im_shape_t* s, const WgradPlan* plan = nullptr);   // plan: as mfma_attention_bwd's
 
-// sv + off_* : Q|K|V rows [R,3d], O [R,d], lse [B,H,T], extra (transposed copies).
+// sv + off_* : Q|K|V rows [R,3d], O [R,d], lse [B,H,T] (off_lse = NO_LSE: not written), extra (transposed copies).
+constexpr size_t NO_LSE = ~(size_t)0;
 int mfma_attention_fwd(const im_shape_t* s, const void* x, const void* wq, const void* wk, const void* wv,
                        const void* wo, const void* bq, const void* bk, const void* bv, const void* bo,
                        const int32_t* valid_len, const uint8_t* key_pad, void* y, const void* res, char* sv,
