@@ -1,6 +1,6 @@
 // Flash-style IM attention on the CDNA4 matrix cores: bf16 operands, fp32
 // accumulation, head dimension 64 (forward also head dimensions 8 / 16 in its
-// sub-head mode).
+// sub-head mode; their backward is in mfma_attn_sub.hip).
 //
 // All three kernels compute "transposed" products so that every per-row
 // quantity of the softmax lives on the lane that owns the row:
@@ -20,248 +20,17 @@
 // exp2 and no kernel multiplies scores; the per-row statistic saved by the forward is the NEGATED
 // log2-sum-exp (-inf for a row without any valid key), which the backward kernels add to the score --
 // by starting their score accumulators from it, as the dP accumulators start from -delta: the MFMA
-// chains end as S - lse and dP - delta and the softmax needs no add per element (dK/dV in sub-head
-// mode still adds them per element).  The forward exponentiates its scores as they are.
+// chains end as S - lse and dP - delta and the softmax needs no add per element.  The forward exponentiates its scores as they are.
 //
 // Only live (query segment, key segment) blocks of the Interlaced Mask are
 // visited (Sec. 6 "Decomposition"); a row with several live segments carries
 // one running max / sum across all of them (Sec. "Information Disorder").
 #include <algorithm>
 #include <type_traits>
-#include "mfma_common.hpp"
+#include "mfma_attn_common.hpp"
 #include "mfma_path.hpp"
 
 namespace imattn {
-
-constexpr int KT = 64;  // keys (or query rows) per staged tile
-
-// the lane's index from the hardware, where keeping it over a loop would cost a register that the loop does not have
-__device__ __forceinline__ int lane_id() { return __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)); }
-
-// Workgroup -> (tile, head, batch element).  As with xcd_block_index every XCD owns a contiguous range of (batch element,
-// head, tile), but inside that range the workgroups are ordered by segment first (the tile order lists the segments by
-// decreasing work per tile), then pair, then tile.  A workgroup of a long live range runs several times longer than one of
-// a short range; started pair by pair, the long workgroups of the last pairs begin late and the XCD drains with most of its
-// CUs idle.  Started first, they leave the short ones to fill the tail.
-//
-// cus != 0: the whole launch is resident at once and its tiles differ in length, so that nothing is left to fill a tail.  The
-// dispatcher deals the workgroups of an XCD to its `cus` CUs in turn (measured: workgroups i, i + cus, i + 2 cus share
-// a CU), and in plain order the CUs that get one workgroup more are those with the longest ones.  Here the CUs with one less
-// take the longest, and each group of CUs is dealt to and fro.  3 x 333/1501/1290 rows, 4 heads of 64 (12 pairs), forward + dQ +
-// dK/dV: in pair order 52 + 59 + 61 us, segment first and dealt like this 44 + 51 + 52.
-__device__ __forceinline__ unsigned even_rank(unsigned pos, unsigned n, unsigned cus) {
-  const unsigned full = n / cus, more = n % cus, round = pos / cus, cu = pos % cus;
-  const bool a = cu >= more;
-  const unsigned w = a ? cus - more : more, c = a ? cu - more : cu;
-  return (a ? 0u : (cus - more) * full) + round * w + ((round & 1u) ? w - 1u - c : c);
-}
-__device__ __forceinline__ void xcd_tile_index(const int (&prefix)[IM_MAX_SEG + 1], int nord, bool tile_first, unsigned cus, int& tile, int& h,
-                                               int& b) {
-  const unsigned gx = gridDim.x, gy = gridDim.y, npair = gy * gridDim.z, total = gx * npair;
-  const unsigned lin = blockIdx.x + gx * (blockIdx.y + gy * blockIdx.z);
-  const unsigned xcd = lin & 7u, q = total >> 3, r = total & 7u, n = q + (xcd < r ? 1u : 0u);
-  unsigned idx = lin >> 3, pair, t;
-  if (cus) idx = even_rank(idx, n, cus);
-  if ((npair & 7u) == 0u) {   // whole pairs
-    const unsigned per = npair >> 3;  // pairs per XCD
-    int first = 0, last = prefix[1];
-#pragma unroll
-    for (int k = 1; k < IM_MAX_SEG; ++k)
-      if ((k < nord) & (idx >= per * (unsigned)prefix[k])) { first = prefix[k]; last = prefix[k + 1]; }
-    const unsigned nt = (unsigned)(last - first), j = idx - per * (unsigned)first;
-    if (tile_first) udivmod(j, per, t, pair);  // packed rows: the later tiles of most pairs find no rows
-    else udivmod(j, nt, pair, t);
-    pair += xcd * per;
-    t += (unsigned)first;
-  } else {
-    // tiles a .. of pair p0, all tiles of the pairs between, tiles .. c - 1 of pair p1
-    const unsigned start = xcd * q + (xcd < r ? xcd : r);
-    unsigned p0, a, p1, c;
-    udivmod(start, gx, p0, a);
-    udivmod(start + n, gx, p1, c);
-    const bool one = p0 == p1;
-    const unsigned e0 = one ? c : gx, mid = one ? 0u : p1 - p0 - 1u, e1 = one ? 0u : c;
-    pair = p0;
-    t = a;
-#pragma unroll 1
-    for (int k = 0; k < nord; ++k) {
-      const unsigned lo = (unsigned)prefix[k], nt = (unsigned)prefix[k + 1] - lo;
-      const unsigned f0 = max(lo, a), f1 = min(lo + nt, e0), nf = f1 > f0 ? f1 - f0 : 0u;
-      const unsigned l1 = min(lo + nt, e1), nl = l1 > lo ? l1 - lo : 0u;
-      if (idx < nf) { t = f0 + idx; break; }
-      idx -= nf;
-      if (idx < mid * nt) {
-        unsigned pl;
-        udivmod(idx, nt, pl, t);
-        pair = p0 + 1u + pl;
-        t += lo;
-        break;
-      }
-      idx -= mid * nt;
-      if (idx < nl) { pair = p1; t = lo + idx; break; }
-      idx -= nl;
-    }
-  }
-  unsigned bb, hh;
-  udivmod(pair, gy, bb, hh);
-  tile = (int)t;
-  h = (int)hh;
-  b = (int)bb;
-}
-
-// decode_tile with constant indexes: the tables come in one scalar load each, where a loop over them is a chain of loads.
-// k: position of the segment in `order`.
-__device__ __forceinline__ void tile_segment(const int (&order)[IM_MAX_SEG], const int (&prefix)[IM_MAX_SEG + 1], int nord,
-                                             int tile, int& seg, int& in_seg, int& k) {
-  int first = 0;
-  k = 0;
-  seg = order[0];
-#pragma unroll
-  for (int i = 1; i < IM_MAX_SEG; ++i)
-    if ((i < nord) & (tile >= prefix[i])) { k = i; seg = order[i]; first = prefix[i]; }
-  in_seg = tile - first;
-}
-
-// The segments of one batch element: first row inside the batch element (packed rows: in the tensor), rows, and the rows
-// that are streamed (rows, or a key segment's valid length if that is less).  Read by lane s for segment s, in one memory
-// round trip at most and beside the loads of the workgroup's own rows, and kept in LDS, a copy per wave; reading valid_len
-// segment by segment put a chain of loads in front of the first tile and one into the loop at every segment's end.
-struct SegTable { int off[IM_MAX_SEG], rows[IM_MAX_SEG], len[IM_MAX_SEG]; };
-__device__ __forceinline__ int seg_get(const int (&v)[IM_MAX_SEG], int s) { return __builtin_amdgcn_readfirstlane(v[s]); }
-// fills the wave's table; qs_off, qs_rows: of segment qs; returns the set of segments of `live` with rows to stream
-__device__ __forceinline__ unsigned seg_table(SegTable& t, const Geo& g, int b, const int32_t* valid_row, unsigned live, int lane, int qs,
-                                              int& qs_off, int& qs_rows) {
-  int off = 0, rows = 0;
-  if (g.cu) {
-    const int32_t* c = g.cu + b * g.n_seg + min(lane, g.n_seg - 1);
-    off = c[0];
-    rows = c[1] - c[0];
-  } else {
-#pragma unroll
-    for (int s = 0; s < IM_MAX_SEG; ++s)
-      if (lane == s) { off = g.seg_off[s]; rows = g.seg_len[s]; }
-  }
-  int len = rows;
-  if (valid_row) len = min(len, max(0, valid_row[min(lane, g.n_seg - 1)]));
-  if (lane < IM_MAX_SEG) { t.off[lane] = off; t.rows[lane] = rows; t.len[lane] = len; }
-  qs_off = __builtin_amdgcn_readlane(off, qs);
-  qs_rows = __builtin_amdgcn_readlane(rows, qs);
-  return (unsigned)__ballot(lane < g.n_seg && ((live >> (lane & 31)) & 1u) && len > 0);
-}
-
-// Validity of the 64 keys of a staged tile as masks for packed bf16 pairs, 0xffff per valid key: keys from `keys` on and
-// those with a key_pad byte (kp: one per dword, or NULL) are not valid.  A lane makes one pair's mask and reads the eight of
-// its registers of a 32-key block back (block_masks): 10 vector instructions for a block where testing a bit per register
-// took 32 (forward) and 48 (dQ).  The table is the wave's own, so no barrier stands between.
-__device__ __forceinline__ void tile_masks(unsigned* pm, const unsigned* kp, int keys) {
-  const int i = lane_id() & 31;
-  u32x2 pad = {0u, 0u};
-  if (kp) pad = *(const u32x2*)(kp + 2 * i);
-  pm[i] = (2 * i < keys && pad[0] == 0u ? 0xffffu : 0u) | (2 * i + 1 < keys && pad[1] == 0u ? 0xffff0000u : 0u);
-}
-// register r of block kb on lane half hi is key kb*32 + 16*(r/8) + 8*hi + r%8
-__device__ __forceinline__ void block_masks(const unsigned* pm, int kb, int hi, unsigned (&m)[8]) {
-  const u32x4 a = *(const u32x4*)(pm + 16 * kb + 4 * hi), b = *(const u32x4*)(pm + 16 * kb + 8 + 4 * hi);
-#pragma unroll
-  for (int e = 0; e < 4; ++e) { m[e] = a[e]; m[4 + e] = b[e]; }
-}
-
-// Streamed operands (K and V tiles in the forward and dQ kernels, Q and dO tiles in the dK/dV
-// kernel) go from global memory straight into a ring of RING_NST LDS stages with asynchronous
-// global->LDS copies (no staging registers, no LDS store instructions): stage t+2 is requested
-// while stage t is consumed, with one workgroup barrier per stage.  Each lane fetches the 16-byte
-// chunk that belongs at ITS position of the swizzled tile (see sw_f), so the copy produces the
-// conflict-free layout directly.  The tiles of all live segments form one sequence, so the ring
-// does not drain between segments.
-constexpr int RING_NST = 3;
-constexpr int RING_STAGE = 2 * KT * SW_LD;  // bf16 elements per stage: two 64 x 64 tiles
-
-// Cursor over the 64-row tiles of the live segments, ascending segment order; segments of length <= 0 are not in `rest`.
-// left: rows from the next tile's first one to the end of its segment; <= 0 <=> exhausted.  All scalar.
-struct TileCursor {
-  unsigned rest;  // live segments not started yet
-  int seg, left;
-};
-__device__ __forceinline__ bool cursor_next_seg(TileCursor& c, const SegTable& t) {
-  if (!c.rest) { c.left = 0; return false; }
-  c.seg = __builtin_ctz(c.rest);
-  c.rest &= c.rest - 1;
-  c.left = seg_get(t.len, c.seg);
-  return true;
-}
-
-// Per-lane constants of the ring copies: the two tile rows whose chunk positions this lane fills
-// and the byte offset of the logical chunk inside a row of head h.
-struct RingLane {
-  int trow0, trow1;
-  unsigned col0, col1;
-};
-// NW = waves per workgroup: with 4 waves a lane fills chunk positions in two tile rows (trow0, trow0 + 32) of
-// each streamed matrix, with 8 waves in one row (trow1 / col1 unused).
-template <int NW = 4>
-__device__ __forceinline__ RingLane ring_lane(int wave, int lane, int h) {
-  RingLane r;
-  r.trow0 = wave * 8 + (lane >> 3);
-  r.trow1 = NW == 4 ? r.trow0 + 32 : r.trow0;
-  r.col0 = (unsigned)(h * 64 + (((lane & 7) ^ sw_f(r.trow0)) << 3)) * 2u;
-  r.col1 = (unsigned)(h * 64 + (((lane & 7) ^ sw_f(r.trow1)) << 3)) * 2u;
-  return r;
-}
-// Scalar state of the ring copies inside the current segment: byte pointers to the first row of the
-// next tile of the two streamed matrices, and the rows the segment has from there on (> 0).  Kept in
-// scalar registers and advanced by one tile per request, so a request costs a handful of scalar adds.
-struct RingFeed {
-  const char* a;
-  const char* b;
-  int rows;
-};
-// per-lane byte offsets of this lane's four chunks in a tile that lies wholly inside the segment
-struct RingLaneOff { unsigned a0, b0, a1, b1; };
-__device__ __forceinline__ RingLaneOff ring_lane_off(const RingLane& rl, unsigned pitch_a, unsigned pitch_b) {
-  return {__umul24((unsigned)rl.trow0, pitch_a) + rl.col0, __umul24((unsigned)rl.trow0, pitch_b) + rl.col0,
-          __umul24((unsigned)rl.trow1, pitch_a) + rl.col1, __umul24((unsigned)rl.trow1, pitch_b) + rl.col1};
-}
-// Request the next 64-row tile pair of the segment into LDS stage `stage` (4 copies per wave with 4 waves, 2
-// with 8; row pitches in bytes) and advance the feed.  Only the last tile of a segment can be ragged; its
-// missing rows repeat the segment's last row.
-template <int NW = 4>
-__device__ __forceinline__ void ring_feed_issue(const RingLane& rl, const RingLaneOff& lo, RingFeed& f, unsigned pitch_a,
-                                                unsigned pitch_b, int wave, bf16_t* stage) {
-  if (f.rows >= KT) {
-    dma16_off(f.a, lo.a0, stage + wave * 512);
-    dma16_off(f.b, lo.b0, stage + KT * SW_LD + wave * 512);
-    if (NW == 4) {
-      dma16_off(f.a, lo.a1, stage + (4 + wave) * 512);
-      dma16_off(f.b, lo.b1, stage + KT * SW_LD + (4 + wave) * 512);
-    }
-  } else {
-    const unsigned r0c = (unsigned)min(rl.trow0, f.rows - 1), r1c = (unsigned)min(rl.trow1, f.rows - 1);
-    dma16_off(f.a, __umul24(r0c, pitch_a) + rl.col0, stage + wave * 512);
-    dma16_off(f.b, __umul24(r0c, pitch_b) + rl.col0, stage + KT * SW_LD + wave * 512);
-    if (NW == 4) {
-      dma16_off(f.a, __umul24(r1c, pitch_a) + rl.col1, stage + (4 + wave) * 512);
-      dma16_off(f.b, __umul24(r1c, pitch_b) + rl.col1, stage + KT * SW_LD + (4 + wave) * 512);
-    }
-  }
-  f.a += (size_t)KT * pitch_a;
-  f.b += (size_t)KT * pitch_b;
-  f.rows -= KT;
-}
-// wait for the oldest stage requested (later: one more stage has been requested after it; 4 copies per wave and stage with
-// 4 waves, 2 with 8), then meet the other waves: the wanted stage is visible to all, and every wave
-// has finished reading the stage consumed before it.
-// `extra`: this wave issues one more copy per stage, ahead of the others.
-template <int NW = 4>
-__device__ __forceinline__ void ring_wait(bool later, bool extra = false) {
-  if (later) {
-    if (NW != 4) asm volatile("s_waitcnt vmcnt(2)" ::: "memory");
-    else if (extra) asm volatile("s_waitcnt vmcnt(5)" ::: "memory");
-    else asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
-  } else {
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  }
-  __builtin_amdgcn_s_barrier();
-}
 
 // ------------------------------------------------------------------------------------------
 // Forward.  Workgroup = 4 waves; each wave owns QB blocks of 32 query rows.
@@ -275,7 +44,7 @@ __device__ __forceinline__ void ring_wait(bool later, bool extra = false) {
 // quarter of the VALU instructions of the row-per-lane kernel at these head sizes.
 // KS = 2: tiles of half the height, see split_rows.
 // PAIR: two problems of the same shape in one launch (two encoders side by side; see Geo::pair_B): grid z = 2 B.
-template <int QB, int DH, int NST, int WGS, int NW, bool PAIR, bool HEADW = false, int KS = 1>
+template <int QB, int DH, int NST, int WGS, int NW, bool PAIR, int KS = 1>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WGS * NW / 4, WGS * NW / 4))) void mfma_fwd_kernel(Geo g, const bf16_t* __restrict__ QKV, long ld,
                                                        const int32_t* __restrict__ valid_len,
                                                        const uint8_t* __restrict__ key_pad, bf16_t* __restrict__ O,
@@ -295,7 +64,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WGS * N
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // scalar: branches on it are wave-uniform
   int tile, h, b;
   xcd_tile_index(g.q_tile_prefix, g.q_nord, g.cu != nullptr, g.even_cus, tile, h, b);
-  // HEADW (sub-head mode): the NW waves of a workgroup are NW heads of one 64-column group over the SAME 32 QB query
+  constexpr bool HEADW = DH != 64;
+  // HEADW (sub-head mode, where the head count is a multiple of 4): the NW waves of a workgroup are NW heads of one 64-column group over the SAME 32 QB query
   // rows (grid.y counts groups of NW heads) -- the K/V stream is shared as before, but a tile is 64 rows instead of
   // 256, which at segment lengths like 50 / 500 / 375 leaves 4 % of the rows of the tiles empty instead of 28 %.
   if (HEADW) h = h * NW + wave;
@@ -315,7 +85,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WGS * N
   const unsigned live = second ? g.q_live2[qs] : g.q_live[qs];   // live key segments of the tile's query segment
   int qoff, qlen;
   SegTable& sg = sSeg[wave];
-  const unsigned stream_set = seg_table(sg, g, b, valid_len ? valid_len + bm * g.n_seg : nullptr, live, lane, qs, qoff, qlen);
+  const unsigned row_set = seg_rows_table(sg, g, b, live, lane, qs, qoff, qlen);
   if (q0 >= qlen) return;  // packed rows: this batch element's segment ends before the tile
   const int d = g.d;
   const long row_b = g.cu ? 0 : (long)b * g.T, qrow0 = row_b + qoff;   // rows of the batch element, of segment qs
@@ -326,6 +96,46 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WGS * N
   const int wo = (h * DH) & 63;           // first column of the head inside the group
   const int s0 = DH == 64 ? 0 : wo >> 4;  // k-step and O^T block that hold the head (sub-head mode)
   const int db0 = DH == 64 ? 0 : wo >> 5;
+
+  const RingLane rl = ring_lane<NW>(wave, lane, cg);
+  const unsigned ldb = (unsigned)ld * 2u;
+  const RingLaneOff rlo = ring_lane_off(rl, ldb, ldb);
+  const bool kp_copy = wave == 0 && key_pad != nullptr;   // this wave fetches a stage's key_pad bytes
+  TileCursor ic = {0u, 0, 0};
+  int islot = 0;
+  RingFeed feed = {nullptr, nullptr, 0};
+  const uint8_t* feed_kp = nullptr;
+  // K and V rows of a segment; rows past the valid length but inside the segment are fetched and masked
+  auto seg_begin = [&](int seg) __attribute__((always_inline)) {
+    const int off = seg_get(sg.off, seg);
+    feed.a = (const char*)(QKV + (row_b + off) * ld + d);
+    feed.b = feed.a + (size_t)d * 2;
+    feed.rows = seg_get(sg.rows, seg);
+    if (key_pad) feed_kp = key_pad + ((g.cu ? 0 : (long)bm * g.T) + off);
+  };
+  auto copy = [&]() __attribute__((always_inline)) {   // requests the feed's next tile
+    // The key_pad bytes travel with the stage: an ordinary load inside the loop would wait for every copy before it.
+    if (kp_copy) dma1_off(feed_kp, (unsigned)min(lane_id(), feed.rows - 1), sKP + islot * KT);
+    feed_kp += KT;
+    ring_feed_issue<NW>(rl, rlo, feed, ldb, ldb, wave, sT + islot * RING_STAGE);
+    islot = (islot + 1 == NST) ? 0 : islot + 1;
+  };
+  auto next_seg = [&]() __attribute__((always_inline)) { if (cursor_next_seg(ic, sg)) seg_begin(ic.seg); };
+  // requests the next stage; returns its number of valid keys (key_pad aside), -1 if there is none
+  auto issue = [&]() __attribute__((always_inline)) {
+    if (ic.left <= 0) return -1;
+    const int keys = ic.left;
+    copy();
+    ic.left -= KT;
+    if (ic.left <= 0) next_seg();
+    return keys;
+  };
+  const int seg1 = row_set ? __builtin_ctz(row_set) : 0;   // its first tile goes ahead of everything
+  if (row_set) {
+    seg_begin(seg1);
+    copy();
+  }
+  const int valid = valid_len ? valid_len[bm * g.n_seg + min(lane, g.n_seg - 1)] : 0;
 
   // Q operand (B of S^T = K Q^T): lane holds query row lo of each block, 8 consecutive dh per k-step
   bf16x8 qreg[QB][NS];
@@ -369,10 +179,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WGS * N
 #pragma unroll
     for (int s = 0; s < NS; ++s) asm volatile("" :: "v"(qreg[qb][s]));
 
-  const RingLane rl = ring_lane<NW>(wave, lane, cg);
-  const unsigned ldb = (unsigned)ld * 2u;
-  const RingLaneOff rlo = ring_lane_off(rl, ldb, ldb);
-  const bool kp_copy = wave == 0 && key_pad != nullptr;   // this wave fetches a stage's key_pad bytes
+  const unsigned key_set = valid_len ? seg_lens_table(sg, valid, row_set, lane) : row_set;
 
   // One pass over the live key tiles, for NQB of the wave's QB query blocks (NQB < QB: a tile of half the height).
   //
@@ -395,37 +202,22 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WGS * N
 #pragma unroll
         for (int r = 0; r < 16; ++r) oacc[db][qb][r] = 0.f;
     }
-    TileCursor ic = {stream_set, 0, 0};
-    int islot = 0, cslot = 0;
-    RingFeed feed = {nullptr, nullptr, 0};
-    const uint8_t* feed_kp = nullptr;
-    // K and V rows of the next segment; rows past the valid length but inside the segment are fetched and masked
-    auto next_seg = [&]() {
-      if (!cursor_next_seg(ic, sg)) return;
-      const int off = seg_get(sg.off, ic.seg);
-      feed.a = (const char*)(QKV + (row_b + off) * ld + d);
-      feed.b = feed.a + (size_t)d * 2;
-      feed.rows = seg_get(sg.rows, ic.seg);
-      if (key_pad) feed_kp = key_pad + ((g.cu ? 0 : (long)bm * g.T) + off);
-    };
-    next_seg();
-    // requests the next stage; returns its number of valid keys (key_pad aside), 0 if there is none
-    auto issue = [&]() {
-      if (ic.left <= 0) return 0;
-      const int keys = ic.left;
-      // The key_pad bytes travel with the stage: an ordinary load inside the loop would wait for every copy before it.
-      if (kp_copy) dma1_off(feed_kp, (unsigned)min(lane_id(), feed.rows - 1), sKP + islot * KT);
-      feed_kp += KT;
-      ring_feed_issue<NW>(rl, rlo, feed, ldb, ldb, wave, sT + islot * RING_STAGE);
-      islot = (islot + 1 == NST) ? 0 : islot + 1;
-      ic.left -= KT;
-      if (ic.left <= 0) next_seg();
-      return keys;
-    };
     // NST - 1 stages are requested ahead: the slot refilled in an iteration is the one consumed in the one before
-    int keys1 = issue(), keys2 = NST > 2 ? issue() : 0;   // of the next stage, of the one after it
-    while (keys1 > 0) {
-      ring_wait<NW>(keys2 > 0, kp_copy);
+    int cslot = 0, keys1, keys2 = -1;   // valid keys of the next stage, of the one after it
+    ic.rest = key_set;
+    if (!GUARD && row_set) {   // the first one is under way
+      ic.rest &= ~(1u << seg1);
+      keys1 = seg_get(sg.len, seg1);
+      ic.left = keys1 - KT;
+      if (ic.left <= 0) next_seg();
+    } else {
+      islot = 0;
+      next_seg();
+      keys1 = issue();
+    }
+    if (NST > 2) keys2 = issue();
+    while (keys1 >= 0) {
+      ring_wait<NW>(keys2 >= 0, kp_copy);
       const int keys = keys1;   // valid keys from the tile's first one on
       keys1 = keys2;
       (NST > 2 ? keys2 : keys1) = issue();
@@ -610,7 +402,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WGS * N
 // The two constant accumulator seeds (negated lse, -delta: 32 registers) put the kernel at 194 registers
 // and two workgroups per CU; with them the softmax is exp2, one multiply and the bf16 pack per score, and
 // that was measured faster than three workgroups per CU with two more vector instructions per score.
-template <int QB, int DH, int NST, int WGS, bool SEED, int KS = 1>
+template <int QB, int NST, int WGS, int KS = 1>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WGS, WGS))) void mfma_dq_kernel(Geo g, const bf16_t* __restrict__ QKV, long ld,
                                                       const bf16_t* __restrict__ O,
                                                       const bf16_t* __restrict__ dO, long ldo,
@@ -627,25 +419,58 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WGS, WGS)))
   int tile, h, b;
   xcd_tile_index(g.q_tile_prefix, g.q_nord, g.cu != nullptr, g.even_cus, tile, h, b);
   constexpr int WG_ROWS = 128 * QB / KS;
-  static_assert(KS == 1 || (DH == 64 && QB == 1), "");
+  static_assert(KS == 1 || QB == 1, "");
   const int rb = wave / KS, kg = wave % KS;   // row block of the tile, key block of a stage (KS = 2)
   int qs, q0, ord;
   tile_segment(g.q_order, g.q_tile_prefix, g.q_nord, tile, qs, q0, ord);
   q0 *= WG_ROWS;
   int qoff, qlen;
   SegTable& sg = sSeg[wave];
-  const unsigned stream_set = seg_table(sg, g, b, valid_len ? valid_len + b * g.n_seg : nullptr, g.q_live[qs], lane, qs, qoff, qlen);
+  const unsigned row_set = seg_rows_table(sg, g, b, g.q_live[qs], lane, qs, qoff, qlen);
   if (q0 >= qlen) return;  // packed rows: this batch element's segment ends before the tile
   const int d = g.d;
   const long row_b = g.cu ? 0 : (long)b * g.T, qrow0 = row_b + qoff;   // rows of the batch element, of segment qs
   const long stat0 = (g.cu ? (long)h * g.R : ((long)b * g.H + h) * g.T) + qoff;
 
-  // sub-head mode (DH = 8 / 16) as in the forward: one k-step for S^T and dP^T, one 32-row block of dQ^T
-  constexpr int NS = DH == 64 ? 4 : 1;
-  constexpr int NDB = DH == 64 ? 2 : 1;
-  const int cg = (h * DH) >> 6, wo = (h * DH) & 63;
-  const int s0 = DH == 64 ? 0 : wo >> 4, db0 = DH == 64 ? 0 : wo >> 5;
-  const bool other_half = DH == 8 && hi != ((wo >> 3) & 1);  // this lane half holds another head's columns
+  constexpr int NS = 4, NDB = 2;   // k-steps of the scores, 32-column blocks of the gradients
+
+  const RingLane rl = ring_lane(wave, lane, h);
+  const unsigned ldb = (unsigned)ld * 2u;
+  const RingLaneOff rlo = ring_lane_off(rl, ldb, ldb);
+  const bool kp_copy = wave == 0 && key_pad != nullptr;   // this wave fetches a stage's key_pad bytes
+  TileCursor ic = {0u, 0, 0};
+  int islot = 0;
+  RingFeed feed = {nullptr, nullptr, 0};
+  const uint8_t* feed_kp = nullptr;
+  // as in the forward
+  auto seg_begin = [&](int seg) __attribute__((always_inline)) {
+    const long row0 = row_b + seg_get(sg.off, seg);
+    feed.a = (const char*)(QKV + row0 * ld + d);
+    feed.b = feed.a + (size_t)d * 2;
+    feed.rows = seg_get(sg.rows, seg);
+    if (key_pad) feed_kp = key_pad + row0;
+  };
+  auto copy = [&]() __attribute__((always_inline)) {
+    if (kp_copy) dma1_off(feed_kp, (unsigned)min(lane_id(), feed.rows - 1), sKP + islot * KT);
+    feed_kp += KT;
+    ring_feed_issue(rl, rlo, feed, ldb, ldb, wave, sT + islot * RING_STAGE);
+    islot = (islot + 1 == NST) ? 0 : islot + 1;
+  };
+  auto next_seg = [&]() __attribute__((always_inline)) { if (cursor_next_seg(ic, sg)) seg_begin(ic.seg); };
+  auto issue = [&]() __attribute__((always_inline)) {
+    if (ic.left <= 0) return -1;
+    const int keys = ic.left;
+    copy();
+    ic.left -= KT;
+    if (ic.left <= 0) next_seg();
+    return keys;
+  };
+  const int seg1 = row_set ? __builtin_ctz(row_set) : 0;   // its first tile goes ahead of everything
+  if (row_set) {
+    seg_begin(seg1);
+    copy();
+  }
+  const int valid = valid_len ? valid_len[b * g.n_seg + min(lane, g.n_seg - 1)] : 0;
 
   bf16x8 qreg[QB][NS], greg[QB][NS];
   int qrow[QB];
@@ -655,16 +480,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WGS, WGS)))
     qrow[qb] = q0 + (rb * QB + qb) * 32 + lo;
     const int rc = min(qrow[qb], qlen - 1);
     const long t = qrow0 + rc;
-    const bf16_t* p = QKV + t * ld + cg * 64 + hi * 8;
-    const bf16_t* pg = dO + t * ldo + cg * 64 + hi * 8;
-    const bf16_t* po = O + t * ldo + cg * 64 + hi * 8;
+    const bf16_t* p = QKV + t * ld + h * 64 + hi * 8;
+    const bf16_t* pg = dO + t * ldo + h * 64 + hi * 8;
+    const bf16_t* po = O + t * ldo + h * 64 + hi * 8;
     float acc = 0.f;
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
-      u32x4 qv = *(const u32x4*)(p + (s0 + s) * 16);
-      u32x4 gv = *(const u32x4*)(pg + (s0 + s) * 16);
-      const u32x4 ov = *(const u32x4*)(po + (s0 + s) * 16);
-      if (other_half) { qv = u32x4{0u, 0u, 0u, 0u}; gv = qv; }
+      u32x4 qv = *(const u32x4*)(p + s * 16);
+      u32x4 gv = *(const u32x4*)(pg + s * 16);
+      const u32x4 ov = *(const u32x4*)(po + s * 16);
       qreg[qb][s] = as_bf16x8(qv);
       greg[qb][s] = as_bf16x8(gv);
 #pragma unroll
@@ -678,7 +502,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WGS, WGS)))
     const long li = stat0 + rc;
     const float lv = lse2[li];
     ls[qb] = lv;  // negated log2-sum-exp; -inf for a row without valid keys: every probability is exactly zero
-    if (hi == 0 && kg == 0 && qrow[qb] < qlen) delta[li] = DH == 64 ? -acc : acc;  // see the dK/dV kernel
+    if (hi == 0 && kg == 0 && qrow[qb] < qlen) delta[li] = -acc;  // see the dK/dV kernel
   }
 
   f32x16 dqacc[NDB][QB], nlb[QB], ndb[QB];
@@ -689,7 +513,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WGS, WGS)))
 #pragma unroll
       for (int r = 0; r < 16; ++r) dqacc[db][qb][r] = 0.f;
 #pragma unroll
-    for (int r = 0; r < 16; ++r) { nlb[qb][r] = SEED ? ls[qb] : 0.f; ndb[qb][r] = SEED ? -dl[qb] : 0.f; }
+    for (int r = 0; r < 16; ++r) { nlb[qb][r] = ls[qb]; ndb[qb][r] = -dl[qb]; }
   }
 
   const int prow = perm32(lo);
@@ -702,38 +526,18 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WGS, WGS)))
     asm volatile("" :: "v"(ls[qb]), "v"(dl[qb]));
   }
 
-  const RingLane rl = ring_lane(wave, lane, cg);
-  const unsigned ldb = (unsigned)ld * 2u;
-  const RingLaneOff rlo = ring_lane_off(rl, ldb, ldb);
-  const bool kp_copy = wave == 0 && key_pad != nullptr;   // this wave fetches a stage's key_pad bytes
-  TileCursor ic = {stream_set, 0, 0};
-  int islot = 0, cslot = 0;
-  RingFeed feed = {nullptr, nullptr, 0};
-  const uint8_t* feed_kp = nullptr;
-  // K and V rows of the next segment; rows past the valid length but inside the segment are fetched and masked
-  auto next_seg = [&]() {
-    if (!cursor_next_seg(ic, sg)) return;
-    const long row0 = row_b + seg_get(sg.off, ic.seg);
-    feed.a = (const char*)(QKV + row0 * ld + d);
-    feed.b = feed.a + (size_t)d * 2;
-    feed.rows = seg_get(sg.rows, ic.seg);
-    if (key_pad) feed_kp = key_pad + row0;
-  };
-  next_seg();
-  auto issue = [&]() {   // as in the forward
-    if (ic.left <= 0) return 0;
-    const int keys = ic.left;
-    if (kp_copy) dma1_off(feed_kp, (unsigned)min(lane_id(), feed.rows - 1), sKP + islot * KT);
-    feed_kp += KT;
-    ring_feed_issue(rl, rlo, feed, ldb, ldb, wave, sT + islot * RING_STAGE);
-    islot = (islot + 1 == NST) ? 0 : islot + 1;
-    ic.left -= KT;
+  const unsigned key_set = valid_len ? seg_lens_table(sg, valid, row_set, lane) : row_set;
+  int cslot = 0, keys1 = -1;
+  ic.rest = key_set;
+  if (row_set) {   // the first stage is under way
+    ic.rest &= ~(1u << seg1);
+    keys1 = seg_get(sg.len, seg1);
+    ic.left = keys1 - KT;
     if (ic.left <= 0) next_seg();
-    return keys;
-  };
-  int keys1 = issue(), keys2 = NST > 2 ? issue() : 0;
-  while (keys1 > 0) {
-    ring_wait(keys2 > 0, kp_copy);
+  }
+  int keys2 = NST > 2 ? issue() : -1;
+  while (keys1 >= 0) {
+    ring_wait(keys2 >= 0, kp_copy);
     const int keys = keys1;
     keys1 = keys2;
     (NST > 2 ? keys2 : keys1) = issue();
@@ -755,8 +559,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WGS, WGS)))
         f32x16 sacc[QB], pacc[QB];
 #pragma unroll
         for (int s = 0; s < NS; ++s) {
-          const bf16x8 ak = lds_frag_sw(sK, kb * 32, prow, 2 * (s0 + s) + hi);
-          const bf16x8 av = lds_frag_sw(sV, kb * 32, prow, 2 * (s0 + s) + hi);
+          const bf16x8 ak = lds_frag_sw(sK, kb * 32, prow, 2 * s + hi);
+          const bf16x8 av = lds_frag_sw(sV, kb * 32, prow, 2 * s + hi);
 #pragma unroll
           for (int qb = 0; qb < QB; ++qb) {
             sacc[qb] = mfma32(ak, qreg[qb][s], s == 0 ? nlb[qb] : sacc[qb]);   // S^T  = K Q^T
@@ -768,8 +572,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WGS, WGS)))
           float ds[16];
 #pragma unroll
           for (int r = 0; r < 16; ++r) {
-            const float p = fast_exp2(SEED ? sacc[qb][r] : sacc[qb][r] + ls[qb]);
-            ds[r] = p * (SEED ? pacc[qb][r] : pacc[qb][r] - dl[qb]);
+            const float p = fast_exp2(sacc[qb][r]);
+            ds[r] = p * pacc[qb][r];
           }
           dsb[qb][0] = pack8(ds);
           dsb[qb][1] = pack8(ds + 8);
@@ -785,7 +589,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WGS, WGS)))
         for (int db = 0; db < NDB; ++db)
 #pragma unroll
           for (int half = 0; half < 2; ++half) {
-            const bf16x8 a = lds_frag_tr_sw(sK, kb * 32 + half * 16, (db0 + db) * 32, lane);
+            const bf16x8 a = lds_frag_tr_sw(sK, kb * 32 + half * 16, db * 32, lane);
 #pragma unroll
             for (int qb = 0; qb < QB; ++qb) dqacc[db][qb] = mfma32(a, dsb[qb][half], dqacc[db][qb]);
           }
@@ -812,13 +616,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WGS, WGS)))
     for (int db = 0; db < NDB / KS; ++db)
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const int dh0 = (KS == 2 ? kg : db0 + db) * 32 + 8 * i + 4 * hi;  // column inside the 64-column group
-        if (DH < 64 && (dh0 < wo || dh0 >= wo + DH)) continue;
+        const int dh0 = (KS == 2 ? kg : db) * 32 + 8 * i + 4 * hi;  // column inside the 64-column group
         float v[4];
 #pragma unroll
         for (int jj = 0; jj < 4; ++jj) v[jj] = dqacc[db][qb][4 * i + jj] * g.scale;
         const u32x2 pk = {pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3])};
-        *(u32x2*)(dQKV + t * ldg + cg * 64 + dh0) = pk;
+        *(u32x2*)(dQKV + t * ldg + h * 64 + dh0) = pk;
       }
   }
 }
@@ -829,12 +632,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WGS, WGS)))
 // has exactly one producer, so the result is deterministic without atomics.
 //
 // Ring stage = Q tile, dO tile (see RING_STAGE) plus the 64 lse and 64 delta values of the rows.
-// At head dim 64 the delta buffer holds -delta (the dQ kernel writes it so): the dP accumulator
+// The delta buffer holds -delta (the dQ kernel writes it so): the dP accumulator
 // starts from it, so the MFMA chain ends as dP - delta and no separate subtraction is needed.
 __device__ const float k_neg_inf = -__builtin_inff();
 
-template <int KB, int DH, int KS = 1>
-__global__ __launch_bounds__(256, DH == 64 ? 3 : 2) void mfma_dkv_kernel(Geo g, const bf16_t* __restrict__ QKV, long ld,
+template <int KB, int KS = 1>
+__global__ __launch_bounds__(256, 3) void mfma_dkv_kernel(Geo g, const bf16_t* __restrict__ QKV, long ld,
                                                        const bf16_t* __restrict__ dO, long ldo,
                                                        const float* __restrict__ lse2, const float* __restrict__ delta,
                                                        const int32_t* __restrict__ valid_len,
@@ -848,30 +651,25 @@ __global__ __launch_bounds__(256, DH == 64 ? 3 : 2) void mfma_dkv_kernel(Geo g, 
   int tile, h, b;
   xcd_tile_index(g.k_tile_prefix, g.k_nord, g.cu != nullptr, g.even_cus, tile, h, b);
   constexpr int WG_ROWS = 128 * KB / KS;
-  static_assert(KS == 1 || (DH == 64 && KB == 1), "");
+  static_assert(KS == 1 || KB == 1, "");
   const int rb = wave / KS, rg = wave % KS;   // key block of the tile, row block of a stage (KS = 2)
   int ks, k0, ord;
   tile_segment(g.k_order, g.k_tile_prefix, g.k_nord, tile, ks, k0, ord);
   k0 *= WG_ROWS;
   int koff, klen_seg;
   SegTable& sg = sSeg[wave];
-  const unsigned stream_set = seg_table(sg, g, b, nullptr, g.k_live[ks], lane, ks, koff, klen_seg);
+  const unsigned row_set = seg_rows_table(sg, g, b, g.k_live[ks], lane, ks, koff, klen_seg);
   if (k0 >= klen_seg) return;  // packed rows: this batch element's segment ends before the tile
   const int d = g.d;
   const long row_b = g.cu ? 0 : (long)b * g.T, krow0 = row_b + koff;   // rows of the batch element, of segment ks
   const long stat_b = g.cu ? (long)h * g.R : ((long)b * g.H + h) * g.T;
 
-  // sub-head mode (DH = 8 / 16): one k-step for S and dP, one 32-row block of dV^T and dK^T
-  constexpr int NS = DH == 64 ? 4 : 1;
-  constexpr int NDB = DH == 64 ? 2 : 1;
-  const int cg = (h * DH) >> 6, wo = (h * DH) & 63;
-  const int s0 = DH == 64 ? 0 : wo >> 4, db0 = DH == 64 ? 0 : wo >> 5;
-  const bool other_half = DH == 8 && hi != ((wo >> 3) & 1);  // this lane half holds another head's columns
+  constexpr int NS = 4, NDB = 2;   // k-steps of the scores, 32-column blocks of the gradients
 
-  const RingLane rl = ring_lane(wave, lane, cg);
+  const RingLane rl = ring_lane(wave, lane, h);
   const unsigned ldb = (unsigned)ld * 2u, ldob = (unsigned)ldo * 2u;  // row pitches in bytes
   const RingLaneOff rlo = ring_lane_off(rl, ldb, ldob);
-  TileCursor ic = {stream_set, 0, 0};
+  TileCursor ic = {row_set, 0, 0};
   int islot = 0, cslot = 0;
   RingFeed feed = {nullptr, nullptr, 0};
   const float* feed_l = nullptr;  // lse and delta of the next tile's first row
@@ -886,8 +684,8 @@ __global__ __launch_bounds__(256, DH == 64 ? 3 : 2) void mfma_dkv_kernel(Geo g, 
     feed_d = delta + stat_b + off;
   };
   next_seg();
-  auto issue = [&]() {   // requests the next stage; returns the rows left of its segment, 0 if there is none
-    if (ic.left <= 0) return 0;
+  auto issue = [&]() {   // requests the next stage; returns the rows left of its segment, -1 if there is none
+    if (ic.left <= 0) return -1;
     const int rows = ic.left;
     // negated lse (wave 0) and delta (wave 1), one float per lane.  Rows past the segment read -inf
     // as negated lse, so their probabilities are exactly zero.
@@ -908,6 +706,7 @@ __global__ __launch_bounds__(256, DH == 64 ? 3 : 2) void mfma_dkv_kernel(Geo g, 
     if (ic.left <= 0) next_seg();
     return rows;
   };
+  int rows1 = issue();   // the first stage, ahead of everything
 
   bf16x8 kreg[KB][NS], vreg[KB][NS];
   int krow[KB];
@@ -917,11 +716,10 @@ __global__ __launch_bounds__(256, DH == 64 ? 3 : 2) void mfma_dkv_kernel(Geo g, 
     krow[kb] = k0 + (rb * KB + kb) * 32 + lo;
     const int rc = min(krow[kb], klen_seg - 1);
     const long t = krow0 + rc;
-    const bf16_t* p = QKV + t * ld + d + cg * 64 + hi * 8;
+    const bf16_t* p = QKV + t * ld + d + h * 64 + hi * 8;
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
-      u32x4 kv = *(const u32x4*)(p + (s0 + s) * 16), vv = *(const u32x4*)(p + d + (s0 + s) * 16);
-      if (other_half) { kv = u32x4{0u, 0u, 0u, 0u}; vv = kv; }
+      u32x4 kv = *(const u32x4*)(p + s * 16), vv = *(const u32x4*)(p + d + s * 16);
       kreg[kb][s] = as_bf16x8(kv);
       vreg[kb][s] = as_bf16x8(vv);
     }
@@ -947,13 +745,13 @@ __global__ __launch_bounds__(256, DH == 64 ? 3 : 2) void mfma_dkv_kernel(Geo g, 
 #pragma unroll
     for (int s = 0; s < NS; ++s) asm volatile("" :: "v"(kreg[kb][s]), "v"(vreg[kb][s]));
 
-  int rows1 = issue(), rows2 = issue();
+  int rows2 = issue();
   const int prow = perm32(lo);
-  while (rows1 > 0) {
+  while (rows1 >= 0) {
     // Copies complete in issue order.  The wanted stage is complete once at most the copies of the
     // stage requested after it (4 tile chunks, plus 1 on the waves that fetch lse / delta) are
     // outstanding.  Behind the barrier the stage is visible to all waves, and everyone is done with the one before.
-    ring_wait(rows2 > 0, wave < 2);
+    ring_wait(rows2 >= 0, wave < 2);
     const int rows = rows1;
     rows1 = rows2;
     rows2 = issue();  // refills the slot of the stage consumed before
@@ -966,10 +764,9 @@ __global__ __launch_bounds__(256, DH == 64 ? 3 : 2) void mfma_dkv_kernel(Geo g, 
     for (int qq = 0; qq < 2 / KS; ++qq) {
       const int qb = KS == 1 ? qq : rg;
       if (qb == 1 && rows <= 32) break;
-      // negated lse / delta of the query rows of the block: register r of an accumulator holds row
-      // (r / 8) * 16 + hi * 8 + r % 8.  At head dim 64 both go straight into the accumulators (the delta buffer
-      // holds -delta): the MFMA chains then end as S - lse and dP - delta, and neither needs a vector
-      // instruction per element.  In sub-head mode they are fetched four rows at a time where they are used.
+      // negated lse / -delta of the query rows of the block: register r of an accumulator holds row
+      // (r / 8) * 16 + hi * 8 + r % 8.  Both go straight into the accumulators: the MFMA chains then end as S - lse and
+      // dP - delta, and neither needs a vector instruction per element.
       auto rows4 = [&](const float* base, int r4) {   // values of registers 4 r4 .. 4 r4 + 3
         return *(const float4*)&base[qb * 32 + (r4 >> 1) * 16 + hi * 8 + (r4 & 1) * 4];
       };
@@ -980,19 +777,17 @@ __global__ __launch_bounds__(256, DH == 64 ? 3 : 2) void mfma_dkv_kernel(Geo g, 
       for (int r4 = 0; r4 < 4; ++r4) {
         const float4 d4 = rows4(sD, r4);
         D[4 * r4] = d4.x; D[4 * r4 + 1] = d4.y; D[4 * r4 + 2] = d4.z; D[4 * r4 + 3] = d4.w;
-        if (DH == 64) {
-          const float4 l4 = rows4(sL, r4);
-          NL[4 * r4] = l4.x; NL[4 * r4 + 1] = l4.y; NL[4 * r4 + 2] = l4.z; NL[4 * r4 + 3] = l4.w;
-        }
+        const float4 l4 = rows4(sL, r4);
+        NL[4 * r4] = l4.x; NL[4 * r4 + 1] = l4.y; NL[4 * r4 + 2] = l4.z; NL[4 * r4 + 3] = l4.w;
       }
 #pragma unroll
       for (int kb = 0; kb < KB; ++kb)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) { sacc[kb][r] = DH == 64 ? NL[r] : 0.f; pacc[kb][r] = DH == 64 ? D[r] : 0.f; }
+        for (int r = 0; r < 16; ++r) { sacc[kb][r] = NL[r]; pacc[kb][r] = D[r]; }
 #pragma unroll
       for (int s = 0; s < NS; ++s) {
-        const bf16x8 aq = lds_frag_sw(sQ, qb * 32, prow, 2 * (s0 + s) + hi);
-        const bf16x8 ag = lds_frag_sw(sG, qb * 32, prow, 2 * (s0 + s) + hi);
+        const bf16x8 aq = lds_frag_sw(sQ, qb * 32, prow, 2 * s + hi);
+        const bf16x8 ag = lds_frag_sw(sG, qb * 32, prow, 2 * s + hi);
 #pragma unroll
         for (int kb = 0; kb < KB; ++kb) {
           sacc[kb] = mfma32(aq, kreg[kb][s], sacc[kb]);   // S  = Q K^T
@@ -1003,18 +798,9 @@ __global__ __launch_bounds__(256, DH == 64 ? 3 : 2) void mfma_dkv_kernel(Geo g, 
       for (int kb = 0; kb < KB; ++kb) {
         float p[16], ds[16];
 #pragma unroll
-        for (int r4 = 0; r4 < 4; ++r4) {
-          float L[4] = {0.f, 0.f, 0.f, 0.f};
-          if (DH != 64) {
-            const float4 l4 = rows4(sL, r4);
-            L[0] = l4.x; L[1] = l4.y; L[2] = l4.z; L[3] = l4.w;
-          }
-#pragma unroll
-          for (int u = 0; u < 4; ++u) {
-            const int r = 4 * r4 + u;
-            p[r] = DH == 64 ? fast_exp2(sacc[kb][r]) : fast_exp2(sacc[kb][r] + L[u]);
-            ds[r] = DH == 64 ? p[r] * pacc[kb][r] : p[r] * (pacc[kb][r] - D[r]);
-          }
+        for (int r = 0; r < 16; ++r) {
+          p[r] = fast_exp2(sacc[kb][r]);
+          ds[r] = p[r] * pacc[kb][r];
         }
         pb[kb][0] = pack8(p); pb[kb][1] = pack8(p + 8);
         dsb[kb][0] = pack8(ds); dsb[kb][1] = pack8(ds + 8);
@@ -1024,8 +810,8 @@ __global__ __launch_bounds__(256, DH == 64 ? 3 : 2) void mfma_dkv_kernel(Geo g, 
       for (int db = 0; db < NDB; ++db)
 #pragma unroll
         for (int half = 0; half < 2; ++half) {
-          const bf16x8 agt = lds_frag_tr_sw(sG, qb * 32 + half * 16, (db0 + db) * 32, lane);
-          const bf16x8 aqt = lds_frag_tr_sw(sQ, qb * 32 + half * 16, (db0 + db) * 32, lane);
+          const bf16x8 agt = lds_frag_tr_sw(sG, qb * 32 + half * 16, db * 32, lane);
+          const bf16x8 aqt = lds_frag_tr_sw(sQ, qb * 32 + half * 16, db * 32, lane);
 #pragma unroll
           for (int kb = 0; kb < KB; ++kb) {
             dvacc[db][kb] = mfma32(agt, pb[kb][half], dvacc[db][kb]);
@@ -1053,7 +839,7 @@ __global__ __launch_bounds__(256, DH == 64 ? 3 : 2) void mfma_dkv_kernel(Geo g, 
     const int krow_e = k0 + rb * 32 + (lane_e & 31);
     if (krow_e >= klen_seg) return;
     const float z = kvalid[0] ? (rg ? 1.f : 0.69314718055994530942f) : 0.f;   // see below
-    bf16_t* p = dQKV + (krow0 + krow_e) * ldg + (rg ? 2 * d : d) + cg * 64;
+    bf16_t* p = dQKV + (krow0 + krow_e) * ldg + (rg ? 2 * d : d) + h * 64;
 #pragma unroll
     for (int db = 0; db < NDB; ++db)
 #pragma unroll
@@ -1073,14 +859,13 @@ __global__ __launch_bounds__(256, DH == 64 ? 3 : 2) void mfma_dkv_kernel(Geo g, 
     for (int db = 0; db < NDB; ++db)
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const int dh0 = (db0 + db) * 32 + 8 * i + 4 * hi_e;  // column inside the 64-column group
-        if (DH < 64 && (dh0 < wo || dh0 >= wo + DH)) continue;
+        const int dh0 = db * 32 + 8 * i + 4 * hi_e;  // column inside the 64-column group
         const u32x2 pk = {pack_bf16(dkacc[db][kb][4 * i] * zk, dkacc[db][kb][4 * i + 1] * zk),
                           pack_bf16(dkacc[db][kb][4 * i + 2] * zk, dkacc[db][kb][4 * i + 3] * zk)};
         const u32x2 pv = {pack_bf16(dvacc[db][kb][4 * i] * zv, dvacc[db][kb][4 * i + 1] * zv),
                           pack_bf16(dvacc[db][kb][4 * i + 2] * zv, dvacc[db][kb][4 * i + 3] * zv)};
-        *(u32x2*)(dQKV + t * ldg + d + cg * 64 + dh0) = pk;
-        *(u32x2*)(dQKV + t * ldg + 2 * d + cg * 64 + dh0) = pv;
+        *(u32x2*)(dQKV + t * ldg + d + h * 64 + dh0) = pk;
+        *(u32x2*)(dQKV + t * ldg + 2 * d + h * 64 + dh0) = pv;
       }
   }
 }
@@ -1095,9 +880,7 @@ __global__ __launch_bounds__(256, DH == 64 ? 3 : 2) void mfma_dkv_kernel(Geo g, 
 //     with 2 and 4, 150 with the row sums on the matrix cores);
 //   dQ, head dim 64: 3 stages, 3 workgroups per CU, accumulators seeded with -lse and -delta (unseeded: 7 % slower;
 //     4 workgroups need spills);
-//   dQ, sub-head mode: 3 workgroups per CU as well (114 registers; 27 against 33 us with two at B = 32, 50 / 500 / 375
-//     rows, 8 heads of 8);
-//   dK/dV: 1 key block per wave, 3 workgroups per CU at head dim 64, 2 in sub-head mode (3 measured the same).
+//   dK/dV: 1 key block per wave, 3 workgroups per CU.  (Sub-head backward: mfma_attn_sub.hip.)
 constexpr int FWD_QB = 1, FWD_QB_SUB = 2, DQ_QB = 1, DKV_KB = 1;
 constexpr int FWD_NST = 2, FWD_WGS = 4, FWD_NW = 4;   // ring stages, workgroups per CU, waves per workgroup (head dim 64)
 constexpr int FWD_SUB_NST = 2, FWD_SUB_WGS = 4;       // the same in sub-head mode (4 waves)
@@ -1125,13 +908,12 @@ static bool split_rows(const Geo& g, const int* prefix, int nord) {
 static void retile(const Geo& g, const int* order, int nord, int rows, int* prefix) {
   for (int k = 0; k < nord; ++k) prefix[k + 1] = prefix[k] + (g.seg_len[order[k]] + rows - 1) / rows;
 }
-// sub-head mode with a multiple of 4 heads: four heads of a 64-column group per workgroup, 64-row tiles
-static bool fwd_headw(int dh, int H) { return dh != 64 && H % 4 == 0; }
-int mfma_fwd_tile_rows(int dh, int H) { return dh == 64 ? 32 * FWD_NW * FWD_QB : fwd_headw(dh, H) ? 32 * FWD_QB_SUB : 128 * FWD_QB_SUB; }
+// sub-head mode: four heads of a 64-column group per workgroup, 64-row tiles
+int mfma_fwd_tile_rows(int dh) { return dh == 64 ? 32 * FWD_NW * FWD_QB : 32 * FWD_QB_SUB; }
 int mfma_dq_tile_rows() { return 128 * DQ_QB; }
 int mfma_dkv_tile_rows() { return 128 * DKV_KB; }
 
-// Sub-head forward with four heads per workgroup, padded rows.  The workgroups of the query segment with the longest
+// Sub-head forward, padded rows.  The workgroups of the query segment with the longest
 // key range finish last; when they are few (at most a quarter of the workgroup slots -- segments 50 / 500 / 375 under
 // the forward inter-modal mask: the one tile of the 50 text rows reads 500 keys, the eight tiles of the vision rows
 // 375) and clearly the longest, their tiles become 32 rows tall: twice the workgroups, one query block per wave,
@@ -1176,7 +958,7 @@ void launch_mfma_fwd(const Geo& g_in, const bf16_t* qkv, long ld, const int32_t*
                      bf16_t* o, long ldo, float* lse2, hipStream_t st) {
   Geo g = g_in;
   g.q_half = 0;
-  if (fwd_headw(g.dh, g.H)) fwd_half_tiles(g);
+  if (g.dh != 64) fwd_half_tiles(g);
   const bool split = split_rows(g, g.q_tile_prefix, g.q_nord);
   if (split) retile(g, g.q_order, g.q_nord, 64 * FWD_QB, g.q_tile_prefix);
   // query segments with no live block: output 0, lse -inf
@@ -1190,13 +972,10 @@ void launch_mfma_fwd(const Geo& g_in, const bf16_t* qkv, long ld, const int32_t*
   g.even_cus = g.dh == 64 ? even_cus(g, g.q_nord, (long)nt * g.H * g.B, FWD_WGS) : 0u;
   ProfScope ps(PF_ATTN_FWD, st);
   const dim3 grid(nt, g.H, g.B), gridw(nt, g.H / 4, g.B);
-  const bool hw = fwd_headw(g.dh, g.H);
-  if (split) hipLaunchKernelGGL((mfma_fwd_kernel<FWD_QB, 64, FWD_NST, FWD_WGS, FWD_NW, false, false, 2>), grid, dim3(64 * FWD_NW), 0, st, g, qkv, ld, valid_len, key_pad, o, ldo, lse2);
+  if (split) hipLaunchKernelGGL((mfma_fwd_kernel<FWD_QB, 64, FWD_NST, FWD_WGS, FWD_NW, false, 2>), grid, dim3(64 * FWD_NW), 0, st, g, qkv, ld, valid_len, key_pad, o, ldo, lse2);
   else if (g.dh == 64) hipLaunchKernelGGL((mfma_fwd_kernel<FWD_QB, 64, FWD_NST, FWD_WGS, FWD_NW, false>), grid, dim3(64 * FWD_NW), 0, st, g, qkv, ld, valid_len, key_pad, o, ldo, lse2);
-  else if (g.dh == 16 && hw) hipLaunchKernelGGL((mfma_fwd_kernel<FWD_QB_SUB, 16, FWD_SUB_NST, FWD_SUB_WGS, 4, false, true>), gridw, dim3(256), 0, st, g, qkv, ld, valid_len, key_pad, o, ldo, lse2);
-  else if (hw) hipLaunchKernelGGL((mfma_fwd_kernel<FWD_QB_SUB, 8, FWD_SUB_NST, FWD_SUB_WGS, 4, false, true>), gridw, dim3(256), 0, st, g, qkv, ld, valid_len, key_pad, o, ldo, lse2);
-  else if (g.dh == 16) hipLaunchKernelGGL((mfma_fwd_kernel<FWD_QB_SUB, 16, FWD_SUB_NST, FWD_SUB_WGS, 4, false>), grid, dim3(256), 0, st, g, qkv, ld, valid_len, key_pad, o, ldo, lse2);
-  else hipLaunchKernelGGL((mfma_fwd_kernel<FWD_QB_SUB, 8, FWD_SUB_NST, FWD_SUB_WGS, 4, false>), grid, dim3(256), 0, st, g, qkv, ld, valid_len, key_pad, o, ldo, lse2);
+  else if (g.dh == 16) hipLaunchKernelGGL((mfma_fwd_kernel<FWD_QB_SUB, 16, FWD_SUB_NST, FWD_SUB_WGS, 4, false>), gridw, dim3(256), 0, st, g, qkv, ld, valid_len, key_pad, o, ldo, lse2);
+  else hipLaunchKernelGGL((mfma_fwd_kernel<FWD_QB_SUB, 8, FWD_SUB_NST, FWD_SUB_WGS, 4, false>), gridw, dim3(256), 0, st, g, qkv, ld, valid_len, key_pad, o, ldo, lse2);
 }
 
 // Forward of two problems of the same shape (masks g0 / g1) in one launch; their rows follow each other in
@@ -1216,18 +995,19 @@ void launch_mfma_fwd_pair(const Geo& g0, const Geo& g1, const bf16_t* qkv, long 
   for (int i = 0; i < IM_MAX_SEG; ++i) { g.q_live2[i] = g1.q_live[i]; g.q_order2[i] = g1.q_order[i]; }
   for (int i = 0; i <= IM_MAX_SEG; ++i) g.q_tile_prefix2[i] = g1.q_tile_prefix[i];
   ProfScope ps(PF_ATTN_FWD, st);
-  const dim3 grid(g.q_tile_prefix[g.q_nord], g.H, 2 * g.B), gridw(g.q_tile_prefix[g.q_nord], g.H / 4, 2 * g.B);
-  const bool hw = fwd_headw(g.dh, g.H);
-  if (g.dh == 16 && hw) hipLaunchKernelGGL((mfma_fwd_kernel<FWD_QB_SUB, 16, FWD_SUB_NST, FWD_SUB_WGS, 4, true, true>), gridw, dim3(256), 0, st, g, qkv, ld, valid_len, key_pad, o, ldo, lse2);
-  else if (hw) hipLaunchKernelGGL((mfma_fwd_kernel<FWD_QB_SUB, 8, FWD_SUB_NST, FWD_SUB_WGS, 4, true, true>), gridw, dim3(256), 0, st, g, qkv, ld, valid_len, key_pad, o, ldo, lse2);
-  else if (g.dh == 16) hipLaunchKernelGGL((mfma_fwd_kernel<FWD_QB_SUB, 16, FWD_SUB_NST, FWD_SUB_WGS, 4, true>), grid, dim3(256), 0, st, g, qkv, ld, valid_len, key_pad, o, ldo, lse2);
-  else hipLaunchKernelGGL((mfma_fwd_kernel<FWD_QB_SUB, 8, FWD_SUB_NST, FWD_SUB_WGS, 4, true>), grid, dim3(256), 0, st, g, qkv, ld, valid_len, key_pad, o, ldo, lse2);
+  const dim3 gridw(g.q_tile_prefix[g.q_nord], g.H / 4, 2 * g.B);
+  if (g.dh == 16) hipLaunchKernelGGL((mfma_fwd_kernel<FWD_QB_SUB, 16, FWD_SUB_NST, FWD_SUB_WGS, 4, true>), gridw, dim3(256), 0, st, g, qkv, ld, valid_len, key_pad, o, ldo, lse2);
+  else hipLaunchKernelGGL((mfma_fwd_kernel<FWD_QB_SUB, 8, FWD_SUB_NST, FWD_SUB_WGS, 4, true>), gridw, dim3(256), 0, st, g, qkv, ld, valid_len, key_pad, o, ldo, lse2);
 }
 
 void launch_mfma_bwd(const Geo& g_in, const bf16_t* qkv, long ld, const bf16_t* o, const bf16_t* d_o, long ldo,
                      const float* lse2, const int32_t* valid_len, const uint8_t* key_pad, float* delta, bf16_t* dqkv,
                      long ldg, hipStream_t st) {
   Geo g = g_in;
+  if (g.dh != 64) {
+    retile(g, g.q_order, g.q_nord, mfma_sub_dq_tile_rows(), g.q_tile_prefix);
+    retile(g, g.k_order, g.k_nord, mfma_sub_dkv_tile_rows(g.dh), g.k_tile_prefix);
+  }
   const bool split_q = split_rows(g, g.q_tile_prefix, g.q_nord), split_k = split_rows(g, g.k_tile_prefix, g.k_nord);
   if (split_q) retile(g, g.q_order, g.q_nord, 64 * DQ_QB, g.q_tile_prefix);
   if (split_k) retile(g, g.k_order, g.k_nord, 64 * DKV_KB, g.k_tile_prefix);
@@ -1239,20 +1019,20 @@ void launch_mfma_bwd(const Geo& g_in, const bf16_t* qkv, long ld, const bf16_t* 
   }
   const int nq = g.q_tile_prefix[g.q_nord], nk = g.k_tile_prefix[g.k_nord];
   if (nq == 0) return;
+  if (g.dh != 64) {
+    launch_mfma_sub_bwd(g, qkv, ld, o, d_o, ldo, lse2, valid_len, key_pad, delta, dqkv, ldg, st);
+    return;
+  }
   { ProfScope ps(PF_ATTN_DQ, st);
     const dim3 grid(nq, g.H, g.B);
-    g.even_cus = g.dh == 64 ? even_cus(g, g.q_nord, (long)nq * g.H * g.B, 3) : 0u;
-    if (split_q) hipLaunchKernelGGL((mfma_dq_kernel<DQ_QB, 64, DQ_NST, DQ_WGS, true, 2>), grid, dim3(256), 0, st, g, qkv, ld, o, d_o, ldo, lse2, valid_len, key_pad, delta, dqkv, ldg);
-    else if (g.dh == 64) hipLaunchKernelGGL((mfma_dq_kernel<DQ_QB, 64, DQ_NST, DQ_WGS, true>), grid, dim3(256), 0, st, g, qkv, ld, o, d_o, ldo, lse2, valid_len, key_pad, delta, dqkv, ldg);
-    else if (g.dh == 16) hipLaunchKernelGGL((mfma_dq_kernel<DQ_QB, 16, 3, 3, true>), grid, dim3(256), 0, st, g, qkv, ld, o, d_o, ldo, lse2, valid_len, key_pad, delta, dqkv, ldg);
-    else hipLaunchKernelGGL((mfma_dq_kernel<DQ_QB, 8, 3, 3, true>), grid, dim3(256), 0, st, g, qkv, ld, o, d_o, ldo, lse2, valid_len, key_pad, delta, dqkv, ldg); }
+    g.even_cus = even_cus(g, g.q_nord, (long)nq * g.H * g.B, DQ_WGS);
+    if (split_q) hipLaunchKernelGGL((mfma_dq_kernel<DQ_QB, DQ_NST, DQ_WGS, 2>), grid, dim3(256), 0, st, g, qkv, ld, o, d_o, ldo, lse2, valid_len, key_pad, delta, dqkv, ldg);
+    else hipLaunchKernelGGL((mfma_dq_kernel<DQ_QB, DQ_NST, DQ_WGS>), grid, dim3(256), 0, st, g, qkv, ld, o, d_o, ldo, lse2, valid_len, key_pad, delta, dqkv, ldg); }
   { ProfScope ps(PF_ATTN_DKV, st);
     const dim3 grid(nk, g.H, g.B);
-    g.even_cus = g.dh == 64 ? even_cus(g, g.k_nord, (long)nk * g.H * g.B, 3) : 0u;
-    if (split_k) hipLaunchKernelGGL((mfma_dkv_kernel<DKV_KB, 64, 2>), grid, dim3(256), 0, st, g, qkv, ld, d_o, ldo, lse2, delta, valid_len, key_pad, dqkv, ldg);
-    else if (g.dh == 64) hipLaunchKernelGGL((mfma_dkv_kernel<DKV_KB, 64>), grid, dim3(256), 0, st, g, qkv, ld, d_o, ldo, lse2, delta, valid_len, key_pad, dqkv, ldg);
-    else if (g.dh == 16) hipLaunchKernelGGL((mfma_dkv_kernel<DKV_KB, 16>), grid, dim3(256), 0, st, g, qkv, ld, d_o, ldo, lse2, delta, valid_len, key_pad, dqkv, ldg);
-    else hipLaunchKernelGGL((mfma_dkv_kernel<DKV_KB, 8>), grid, dim3(256), 0, st, g, qkv, ld, d_o, ldo, lse2, delta, valid_len, key_pad, dqkv, ldg); }
+    g.even_cus = even_cus(g, g.k_nord, (long)nk * g.H * g.B, 3);
+    if (split_k) hipLaunchKernelGGL((mfma_dkv_kernel<DKV_KB, 2>), grid, dim3(256), 0, st, g, qkv, ld, d_o, ldo, lse2, delta, valid_len, key_pad, dqkv, ldg);
+    else hipLaunchKernelGGL((mfma_dkv_kernel<DKV_KB>), grid, dim3(256), 0, st, g, qkv, ld, d_o, ldo, lse2, delta, valid_len, key_pad, dqkv, ldg); }
 }
 
 }  // namespace imattn

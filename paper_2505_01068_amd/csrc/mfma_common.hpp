@@ -190,6 +190,12 @@ __device__ __forceinline__ bf16x8 lds_frag_tr_sw(const bf16_t* lds, int k_base, 
   return x.v;
 }
 
+// 16 bytes from an LDS byte address
+__device__ __forceinline__ bf16x8 lds_b128(unsigned at) {
+  typedef u32x4 __attribute__((address_space(3))) * lds_u4_ptr;
+  return as_bf16x8(*(lds_u4_ptr)at);
+}
+
 // transposed fragment from the LDS byte addresses of its two reads, `off` bytes further on (a constant)
 __device__ __forceinline__ bf16x8 lds_frag_tr_at(unsigned a0, unsigned a1, int off) {
   typedef v4i16 __attribute__((address_space(3))) * lds_v4_ptr;

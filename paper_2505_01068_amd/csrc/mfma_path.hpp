@@ -93,7 +93,7 @@ int mfma_gemm_split(int M, int N, int K);
 void launch_splitk_reduce(const float* partial, int split_k, int M, int N, float* o0, float* o1, float* o2, int n_per,
                           hipStream_t st);
 
-int mfma_fwd_tile_rows(int dh, int n_heads);
+int mfma_fwd_tile_rows(int dh);
 int mfma_dq_tile_rows();
 int mfma_dkv_tile_rows();
 void launch_mfma_fwd(const Geo& g, const bf16_t* qkv, long ld, const int32_t* valid_len, const uint8_t* key_pad,
@@ -101,6 +101,10 @@ void launch_mfma_fwd(const Geo& g, const bf16_t* qkv, long ld, const int32_t* va
 bool mfma_fwd_pair_ok(const Geo& g0, const Geo& g1);
 void launch_mfma_fwd_pair(const Geo& g0, const Geo& g1, const bf16_t* qkv, long ld, const int32_t* valid_len,
                           const uint8_t* key_pad, bf16_t* o, long ldo, float* lse2, hipStream_t st);
+int mfma_sub_dq_tile_rows();
+int mfma_sub_dkv_tile_rows(int dh);
+void launch_mfma_sub_bwd(const Geo& g, const bf16_t* qkv, long ld, const bf16_t* o, const bf16_t* d_o, long ldo, const float* lse2,
+                         const int32_t* valid_len, const uint8_t* key_pad, float* delta, bf16_t* dqkv, long ldg, hipStream_t st);
 void launch_mfma_bwd(const Geo& g, const bf16_t* qkv, long ld, const bf16_t* o, const bf16_t* d_o, long ldo,
                      const float* lse2, const int32_t* valid_len, const uint8_t* key_pad, float* delta, bf16_t* dqkv,
                      long ldg, hipStream_t st);

@@ -1,5 +1,6 @@
 """bf16 matrix-core attention at head dimension 64 on both sides of the line between 128-row tiles and 64-row tiles whose stages
-are split between two waves, and where the workgroups are dealt out evenly: against the fp64 oracle, forward and backward."""
+are split between two waves, and where the workgroups are dealt out evenly, and tile edges at all head dimensions: against the
+fp64 oracle, forward and backward."""
 import pytest
 
 import oracle
@@ -20,11 +21,12 @@ def test_split_line(batch, name, padding):
     Problem(g, oracle.NAMED_PATTERNS[name]).check(what=f"{name}/{padding}/{batch}")
 
 
-# one sample, one head: lengths around the 64-row tile, the 32-row blocks of a stage and a stage's second half
+# one sample, 64 columns: lengths around the 64-row tile, the 32-row blocks of a stage and a stage's second half
 @pytest.mark.parametrize("seg", [(63, 64, 65), (1, 32, 33), (96, 97, 31), (129, 160, 2)])
 @pytest.mark.parametrize("padding", ["none", "valid_len", "key_pad"])
-def test_split_edges(seg, padding):
-    print(f"[case] split edges seg={seg} {padding}", flush=True)
-    g = synth.attention_inputs(1, seg, 64, 1, "bf16", padding, seed=sum(seg))
+@pytest.mark.parametrize("H", [1, 4, 8])   # of 64, 16 and 8 columns: 4 and 8 run the sub-head kernels (32- and 64-row tiles)
+def test_tile_edges(seg, padding, H):
+    print(f"[case] tile edges seg={seg} H={H} {padding}", flush=True)
+    g = synth.attention_inputs(1, seg, 64, H, "bf16", padding, seed=sum(seg))
     for name in ("ifm_backward", "self_only"):
         Problem(g, oracle.NAMED_PATTERNS[name]).check(what=f"{name}/{seg}/{padding}")
