@@ -208,6 +208,22 @@ __device__ __forceinline__ bf16x8 lds_frag_tr_at(unsigned a0, unsigned a1, int o
   return x.v;
 }
 
+// the same with the 32 columns in the order perm32 (see lds_frag_tr_perm)
+__device__ __forceinline__ bf16x8 lds_frag_tr_sw_perm(const bf16_t* lds, int k_base, int m_base, int lane) {
+  const int j = lane & 15, g = lane >> 4;
+  const int lrow = 8 * (g >> 1) + (j >> 2), lchunk = 2 * (g & 1) + (j & 1), within = 4 * ((j >> 1) & 1);
+  const int f = sw_f(lrow), mb = m_base >> 3;
+  typedef v4i16 __attribute__((address_space(3))) * lds_v4_ptr;
+  const bf16_t* p0 = lds + (k_base + lrow) * SW_LD + (((mb | lchunk) ^ f) << 3) + within;
+  const bf16_t* p1 = lds + (k_base + lrow + 4) * SW_LD + (((mb | lchunk) ^ f ^ 1) << 3) + within;
+  const v4i16 a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4_ptr)(p0));
+  const v4i16 b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4_ptr)(p1));
+  union { v4i16 h[2]; bf16x8 v; } x;
+  x.h[0] = a;
+  x.h[1] = b;
+  return x.v;
+}
+
 __device__ __forceinline__ bf16x8 lds_frag(const bf16_t* lds, int row, int col) {
   return as_bf16x8(*(const u32x4*)(lds + row * LDS_LD + col));
 }

@@ -664,21 +664,24 @@ struct QkvRows {
   bf16_t* qkv[2];
   int R, groups; float ln_eps, qscale;   // groups = ceil(R / 128)
 };
-template <int D> constexpr int qkv_rows_lds_bytes() { return 3 * D * (D + 32) * 2 + 5 * D * 4; }
-template <int D>
+template <int D, int PARTS> constexpr int qkv_rows_lds_bytes() { return PARTS * D * (D + 32) * 2 + (2 + PARTS) * D * 4; }
+// PARTS = 3: a workgroup has all three projections of its rows.  PARTS = 1, for few rows: one of them, three workgroups per 128
+// rows, each fetching a third of the weights -- with a handful of workgroups that fetch is the kernel's time.
+template <int D, int PARTS>
 __global__ __launch_bounds__(256) void qkv_rows_kernel(QkvRows p) {
   constexpr int KS = D / 16, NBK = D / 32, LD = D + 32;   // row stride = 64 bytes mod 256: conflict-free transpose reads
   constexpr int WCH = D * D / 8 / 256;                    // 16-byte requests per thread and weight
   extern __shared__ __attribute__((aligned(16))) unsigned char qkv_smem[];
-  bf16_t* const sW = (bf16_t*)qkv_smem;                   // [3][D][LD]
-  float* const sG = (float*)(qkv_smem + 3 * D * LD * 2);  // gamma, beta, then the three biases
+  bf16_t* const sW = (bf16_t*)qkv_smem;                   // [PARTS][D][LD]
+  float* const sG = (float*)(qkv_smem + PARTS * D * LD * 2);  // gamma, beta, then the three biases
   float* const sBt = sG + D;
   float* const sBias = sG + 2 * D;
-  int rg, z;
+  int rg, z, part0 = 0;
   {
     int lin, u0, u1;
     xcd_block_index(lin, u0, u1);
     rg = lin % p.groups; z = lin / p.groups;
+    if (PARTS == 1) { part0 = z % 3; z /= 3; }
   }
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, lo = lane & 31, hi = lane >> 5;
   const bf16_t* const x = z ? p.x[1] : p.x[0];
@@ -692,10 +695,10 @@ __global__ __launch_bounds__(256) void qkv_rows_kernel(QkvRows p) {
 #pragma unroll
   for (int s = 0; s < KS; ++s) xr[s] = *(const u32x4*)(x + mc * D + s * 16 + hi * 8);
   {   // the weights as stored: every request of the three is in flight before the first is written to LDS
-    u32x4 wr[3][WCH];
+    u32x4 wr[PARTS][WCH];
 #pragma unroll
-    for (int part = 0; part < 3; ++part) {
-      const bf16_t* const w = z ? p.w[1][part] : p.w[0][part];
+    for (int part = 0; part < PARTS; ++part) {
+      const bf16_t* const w = z ? p.w[1][part0 + part] : p.w[0][part0 + part];
 #pragma unroll
       for (int i = 0; i < WCH; ++i) {
         const int idx = tid + i * 256, k = idx / (D / 8), c = (idx % (D / 8)) * 8;
@@ -703,7 +706,7 @@ __global__ __launch_bounds__(256) void qkv_rows_kernel(QkvRows p) {
       }
     }
 #pragma unroll
-    for (int part = 0; part < 3; ++part)
+    for (int part = 0; part < PARTS; ++part)
 #pragma unroll
       for (int i = 0; i < WCH; ++i) {
         const int idx = tid + i * 256, k = idx / (D / 8), c = (idx % (D / 8)) * 8;
@@ -714,20 +717,19 @@ __global__ __launch_bounds__(256) void qkv_rows_kernel(QkvRows p) {
     // the five per-column vectors: every load issued (a NULL vector reads the first weight instead, which has more
     // than D elements, and counts as zero) before the first value goes to LDS
     const bf16_t* const safe = z ? p.w[1][0] : p.w[0][0];
-    const bf16_t* src[5];
+    const bf16_t* src[2 + PARTS];
     src[0] = ln_g; src[1] = ln_b;
 #pragma unroll
-    for (int part = 0; part < 3; ++part) src[2 + part] = z ? p.bias[1][part] : p.bias[0][part];
-    float v[5];
+    for (int part = 0; part < PARTS; ++part) src[2 + part] = z ? p.bias[1][part0 + part] : p.bias[0][part0 + part];
+    float v[2 + PARTS];
 #pragma unroll
-    for (int u = 0; u < 5; ++u) v[u] = __uint_as_float((unsigned)(src[u] ? src[u] : safe)[tid] << 16);
+    for (int u = 0; u < 2 + PARTS; ++u) v[u] = __uint_as_float((unsigned)(src[u] ? src[u] : safe)[tid] << 16);
 #pragma unroll
-    for (int u = 0; u < 5; ++u) v[u] = src[u] ? v[u] : 0.f;
+    for (int u = 0; u < 2 + PARTS; ++u) v[u] = src[u] ? v[u] : 0.f;
     sG[tid] = v[0];
     sBt[tid] = v[1];
-    sBias[tid] = v[2] * p.qscale;
-    sBias[D + tid] = v[3];
-    sBias[2 * D + tid] = v[4];
+#pragma unroll
+    for (int part = 0; part < PARTS; ++part) sBias[part * D + tid] = v[2 + part] * (part0 + part == 0 ? p.qscale : 1.f);
   }
   __syncthreads();
 
@@ -769,7 +771,7 @@ __global__ __launch_bounds__(256) void qkv_rows_kernel(QkvRows p) {
 
   bf16_t* const orow = out + (long)m * (3 * D) + 8 * hi;
 #pragma unroll
-  for (int part = 0; part < 3; ++part) {
+  for (int part = 0; part < PARTS; ++part) {
     // register 4i + j of block nb is column 32 nb + 8i + 4hi + j
     f32x16 acc[NBK];
 #pragma unroll
@@ -784,7 +786,7 @@ __global__ __launch_bounds__(256) void qkv_rows_kernel(QkvRows p) {
 
     // Two neighbouring register quads hold columns 8i + 4hi + 0..3 and 8(i+1) + 4hi + 0..3; swapping the upper
     // half-wave of the first with the lower half-wave of the second leaves every lane 8 consecutive columns.
-    const float cs = part == 0 ? p.qscale : 1.f;
+    const float cs = part0 + part == 0 ? p.qscale : 1.f;
     u32x4 o[NBK][2];
 #pragma unroll
     for (int nb = 0; nb < NBK; ++nb)
@@ -804,7 +806,7 @@ __global__ __launch_bounds__(256) void qkv_rows_kernel(QkvRows p) {
 #pragma unroll
       for (int nb = 0; nb < NBK; ++nb)
 #pragma unroll
-        for (int ip = 0; ip < 2; ++ip) *(u32x4*)(orow + part * D + nb * 32 + 16 * ip) = o[nb][ip];
+        for (int ip = 0; ip < 2; ++ip) *(u32x4*)(orow + (part0 + part) * D + nb * 32 + 16 * ip) = o[nb][ip];
     }
   }
 }
@@ -1581,6 +1583,218 @@ template <int D, bool PROJ>
 __global__ __launch_bounds__(256, D == 64 ? 3 : 2) void mlp_tail_pair_kernel(MlpTailArgs p0, MlpTailArgs p1) {
   mlp_tail_tile<D, PROJ>(blockIdx.y == 0 ? p0 : p1);
 }
+// The same (PROJ form) at D = 128 for few rows, where a workgroup has a CU to itself and a tail is one chain of round trips and
+// barriers: eight waves, 2 row blocks x 4 hidden blocks of 32, so that a chunk is 128 hidden columns and the chain has half as many
+// links.  Weights come by asynchronous copy into 64 x 64 tiles of the swizzled layout, two stages of chunks, one barrier per
+// chunk; the LayerNorm runs on the operand fragments (a row lies in two lanes); the four waves of a row block add their outputs
+// through LDS at the end.  740 rows, d_ff = 512: 17.4 -> 14.8 us, most of which is the weights' way to one CU; up to one
+// workgroup per CU a model gains 3 % (20 x 740 rows: 312.6 -> 302.9 us).  At D = 64, with a quarter of the weights, it is slower (740 rows, two
+// encoders: 8.4 -> 9.1 us), and so are the asynchronous copies in four waves where two workgroups share a CU (11.1 -> 12.4 us).
+template <int D>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void mlp_tail_few_kernel(MlpTailArgs p) {
+  constexpr int NT = D / 64, CB = D / 32, TILE = 64 * SW_LD, STAGE = 4 * NT * TILE;   // 64- and 32-column blocks of a row
+  __shared__ __attribute__((aligned(1024))) bf16_t smem[2 * STAGE + NT * TILE];
+  bf16_t* const sH = smem + 2 * STAGE;             // O rows, then the h rows
+  const int tid = threadIdx.x, lane = tid & 63, lo = lane & 31, hi = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wm = wave >> 2, wh = wave & 3;
+  const int m0 = blockIdx.x * 64, row = wm * 32 + lo;   // first row of the tile; the lane's row inside it
+  const bool writes = wh < CB;                          // the wave projects and writes column block wh of its rows
+  // a copy fills tile rows wave * 8 + lane / 8, each lane the 16 bytes that belong at its position
+  const int trow = wave * 8 + (lane >> 3);
+  const unsigned tcol = (unsigned)(((lane & 7) ^ sw_f(trow)) << 3) * 2u;
+  const unsigned off_d = (unsigned)trow * (D * 2) + tcol, off_f = (unsigned)trow * ((unsigned)p.d_ff * 2u) + tcol;
+  {
+    const unsigned off_o = (unsigned)min(trow, p.R - 1 - m0) * (D * 2) + tcol;   // rows past the end: the last one again
+#pragma unroll
+    for (int t = 0; t < NT; ++t) dma16_off(p.o + (long)m0 * D + t * 64, off_o, sH + t * TILE + wave * 512);
+#pragma unroll
+    for (int kc = 0; kc < NT; ++kc)
+#pragma unroll
+      for (int t = 0; t < NT; ++t) dma16_off(p.wo + (long)kc * 64 * D + t * 64, off_d, smem + (kc * NT + t) * TILE + wave * 512);
+  }
+  // chunk c into stage (c + 1) & 1, by halves of 64 hidden columns (d_ff may end in one): W1[:, ..] by 64 rows, W2[.., :] by 64 columns
+  auto copy_chunk = [&](int c) __attribute__((always_inline)) {
+    bf16_t* const st = smem + ((c + 1) & 1) * STAGE + wave * 512;
+#pragma unroll
+    for (int half = 0; half < 2; ++half) {
+      const int j = 2 * c + half;
+      if (j * 64 >= p.d_ff) break;
+#pragma unroll
+      for (int t = 0; t < NT; ++t) {
+        dma16_off(p.w1 + (long)t * 64 * p.d_ff + j * 64, off_f, st + (half * NT + t) * TILE);
+        dma16_off(p.w2 + (long)j * 64 * D + t * 64, off_d, st + ((2 + half) * NT + t) * TILE);
+      }
+    }
+  };
+  // the 16 bias values that the lane's z accumulator starts from: register 8 u + e is hidden column 16 u + 8 hi + e of the wave's 32
+  u32x4 bi[2];
+  const bool b1_vec = (reinterpret_cast<uintptr_t>(p.b1) & 15) == 0;
+  auto load_b1 = [&](int c) __attribute__((always_inline)) {
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const bf16_t* q = p.b1 + min(c * 128 + wh * 32, p.d_ff - 32) + 16 * u + 8 * hi;
+      if (!p.b1) bi[u] = u32x4{0u, 0u, 0u, 0u};
+      else if (b1_vec) bi[u] = *(const u32x4*)q;
+      else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) bi[u][e] = (unsigned)q[2 * e] | ((unsigned)q[2 * e + 1] << 16);
+      }
+    }
+  };
+  // what else the prologue reads, in the same round trip: residual, biases, LayerNorm vectors
+  const int cb = writes ? wh * 32 : 0;
+  int offb[4];   // columns of the lane's output quads
+#pragma unroll
+  for (int i = 0; i < 4; ++i) offb[i] = cb + 8 * i + 4 * hi;
+  u32x2 hres[4];   // x, then h, at those columns of the lane's row
+  const long mr = min(m0 + row, p.R - 1);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) hres[i] = *(const u32x2*)(p.h + mr * D + offb[i]);
+  u32x4 lg[D / 16], lb[D / 16];
+#pragma unroll
+  for (int s = 0; s < D / 16; ++s) {
+    lg[s] = *(const u32x4*)(p.ln_g + s * 16 + hi * 8);
+    lb[s] = *(const u32x4*)(p.ln_b + s * 16 + hi * 8);
+  }
+  float bo[4][4], b2[4][4];
+  bias_quads<4>(p.bo, offb, bo);
+  bias_quads<4>(p.b2, offb, b2);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) asm volatile("" :: "v"(hres[i]), "v"(bo[i][0]), "v"(b2[i][0]));   // their wait here, not behind the next copies
+#pragma unroll
+  for (int s = 0; s < D / 16; ++s) asm volatile("" :: "v"(lg[s]), "v"(lb[s]));
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  copy_chunk(0);
+  load_b1(0);
+  f32x16 acc;
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) acc[4 * i + j] = bo[i][j];
+  if (writes)
+#pragma unroll
+    for (int s = 0; s < D / 16; ++s)
+      acc = mfma32(lds_frag_tr_sw(smem + ((s >> 2) * NT + (cb >> 6)) * TILE, (s & 3) * 16, cb & 63, lane),
+                   lds_frag_sw(sH + (s >> 2) * TILE, wm * 32, lo, 2 * (s & 3) + hi), acc);
+  auto lds_barrier = [&]() __attribute__((always_inline)) {   // LDS accesses of the workgroup, not the copies in flight
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+  };
+  lds_barrier();   // O and Wo have been read
+  if (writes)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const u32x2 rv = hres[i];
+      hres[i] = u32x2{pack_bf16(acc[4 * i] + __uint_as_float(rv[0] << 16), acc[4 * i + 1] + __uint_as_float(rv[0] & 0xffff0000u)),
+                      pack_bf16(acc[4 * i + 2] + __uint_as_float(rv[1] << 16), acc[4 * i + 3] + __uint_as_float(rv[1] & 0xffff0000u))};
+      const int n = offb[i];
+      *(u32x2*)(sH + (n >> 6) * TILE + row * SW_LD + ((((n & 63) >> 3) ^ sw_f(row)) << 3) + (n & 7)) = hres[i];
+    }
+  lds_barrier();
+  bf16x8 fa[D / 16];
+  {   // LayerNorm, two passes in fp32
+    u32x4 x[D / 16];
+    float sum = 0.f;
+#pragma unroll
+    for (int s = 0; s < D / 16; ++s) {
+      const bf16x8 v = lds_frag_sw(sH + (s >> 2) * TILE, wm * 32, lo, 2 * (s & 3) + hi);
+      x[s] = __builtin_bit_cast(u32x4, v);
+      sum = sum_bf16x8(v, sum);
+    }
+    sum += __shfl_xor(sum, 32, 64);
+    const float mu = sum * (1.f / D);
+    float q = 0.f;
+#pragma unroll
+    for (int s = 0; s < D / 16; ++s)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const float a = __uint_as_float(x[s][j] << 16) - mu, b = __uint_as_float(x[s][j] & 0xffff0000u) - mu;
+        q = fmaf(a, a, q);
+        q = fmaf(b, b, q);
+      }
+    q += __shfl_xor(q, 32, 64);
+    const float rstd = rsqrtf(q * (1.f / D) + p.ln_eps);
+#pragma unroll
+    for (int s = 0; s < D / 16; ++s) {
+      float y[8];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        y[2 * j] = (__uint_as_float(x[s][j] << 16) - mu) * rstd * __uint_as_float(lg[s][j] << 16) + __uint_as_float(lb[s][j] << 16);
+        y[2 * j + 1] = (__uint_as_float(x[s][j] & 0xffff0000u) - mu) * rstd * __uint_as_float(lg[s][j] & 0xffff0000u) + __uint_as_float(lb[s][j] & 0xffff0000u);
+      }
+      fa[s] = pack8(y);
+    }
+  }
+  f32x16 acc2[CB];   // the lane's row, all D columns, contracted over the wave's hidden columns
+#pragma unroll
+  for (int nb = 0; nb < CB; ++nb)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc2[nb][r] = 0.f;
+  const int nchunk = (p.d_ff + 127) / 128;
+  for (int c = 0; c < nchunk; ++c) {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // chunk c; everyone is done with chunk c - 1 behind the barrier
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" : "+v"(bi[0]), "+v"(bi[1]));       // the compiler's own wait for b1, before the next chunk is requested
+    f32x16 acc1;
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        acc1[8 * u + 2 * e] = __uint_as_float(bi[u][e] << 16);
+        acc1[8 * u + 2 * e + 1] = __uint_as_float(bi[u][e] & 0xffff0000u);
+      }
+    if (c + 1 < nchunk) {
+      copy_chunk(c + 1);
+      load_b1(c + 1);
+    }
+    if (c * 128 + wh * 32 >= p.d_ff) continue;
+    const bf16_t* const st = smem + ((c + 1) & 1) * STAGE + (wh >> 1) * NT * TILE;
+#pragma unroll
+    for (int s = 0; s < D / 16; ++s)
+      acc1 = mfma32(lds_frag_tr_sw_perm(st + (s >> 2) * TILE, (s & 3) * 16, (wh & 1) * 32, lane), fa[s], acc1);
+    bf16x8 zb[2];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      float zv[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) zv[e] = gelu_erf_f(acc1[8 * u + e]);
+      zb[u] = pack8(zv);
+    }
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+      for (int nb = 0; nb < CB; ++nb)
+        acc2[nb] = mfma32(lds_frag_tr_sw(st + (2 * NT + (nb >> 1)) * TILE, (wh & 1) * 32 + u * 16, (nb & 1) * 32, lane), zb[u], acc2[nb]);
+  }
+  static_assert(2 * STAGE * 2 >= 8 * CB * 4096, "the exchange buffer must fit in the stages");
+  float4* const xch = (float4*)smem;   // [row block][column block][wave of the row block][quad][lane]
+  lds_barrier();   // the last chunk has been read
+#pragma unroll
+  for (int nb = 0; nb < CB; ++nb)
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      xch[(((wm * CB + nb) * 4 + wh) * 4 + i) * 64 + lane] = make_float4(acc2[nb][4 * i], acc2[nb][4 * i + 1], acc2[nb][4 * i + 2], acc2[nb][4 * i + 3]);
+  lds_barrier();
+  const int m = m0 + row;
+  if (!writes || m >= p.R) return;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    float o[4] = {b2[i][0], b2[i][1], b2[i][2], b2[i][3]};
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+      const float4 v = xch[(((wm * CB + wh) * 4 + w) * 4 + i) * 64 + lane];
+      o[0] += v.x; o[1] += v.y; o[2] += v.z; o[3] += v.w;
+    }
+    const u32x2 rv = hres[i];   // residual: the rows before the LayerNorm
+    *(u32x2*)(p.y + (long)m * p.ldy + offb[i]) =
+        u32x2{pack_bf16(o[0] + __uint_as_float(rv[0] << 16), o[1] + __uint_as_float(rv[0] & 0xffff0000u)),
+              pack_bf16(o[2] + __uint_as_float(rv[1] << 16), o[3] + __uint_as_float(rv[1] & 0xffff0000u))};
+  }
+}
+static int cu_count();
+// at most one 64-row workgroup per CU (see mlp_tail_few_kernel); more run two of the four-wave workgroups per CU
+static bool mlp_tail_few(int R) { return (R + 63) / 64 <= cu_count(); }
 bool mlp_tail_ok(int is_bf16, long d, long d_ff, const void* h, const void* ln_g, const void* ln_b, const void* w1,
                  const void* w2, const void* y) {
   const uintptr_t a = (uintptr_t)h | (uintptr_t)ln_g | (uintptr_t)ln_b | (uintptr_t)w1 | (uintptr_t)w2 | (uintptr_t)y;
@@ -1593,6 +1807,10 @@ void launch_mlp_tail(const void* h, const void* ln_g, const void* ln_b, float ln
                    (const bf16_t*)w2, (const bf16_t*)b2, (bf16_t*)y, R, d_ff, (const bf16_t*)o, (const bf16_t*)wo,
                    (const bf16_t*)bo, (long)d};
   const dim3 grid((R + 63) / 64), block(256);
+  if (o && d == 128 && mlp_tail_few(R)) {
+    hipLaunchKernelGGL((mlp_tail_few_kernel<128>), grid, dim3(512), 0, st, p);
+    return;
+  }
   if (d == 64) {
     if (o) hipLaunchKernelGGL((mlp_tail_kernel<64, true>), grid, block, 0, st, p);
     else hipLaunchKernelGGL((mlp_tail_kernel<64, false>), grid, block, 0, st, p);
@@ -1879,15 +2097,22 @@ static void launch_qkv_rows(const MGemm& a, const MGemm* b, hipStream_t st) {
   }
   q.R = a.M; q.ln_eps = a.ln_eps; q.qscale = a.scale0_on ? a.scale0 : 1.f;
   q.groups = (a.M + 127) / 128;
-  const dim3 grid((unsigned)q.groups * (b ? 2 : 1));
+  const int wgs = q.groups * (b ? 2 : 1);
+  // one projection per workgroup up to a quarter of the CUs.  us of a launch, three / one: 6 workgroups at d = 128 10.3 / 7.2, 12 at
+  // d = 64 5.2 / 4.4; an encoder of four layers with 58 workgroups per launch 94.1 / 94.4, with 116 101.5 / 109.5; a model with 140 and
+  // 70 266.5 / 266.7
+  const bool few = 4 * wgs <= cu_count();
+  const dim3 grid((unsigned)wgs * (few ? 3 : 1));
   static bool configured = false;
   if (!configured) {
-    (void)hipFuncSetAttribute((const void*)qkv_rows_kernel<64>, hipFuncAttributeMaxDynamicSharedMemorySize, qkv_rows_lds_bytes<64>());
-    (void)hipFuncSetAttribute((const void*)qkv_rows_kernel<128>, hipFuncAttributeMaxDynamicSharedMemorySize, qkv_rows_lds_bytes<128>());
+    (void)hipFuncSetAttribute((const void*)qkv_rows_kernel<64, 3>, hipFuncAttributeMaxDynamicSharedMemorySize, qkv_rows_lds_bytes<64, 3>());
+    (void)hipFuncSetAttribute((const void*)qkv_rows_kernel<128, 3>, hipFuncAttributeMaxDynamicSharedMemorySize, qkv_rows_lds_bytes<128, 3>());
     configured = true;
   }
-  if (a.K == 64) hipLaunchKernelGGL(qkv_rows_kernel<64>, grid, dim3(256), qkv_rows_lds_bytes<64>(), st, q);
-  else hipLaunchKernelGGL(qkv_rows_kernel<128>, grid, dim3(256), qkv_rows_lds_bytes<128>(), st, q);
+  if (a.K == 64 && few) hipLaunchKernelGGL((qkv_rows_kernel<64, 1>), grid, dim3(256), (qkv_rows_lds_bytes<64, 1>()), st, q);
+  else if (a.K == 64) hipLaunchKernelGGL((qkv_rows_kernel<64, 3>), grid, dim3(256), (qkv_rows_lds_bytes<64, 3>()), st, q);
+  else if (few) hipLaunchKernelGGL((qkv_rows_kernel<128, 1>), grid, dim3(256), (qkv_rows_lds_bytes<128, 1>()), st, q);
+  else hipLaunchKernelGGL((qkv_rows_kernel<128, 3>), grid, dim3(256), (qkv_rows_lds_bytes<128, 3>()), st, q);
 }
 
 // Two GEMMs of identical shape and layout (row-major A, k-major B, 64-row tiles, no split-K) in one launch.
