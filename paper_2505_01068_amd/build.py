@@ -11,7 +11,7 @@ import sys
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
-SOURCES = ["api.hip", "attn_split.hip", "gemm_alu.hip", "gemm_split.hip", "mfma_path.hip", "mfma_gemm.hip", "wgrad_ring.hip", "mfma_attn.hip", "mfma_attn_sub.hip",
+SOURCES = ["api.hip", "attn_split.hip", "attn_tiny.hip", "gemm_alu.hip", "gemm_split.hip", "mfma_path.hip", "mfma_gemm.hip", "wgrad_ring.hip", "mfma_attn.hip", "mfma_attn_sub.hip",
            "gsit_model.hip", "calibrate.hip"]
 LIB = os.path.join(HERE, "libimattn.so")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Xclang", "-target-feature", "-Xclang",

@@ -237,11 +237,15 @@ static int scratch_of_current_device(char** out) {
 static int fwd_smallhead(const im_shape_t* s, const void* x, const void* wq, const void* wk, const void* wv,
                        const void* wo, const void* bq, const void* bk, const void* bv, const void* bo,
                        const int32_t* valid_len, const uint8_t* key_pad, void* y, const void* res, char* sv,
-                       hipStream_t st) {
+                       hipStream_t st, bool keep = true) {   // keep: sv holds what a backward pass needs afterwards
   const int bf = s->dtype == IM_DTYPE_BF16;
   const size_t es = bf ? 2 : 4;
   Geo g;
   build_geo(s, 64, 64, &g);
+  if (!keep && !bf && tiny_fwd_ok(g, x, y)) {
+    launch_tiny_fwd(g, x, {wq, wk, wv, wo}, {bq, bk, bv, bo}, valid_len, key_pad, y, res, st);
+    return check_hip("im_attention_fwd launch");
+  }
   const SavedLayout L = saved_layout(s);
   const long R = g.R, d = g.d;
   char* qkv = sv + L.qkv;
@@ -494,7 +498,7 @@ int im_attention_fwd(const im_shape_t* shape, const void* x, const void* wq, con
     return mfma_attention_fwd(shape, x, wq, wk, wv, wo, bq, bk, bv, bo, valid_len, key_pad, y, nullptr, sv, L.qkv,
                               L.o, saved ? L.lse : NO_LSE, L.extra, ws, as_stream(hip_stream));
   return fwd_smallhead(shape, x, wq, wk, wv, wo, bq, bk, bv, bo, valid_len, key_pad, y, nullptr, sv,
-                     as_stream(hip_stream));
+                     as_stream(hip_stream), saved != nullptr);
 }
 
 int im_attention_bwd(const im_shape_t* shape, const void* x, const void* wq, const void* wk, const void* wv,
@@ -557,7 +561,7 @@ int im_attention_fwd_noalloc(const im_shape_t* shape, const void* x, const void*
     return mfma_attention_fwd(shape, x, wq, wk, wv, wo, bq, bk, bv, bo, valid_len, key_pad, y, nullptr, sv, L.qkv,
                               L.o, NO_LSE, L.extra, sv + L.total, as_stream(hip_stream));
   return fwd_smallhead(shape, x, wq, wk, wv, wo, bq, bk, bv, bo, valid_len, key_pad, y, nullptr, sv,
-                     as_stream(hip_stream));
+                     as_stream(hip_stream), false);
 }
 
 static int layer_check(const im_shape_t* shape, int32_t d_ff) {
@@ -629,7 +633,7 @@ int gsit_layer_fwd(const im_shape_t* shape, int32_t d_ff, const void* x, const v
                             tail_fused ? nullptr : h, x, aw, L.qkv, L.o, NO_LSE, L.extra, aw + L.total, st,
                             ln1_fused ? LnArgs{ln1_g, ln1_b, ln_eps} : LnArgs{nullptr, nullptr, 0.f});
   else
-    rc = fwd_smallhead(shape, u, wq, wk, wv, wo, bq, bk, bv, bo, valid_len, key_pad, h, x, aw, st);
+    rc = fwd_smallhead(shape, u, wq, wk, wv, wo, bq, bk, bv, bo, valid_len, key_pad, h, x, aw, st, false);
   if (rc) return rc;
   if (tail_fused) {
     ProfScope ps(PF_MISC, st);

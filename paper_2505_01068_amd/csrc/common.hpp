@@ -191,6 +191,19 @@ int launch_smallhead_bwd(const Geo& g, int bf16, const void* q, const void* k, c
                        const void* d_o, long ldo, const float* lse2, const int32_t* valid_len, const uint8_t* key_pad,
                        float* delta, void* dq, void* dk, void* dv, long ldg, hipStream_t st);
 bool smallhead_supports(int dh);
+// compute units of the device (the first device that launches; one GPU per process)
+inline int cu_count() {
+  static const int cus = [] {
+    int dev = 0, n = 0;
+    const bool ok = hipGetDevice(&dev) == hipSuccess && hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess;
+    return ok && n > 0 ? n : 256;
+  }();
+  return cus;
+}
+// the smallest fp32 inference calls, projections included, in one launch (attn_tiny.hip); w, b: q, k, v, o; res added to y if given
+bool tiny_fwd_ok(const Geo& g, const void* x, const void* y);
+void launch_tiny_fwd(const Geo& g, const void* x, const void* const (&w)[4], const void* const (&b)[4], const int32_t* valid_len,
+                     const uint8_t* key_pad, void* y, const void* res, hipStream_t st);
 
 // LayerNorm rows
 int launch_layernorm(const void* x, const void* gamma, const void* beta, void* y, int R, int d, float eps, int bf16,

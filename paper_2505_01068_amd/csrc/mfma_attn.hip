@@ -885,11 +885,10 @@ constexpr int FWD_QB = 1, FWD_QB_SUB = 2, DQ_QB = 1, DKV_KB = 1;
 constexpr int FWD_NST = 2, FWD_WGS = 4, FWD_NW = 4;   // ring stages, workgroups per CU, waves per workgroup (head dim 64)
 constexpr int FWD_SUB_NST = 2, FWD_SUB_WGS = 4;       // the same in sub-head mode (4 waves)
 constexpr int DQ_NST = 3, DQ_WGS = 3;                 // dQ at head dim 64
-static int device_cus();
 // CUs per XCD if a launch of `wgs` workgroups is dealt out evenly (see xcd_tile_index), else 0: all resident with `per_cu`
 // workgroups on a CU, of different lengths.  Lengths of packed rows are not known here.
 static unsigned even_cus(const Geo& g, int nord, long wgs, int per_cu) {
-  const int cus = device_cus();
+  const int cus = cu_count();
   return !g.cu && nord > 1 && cus % 8 == 0 && wgs > cus && wgs <= (long)per_cu * cus ? (unsigned)cus / 8u : 0u;
 }
 // Head dimension 64, few workgroups: tiles of 64 rows instead of 128, the two 32-row blocks of a stage going to two waves of
@@ -902,7 +901,7 @@ static unsigned even_cus(const Geo& g, int nord, long wgs, int per_cu) {
 //                            416                            238 / 239      432 (50/500/500 x 4, layer) 255 / 257
 //                            624                            286 / 319      576 (512/2048/2048 x 8)  269 / 264
 static bool split_rows(const Geo& g, const int* prefix, int nord) {
-  return g.dh == 64 && 2 * (long)prefix[nord] * g.H * g.B <= 3L * device_cus();
+  return g.dh == 64 && 2 * (long)prefix[nord] * g.H * g.B <= 3L * cu_count();
 }
 // Tables of a schedule for tiles of `rows` rows (build_geo's for another height)
 static void retile(const Geo& g, const int* order, int nord, int rows, int* prefix) {
@@ -920,20 +919,11 @@ int mfma_dkv_tile_rows() { return 128 * DKV_KB; }
 // a shorter tail of the launch (measured: -3 % at that shape).  A half-height workgroup does more work per score (the
 // K/V fragments are read per block), so a launch whose long workgroups are many -- it is bound by the CUs'
 // instruction issue, not by its last workgroup -- keeps the full tiles (halving them there measured +3 %).
-static int device_cus() {
-  static int cus = 0;   // compute units of the device (the first device that launches; one GPU per process)
-  if (cus == 0) {
-    int dev = 0, n = 0;
-    if (hipGetDevice(&dev) == hipSuccess && hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && n > 0) cus = n;
-    else cus = 256;
-  }
-  return cus;
-}
 static void fwd_half_tiles(Geo& g) {
   g.q_half = 0;
   if (g.cu || g.q_nord < 2) return;
   const int rows = 32 * FWD_QB_SUB;
-  const long units = (long)g.B * (g.H / 4), slots = (long)FWD_SUB_WGS * device_cus();
+  const long units = (long)g.B * (g.H / 4), slots = (long)FWD_SUB_WGS * cu_count();
   long len[IM_MAX_SEG], tiles[IM_MAX_SEG];
   int longest = 0;
   for (int k = 0; k < g.q_nord; ++k) {

@@ -1792,7 +1792,6 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
               pack_bf16(o[2] + __uint_as_float(rv[1] << 16), o[3] + __uint_as_float(rv[1] & 0xffff0000u))};
   }
 }
-static int cu_count();
 // at most one 64-row workgroup per CU (see mlp_tail_few_kernel); more run two of the four-wave workgroups per CU
 static bool mlp_tail_few(int R) { return (R + 63) / 64 <= cu_count(); }
 bool mlp_tail_ok(int is_bf16, long d, long d_ff, const void* h, const void* ln_g, const void* ln_b, const void* w1,
@@ -1940,15 +1939,6 @@ static void launch_dma(const MGemm& p, hipStream_t st) {
   }
   dim3 grid((p.N + DN - 1) / DN, (p.M + DM - 1) / DM, p.split_k);
   hipLaunchKernelGGL((mfma_gemm_dma_kernel<AKM, BKM, DMA_WAVES>), grid, dim3(DMA_WAVES * 64), DMA_LDS_BYTES, st, p);
-}
-static int cu_count() {   // of the device (the first device that launches; one GPU per process)
-  static int cus = 0;
-  if (cus == 0) {
-    int dev = 0, n = 0;
-    if (hipGetDevice(&dev) == hipSuccess && hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && n > 0) cus = n;
-    else cus = 256;
-  }
-  return cus;
 }
 // the 288-row variant when its workgroups need fewer (weighted) rounds of the CUs than the 256-row tiles
 static bool use_dma12(const MGemm& p) {
