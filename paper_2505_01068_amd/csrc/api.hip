@@ -281,14 +281,15 @@ static int fwd_smallhead(const im_shape_t* s, const void* x, const void* wq, con
   return check_hip("im_attention_fwd launch");
 }
 
-// later / wlater, both or neither: second-stage sums resp. fp32 weight gradients that the caller launches at the end of its
-// own pass (NULL: launched here); with wlater the operands (x, dy and the workspace) stay as they are until then, and wrows is the
-// caller's number of rows per workgroup.
+// later / wlater / dxlater, all or none: second-stage sums resp. fp32 weight gradients and the product that is dx, which the caller
+// launches at the end of its own pass (NULL: launched here); with them the operands (x, dy and the workspace) stay as they are until
+// then, and wrows is the caller's number of rows per workgroup.
 static int bwd_smallhead(const im_shape_t* s, const void* x, const void* wq, const void* wk, const void* wv,
                          const void* wo, const int32_t* valid_len, const uint8_t* key_pad, const char* sv,
                          const void* dy, void* dx, void* dwq, void* dwk, void* dwv, void* dwo, void* dbq, void* dbk,
                          void* dbv, void* dbo, char* ws, hipStream_t st, ReduceList* later = nullptr,
-                         WgradSplitList* wlater = nullptr, int wrows = 0) {
+                         WgradSplitList* wlater = nullptr, int wrows = 0,
+                         GemmDesc* dxlater = nullptr) {
   const int bf = s->dtype == IM_DTYPE_BF16;
   const size_t es = bf ? 2 : 4;
   Geo g;
@@ -308,6 +309,12 @@ static int bwd_smallhead(const im_shape_t* s, const void* x, const void* wq, con
 
   GemmDesc p;
   int rc;
+  auto dx_product = [&](GemmDesc* q) {   // dx = dQ Wq^T + dK Wk^T + dV Wv^T
+    memset(q, 0, sizeof(*q));
+    q->A = dqkv; q->sam = 3 * d; q->sak = 1;
+    q->B[0] = wq; q->B[1] = wk; q->B[2] = wv; q->sbk = 1; q->sbn = d; q->b_split = 2; q->k_per = (int)d;
+    q->C[0] = dx; q->ldc = d; q->M = (int)R; q->N = (int)d; q->K = (int)(3 * d);
+  };
   // dO = dy Wo^T
   memset(&p, 0, sizeof(p));
   p.A = dy; p.sam = d; p.sak = 1;
@@ -321,7 +328,10 @@ static int bwd_smallhead(const im_shape_t* s, const void* x, const void* wq, con
   if (rc) return rc;
 
   if (!bf) {
-    // dWo = O^T dy with dbo, dWq | dWk | dWv = x^T [dQ | dK | dV] with dbq | dbk | dbv: one launch, one reduction
+    // dWo = O^T dy with dbo, dWq | dWk | dWv = x^T [dQ | dK | dV] with dbq | dbk | dbv, and dx: one launch, and one reduction
+    GemmDesc dx0;
+    GemmDesc& q = dxlater ? *dxlater : dx0;
+    if (dx) dx_product(&q);
     if (!wrows) wrows = wgrad_split_rows_attention((int)d, (int)R);
     float* po = (float*)b.take(wgrad_split_bytes((int)d, (int)d, (int)R, wrows));
     float* pw = (float*)b.take(wgrad_split_bytes((int)d, (int)(3 * d), (int)R, wrows));
@@ -336,9 +346,11 @@ static int bwd_smallhead(const im_shape_t* s, const void* x, const void* wq, con
                      (float*)dbo, nullptr, nullptr);
     if (!wlater) {
       ProfScope ps(PF_WGRAD, st);
-      launch_wgrad_split(*wl, st);
+      if (dx) launch_wgrad_dx_split(*wl, q, st);
+      else launch_wgrad_split(*wl, st);
       launch_reduce_list(*red, st);
     }
+    return check_hip("im_attention_bwd launch");
   } else {
     int split = 1;
     size_t pbytes = std::max(gemm_alu_partial_bytes((int)d, (int)(3 * d), (int)R, &split),
@@ -393,10 +405,7 @@ static int bwd_smallhead(const im_shape_t* s, const void* x, const void* wq, con
     ProfScope ps(PF_PROJ_BWD, st);
     mfma_dgrad(dqkv, 3 * d, wq, wk, wv, d, (int)d, dx, d, (int)R, (int)d, (int)(3 * d), st);
   } else if (dx) {
-    memset(&p, 0, sizeof(p));
-    p.A = dqkv; p.sam = 3 * d; p.sak = 1;
-    p.B[0] = wq; p.B[1] = wk; p.B[2] = wv; p.sbk = 1; p.sbn = d; p.b_split = 2; p.k_per = (int)d;
-    p.C[0] = dx; p.ldc = d; p.M = (int)R; p.N = (int)d; p.K = (int)(3 * d);
+    dx_product(&p);
     ProfScope ps(PF_PROJ_BWD, st);
     if ((rc = launch_gemm_alu(p, bf, bf, bf, st))) return rc;
   }
@@ -981,11 +990,12 @@ int gsit_layer_bwd(const im_shape_t* shape, int32_t d_ff, const void* x, const g
                             defer, L.ring ? &wr : nullptr, L.ring ? &L.plan : nullptr);
   else
     rc = bwd_smallhead(shape, u, p->wq, p->wk, p->wv, p->wo, valid_len, key_pad, sv + L.att, dh, dv, gr->wq, gr->wk, gr->wv,
-                     gr->wo, gr->bq, gr->bk, gr->bv, gr->bo, ws + L.attws, st, bf ? nullptr : &later, bf ? nullptr : &wl, L.wrows);
+                     gr->wo, gr->bq, gr->bk, gr->bv, gr->bo, ws + L.attws, st, bf ? nullptr : &later, bf ? nullptr : &wl, L.wrows,
+                       bf ? nullptr : &g);
   if (rc) return rc;
-  if (wl.n || wr.n) {
+  if (!bf || wr.n) {
     ProfScope ps(PF_WGRAD, st);
-    launch_wgrad_split(wl, st);
+    if (!bf) launch_wgrad_dx_split(wl, g, st);
     if (L.ring) launch_wgrad_ring(wr, L.plan, (int)R, st);
   }
   // dx = dh + LN1 backward(du)

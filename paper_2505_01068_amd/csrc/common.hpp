@@ -237,6 +237,7 @@ size_t wgrad_split_bytes(int M, int N, int R, int rows);
 void wgrad_split_push(WgradSplitList* l, int rows, ReduceList* red, const float* A, long lda, const float* G, long ldg, int R, int M,
                       int N, float* partial, int n_per, float* w0, float* w1, float* w2, float* b0, float* b1, float* b2);
 void launch_wgrad_split(const WgradSplitList& l, hipStream_t st);
+void launch_wgrad_dx_split(const WgradSplitList& l, const GemmDesc& g, hipStream_t st);   // and g, an input gradient (sbk = 1, no GELU)
 
 // encoder-layer backward pieces: a = GELU(z); g <- g * GELU'(z) in place; LayerNorm backward of rows
 // (dx = input gradient + res (res may be NULL), t: scratch of the rows' size for dy * xhat)

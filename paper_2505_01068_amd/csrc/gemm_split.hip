@@ -74,13 +74,13 @@ __device__ __forceinline__ const float* gs_buffer(const float* b0, const float* 
   i -= sel * per;
   return sel == 0 ? b0 : sel == 1 ? b1 : b2;
 }
+constexpr int gs_lds(int ks) { return ks * 2 * 3 * 64; }   // of u32x4
 template <int KS, bool BT, bool OCT, bool GELU>
-__global__ __launch_bounds__(256, 3) void gemm_split_kernel(GemmDesc g) {
+__device__ __forceinline__ void gemm_split_tile(const GemmDesc& g, unsigned bx, unsigned by, u32x4* sB) {
   constexpr int UNITS = KS * 2, UPW = (UNITS + 3) / 4;   // (k-step, 32-column block) units of the weight; per wave
-  __shared__ u32x4 sB[UNITS * 3 * 64];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lo = lane & 31, h = lane >> 5, wr = wave & 1, wc = wave >> 1;
-  const int m0 = blockIdx.x * 64 + wr * 32, n0 = blockIdx.y * 64;
+  const int m0 = bx * 64 + wr * 32, n0 = by * 64;
   const int K = g.K, N = g.N;
   const float* const arow = (const float*)g.A + (long)min(m0 + lo, g.M - 1) * g.sam;
   const int ldw = (int)(BT ? g.sbn : g.sbk);
@@ -217,20 +217,31 @@ __global__ __launch_bounds__(256, 3) void gemm_split_kernel(GemmDesc g) {
   }
 }
 
+template <int KS, bool BT, bool OCT, bool GELU>
+__global__ __launch_bounds__(256, 3) void gemm_split_kernel(GemmDesc g) {
+  __shared__ u32x4 sB[gs_lds(KS)];
+  gemm_split_tile<KS, BT, OCT, GELU>(g, blockIdx.x, blockIdx.y, sB);
+}
+
 bool gemm_split_ok(const GemmDesc& g) {
   return g.split_k <= 1 && g.kb <= 1 && !g.c_split && g.sak == 1 && (g.sbn == 1 || g.sbk == 1);
 }
+// Octets of k are inside or outside K, and inside one row block of the weight, as a whole: all widths that are
+// multiples of 8 (one address and two 16-byte loads per octet).  Both forms in one kernel cost every width the 16-byte
+// loads: the compiler merges the two branches' requests into one list of 4-byte loads at computed addresses (QKV
+// projection at 29 600 x 40 x 120: 18.4 us instead of 10.4).
+static bool gs_oct(const GemmDesc& g) { return g.K % 8 == 0 && (g.b_split != 2 || g.k_per % 8 == 0); }
+// k-steps per chunk: one chunk up to K = 64, two up to K = 128 (33 600 x 120 x 40: 10.6 us with two chunks of four
+// k-steps, 11.5 with four of two), beyond that short ones (33 600 x 160 x 40: 16 us with chunks of two, 20 with chunks
+// of four or five, whose next chunk waits in registers that cost resident waves)
+static int gs_ksteps(const GemmDesc& g) {
+  const int nk = (g.K + 15) / 16;
+  return nk <= 4 ? nk : nk <= 8 ? (nk + 1) / 2 : 2;
+}
 void launch_gemm_split(const GemmDesc& g, hipStream_t st) {
   const bool bt = g.sbn != 1;
-  // Octets of k are inside or outside K, and inside one row block of the weight, as a whole: all widths that are
-  // multiples of 8 (one address and two 16-byte loads per octet).  Both forms in one kernel cost every width the 16-byte
-  // loads: the compiler merges the two branches' requests into one list of 4-byte loads at computed addresses (QKV
-  // projection at 29 600 x 40 x 120: 18.4 us instead of 10.4).
-  const bool oct = g.K % 8 == 0 && (g.b_split != 2 || g.k_per % 8 == 0);
-  // k-steps per chunk: one chunk up to K = 64, two up to K = 128 (33 600 x 120 x 40: 10.6 us with two chunks of four
-  // k-steps, 11.5 with four of two), beyond that short ones (33 600 x 160 x 40: 16 us with chunks of two, 20 with chunks
-  // of four or five, whose next chunk waits in registers that cost resident waves)
-  const int nk = (g.K + 15) / 16, ks = nk <= 4 ? nk : nk <= 8 ? (nk + 1) / 2 : 2;
+  const bool oct = gs_oct(g);
+  const int ks = gs_ksteps(g);
   const dim3 grid((g.M + 63) / 64, (g.N + 63) / 64);
 #define GS_LAUNCH(KS, OCT)                                                                                          \
   do {                                                                                                              \
@@ -259,19 +270,19 @@ void launch_gemm_split(const GemmDesc& g, hipStream_t st) {
 // bias gradients cost nothing).  At a few thousand rows a workgroup's chain of steps, 0.5 us each, and the launch: 2850
 // rows 5 us (8.2), 9600 rows 7.5 us (6.3, with 75 longer workgroups whose bias gradients were another pair of launches).
 // More steps in flight did not help: the chain is splitting, LDS and matrix instructions, not the requests.
-__global__ __launch_bounds__(256, 4) void wgrad_split_kernel(WgradSplitList l) {
-  __shared__ u32x4 frag[2][4][3][64];   // [step parity][A block 0, 1, G block 0, 1][part][lane]
+typedef u32x4 WgradFrag[2][4][3][64];   // [step parity][A block 0, 1, G block 0, 1][part][lane]
+__device__ __forceinline__ void wgrad_split_tile(const WgradSplitList& l, unsigned bx, unsigned by, unsigned bz, WgradFrag& frag) {
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lo = lane & 31, h = lane >> 5;
-  const WgradSplit& p = l.p[blockIdx.z];
-  const int tm = p.tn_magic ? __umulhi(blockIdx.y, p.tn_magic) : blockIdx.y, tn = blockIdx.y - tm * ((p.N + 63) >> 6);
+  const WgradSplit& p = l.p[bz];
+  const int tm = p.tn_magic ? __umulhi(by, p.tn_magic) : by, tn = by - tm * ((p.N + 63) >> 6);
   if (tm * 64 >= p.M) return;
   // this wave's share of the operands: a 32-column block of A (waves 0, 1) or G (2, 3); and its block of C
   const bool is_g = wave >= 2;
   const int ld = (int)(is_g ? p.ldg : p.lda), width = is_g ? p.N : p.M, x0 = (is_g ? tn : tm) * 64 + (wave & 1) * 32;
   const int m0 = tm * 64 + (wave & 1) * 32, n0 = tn * 64 + (wave >> 1) * 32;
   const bool stage = x0 < width, mine = m0 < p.M && n0 < p.N;
-  const int r0 = blockIdx.x * l.rows, nrows = min(l.rows, l.R - r0), nst = (nrows + 15) >> 4;
+  const int r0 = bx * l.rows, nrows = min(l.rows, l.R - r0), nst = (nrows + 15) >> 4;
   const float* const X = (is_g ? p.G : p.A) + (long)r0 * ld;
   const int col = min(x0 + lo, width - 1);
   const unsigned off = 8 * h * ld + col;
@@ -314,11 +325,11 @@ __global__ __launch_bounds__(256, 4) void wgrad_split_kernel(WgradSplitList l) {
   }
   if (p.csum && is_g && tm == 0 && x0 + lo < p.N) {
     cs += __shfl_xor(cs, 32);
-    if (h == 0) p.csum[(long)blockIdx.x * ((p.N + 3) & ~3) + x0 + lo] = cs;
+    if (h == 0) p.csum[(long)bx * ((p.N + 3) & ~3) + x0 + lo] = cs;
   }
   const int n = n0 + lo;
   if (!p.partial || m0 >= p.M || n >= p.N) return;
-  float* const out = p.partial + (long)blockIdx.x * p.stride + n;
+  float* const out = p.partial + (long)bx * p.stride + n;
   float check = 0.f;
 #pragma unroll
   for (int r = 0; r < 16; ++r) {
@@ -336,6 +347,34 @@ __global__ __launch_bounds__(256, 4) void wgrad_split_kernel(WgradSplitList l) {
       for (int i = 0; i < nrows && v == v; ++i) v = fmaf(A[(long)i * p.lda + m], G[(long)i * p.ldg + n], v);
       out[m * p.N] = v;
     }
+  }
+}
+
+__global__ __launch_bounds__(256, 4) void wgrad_split_kernel(WgradSplitList l) {
+  __shared__ WgradFrag frag;
+  wgrad_split_tile(l, blockIdx.x, blockIdx.y, blockIdx.z, frag);
+}
+
+// The weight gradients and the input gradient dx = G W^T beside them (both read what the attention backward wrote, neither reads
+// what the other writes): one launch.  Alone each of them is a chain of memory round trips on workgroups that leave most of the
+// chip's issue slots idle; together the launch takes what the longer one takes.  The gradients' workgroups come first, their
+// chains are the longer ones.  The product takes chunks of two k-steps at every width (107 registers: four resident workgroups).
+// Training step of 9600 x 40 67 -> 62.5 us, 2850 x 40 57.7 -> 53.6, 29 600 x 40 145.2 -> 142.5, layer of 33 600 x 40 x 160 305 -> 297
+// (with the product's own chunks and three resident workgroups 62.4, 53.3, 144.5, 303).
+__global__ __launch_bounds__(256, 4) void wgrad_dx_split_kernel(WgradSplitList l, GemmDesc g, unsigned ranges, unsigned nw) {
+  __shared__ union {
+    WgradFrag frag;
+    u32x4 sB[gs_lds(2)];
+  } lds;
+  unsigned id = blockIdx.x, q, r;
+  if (id < nw) {
+    udivmod(id, ranges, q, r);
+    unsigned z, t;
+    udivmod(q, l.tiles, z, t);
+    wgrad_split_tile(l, __builtin_amdgcn_readfirstlane(r), __builtin_amdgcn_readfirstlane(t), __builtin_amdgcn_readfirstlane(z), lds.frag);
+  } else {
+    udivmod(id - nw, (g.M + 63) / 64, q, r);
+    gemm_split_tile<2, true, true, false>(g, __builtin_amdgcn_readfirstlane(r), __builtin_amdgcn_readfirstlane(q), lds.sB);
   }
 }
 
@@ -381,6 +420,27 @@ void wgrad_split_push(WgradSplitList* l, int rows, ReduceList* red, const float*
 void launch_wgrad_split(const WgradSplitList& l, hipStream_t st) {
   if (l.n == 0) return;
   hipLaunchKernelGGL(wgrad_split_kernel, dim3((l.R + l.rows - 1) / l.rows, l.tiles, l.n), dim3(256), 0, st, l);
+}
+static bool overlap(const void* a, long na, const void* b, long nb) {   // of fp32 elements
+  const uintptr_t x = (uintptr_t)a, y = (uintptr_t)b;
+  return x < y + 4 * (size_t)nb && y < x + 4 * (size_t)na;
+}
+// The two launches stay two where dx lies over one of the gradients' operands (dx in place of x or dy: the second launch alone
+// writes it), where there is nothing on the list, and at widths that are not multiples of 8: the element-wise form of the product
+// needs 154 registers, and three resident workgroups instead of four cost the gradients more than a launch (training step of
+// 17 600 x 44 166.6 us in one launch, 159.8 in two; 17 600 x 52 204 / 196).
+void launch_wgrad_dx_split(const WgradSplitList& l, const GemmDesc& g, hipStream_t st) {
+  bool two = l.n == 0 || !gs_oct(g);
+  for (int i = 0; i < l.n; ++i)
+    two |= overlap(g.C[0], (long)g.M * g.ldc, l.p[i].A, (long)l.R * l.p[i].lda) || overlap(g.C[0], (long)g.M * g.ldc, l.p[i].G, (long)l.R * l.p[i].ldg);
+  const long ranges = l.n ? (l.R + l.rows - 1) / l.rows : 0, nw = ranges * l.tiles * l.n;
+  const long wgs = nw + (long)((g.M + 63) / 64) * ((g.N + 63) / 64);
+  if (two || wgs >= 1L << 31) {
+    launch_wgrad_split(l, st);
+    launch_gemm_split(g, st);
+    return;
+  }
+  hipLaunchKernelGGL(wgrad_dx_split_kernel, dim3((unsigned)wgs), dim3(256), 0, st, l, g, (unsigned)ranges, (unsigned)nw);
 }
 
 }  // namespace imattn
