@@ -24,7 +24,7 @@
 //
 // Only live (query segment, key segment) blocks of the Interlaced Mask are
 // visited (Sec. 6 "Decomposition"); a row with several live segments carries
-// one running max / sum across all of them (Sec. "Information Disorder").
+// one running sum across all of them (Sec. "Information Disorder").
 #include <algorithm>
 #include <type_traits>
 #include "mfma_attn_common.hpp"
@@ -186,6 +186,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WGS * N
   // GUARD = false: the scores are exponentiated as they leave the matrix cores, with no reference subtracted.  fp32 and
   // bf16 share their exponent range, so the probabilities 2^s have full precision at any size; only the sum has to stay in
   // range, which is checked once, behind the loop.  No maximum, no rescaling, no accumulator seed, no branch per block.
+  // Every probability is rounded to bf16 once, as with a reference; the one difference is that the first tile's maximum was exactly
+  // 1 there (relative error of y against fp64: the same at 2048 keys, 1.02 times at a few dozen valid keys).
   // (Four layers' attention at 32 x 50/500/375 rows, 8 heads of 8, valid lengths: 80 -> 70 us against the pass with a reference
   // in every block; 3 x 333/1501/1290 rows, 4 heads of 64, single masked keys: 72 -> 55 us, of which the key_pad bytes in the
   // ring are the larger part.)
