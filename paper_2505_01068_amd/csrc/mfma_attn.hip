@@ -20,7 +20,8 @@
 // exp2 and no kernel multiplies scores; the per-row statistic saved by the forward is the NEGATED
 // log2-sum-exp (-inf for a row without any valid key), which the backward kernels add to the score --
 // by starting their score accumulators from it, as the dP accumulators start from -delta: the MFMA
-// chains end as S - lse and dP - delta and the softmax needs no add per element.  The forward exponentiates its scores as they are.
+// chains end as S - lse and dP - delta and the softmax needs no add per element.  The forward's start from the negated reference of
+// the row, the largest score of its first 32 keys.
 //
 // Only live (query segment, key segment) blocks of the Interlaced Mask are
 // visited (Sec. 6 "Decomposition"); a row with several live segments carries
@@ -44,6 +45,8 @@ namespace imattn {
 // quarter of the VALU instructions of the row-per-lane kernel at these head sizes.
 // KS = 2: tiles of half the height, see split_rows.
 // PAIR: two problems of the same shape in one launch (two encoders side by side; see Geo::pair_B): grid z = 2 B.
+constexpr float ROW_SUM_MAX = 16777216.f;   // sum of exponentials relative to the reference, beyond which the reference moves
+constexpr float BF16_MAX = 3.3895313892515355e38f;
 template <int QB, int DH, int NST, int WGS, int NW, bool PAIR, int KS = 1>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WGS * NW / 4, WGS * NW / 4))) void mfma_fwd_kernel(Geo g, const bf16_t* __restrict__ QKV, long ld,
                                                        const int32_t* __restrict__ valid_len,
@@ -168,10 +171,29 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WGS * N
     vt1 = own ? (unsigned)((lrow + 4) * SW_LD + ((chunk ^ f ^ 1) << 3) + 4 * (j & 1)) * 2u : ones;
     vt_tile = own ? ~0u : 0u;
     if (lane < 16) sOnes[(lane >> 2) * 16 * SW_LD + (lane & 3)] = 0x3f80;   // every wave, so that none waits for another
+    else if (lane < 24) sOnes[8 + (lane & 7)] = (lane & 7) < 3 ? 0x3f80 : 0;   // three ones and zeros: what the reference's parts meet
   }
 
   const int prow = perm32(lo);
   constexpr float tau = 8.f;  // scores are exponents of 2 (Q carries scale * log2(e))
+  // The negated reference of the query rows enters S^T through the matrix cores, as three bf16 parts that meet ones (bf16_parts):
+  // in the lane half of the k-step that is not the head's (head dimension 8), or in an 8-deep k-step of their own, which has room
+  // in the 128 registers where a seed of 16 accumulator registers has not.
+  u32x2 nmp[DH == 16 ? QB : 1];
+  f32x16 nm[DH == 64 ? QB : 1];
+  const bool spare = DH == 8 && hi != ((wo >> 3) & 1);
+  const unsigned kf = spare ? (unsigned)(uintptr_t)(sOnes + 8) : (unsigned)(prow * SW_LD + (((2 * s0 + hi) ^ sw_f(prow)) << 3)) * 2u;
+  const unsigned kf_tile = spare ? 0u : ~0u;
+  auto set_reference = [&](int qb, float v) __attribute__((always_inline)) {   // v: negated
+    if (DH == 64) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r) nm[DH == 64 ? qb : 0][r] = v;
+      return;
+    }
+    const u32x2 pt = bf16_parts(v);
+    if (DH == 8) qreg[qb][0] = spare ? as_bf16x8(u32x4{pt[0], pt[1], 0u, 0u}) : qreg[qb][0];
+    else nmp[DH == 16 ? qb : 0] = hi == 0 ? pt : u32x2{0u, 0u};
+  };
   // The compiler does not see the asynchronous copies in its vmcnt bookkeeping: consuming the Q
   // registers here makes it wait for their (ordinary) loads now, not inside the ring loop.
 #pragma unroll
@@ -183,29 +205,30 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WGS * N
 
   // One pass over the live key tiles, for NQB of the wave's QB query blocks (NQB < QB: a tile of half the height).
   //
-  // GUARD = false: the scores are exponentiated as they leave the matrix cores, with no reference subtracted.  fp32 and
-  // bf16 share their exponent range, so the probabilities 2^s have full precision at any size; only the sum has to stay in
-  // range, which is checked once, behind the loop.  No maximum, no rescaling, no accumulator seed, no branch per block.
-  // Every probability is rounded to bf16 once, as with a reference; the one difference is that the first tile's maximum was exactly
-  // 1 there (relative error of y against fp64: the same at 2048 keys, 1.02 times at a few dozen valid keys).
-  // (Four layers' attention at 32 x 50/500/375 rows, 8 heads of 8, valid lengths: 80 -> 70 us against the pass with a reference
-  // in every block; 3 x 333/1501/1290 rows, 4 heads of 64, single masked keys: 72 -> 55 us, of which the key_pad bytes in the
-  // ring are the larger part.)
-  // GUARD = true: the same with a running reference m per query row; the pass that rows whose sum left the range take.
+  // GUARD = false: the reference of a row is its largest score in the first 32-key block that has a valid key, and stays.  fp32 and
+  // bf16 share their exponent range, so probabilities far above 1 lose nothing; only the sum has to stay in range, which is
+  // checked once, behind the loop: no maximum, no rescaling and no branch on the scores per block.  (Four encoder layers at 32 x
+  // 50/500/375 rows, 8 heads of 8: 129 us; with a check of every block's sum, as in the other pass, 146.)
+  // Without any reference it is 127 us, but then the largest probability of the first block is rounded to bf16 like the others instead
+  // of being exactly 1, and with it the log-sum-exp that the backward takes all probabilities from.  Errors against fp64, rms of
+  // 6 seeds, times those with a running reference: y up to 1.03, dWo 1.04, dWv 1.05, dWq and dWk 1.04 at 8 and 30 keys, ordinary
+  // and peaked scores; with this one 0.99 to 1.00 everywhere.
+  // GUARD = true: a running reference m per query row; the pass that rows whose sum left the range take.
   auto stream = [&](auto nqb_tag, auto guard_tag) __attribute__((always_inline)) {
     constexpr int NQB = decltype(nqb_tag)::value;
     constexpr bool GUARD = decltype(guard_tag)::value;
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb) {
-      m[qb] = GUARD ? IM_NEG_INF : 0.f;
+      m[qb] = IM_NEG_INF;
       l[qb] = 0.f;
+      if (!GUARD || DH == 8) set_reference(qb, 0.f);
 #pragma unroll
       for (int db = 0; db < NDB; ++db)
 #pragma unroll
         for (int r = 0; r < 16; ++r) oacc[db][qb][r] = 0.f;
     }
-    // NST - 1 stages are requested ahead: the slot refilled in an iteration is the one consumed in the one before
-    int cslot = 0, keys1, keys2 = -1;   // valid keys of the next stage, of the one after it
+    static_assert(NST == 2, "the slot refilled while a tile is consumed is that of the tile before");
+    int cslot = 0, keys = 0, keys1;   // valid keys of the present tile, of the one requested after it (-1: there is none)
     ic.rest = key_set;
     if (!GUARD && row_set) {   // the first one is under way
       ic.rest &= ~(1u << seg1);
@@ -217,32 +240,74 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WGS * N
       next_seg();
       keys1 = issue();
     }
-    if (NST > 2) keys2 = issue();
-    while (keys1 >= 0) {
-      ring_wait<NW>(keys2 >= 0, kp_copy);
-      const int keys = keys1;   // valid keys from the tile's first one on
-      keys1 = keys2;
-      (NST > 2 ? keys2 : keys1) = issue();
-      const bf16_t* sK = sT + cslot * RING_STAGE;
-      const bf16_t* sV = sK + KT * SW_LD;
-      const unsigned* kp = sKP + cslot * KT;
-      cslot = (cslot + 1 == NST) ? 0 : cslot + 1;
-      const unsigned vta = (vt_tile & (unsigned)(uintptr_t)sV) + vt0, vtb = (vt_tile & (unsigned)(uintptr_t)sV) + vt1;
-      const bool need_mask = keys < KT || key_pad != nullptr;  // tail tile or key_pad present (wave-uniform)
-      if (need_mask) tile_masks(sPM[wave], key_pad ? kp : nullptr, keys);
-      // The tile is processed as two blocks of 32 keys, each S^T -> softmax -> O^T (KS = 2: one by each of two waves).
-#pragma unroll(GUARD ? 1 : 2)
-      for (int kk = 0; kk < 2 / KS; ++kk) {
+    const bf16_t *sK = sT, *sV = sT;
+    bool need_mask = false;   // tail tile or key_pad present (wave-uniform)
+    auto advance = [&]() __attribute__((always_inline)) {   // to the next tile
+      ring_wait<NW>(false);
+      keys = keys1;
+      keys1 = issue();
+      sK = sT + cslot * RING_STAGE;
+      sV = sK + KT * SW_LD;
+      need_mask = keys < KT || key_pad != nullptr;
+      if (need_mask) tile_masks(sPM[wave], key_pad ? sKP + cslot * KT : nullptr, keys);
+      cslot ^= 1;
+    };
+    // S^T = K Q^T, less the reference
+    auto scores = [&](f32x16 (&sacc)[QB], int kb) __attribute__((always_inline)) {
+#pragma unroll
+      for (int s = 0; s < NS; ++s) {
+        const bf16x8 a = DH == 8 ? lds_b128((kf_tile & ((unsigned)(uintptr_t)sK + kb * 32 * SW_LD * 2)) + kf)
+                                 : lds_frag_sw(sK, kb * 32, prow, 2 * (s0 + s) + hi);
+#pragma unroll
+        for (int qb = 0; qb < NQB; ++qb) {
+          if (s == 0) sacc[qb] = GUARD || DH == 8 ? f32x16{} : DH == 64 ? nm[DH == 64 ? qb : 0] : mfma32_k8(u32x2{ONES01, ONES2}, nmp[DH == 16 ? qb : 0], f32x16{});
+          sacc[qb] = mfma32(a, qreg[qb][s], sacc[qb]);
+        }
+      }
+    };
+    // The references, from the first block with a valid key (wave-uniform); the tiles before it contribute nothing.
+    bool seen = GUARD;
+    while (!GUARD && !seen && keys1 >= 0) {
+      advance();
+#pragma unroll 1
+      for (int kk = 0; kk < 2 / KS && !seen; ++kk) {
         const int kb = KS == 1 ? kk : kg;
         if (kb == 1 && keys <= 32) break;
-        // ---- S^T = K Q^T ----
         f32x16 sacc[QB];
+        scores(sacc, kb);
+        seen = true;
+        if (need_mask) {
+          unsigned pmask[8], some = 0u;
+          block_masks(sPM[wave], kb, hi, pmask);
 #pragma unroll
-        for (int s = 0; s < NS; ++s) {
-          const bf16x8 a = lds_frag_sw(sK, kb * 32, prow, 2 * (s0 + s) + hi);
+          for (int e = 0; e < 8; ++e) some |= pmask[e];
+          seen = __any(some != 0u);
 #pragma unroll
-          for (int qb = 0; qb < NQB; ++qb) sacc[qb] = mfma32(a, qreg[qb][s], s == 0 ? f32x16{} : sacc[qb]);
+          for (int r = 0; r < 16; ++r)
+#pragma unroll
+            for (int qb = 0; qb < NQB; ++qb) sacc[qb][r] = (pmask[r >> 1] >> (16 * (r & 1)) & 1u) ? sacc[qb][r] : IM_NEG_INF;
         }
+        if (!seen) continue;
+#pragma unroll
+        for (int qb = 0; qb < NQB; ++qb) {
+          float mx = sacc[qb][0];
+#pragma unroll
+          for (int r = 1; r < 16; ++r) mx = fmaxf(mx, sacc[qb][r]);
+          const auto both = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
+          mx = fmaxf(__uint_as_float(both[0]), __uint_as_float(both[1]));
+          m[qb] = fminf(fmaxf(mx, -BF16_MAX), BF16_MAX);   // has a bf16 (a row beyond it leaves the range and is taken again)
+        }
+#pragma unroll
+        for (int qb = 0; qb < NQB; ++qb) set_reference(qb, -m[qb]);
+      }
+    }
+    if (GUARD && keys1 >= 0) advance();
+    while (keys > 0) {   // a tile is there
+      const unsigned vta = (vt_tile & (unsigned)(uintptr_t)sV) + vt0, vtb = (vt_tile & (unsigned)(uintptr_t)sV) + vt1;
+      // The tile is processed as two blocks of 32 keys, each S^T -> softmax -> O^T (KS = 2: one by each of two waves).
+      auto block = [&](int kb) __attribute__((always_inline)) {
+        f32x16 sacc[QB];
+        scores(sacc, kb);
         // ---- softmax ----
         bf16x8 pb[QB][2];
         unsigned pmask[8];   // the validity of the keys of a packed pair of probabilities
@@ -283,7 +348,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WGS * N
 #pragma unroll
           for (int r = 0; r < 16; ++r) sacc[qb][r] -= m0;
           float rs = exponentiate(0.f);
-          if (__builtin_expect(__any(m[qb] == IM_NEG_INF || !(rs <= 16777216.f)), 0)) {
+          if (__builtin_expect(__any(m[qb] == IM_NEG_INF || !(rs <= ROW_SUM_MAX)), 0)) {
             asm volatile("" ::: "memory");  // a real branch: nothing of it is to be executed speculatively
             float mx = sacc[qb][0];
 #pragma unroll
@@ -317,7 +382,18 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WGS * N
 #pragma unroll
             for (int qb = 0; qb < NQB; ++qb) oacc[db][qb] = mfma32(a, pb[qb][half], oacc[db][qb]);
           }
+      };
+      if (KS == 2) {
+        if (kg == 0 || keys > 32) block(kg);
+      } else if (GUARD) {
+#pragma unroll 1
+        for (int kb = 0; kb < 2 && (kb == 0 || keys > 32); ++kb) block(kb);
+      } else {
+        block(0);
+        if (keys > 32) block(1);
       }
+      if (keys1 < 0) break;
+      advance();
     }
     if (ONES) {
 #pragma unroll
@@ -326,8 +402,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WGS * N
   };
 
   // ---- epilogue: normalise, write O rows, O^T columns and the log-sum-exp ----
-  // Returns whether a row's results are out of the range of the pass without a reference: its sum not within 2^-80 .. 2^100
-  // (probabilities below 2^-126 are flushed: 2^-46 of such a sum), or an output that is not finite (a NaN sum stays one).
+  // Returns whether a row left the range of the pass without a running reference: its sum, relative to the reference, above 2^24
+  // (where a running one moves), or below what the reference itself contributes (scores of -inf in the whole first block).
   bool redo[QB];
   auto finish = [&](bool again) __attribute__((always_inline)) {
     bool any = false;
@@ -346,7 +422,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WGS * N
       const float m1 = in[17 * 64 + lane], l1 = in[16 * 64 + lane], mm = fmaxf(m[0], m1);
       const float a0 = m[0] == IM_NEG_INF ? 0.f : fast_exp2(m[0] - mm), a1 = m1 == IM_NEG_INF ? 0.f : fast_exp2(m1 - mm);
       m[0] = mm;
-      l[0] = a0 * l[0] + a1 * l1;
+      l[0] = !again && (l[0] > ROW_SUM_MAX || l1 > ROW_SUM_MAX) ? __builtin_inff() : a0 * l[0] + a1 * l1;   // (a sum can be infinite)
 #pragma unroll
       for (int r = 0; r < 16; ++r) oacc[0][0][r] = a0 * (kg ? oacc[NDB - 1][0][r] : oacc[0][0][r]) + a1 * in[r * 64 + lane];
     }
@@ -358,7 +434,6 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WGS * N
       if (row >= qlen || (again && !redo[qb])) continue;
       const long t = qrow0 + row;
       if (hi == 0 && kg == 0 && lse2) lse2[(g.cu ? (long)h * g.R : ((long)b * g.H + h) * g.T) + qoff + row] = lt > 0.f ? -(m[qb] + log2f(lt)) : IM_NEG_INF;  // negated
-      float nf = 0.f;
 #pragma unroll
       for (int db = 0; db < NDB / KS; ++db)
 #pragma unroll
@@ -367,14 +442,11 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WGS * N
           if (DH < 64 && (dh0 < wo || dh0 >= wo + DH)) continue;
           float v[4];
 #pragma unroll
-          for (int jj = 0; jj < 4; ++jj) {
-            v[jj] = oacc[db][qb][4 * i + jj] * inv;
-            nf = fmaf(v[jj], 0.f, nf);   // 0, or NaN as soon as one value is not finite
-          }
+          for (int jj = 0; jj < 4; ++jj) v[jj] = oacc[db][qb][4 * i + jj] * inv;
           const u32x2 pk = {pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3])};
           *(u32x2*)(O + t * ldo + cg * 64 + dh0) = pk;
         }
-      redo[qb] = lt < 0x1p-80f || lt > 0x1p100f || (nf != nf && lt == lt);
+      redo[qb] = lt < 0.5f || lt > ROW_SUM_MAX;
       any |= redo[qb];
     }
     return any;

@@ -144,6 +144,20 @@ __device__ __forceinline__ void block_masks(const unsigned* pm, int kb, int hi, 
   for (int e = 0; e < 4; ++e) { m[e] = a[e]; m[4 + e] = b[e]; }
 }
 
+// x as a sum of three bf16 numbers, packed {p0 | p1 << 16, p2}.  -inf (the log-sum-exp of a row without a valid key) becomes
+// bf16's lowest value, which has the same effect on a finite score and may meet a zero; NaN and +inf stay as they are.
+__device__ __forceinline__ u32x2 bf16_parts(float x) {
+  x = x == IM_NEG_INF ? -3.3895313892515355e38f : x;
+  const unsigned a = pack_bf16(x, 0.f) & 0xffffu;
+  const float ra = x - __uint_as_float(a << 16);
+  const bool fin = (a & 0x7f80u) != 0x7f80u;
+  const unsigned b = fin ? pack_bf16(ra, 0.f) & 0xffffu : 0u;
+  const float rb = ra - __uint_as_float(b << 16);
+  const unsigned c = fin ? pack_bf16(rb, 0.f) & 0xffffu : 0u;
+  return u32x2{a | (b << 16), c};
+}
+constexpr unsigned ONES01 = 0x3f803f80u, ONES2 = 0x00003f80u;   // the three ones that the parts meet
+
 // Streamed operands (K and V tiles in the forward and dQ kernels, Q and dO tiles in the dK/dV
 // kernel) go from global memory straight into a ring of RING_NST LDS stages with asynchronous
 // global->LDS copies (no staging registers, no LDS store instructions): stage t+2 is requested

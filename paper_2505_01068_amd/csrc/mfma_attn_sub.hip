@@ -19,19 +19,6 @@
 
 namespace imattn {
 
-// x as a sum of three bf16 numbers, packed {p0 | p1 << 16, p2}.  -inf (the log-sum-exp of a row without a valid key) becomes
-// bf16's lowest value, which has the same effect on a finite score and may meet a zero; NaN and +inf stay as they are.
-__device__ __forceinline__ u32x2 bf16_parts(float x) {
-  x = x == IM_NEG_INF ? -3.3895313892515355e38f : x;
-  const unsigned a = pack_bf16(x, 0.f) & 0xffffu;
-  const float ra = x - __uint_as_float(a << 16);
-  const bool fin = (a & 0x7f80u) != 0x7f80u;
-  const unsigned b = fin ? pack_bf16(ra, 0.f) & 0xffffu : 0u;
-  const float rb = ra - __uint_as_float(b << 16);
-  const unsigned c = fin ? pack_bf16(rb, 0.f) & 0xffffu : 0u;
-  return u32x2{a | (b << 16), c};
-}
-constexpr unsigned ONES01 = 0x3f803f80u, ONES2 = 0x00003f80u;   // the three ones that the parts meet
 __device__ const u32x4 k_ones_chunk = {ONES01, ONES2, 0u, 0u};
 
 // Head of wave `wave` in unit hw of four heads, and where its columns lie: 64-column group, first column in it, k-step (16

@@ -28,6 +28,11 @@ constexpr int LDS_LD = 72;  // bf16 per row of a padded LDS tile (128 x 128 GEMM
 __device__ __forceinline__ f32x16 mfma32(bf16x8 a, bf16x8 b, f32x16 c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
 }
+// contraction of 8: lane half h holds elements 4 h .. 4 h + 3
+__device__ __forceinline__ f32x16 mfma32_k8(u32x2 a, u32x2 b, f32x16 c) {
+  typedef short s16x4 __attribute__((ext_vector_type(4)));
+  return __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(__builtin_bit_cast(s16x4, a), __builtin_bit_cast(s16x4, b), c, 0, 0, 0);
+}
 
 // m (0..31) -> actual row fed as MFMA row m (see header comment)
 __device__ __forceinline__ int perm32(int m) {

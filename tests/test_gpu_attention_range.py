@@ -1,5 +1,5 @@
-"""bf16 matrix-core forward: rows whose sum of exponentials leaves the range of the pass without a reference are taken
-again with a running one, whatever the other rows of their workgroup hold, and change no bit of those."""
+"""bf16 matrix-core attention: scores far from 0, exactness of a probability of 1, and the forward's second pass for rows whose
+sum of exponentials leaves the range of the first one."""
 import numpy as np
 import pytest
 import torch
@@ -57,3 +57,34 @@ def test_shifted_rows(d, H, seg, padding):
     same[[r for r in range(n) if bits[r] != 0.0]] = False
     same = torch.from_numpy(same).cuda()
     assert torch.equal(y[:, same], y0[:, same])
+
+
+@pytest.mark.parametrize("left", [0, 5, 37, 64, 99])
+@pytest.mark.parametrize("d,H", [(64, 8), (64, 4), (128, 2)])
+def test_one_valid_key_is_exact(d, H, left):
+    """With one valid key a row's probability is 1, in the backward too: V, dO and x are whole numbers, so are y and the gradients
+    of wv and wo, and dQ and dK vanish.  A reference other than the row's maximum leaves the probability off by a bf16 rounding."""
+    print(f"[case] one key d={d} H={H} key {left}", flush=True)
+    seg, n = (9, 100, 4), 6
+    g = synth.attention_inputs(n, seg, d, H, "bf16", "none", seed=17)
+    rng = np.random.default_rng(5)
+    g["wv"] = g["wo"] = np.eye(d, dtype=np.float32)
+    g["x"] = rng.integers(-4, 5, g["x"].shape).astype(np.float32)
+    g["dy"] = rng.integers(-4, 5, g["dy"].shape).astype(np.float32)
+    kp = np.ones((n, sum(seg)), np.uint8)
+    kp[:, seg[0] + left] = 0
+    g["key_pad"] = kp
+    p = Problem(g, 1 << 1)   # t reads v
+    y = p.fwd(save=True)
+    grads = p.bwd()
+    torch.cuda.synchronize()
+    y_ref, cache = p.oracle_fwd(cache=True)
+    ref = oracle.backward(cache, g["dy"])
+    whole = lambda t: t.float().cpu().numpy().astype(np.float64)  # noqa: E731
+    for b in ("bv", "bo"):
+        assert g.get(b) is None
+    assert np.array_equal(whole(y), np.rint(y_ref))
+    for name in ("dwv", "dwo"):
+        assert np.array_equal(whole(grads[name]), np.rint(ref[name])), name
+    for name in ("dwq", "dwk"):
+        assert not grads[name].any(), name
