@@ -912,14 +912,15 @@ __global__ __launch_bounds__(256, 3) void mfma_dkv_kernel(Geo g, const bf16_t* _
         sum[db][r] = (rg ? dvacc[db][0][r] : dkacc[db][0][r]) + ex[((wave ^ 1) * NDB + db) * 1024 + r * 64 + lane_e];
     const int krow_e = k0 + rb * 32 + (lane_e & 31);
     if (krow_e >= klen_seg) return;
-    const float z = kvalid[0] ? (rg ? 1.f : 0.69314718055994530942f) : 0.f;   // see below
+    const bool ok = kvalid[0];   // see below
+    const float z = rg ? 1.f : 0.69314718055994530942f;
     bf16_t* p = dQKV + (krow0 + krow_e) * ldg + (rg ? 2 * d : d) + h * 64;
 #pragma unroll
     for (int db = 0; db < NDB; ++db)
 #pragma unroll
       for (int i = 0; i < 4; ++i)
-        *(u32x2*)(p + db * 32 + 8 * i + 4 * hi_e) = u32x2{pack_bf16(sum[db][4 * i] * z, sum[db][4 * i + 1] * z),
-                                                        pack_bf16(sum[db][4 * i + 2] * z, sum[db][4 * i + 3] * z)};
+        *(u32x2*)(p + db * 32 + 8 * i + 4 * hi_e) = ok ? u32x2{pack_bf16(sum[db][4 * i] * z, sum[db][4 * i + 1] * z),
+                                                             pack_bf16(sum[db][4 * i + 2] * z, sum[db][4 * i + 3] * z)} : u32x2{0u, 0u};
     return;
   }
 #pragma unroll
@@ -927,8 +928,9 @@ __global__ __launch_bounds__(256, 3) void mfma_dkv_kernel(Geo g, const bf16_t* _
     const int row = k0 + (rb * KB + kb) * 32 + (lane_e & 31);
     if (row >= klen_seg) continue;
     const long t = krow0 + row;
-    // dK = scale dS^T Q, and the staged Q rows are scale log2(e) Q: the accumulator needs a factor ln 2
-    const float zk = kvalid[kb] ? 0.69314718055994530942f : 0.f, zv = kvalid[kb] ? 1.f : 0.f;
+    // dK = scale dS^T Q, and the staged Q rows are scale log2(e) Q: the accumulator needs a factor ln 2.  A masked key's accumulators
+    // are dropped, not multiplied by 0: no log-sum-exp bounds its scores, and 2^(S - lse) may have been infinite.
+    constexpr float zk = 0.69314718055994530942f;
 #pragma unroll
     for (int db = 0; db < NDB; ++db)
 #pragma unroll
@@ -936,10 +938,9 @@ __global__ __launch_bounds__(256, 3) void mfma_dkv_kernel(Geo g, const bf16_t* _
         const int dh0 = db * 32 + 8 * i + 4 * hi_e;  // column inside the 64-column group
         const u32x2 pk = {pack_bf16(dkacc[db][kb][4 * i] * zk, dkacc[db][kb][4 * i + 1] * zk),
                           pack_bf16(dkacc[db][kb][4 * i + 2] * zk, dkacc[db][kb][4 * i + 3] * zk)};
-        const u32x2 pv = {pack_bf16(dvacc[db][kb][4 * i] * zv, dvacc[db][kb][4 * i + 1] * zv),
-                          pack_bf16(dvacc[db][kb][4 * i + 2] * zv, dvacc[db][kb][4 * i + 3] * zv)};
-        *(u32x2*)(dQKV + t * ldg + d + h * 64 + dh0) = pk;
-        *(u32x2*)(dQKV + t * ldg + 2 * d + h * 64 + dh0) = pv;
+        const u32x2 pv = {pack_bf16(dvacc[db][kb][4 * i], dvacc[db][kb][4 * i + 1]), pack_bf16(dvacc[db][kb][4 * i + 2], dvacc[db][kb][4 * i + 3])};
+        *(u32x2*)(dQKV + t * ldg + d + h * 64 + dh0) = kvalid[kb] ? pk : u32x2{0u, 0u};
+        *(u32x2*)(dQKV + t * ldg + 2 * d + h * 64 + dh0) = kvalid[kb] ? pv : u32x2{0u, 0u};
       }
   }
 }

@@ -373,15 +373,19 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WGS, WGS)))
   for (int kb = 0; kb < KB; ++kb) {
     const int row = k0 + kb * 32 + (lane_e & 31);
     if (row >= klen_seg) continue;
-    // dK = scale dS^T Q, and the staged Q rows are scale log2(e) Q: the accumulator needs a factor ln 2
-    const float zk = kvalid[kb] ? 0.69314718055994530942f : 0.f, zv = kvalid[kb] ? 1.f : 0.f;
+    // dK = scale dS^T Q, and the staged Q rows are scale log2(e) Q: the accumulator needs a factor ln 2.  A masked key's accumulators
+    // are dropped, not multiplied by 0: no log-sum-exp bounds its scores, and 2^(S - lse) may have been infinite.
+    constexpr float zk = 0.69314718055994530942f;
+    const bool ok = kvalid[kb];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int dh0 = sh.db0 * 32 + 8 * i + 4 * (lane_e >> 5);  // column inside the 64-column group
       if (dh0 < sh.wo || dh0 >= sh.wo + DH) continue;
       bf16_t* o = dQKV + (krow0 + row) * ldg + d + sh.cg * 64 + dh0;
-      *(u32x2*)o = u32x2{pack_bf16(dkacc[kb][4 * i] * zk, dkacc[kb][4 * i + 1] * zk), pack_bf16(dkacc[kb][4 * i + 2] * zk, dkacc[kb][4 * i + 3] * zk)};
-      *(u32x2*)(o + d) = u32x2{pack_bf16(dvacc[kb][4 * i] * zv, dvacc[kb][4 * i + 1] * zv), pack_bf16(dvacc[kb][4 * i + 2] * zv, dvacc[kb][4 * i + 3] * zv)};
+      const u32x2 pk = {pack_bf16(dkacc[kb][4 * i] * zk, dkacc[kb][4 * i + 1] * zk), pack_bf16(dkacc[kb][4 * i + 2] * zk, dkacc[kb][4 * i + 3] * zk)};
+      const u32x2 pv = {pack_bf16(dvacc[kb][4 * i], dvacc[kb][4 * i + 1]), pack_bf16(dvacc[kb][4 * i + 2], dvacc[kb][4 * i + 3])};
+      *(u32x2*)o = ok ? pk : u32x2{0u, 0u};
+      *(u32x2*)(o + d) = ok ? pv : u32x2{0u, 0u};
     }
   }
 }

@@ -14,15 +14,27 @@ pytestmark = pytest.mark.gpu
 LIVE = (1 << 1) | (1 << 4) | (1 << 8)
 
 
-def shifted(d, H, seg, padding, shift_bits):
+def padded_rows(g, seg):
+    """[B, T_m]: the rows that are masked as keys."""
+    n, T = g["x"].shape[:2]
+    if g["key_pad"] is not None:
+        return g["key_pad"] != 0
+    if g["valid_len"] is None:
+        return np.zeros((n, T), bool)
+    pos = np.concatenate([np.arange(k) for k in seg])
+    return pos[None, :] >= np.asarray(g["valid_len"])[:, np.repeat(np.arange(len(seg)), seg)]
+
+
+def shifted(d, H, seg, padding, shift_bits, left=0.0):
     """Every score of query row r of t is off by shift_bits[r] in the exponent of 2, by the first channel of each head: 8 in
-    every key, the shift in the query.  Softmax does not see it; 2^s overflows or vanishes."""
+    every valid key, the shift in the query.  Softmax does not see it; 2^s overflows or vanishes.  left: what the masked keys' rows
+    hold there, so that their scores lie elsewhere than those that the row's sum is made of."""
     g = synth.attention_inputs(2, seg, d, H, "bf16", padding, seed=31)
     dh = d // H
     eye = np.eye(d, dtype=np.float32)
     g["wq"], g["wk"] = eye, eye
     x = g["x"].copy()
-    x[:, :, ::dh] = 8.0
+    x[:, :, ::dh] = np.where(padded_rows(g, seg), np.float32(left), np.float32(8.0))[:, :, None]
     a = np.zeros(seg[0], np.float32)
     a[:len(shift_bits)] = np.asarray(shift_bits, np.float32) / (8.0 * g["scale"] * np.log2(np.e))
     x[:, :seg[0], ::dh] = np.asarray(torch.from_numpy(a).to(torch.bfloat16).float())[None, :, None]
@@ -30,15 +42,15 @@ def shifted(d, H, seg, padding, shift_bits):
     return g
 
 
-@pytest.mark.parametrize("padding", ["none", "valid_len", "key_pad"])
+@pytest.mark.parametrize("padding,left", [("none", 0.0), ("valid_len", 0.0), ("valid_len", 96.0), ("key_pad", 0.0), ("key_pad", -96.0)])
 @pytest.mark.parametrize("d,H,seg", [(64, 8, (70, 150, 33)), (64, 4, (33, 97, 20)), (192, 24, (65, 64, 65)), (128, 2, (140, 200, 50))])
-def test_shifted_rows(d, H, seg, padding):
+def test_shifted_rows(d, H, seg, padding, left):
     n = seg[0]
     bits = [0.0] * n
     for r, v in ((1, 180.0), (2, -180.0), (5, 110.0), (6, -95.0), (n - 1, 300.0), (n // 2, -300.0)):
         bits[r] = v
-    print(f"[case] shifted rows d={d} H={H} seg={seg} {padding}", flush=True)
-    g = shifted(d, H, seg, padding, bits)
+    print(f"[case] shifted rows d={d} H={H} seg={seg} {padding} {left}", flush=True)
+    g = shifted(d, H, seg, padding, bits, left)
     p = Problem(g, LIVE)
     y = p.fwd(save=True).clone()
     grads = p.bwd()
@@ -49,8 +61,10 @@ def test_shifted_rows(d, H, seg, padding):
     # dV, dO and P from the saved log-sum-exp; the first channels of dQ and dK are differences of large numbers here
     for name in ("dwv", "dwo"):
         assert_close(grads[name], ref[name], TOL["bf16"], name)
+    for name in ("dx", "dwq", "dwk"):
+        assert torch.isfinite(grads[name]).all(), name
     assert torch.equal(p.fwd(save=False), y)
-    q = Problem(shifted(d, H, seg, padding, [0.0] * n), LIVE)
+    q = Problem(shifted(d, H, seg, padding, [0.0] * n, left), LIVE)
     y0 = q.fwd(save=False)
     torch.cuda.synchronize()
     same = np.ones(sum(seg), bool)
