@@ -608,6 +608,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WGS, WGS)))
     keys1 = seg_get(sg.len, seg1);
     ic.left = keys1 - KT;
     if (ic.left <= 0) next_seg();
+    if (keys1 == 0) {   // the segment has no valid key: what its rows hold must not meet a dS of 0
+      cslot = 1;
+      keys1 = issue();
+      if (keys1 < 0) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the copy ends before its stage is used otherwise
+    }
   }
   int keys2 = NST > 2 ? issue() : -1;
   while (keys1 >= 0) {

@@ -100,7 +100,7 @@ __device__ __forceinline__ void tile_segment(const int (&order)[IM_MAX_SEG], con
 // loop at every segment's end.  Padded rows need no memory for off and rows, so that a kernel requests the first tile of the
 // first live segment before it waits for anything: the valid lengths, its own rows and that tile come in one round trip
 // where they were two or three (workgroups of the small shapes live for 4 to 8 stages).  If the segment turns out to have no valid
-// key its tile is consumed with every key masked.
+// key its tile is not consumed.
 struct SegTable { int off[IM_MAX_SEG], rows[IM_MAX_SEG], len[IM_MAX_SEG]; };
 __device__ __forceinline__ int seg_get(const int (&v)[IM_MAX_SEG], int s) { return __builtin_amdgcn_readfirstlane(v[s]); }
 // off and rows (len = rows) of the wave's table; qs_off, qs_rows: of segment qs; returns the segments of `live` that have rows

@@ -102,3 +102,35 @@ def test_one_valid_key_is_exact(d, H, left):
         assert np.array_equal(whole(grads[name]), np.rint(ref[name])), name
     for name in ("dwq", "dwk"):
         assert not grads[name].any(), name
+
+
+@pytest.mark.parametrize("d,H,seg,n", [(64, 8, (70, 90, 40), 3), (64, 4, (33, 64, 65), 3), (128, 2, (140, 90, 50), 3), (128, 2, (140, 90, 50), 100)])
+def test_first_segment_without_valid_keys(d, H, seg, n):
+    """The first live segment of a row has no valid key, and its K and V rows are infinite: they are multiplied by nothing.
+    (3 and 100 samples: 64- and 128-row tiles at head dimension 64.)"""
+    print(f"[case] empty first segment d={d} H={H} seg={seg} n={n}", flush=True)
+    g = synth.attention_inputs(n, seg, d, H, "bf16", "none", seed=23)
+    vl = np.tile(np.array(seg, np.int32), (n, 1))
+    vl[:, 1] = 0
+    vl[1, 2] = 0              # no key at all
+    vl[2, 1], vl[2, 2] = 10, 0
+    vl[3:, 2] = np.arange(n - 3) % (seg[2] + 1)
+    g["valid_len"] = vl
+    x = g["x"].copy()
+    v_rows = (np.arange(sum(seg)) >= seg[0]) & (np.arange(sum(seg)) < seg[0] + seg[1])
+    x[:, :, 0] = 0.0
+    x[np.ix_(vl[:, 1] == 0, v_rows, [0])] = 2.0 ** 127
+    g["x"] = x
+    for name, v in (("wq", 0.0), ("wk", 4.0), ("wv", 4.0)):
+        w = g[name].copy()
+        w[0, :] = v
+        g[name] = w
+    p = Problem(g, (1 << 1) | (1 << 2))   # t reads v and a
+    y = p.fwd(save=True)
+    grads = p.bwd()
+    torch.cuda.synchronize()
+    y_ref, cache = p.oracle_fwd(cache=True)
+    ref = oracle.backward(cache, g["dy"])
+    assert_close(y, y_ref, TOL["bf16"], "y")
+    for name in ("dx", "dwq", "dwk", "dwv", "dwo"):
+        assert_close(grads[name], ref[name], TOL["bf16"], name)
