@@ -403,7 +403,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WGS * N
 
   // ---- epilogue: normalise, write O rows, O^T columns and the log-sum-exp ----
   // Returns whether a row left the range of the pass without a running reference: its sum, relative to the reference, above 2^24
-  // (where a running one moves), or below what the reference itself contributes (scores of -inf in the whole first block).
+  // (where a running one moves), or below what the reference itself contributes (scores of -inf in the whole first block).  A row
+  // without a valid key has no reference and its results already: 0 and -inf.
   bool redo[QB];
   auto finish = [&](bool again) __attribute__((always_inline)) {
     bool any = false;
@@ -446,7 +447,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WGS * N
           const u32x2 pk = {pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3])};
           *(u32x2*)(O + t * ldo + cg * 64 + dh0) = pk;
         }
-      redo[qb] = lt < 0.5f || lt > ROW_SUM_MAX;
+      redo[qb] = (lt < 0.5f && m[qb] != IM_NEG_INF) || lt > ROW_SUM_MAX;
       any |= redo[qb];
     }
     return any;

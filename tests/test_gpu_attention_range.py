@@ -134,3 +134,25 @@ def test_first_segment_without_valid_keys(d, H, seg, n):
     assert_close(y, y_ref, TOL["bf16"], "y")
     for name in ("dx", "dwq", "dwk", "dwv", "dwo"):
         assert_close(grads[name], ref[name], TOL["bf16"], name)
+
+
+@pytest.mark.parametrize("d,H", [(64, 8), (64, 4), (128, 2)])
+def test_masked_samples_take_one_pass(d, H):
+    """Keys that are all masked give zeros, and no row asks for a second pass: the call takes no longer than with valid keys
+    (with a second pass, the slower one, it took 2.0 to 3.0 times as long)."""
+    print(f"[case] all keys masked d={d} H={H}", flush=True)
+    g = synth.attention_inputs(16, (64, 2048), d, H, "bf16", "none", seed=3, with_dy=False)
+    times = []
+    for masked in (0, 1):
+        p = Problem(dict(g, key_pad=np.full(g["x"].shape[:2], masked, np.uint8)), 1 << 3)   # v reads v
+        p.fwd()
+        ev = [torch.cuda.Event(enable_timing=True) for _ in range(9)]
+        ev[0].record()
+        for e in ev[1:]:
+            y = p.fwd()
+            e.record()
+        torch.cuda.synchronize()
+        times.append(min(a.elapsed_time(b) for a, b in zip(ev, ev[1:])))
+        assert torch.isfinite(y).all() and (not masked or not y.any())
+    print(f"    {times[0] * 1e3:.1f} us, masked {times[1] * 1e3:.1f} us", flush=True)
+    assert times[1] < 1.2 * times[0]
