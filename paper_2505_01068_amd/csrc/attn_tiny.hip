@@ -18,10 +18,13 @@ namespace imattn {
 constexpr int TINY_ROWS = 8, TINY_KEYS = 40, TINY_D = 32, TINY_THREADS = 512;   // of a workgroup: query rows, keys at most,
                                                                                    // padded width, threads
 
-// the weights' columns a thread multiplies by: all requests of a column before its first use
+// the weights' columns a thread multiplies by: all requests of a column before its first use; zeros from the width on (the last
+// row again would do for finite weights, but its infinity times the operand's 0 is NaN)
 __device__ __forceinline__ void load_col(const float* w, int d, int c, float (&out)[TINY_D]) {
 #pragma unroll
   for (int k = 0; k < TINY_D; ++k) out[k] = w[(long)min(k, d - 1) * d + c];
+#pragma unroll
+  for (int k = 0; k < TINY_D; ++k) out[k] = k < d ? out[k] : 0.f;
 }
 // x . w + b in 64 bits, rounded once (x holds zeros from the width on)
 template <typename W>

@@ -59,3 +59,25 @@ def test_tiny_output_over_input_and_large_scores():
     torch.cuda.synchronize()
     valid = torch.from_numpy(g["key_pad"] == 0).cuda()
     assert torch.equal(z[valid], y[valid])
+
+
+@pytest.mark.parametrize("name", ["wq", "wk", "wv", "wo"])
+@pytest.mark.parametrize("d,H", [(4, 1), (26, 2), (30, 5), (32, 4)])
+def test_tiny_infinite_weights(d, H, name):
+    # An infinite element in a weight's last row makes the same infinities and NaN as in the three launches (which a call with
+    # saved takes), at widths that fill the kernel's 32 columns and at others.
+    print(f"[case] tiny infinity in {name} d={d}", flush=True)
+    g = synth.attention_inputs(2, (8, 9, 10), d, H, "fp32", "none", seed=6, bias=True)
+    g["x"][:, :, d - 1] = np.abs(g["x"][:, :, d - 1]) + np.float32(0.1)   # infinities of one sign
+    g[name] = g[name].copy()
+    g[name][d - 1, d // 2] = np.inf
+    p = Problem(g, oracle.IM_IFM_FORWARD)
+    y, z = p.fwd(save=False), p.fwd(save=True)
+    torch.cuda.synchronize()
+    for kind in (torch.isnan, torch.isposinf, torch.isneginf):
+        assert torch.equal(kind(y), kind(z)), kind.__name__
+    fin = z.isfinite()
+    if name in ("wv", "wo"):
+        assert not z.isnan().all() and z.isinf().any()
+    if fin.any():
+        assert (y[fin] - z[fin]).abs().max() <= TOL["fp32"] * z[fin].abs().max()
