@@ -169,3 +169,38 @@ class PackedProblem(Problem):
                 scale = grad_scale(n, r, floor, np.max(np.sum(np.abs(ref["dk"]), axis=(0, 1))))
                 errs[n] = assert_close(v, r, tol, what + " " + n, scale)
         return errs
+
+
+def rows_leaving_the_range(p, cache, bits=24):
+    """[B, H, T_m]: rows of Problem p whose sum of exponentials exceeds 2^bits relative to the largest score of their first 32-key
+    block with a valid key (the blocks of a segment start at its first row): the bf16 forward takes them a second time."""
+    g, seg = p.g, p.g["seg_len"]
+    q, k, H = cache["q"], cache["k"], g["n_heads"]
+    B_, T, d = q.shape
+    off = np.concatenate([[0], np.cumsum(seg)])
+    ok = np.ones((B_, T), bool) if g.get("key_pad") is None else np.asarray(g["key_pad"]) == 0
+    lengths = getattr(p, "lengths", g.get("valid_len"))
+    if lengths is not None:
+        for s, n in enumerate(seg):
+            ok[:, off[s]:off[s] + n] &= np.arange(n)[None, :] < np.asarray(lengths)[:, s:s + 1]
+    out = np.zeros((B_, H, T), bool)
+    split = lambda a: a.reshape(B_, T, H, d // H).transpose(0, 2, 1, 3)  # noqa: E731
+    scores = split(q) @ split(k).transpose(0, 1, 3, 2) * (g["scale"] * np.log2(np.e))
+    scores = np.where(ok[:, None, None, :], scores, -np.inf)
+    for i, n in enumerate(seg):
+        ref = np.full((B_, H, n), -np.inf)
+        cols = []
+        for j, m in enumerate(seg):
+            if not (p.lm >> (i * len(seg) + j)) & 1:
+                continue
+            s = scores[:, :, off[i]:off[i] + n, off[j]:off[j] + m]
+            cols.append(s)
+            for c in range(0, m, 32):
+                ref = np.where(np.isinf(ref), s[..., c:c + 32].max(-1), ref)
+        if cols:
+            a = np.concatenate(cols, -1)
+            top = a.max(-1)
+            with np.errstate(invalid="ignore"):
+                total = np.where(np.isinf(top), -np.inf, top + np.log2(np.exp2(a - top[..., None]).sum(-1)))
+                out[:, :, off[i]:off[i] + n] = total - ref > bits
+    return out

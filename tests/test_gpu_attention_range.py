@@ -6,7 +6,7 @@ import torch
 
 import oracle
 from paper_2505_01068_amd import synth
-from tests.gpu_util import Problem, assert_close, TOL
+from tests.gpu_util import PackedProblem, Problem, assert_close, rows_leaving_the_range, TOL
 
 pytestmark = pytest.mark.gpu
 
@@ -156,3 +156,62 @@ def test_masked_samples_take_one_pass(d, H):
         assert torch.isfinite(y).all() and (not masked or not y.any())
     print(f"    {times[0] * 1e3:.1f} us, masked {times[1] * 1e3:.1f} us", flush=True)
     assert times[1] < 1.2 * times[0]
+
+
+# rows of t: how far their scores rise from one 32-key block of v to the next, and at its third block alone, in the exponent of 2
+GROWTH = {1: (30, 0), 2: (13, 0), 5: (-30, 0), 6: (0, 60), 9: (130, 0), -1: (30, -100)}
+
+
+def growing(n, d, H, seg, padding, rows):
+    g = synth.attention_inputs(n, seg, d, H, "bf16", padding if padding != "packed" else "none", seed=37)
+    dh = d // H
+    g["wq"] = g["wk"] = np.eye(d, dtype=np.float32)
+    block = np.concatenate([np.arange(k) for k in seg]) // 32
+    x = g["x"].copy()
+    x[:, :, ::dh] = block[None, :, None]
+    x[:, :, 1::dh] = (block == 2)[None, :, None]
+    x[:, :seg[0], ::dh] = x[:, :seg[0], 1::dh] = 0.0
+    for r, (rise, bump) in rows.items():
+        x[:, r % seg[0], ::dh] = rise / (g["scale"] * np.log2(np.e))
+        x[:, r % seg[0], 1::dh] = bump / (g["scale"] * np.log2(np.e))
+    g["x"] = synth.to_bf16_grid(np.where(padded_rows(g, seg)[:, :, None], np.float32(0), x))
+    return g
+
+
+# 64- and 128-row tiles at head dimension 64 (2 and 70 samples), tiles of half the height (the 50 rows of t that read 500 keys)
+@pytest.mark.parametrize("padding", ["none", "valid_len", "key_pad", "packed"])
+@pytest.mark.parametrize("d,H,seg,n", [(64, 8, (70, 150, 33), 2), (64, 4, (33, 97, 20), 2), (128, 2, (140, 200, 50), 2),
+                                       (128, 2, (140, 200, 50), 70), (64, 8, (50, 500, 375), 2), (64, 4, (50, 500, 375), 2)])
+def test_scores_that_outgrow_the_first_block(d, H, seg, n, padding):
+    """Rows whose sum exceeds 2^24 relative to their first block's maximum, some beyond 2^100 and 2^128, are taken a second time with a
+    moving reference; the other rows of their workgroups keep every bit."""
+    print(f"[case] growing scores d={d} H={H} seg={seg} n={n} {padding}", flush=True)
+    live = (1 << 1) | (1 << 5) | (1 << 8)   # t reads v, v reads a, a reads a: no row of t is a key
+    lengths = [[s if b % 2 == 0 else s - s // 4 for s in seg] for b in range(n)]
+    make = lambda rows: (PackedProblem(growing(n, d, H, seg, padding, rows), live, lengths) if padding == "packed"  # noqa: E731
+                         else Problem(growing(n, d, H, seg, padding, rows), live))
+    p = make(GROWTH)
+    y = p.fwd(save=True).clone()
+    grads = p.bwd()
+    torch.cuda.synchronize()
+    g = p.g
+    pack = (lambda a: synth.pack_rows(a, p.lengths, seg)) if padding == "packed" else (lambda a: a)
+    y_ref, cache = oracle.forward(g["x"], g["wq"], g["wk"], g["wv"], g["wo"], seg, live, H, g["scale"], key_pad=g["key_pad"],
+                                  valid_len=p.lengths if padding == "packed" else g["valid_len"], return_cache=True)
+    again = rows_leaving_the_range(p, cache)
+    for r in (1, 2, 6, 9):
+        assert again[0, :, r].all() and not again[:, :, 5].any()
+    dy = g["dy"] if padding != "packed" else synth.unpack_rows(pack(g["dy"]), p.lengths, seg)
+    ref = oracle.backward(cache, dy)
+    assert_close(y, pack(y_ref), TOL["bf16"], "y")
+    for name in ("dwv", "dwo"):
+        assert_close(grads[name], ref[name], TOL["bf16"], name)
+    for name in ("dx", "dwq", "dwk"):
+        assert torch.isfinite(grads[name]).all(), name
+    assert torch.equal(p.fwd(save=False), y)
+    y0 = make({}).fwd(save=False)
+    torch.cuda.synchronize()
+    same = np.ones((n, sum(seg)), bool)
+    same[:, [r % seg[0] for r in GROWTH]] = False
+    same = torch.from_numpy(pack(same)).cuda()
+    assert torch.equal(y[same], y0[same])

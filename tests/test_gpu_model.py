@@ -110,3 +110,38 @@ def test_model_at_the_benchmark_shape_and_depth(padding):
     ref = oracle.gsit_model_forward(g["x"][pick], m, seg, H, g["scale"], H, scale_intra, valid_len=vl)
     e = assert_close(out[pick], ref, TOL["bf16"], f"model at benchmark shape/{padding}")
     say(f"    error {e:.2e} on batch elements {pick}")
+
+
+@pytest.mark.parametrize("padding", ["none", "key_pad"])
+@pytest.mark.parametrize("H", [8, 4])
+def test_model_scores_that_outgrow_the_first_block(H, padding):
+    """The two inter-modal encoders in shared launches: every row of both scores one key of its second 32-key block 100 (head
+    dimension 8) or 80 (16) in the exponent of 2 above the others, so that each is taken again with a moving reference."""
+    say(f"[case] model, growing scores H={H} {padding}")
+    d, seg, d_ff, at = 64, (50, 130, 75), 128, 40
+    dh = d // H
+    g = synth.attention_inputs(3, seg, d, H, "bf16", padding, seed=405, with_dy=False)
+    off = np.concatenate([[0], np.cumsum(seg)])[:-1] + at
+    x = g["x"].copy()
+    x[:, :, 0] = 0.0
+    x[:, off] = 0.0
+    x[:, off, 0] = 10.0
+    g["x"] = x
+    if g["key_pad"] is not None:
+        g["key_pad"][:, off] = 0
+    m = synth.model_params(d, d_ff, 2 * d_ff, 1, 1, 3, 3, 405, dtype="bf16")
+    top = (1 - 1 / d) / np.sqrt((1 / d) * (1 - 1 / d))   # LayerNorm of a row with one element
+    for p in (m["fwd_layers"][0], m["bwd_layers"][0]):
+        p["ln1_g"], p["ln1_b"] = np.ones(d, np.float32), np.zeros(d, np.float32)
+        p["wq"], p["wk"] = np.zeros((d, d), np.float32), p["wk"].copy()
+        p["wk"][:, ::dh] = 0.0
+        p["wk"][0, ::dh] = 1.0
+        p["bq"] = np.zeros(d, np.float32)
+        p["bq"][::dh] = synth.to_bf16_grid(np.float32((100.0 if H == 8 else 80.0) / (top * g["scale"] * np.log2(np.e))))
+        u = oracle.layer_norm(x, p["ln1_g"], p["ln1_b"], 1e-5)[:, :, 0]
+        bits = float(p["bq"][0]) * g["scale"] * np.log2(np.e) * u
+        for s, n in zip(off - at, seg):
+            assert (bits[:, s + at] - bits[:, s:s + 32].max(1) > 48).all()
+    out, ref = run_model(g, m, "bf16", d_ff, 2 * d_ff, 8)
+    e = assert_close(out, ref, TOL["bf16"], "model/growing scores")
+    say(f"    error {e:.2e}")
