@@ -24,6 +24,7 @@ import sys
 HERE = os.path.join(os.path.dirname(os.path.abspath(__file__)), "paper_2505_01068_amd")
 COPY_BYTES = 1 << 30
 KERNEL_SOURCES = {"mfma_": ["csrc/mfma_attn.hip", "csrc/mfma_attn_common.hpp", "csrc/mfma_common.hpp", "csrc/common.hpp"],
+                  "sub_": ["csrc/mfma_attn_sub.hip", "csrc/mfma_attn_common.hpp", "csrc/mfma_common.hpp", "csrc/common.hpp"],
                   "split_": ["csrc/attn_split.hip", "csrc/mfma_common.hpp", "csrc/common.hpp"]}
 
 

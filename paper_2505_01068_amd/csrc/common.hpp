@@ -53,18 +53,6 @@ __device__ __forceinline__ int seg_rows(const Geo& g, int b, int s) {
 __device__ __forceinline__ long seg_stat0(const Geo& g, int b, int h, int s) {
   return g.cu ? (long)h * g.R + g.cu[b * g.n_seg + s] : ((long)b * g.H + h) * g.T + g.seg_off[s];
 }
-// The same for callers whose b and s are wave-uniform (the matrix-core kernels): the row offsets
-// read from memory are moved to scalar registers, so pointers derived from them stay scalar.
-__device__ __forceinline__ int cu_u(const Geo& g, int i) { return __builtin_amdgcn_readfirstlane(g.cu[i]); }
-__device__ __forceinline__ long useg_row0(const Geo& g, int b, int s) {
-  return g.cu ? (long)cu_u(g, b * g.n_seg + s) : (long)b * g.T + g.seg_off[s];
-}
-__device__ __forceinline__ int useg_rows(const Geo& g, int b, int s) {
-  return g.cu ? cu_u(g, b * g.n_seg + s + 1) - cu_u(g, b * g.n_seg + s) : g.seg_len[s];
-}
-__device__ __forceinline__ long useg_stat0(const Geo& g, int b, int h, int s) {
-  return g.cu ? (long)h * g.R + cu_u(g, b * g.n_seg + s) : ((long)b * g.H + h) * g.T + g.seg_off[s];
-}
 // rows of the [rows, .] tensors of a shape (host)
 inline long shape_rows(const im_shape_t* s) {
   if (s->cu_rows) return (long)s->total_rows;
@@ -73,10 +61,9 @@ inline long shape_rows(const im_shape_t* s) {
   return (long)s->batch * T;
 }
 
-// tile index -> (segment, first row).  Same code on host (schedule listing)
-// and device (kernels), so the listing is what the kernels execute.
-__host__ __device__ inline void decode_tile(const int* order, const int* prefix, int nord, int tile_rows, int tile,
-                                            int& seg, int& start) {
+// tile index -> (segment, first row), for the host's listing of a schedule.  The kernels look the same tables up, at their own
+// tile heights.
+inline void decode_tile(const int* order, const int* prefix, int nord, int tile_rows, int tile, int& seg, int& start) {
   int k = 0;
   while (k + 1 < nord && tile >= prefix[k + 1]) ++k;
   seg = order[k];

@@ -47,16 +47,17 @@ namespace imattn {
 // PAIR: two problems of the same shape in one launch (two encoders side by side; see Geo::pair_B): grid z = 2 B.
 constexpr float ROW_SUM_MAX = 16777216.f;   // sum of exponentials relative to the reference, beyond which the reference moves
 constexpr float BF16_MAX = 3.3895313892515355e38f;
-template <int QB, int DH, int NST, int WGS, int NW, bool PAIR, int KS = 1>
-__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WGS * NW / 4, WGS * NW / 4))) void mfma_fwd_kernel(Geo g, const bf16_t* __restrict__ QKV, long ld,
+constexpr int FWD_NST = 2;                  // stages of its ring
+template <int QB, int DH, int WGS, bool PAIR, int KS = 1>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WGS, WGS))) void mfma_fwd_kernel(Geo g, const bf16_t* __restrict__ QKV, long ld,
                                                        const int32_t* __restrict__ valid_len,
                                                        const uint8_t* __restrict__ key_pad, bf16_t* __restrict__ O,
                                                        long ldo, float* __restrict__ lse2) {
-  __shared__ __attribute__((aligned(1024))) bf16_t sT[NST * RING_STAGE];  // per stage: K tile, V tile
-  __shared__ __attribute__((aligned(256))) unsigned sKP[NST * KT];        // per stage: key_pad bytes of the 64 keys, one per dword
-  __shared__ __attribute__((aligned(16))) unsigned sPM[NW][KT / 2];       // key masks of the wave's tile
-  __shared__ SegTable sSeg[NW];
-  __shared__ int sRedo[NW];
+  __shared__ __attribute__((aligned(1024))) bf16_t sT[FWD_NST * RING_STAGE];  // per stage: K tile, V tile
+  __shared__ __attribute__((aligned(256))) unsigned sKP[FWD_NST * KT];        // per stage: key_pad bytes of the 64 keys, one per dword
+  __shared__ __attribute__((aligned(16))) unsigned sPM[4][KT / 2];            // key masks of the wave's tile
+  __shared__ SegTable sSeg[4];
+  __shared__ int sRedo[4];
   // Sub-head mode: ones, four to each of the 16-key steps of a tile, where the step's V^T fragment has its rows in the tile.
   // The lanes whose four rows of the fragment are not the head's read them: those rows of O^T are then the row sum of P,
   // which the matrix cores take beside the product (a dot product per pair of probabilities otherwise, 8 of 40 vector
@@ -68,13 +69,13 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WGS * N
   int tile, h, b;
   xcd_tile_index(g.q_tile_prefix, g.q_nord, g.cu != nullptr, g.even_cus, tile, h, b);
   constexpr bool HEADW = DH != 64;
-  // HEADW (sub-head mode, where the head count is a multiple of 4): the NW waves of a workgroup are NW heads of one 64-column group over the SAME 32 QB query
-  // rows (grid.y counts groups of NW heads) -- the K/V stream is shared as before, but a tile is 64 rows instead of
+  // HEADW (sub-head mode, where the head count is a multiple of 4): the four waves of a workgroup are four heads of one 64-column group over the SAME 32 QB
+  // query rows (grid.y counts groups of four heads) -- the K/V stream is shared as before, but a tile is 64 rows instead of
   // 256, which at segment lengths like 50 / 500 / 375 leaves 4 % of the rows of the tiles empty instead of 28 %.
-  if (HEADW) h = h * NW + wave;
+  if (HEADW) h = h * 4 + wave;
   const bool second = PAIR && b >= g.pair_B;
   const int bm = second ? b - g.pair_B : b;   // batch element of the masks (valid_len, key_pad)
-  constexpr int WG_ROWS = HEADW ? 32 * QB : 32 * NW * QB / KS;
+  constexpr int WG_ROWS = HEADW ? 32 * QB : 128 * QB / KS;
   static_assert(KS == 1 || (DH == 64 && QB == 1 && !PAIR && !HEADW), "");
   const int rb = wave / KS, kg = wave % KS;   // row block of the tile, key block of a stage (KS = 2)
   // HALF: the launch may give the query segment with the longest key range tiles of half the height (one query
@@ -100,44 +101,9 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WGS * N
   const int s0 = DH == 64 ? 0 : wo >> 4;  // k-step and O^T block that hold the head (sub-head mode)
   const int db0 = DH == 64 ? 0 : wo >> 5;
 
-  const RingLane rl = ring_lane<NW>(wave, lane, cg);
-  const unsigned ldb = (unsigned)ld * 2u;
-  const RingLaneOff rlo = ring_lane_off(rl, ldb, ldb);
-  const bool kp_copy = wave == 0 && key_pad != nullptr;   // this wave fetches a stage's key_pad bytes
-  TileCursor ic = {0u, 0, 0};
-  int islot = 0;
-  RingFeed feed = {nullptr, nullptr, 0};
-  const uint8_t* feed_kp = nullptr;
-  // K and V rows of a segment; rows past the valid length but inside the segment are fetched and masked
-  auto seg_begin = [&](int seg) __attribute__((always_inline)) {
-    const int off = seg_get(sg.off, seg);
-    feed.a = (const char*)(QKV + (row_b + off) * ld + d);
-    feed.b = feed.a + (size_t)d * 2;
-    feed.rows = seg_get(sg.rows, seg);
-    if (key_pad) feed_kp = key_pad + ((g.cu ? 0 : (long)bm * g.T) + off);
-  };
-  auto copy = [&]() __attribute__((always_inline)) {   // requests the feed's next tile
-    // The key_pad bytes travel with the stage: an ordinary load inside the loop would wait for every copy before it.
-    if (kp_copy) dma1_off(feed_kp, (unsigned)min(lane_id(), feed.rows - 1), sKP + islot * KT);
-    feed_kp += KT;
-    ring_feed_issue<NW>(rl, rlo, feed, ldb, ldb, wave, sT + islot * RING_STAGE);
-    islot = (islot + 1 == NST) ? 0 : islot + 1;
-  };
-  auto next_seg = [&]() __attribute__((always_inline)) { if (cursor_next_seg(ic, sg)) seg_begin(ic.seg); };
-  // requests the next stage; returns its number of valid keys (key_pad aside), -1 if there is none
-  auto issue = [&]() __attribute__((always_inline)) {
-    if (ic.left <= 0) return -1;
-    const int keys = ic.left;
-    copy();
-    ic.left -= KT;
-    if (ic.left <= 0) next_seg();
-    return keys;
-  };
+  KvStream<FWD_NST> ring(sg, sT, sKP, QKV + row_b * ld + d, key_pad ? key_pad + (g.cu ? 0 : (long)bm * g.T) : nullptr, ld, d, wave, lane, cg);
   const int seg1 = row_set ? __builtin_ctz(row_set) : 0;   // its first tile goes ahead of everything
-  if (row_set) {
-    seg_begin(seg1);
-    copy();
-  }
+  if (row_set) ring.first(seg1);
   const int valid = valid_len ? valid_len[bm * g.n_seg + min(lane, g.n_seg - 1)] : 0;
 
   // Q operand (B of S^T = K Q^T): lane holds query row lo of each block, 8 consecutive dh per k-step
@@ -227,25 +193,22 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WGS * N
 #pragma unroll
         for (int r = 0; r < 16; ++r) oacc[db][qb][r] = 0.f;
     }
-    static_assert(NST == 2, "the slot refilled while a tile is consumed is that of the tile before");
+    static_assert(FWD_NST == 2, "the slot refilled while a tile is consumed is that of the tile before");
     int cslot = 0, keys = 0, keys1;   // valid keys of the present tile, of the one requested after it (-1: there is none)
-    ic.rest = key_set;
     if (!GUARD && row_set) {   // the first one is under way
-      ic.rest &= ~(1u << seg1);
-      keys1 = seg_get(sg.len, seg1);
-      ic.left = keys1 - KT;
-      if (ic.left <= 0) next_seg();
+      keys1 = ring.begin(seg1, key_set);
     } else {
-      islot = 0;
-      next_seg();
-      keys1 = issue();
+      ring.slot = 0;
+      ring.at.rest = key_set;
+      ring.next_seg();
+      keys1 = ring.issue();
     }
     const bf16_t *sK = sT, *sV = sT;
     bool need_mask = false;   // tail tile or key_pad present (wave-uniform)
     auto advance = [&]() __attribute__((always_inline)) {   // to the next tile
-      ring_wait<NW>(false);
+      ring_wait(false);
       keys = keys1;
-      keys1 = issue();
+      keys1 = ring.issue();
       sK = sT + cslot * RING_STAGE;
       sV = sK + KT * SW_LD;
       need_mask = keys < KT || key_pad != nullptr;
@@ -465,7 +428,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WGS * N
   __syncthreads();
   int again = 0;
 #pragma unroll
-  for (int w = 0; w < NW; ++w) again |= sRedo[w];
+  for (int w = 0; w < 4; ++w) again |= sRedo[w];
   if (__builtin_expect(__builtin_amdgcn_readfirstlane(again), 0)) {
     run(std::integral_constant<bool, true>{});
     finish(true);
@@ -509,42 +472,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WGS, WGS)))
 
   constexpr int NS = 4, NDB = 2;   // k-steps of the scores, 32-column blocks of the gradients
 
-  const RingLane rl = ring_lane(wave, lane, h);
-  const unsigned ldb = (unsigned)ld * 2u;
-  const RingLaneOff rlo = ring_lane_off(rl, ldb, ldb);
-  const bool kp_copy = wave == 0 && key_pad != nullptr;   // this wave fetches a stage's key_pad bytes
-  TileCursor ic = {0u, 0, 0};
-  int islot = 0;
-  RingFeed feed = {nullptr, nullptr, 0};
-  const uint8_t* feed_kp = nullptr;
-  // as in the forward
-  auto seg_begin = [&](int seg) __attribute__((always_inline)) {
-    const long row0 = row_b + seg_get(sg.off, seg);
-    feed.a = (const char*)(QKV + row0 * ld + d);
-    feed.b = feed.a + (size_t)d * 2;
-    feed.rows = seg_get(sg.rows, seg);
-    if (key_pad) feed_kp = key_pad + row0;
-  };
-  auto copy = [&]() __attribute__((always_inline)) {
-    if (kp_copy) dma1_off(feed_kp, (unsigned)min(lane_id(), feed.rows - 1), sKP + islot * KT);
-    feed_kp += KT;
-    ring_feed_issue(rl, rlo, feed, ldb, ldb, wave, sT + islot * RING_STAGE);
-    islot = (islot + 1 == NST) ? 0 : islot + 1;
-  };
-  auto next_seg = [&]() __attribute__((always_inline)) { if (cursor_next_seg(ic, sg)) seg_begin(ic.seg); };
-  auto issue = [&]() __attribute__((always_inline)) {
-    if (ic.left <= 0) return -1;
-    const int keys = ic.left;
-    copy();
-    ic.left -= KT;
-    if (ic.left <= 0) next_seg();
-    return keys;
-  };
+  KvStream<NST> ring(sg, sT, sKP, QKV + row_b * ld + d, key_pad ? key_pad + row_b : nullptr, ld, d, wave, lane, h);
   const int seg1 = row_set ? __builtin_ctz(row_set) : 0;   // its first tile goes ahead of everything
-  if (row_set) {
-    seg_begin(seg1);
-    copy();
-  }
+  if (row_set) ring.first(seg1);
   const int valid = valid_len ? valid_len[b * g.n_seg + min(lane, g.n_seg - 1)] : 0;
 
   bf16x8 qreg[QB][NS], greg[QB][NS];
@@ -603,24 +533,20 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WGS, WGS)))
 
   const unsigned key_set = valid_len ? seg_lens_table(sg, valid, row_set, lane) : row_set;
   int cslot = 0, keys1 = -1;
-  ic.rest = key_set;
   if (row_set) {   // the first stage is under way
-    ic.rest &= ~(1u << seg1);
-    keys1 = seg_get(sg.len, seg1);
-    ic.left = keys1 - KT;
-    if (ic.left <= 0) next_seg();
+    keys1 = ring.begin(seg1, key_set);
     if (keys1 == 0) {   // the segment has no valid key: what its rows hold must not meet a dS of 0
       cslot = 1;
-      keys1 = issue();
+      keys1 = ring.issue();
       if (keys1 < 0) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the copy ends before its stage is used otherwise
     }
   }
-  int keys2 = NST > 2 ? issue() : -1;
+  int keys2 = NST > 2 ? ring.issue() : -1;
   while (keys1 >= 0) {
-    ring_wait(keys2 >= 0, kp_copy);
+    ring_wait(keys2 >= 0, ring.kp_copy);
     const int keys = keys1;
     keys1 = keys2;
-    (NST > 2 ? keys2 : keys1) = issue();
+    (NST > 2 ? keys2 : keys1) = ring.issue();
     const bf16_t* sK = sT + cslot * RING_STAGE;
     const bf16_t* sV = sK + KT * SW_LD;
     cslot = (cslot + 1 == NST) ? 0 : cslot + 1;
@@ -963,8 +889,7 @@ __global__ __launch_bounds__(256, 3) void mfma_dkv_kernel(Geo g, const bf16_t* _
 //     4 workgroups need spills);
 //   dK/dV: 1 key block per wave, 3 workgroups per CU.  (Sub-head backward: mfma_attn_sub.hip.)
 constexpr int FWD_QB = 1, FWD_QB_SUB = 2, DQ_QB = 1, DKV_KB = 1;
-constexpr int FWD_NST = 2, FWD_WGS = 4, FWD_NW = 4;   // ring stages, workgroups per CU, waves per workgroup (head dim 64)
-constexpr int FWD_SUB_NST = 2, FWD_SUB_WGS = 4;       // the same in sub-head mode (4 waves)
+constexpr int FWD_WGS = 4, FWD_SUB_WGS = 4;           // workgroups per CU, head dimension 64 and sub-head mode
 constexpr int DQ_NST = 3, DQ_WGS = 3;                 // dQ at head dim 64
 // CUs per XCD if a launch of `wgs` workgroups is dealt out evenly (see xcd_tile_index), else 0: all resident with `per_cu`
 // workgroups on a CU, of different lengths.  Lengths of packed rows are not known here.
@@ -989,7 +914,7 @@ static void retile(const Geo& g, const int* order, int nord, int rows, int* pref
   for (int k = 0; k < nord; ++k) prefix[k + 1] = prefix[k] + (g.seg_len[order[k]] + rows - 1) / rows;
 }
 // sub-head mode: four heads of a 64-column group per workgroup, 64-row tiles
-int mfma_fwd_tile_rows(int dh) { return dh == 64 ? 32 * FWD_NW * FWD_QB : 32 * FWD_QB_SUB; }
+int mfma_fwd_tile_rows(int dh) { return dh == 64 ? 128 * FWD_QB : 32 * FWD_QB_SUB; }
 int mfma_dq_tile_rows() { return 128 * DQ_QB; }
 int mfma_dkv_tile_rows() { return 128 * DKV_KB; }
 
@@ -1043,10 +968,10 @@ void launch_mfma_fwd(const Geo& g_in, const bf16_t* qkv, long ld, const int32_t*
   g.even_cus = g.dh == 64 ? even_cus(g, g.q_nord, (long)nt * g.H * g.B, FWD_WGS) : 0u;
   ProfScope ps(PF_ATTN_FWD, st);
   const dim3 grid(nt, g.H, g.B), gridw(nt, g.H / 4, g.B);
-  if (split) hipLaunchKernelGGL((mfma_fwd_kernel<FWD_QB, 64, FWD_NST, FWD_WGS, FWD_NW, false, 2>), grid, dim3(64 * FWD_NW), 0, st, g, qkv, ld, valid_len, key_pad, o, ldo, lse2);
-  else if (g.dh == 64) hipLaunchKernelGGL((mfma_fwd_kernel<FWD_QB, 64, FWD_NST, FWD_WGS, FWD_NW, false>), grid, dim3(64 * FWD_NW), 0, st, g, qkv, ld, valid_len, key_pad, o, ldo, lse2);
-  else if (g.dh == 16) hipLaunchKernelGGL((mfma_fwd_kernel<FWD_QB_SUB, 16, FWD_SUB_NST, FWD_SUB_WGS, 4, false>), gridw, dim3(256), 0, st, g, qkv, ld, valid_len, key_pad, o, ldo, lse2);
-  else hipLaunchKernelGGL((mfma_fwd_kernel<FWD_QB_SUB, 8, FWD_SUB_NST, FWD_SUB_WGS, 4, false>), gridw, dim3(256), 0, st, g, qkv, ld, valid_len, key_pad, o, ldo, lse2);
+  if (split) hipLaunchKernelGGL((mfma_fwd_kernel<FWD_QB, 64, FWD_WGS, false, 2>), grid, dim3(256), 0, st, g, qkv, ld, valid_len, key_pad, o, ldo, lse2);
+  else if (g.dh == 64) hipLaunchKernelGGL((mfma_fwd_kernel<FWD_QB, 64, FWD_WGS, false>), grid, dim3(256), 0, st, g, qkv, ld, valid_len, key_pad, o, ldo, lse2);
+  else if (g.dh == 16) hipLaunchKernelGGL((mfma_fwd_kernel<FWD_QB_SUB, 16, FWD_SUB_WGS, false>), gridw, dim3(256), 0, st, g, qkv, ld, valid_len, key_pad, o, ldo, lse2);
+  else hipLaunchKernelGGL((mfma_fwd_kernel<FWD_QB_SUB, 8, FWD_SUB_WGS, false>), gridw, dim3(256), 0, st, g, qkv, ld, valid_len, key_pad, o, ldo, lse2);
 }
 
 // Forward of two problems of the same shape (masks g0 / g1) in one launch; their rows follow each other in
@@ -1067,8 +992,8 @@ void launch_mfma_fwd_pair(const Geo& g0, const Geo& g1, const bf16_t* qkv, long 
   for (int i = 0; i <= IM_MAX_SEG; ++i) g.q_tile_prefix2[i] = g1.q_tile_prefix[i];
   ProfScope ps(PF_ATTN_FWD, st);
   const dim3 gridw(g.q_tile_prefix[g.q_nord], g.H / 4, 2 * g.B);
-  if (g.dh == 16) hipLaunchKernelGGL((mfma_fwd_kernel<FWD_QB_SUB, 16, FWD_SUB_NST, FWD_SUB_WGS, 4, true>), gridw, dim3(256), 0, st, g, qkv, ld, valid_len, key_pad, o, ldo, lse2);
-  else hipLaunchKernelGGL((mfma_fwd_kernel<FWD_QB_SUB, 8, FWD_SUB_NST, FWD_SUB_WGS, 4, true>), gridw, dim3(256), 0, st, g, qkv, ld, valid_len, key_pad, o, ldo, lse2);
+  if (g.dh == 16) hipLaunchKernelGGL((mfma_fwd_kernel<FWD_QB_SUB, 16, FWD_SUB_WGS, true>), gridw, dim3(256), 0, st, g, qkv, ld, valid_len, key_pad, o, ldo, lse2);
+  else hipLaunchKernelGGL((mfma_fwd_kernel<FWD_QB_SUB, 8, FWD_SUB_WGS, true>), gridw, dim3(256), 0, st, g, qkv, ld, valid_len, key_pad, o, ldo, lse2);
 }
 
 void launch_mfma_bwd(const Geo& g_in, const bf16_t* qkv, long ld, const bf16_t* o, const bf16_t* d_o, long ldo,

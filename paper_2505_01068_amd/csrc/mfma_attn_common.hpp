@@ -81,7 +81,8 @@ __device__ __forceinline__ void xcd_tile_index(const int (&prefix)[IM_MAX_SEG + 
   b = (int)bb;
 }
 
-// decode_tile with constant indexes: the tables come in one scalar load each, where a loop over them is a chain of loads.
+// Segment of a tile and the tile's position in it, with constant indexes: the tables come in one scalar load each, where a loop over
+// them is a chain of loads.
 // k: position of the segment in `order`.
 __device__ __forceinline__ void tile_segment(const int (&order)[IM_MAX_SEG], const int (&prefix)[IM_MAX_SEG + 1], int nord,
                                              int tile, int& seg, int& in_seg, int& k) {
@@ -182,19 +183,16 @@ __device__ __forceinline__ bool cursor_next_seg(TileCursor& c, const SegTable& t
   return true;
 }
 
-// Per-lane constants of the ring copies: the two tile rows whose chunk positions this lane fills
-// and the byte offset of the logical chunk inside a row of head h.
+// Per-lane constants of the ring copies: the two tile rows (32 apart) whose chunk positions this lane fills in each streamed matrix,
+// and the byte offset of the logical chunk inside a row of head h.  Workgroups have four waves.
 struct RingLane {
   int trow0, trow1;
   unsigned col0, col1;
 };
-// NW = waves per workgroup: with 4 waves a lane fills chunk positions in two tile rows (trow0, trow0 + 32) of
-// each streamed matrix, with 8 waves in one row (trow1 / col1 unused).
-template <int NW = 4>
 __device__ __forceinline__ RingLane ring_lane(int wave, int lane, int h) {
   RingLane r;
   r.trow0 = wave * 8 + (lane >> 3);
-  r.trow1 = NW == 4 ? r.trow0 + 32 : r.trow0;
+  r.trow1 = r.trow0 + 32;
   r.col0 = (unsigned)(h * 64 + (((lane & 7) ^ sw_f(r.trow0)) << 3)) * 2u;
   r.col1 = (unsigned)(h * 64 + (((lane & 7) ^ sw_f(r.trow1)) << 3)) * 2u;
   return r;
@@ -213,46 +211,101 @@ __device__ __forceinline__ RingLaneOff ring_lane_off(const RingLane& rl, unsigne
   return {__umul24((unsigned)rl.trow0, pitch_a) + rl.col0, __umul24((unsigned)rl.trow0, pitch_b) + rl.col0,
           __umul24((unsigned)rl.trow1, pitch_a) + rl.col1, __umul24((unsigned)rl.trow1, pitch_b) + rl.col1};
 }
-// Request the next 64-row tile pair of the segment into LDS stage `stage` (4 copies per wave with 4 waves, 2
-// with 8; row pitches in bytes) and advance the feed.  Only the last tile of a segment can be ragged; its
-// missing rows repeat the segment's last row.
-template <int NW = 4>
+// Request the next 64-row tile pair of the segment into LDS stage `stage` (4 copies per wave; row pitches in bytes) and advance the
+// feed.  Only the last tile of a segment can be ragged; its missing rows repeat the segment's last row.
 __device__ __forceinline__ void ring_feed_issue(const RingLane& rl, const RingLaneOff& lo, RingFeed& f, unsigned pitch_a,
                                                 unsigned pitch_b, int wave, bf16_t* stage) {
   if (f.rows >= KT) {
     dma16_off(f.a, lo.a0, stage + wave * 512);
     dma16_off(f.b, lo.b0, stage + KT * SW_LD + wave * 512);
-    if (NW == 4) {
-      dma16_off(f.a, lo.a1, stage + (4 + wave) * 512);
-      dma16_off(f.b, lo.b1, stage + KT * SW_LD + (4 + wave) * 512);
-    }
+    dma16_off(f.a, lo.a1, stage + (4 + wave) * 512);
+    dma16_off(f.b, lo.b1, stage + KT * SW_LD + (4 + wave) * 512);
   } else {
     const unsigned r0c = (unsigned)min(rl.trow0, f.rows - 1), r1c = (unsigned)min(rl.trow1, f.rows - 1);
     dma16_off(f.a, __umul24(r0c, pitch_a) + rl.col0, stage + wave * 512);
     dma16_off(f.b, __umul24(r0c, pitch_b) + rl.col0, stage + KT * SW_LD + wave * 512);
-    if (NW == 4) {
-      dma16_off(f.a, __umul24(r1c, pitch_a) + rl.col1, stage + (4 + wave) * 512);
-      dma16_off(f.b, __umul24(r1c, pitch_b) + rl.col1, stage + KT * SW_LD + (4 + wave) * 512);
-    }
+    dma16_off(f.a, __umul24(r1c, pitch_a) + rl.col1, stage + (4 + wave) * 512);
+    dma16_off(f.b, __umul24(r1c, pitch_b) + rl.col1, stage + KT * SW_LD + (4 + wave) * 512);
   }
   f.a += (size_t)KT * pitch_a;
   f.b += (size_t)KT * pitch_b;
   f.rows -= KT;
 }
-// wait for the oldest stage requested (later: one more stage has been requested after it; 4 copies per wave and stage with
-// 4 waves, 2 with 8), then meet the other waves: the wanted stage is visible to all, and every wave
-// has finished reading the stage consumed before it.
+// wait for the oldest stage requested (later: one more stage has been requested after it; 4 copies per wave and stage), then meet
+// the other waves: the wanted stage is visible to all, and every wave has finished reading the stage consumed before it.
 // `extra`: this wave issues one more copy per stage, ahead of the others.
-template <int NW = 4>
 __device__ __forceinline__ void ring_wait(bool later, bool extra = false) {
   if (later) {
-    if (NW != 4) asm volatile("s_waitcnt vmcnt(2)" ::: "memory");
-    else if (extra) asm volatile("s_waitcnt vmcnt(5)" ::: "memory");
+    if (extra) asm volatile("s_waitcnt vmcnt(5)" ::: "memory");
     else asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
   } else {
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   }
   __builtin_amdgcn_s_barrier();
 }
+
+// The K and V tiles of the live segments that a workgroup's query rows read, through a ring of NST stages (forward and dQ).
+template <int NST>
+struct KvStream {
+  const SegTable& sg;
+  bf16_t* sT;               // the stages: K tile, V tile
+  unsigned* sKP;            // per stage: key_pad bytes of the 64 keys, one per dword
+  const bf16_t* k;          // K columns of the batch element's first row; V is d columns further on
+  const uint8_t* key_pad;   // of that row, or NULL
+  long ld, d;
+  int wave;
+  RingLane rl;
+  RingLaneOff rlo;
+  bool kp_copy;             // this wave fetches a stage's key_pad bytes
+  TileCursor at = {0u, 0, 0};
+  int slot = 0;
+  RingFeed feed = {nullptr, nullptr, 0};
+  const uint8_t* feed_kp = nullptr;
+
+  __device__ __forceinline__ KvStream(const SegTable& t, bf16_t* st, unsigned* skp, const bf16_t* kcols, const uint8_t* kpad, long pitch,
+                                      long width, int w, int lane, int group)
+      : sg(t), sT(st), sKP(skp), k(kcols), key_pad(kpad), ld(pitch), d(width), wave(w), rl(ring_lane(w, lane, group)),
+        rlo(ring_lane_off(rl, (unsigned)pitch * 2u, (unsigned)pitch * 2u)), kp_copy(w == 0 && kpad != nullptr) {}
+  // K and V rows of a segment; rows past the valid length but inside the segment are fetched and masked
+  __device__ __forceinline__ void seg_begin(int seg) {
+    const int off = seg_get(sg.off, seg);
+    feed.a = (const char*)(k + off * ld);
+    feed.b = feed.a + (size_t)d * 2;
+    feed.rows = seg_get(sg.rows, seg);
+    if (key_pad) feed_kp = key_pad + off;
+  }
+  __device__ __forceinline__ void copy() {   // requests the feed's next tile
+    // The key_pad bytes travel with the stage: an ordinary load inside the loop would wait for every copy before it.
+    if (kp_copy) dma1_off(feed_kp, (unsigned)min(lane_id(), feed.rows - 1), sKP + slot * KT);
+    feed_kp += KT;
+    ring_feed_issue(rl, rlo, feed, (unsigned)ld * 2u, (unsigned)ld * 2u, wave, sT + slot * RING_STAGE);
+    slot = (slot + 1 == NST) ? 0 : slot + 1;
+  }
+  __device__ __forceinline__ void next_seg() {
+    if (cursor_next_seg(at, sg)) seg_begin(at.seg);
+  }
+  // requests the next stage; returns its number of valid keys (key_pad aside), -1 if there is none
+  __device__ __forceinline__ int issue() {
+    if (at.left <= 0) return -1;
+    const int keys = at.left;
+    copy();
+    at.left -= KT;
+    if (at.left <= 0) next_seg();
+    return keys;
+  }
+  // The first tile of segment seg, ahead of everything; begin(): its valid keys, once the lengths are in the table, and the cursor
+  // behind it (set: the segments with valid keys).
+  __device__ __forceinline__ void first(int seg) {
+    seg_begin(seg);
+    copy();
+  }
+  __device__ __forceinline__ int begin(int seg, unsigned set) {
+    at.rest = set & ~(1u << seg);
+    const int keys = seg_get(sg.len, seg);
+    at.left = keys - KT;
+    if (at.left <= 0) next_seg();
+    return keys;
+  }
+};
 
 }  // namespace imattn

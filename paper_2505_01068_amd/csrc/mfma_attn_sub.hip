@@ -31,14 +31,18 @@ __device__ __forceinline__ SubHead sub_head(int hw, int wave) {
 }
 
 // ------------------------------------------------------------------------------------------
-// dQ and -delta = -rowsum(dO * O).  lane <-> query row; a wave owns QB blocks of 32 rows of its head.
-template <int DH, int QB, int NST, int WGS>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WGS, WGS))) void sub_dq_kernel(
+// dQ and -delta = -rowsum(dO * O).  lane <-> query row; a wave owns 32 rows of its head.
+//
+// Four workgroups per CU (78 registers at head dimension 8, 100 at 16).  Two row blocks per wave and three workgroups: 21.8 against 22.4 us at 32 x 50/500/375 rows,
+// 8 heads of 8, but 26.7 against 21.7 at 8 heads of 16.
+constexpr int SUB_DQ_NST = 2, SUB_DQ_WGS = 4;
+template <int DH>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(SUB_DQ_WGS, SUB_DQ_WGS))) void sub_dq_kernel(
     Geo g, const bf16_t* __restrict__ QKV, long ld, const bf16_t* __restrict__ O, const bf16_t* __restrict__ dO, long ldo,
     const float* __restrict__ lse2, const int32_t* __restrict__ valid_len, const uint8_t* __restrict__ key_pad,
     float* __restrict__ delta, bf16_t* __restrict__ dQKV, long ldg) {
-  __shared__ __attribute__((aligned(1024))) bf16_t sT[NST * RING_STAGE];  // per stage: K tile, V tile
-  __shared__ __attribute__((aligned(256))) unsigned sKP[NST * KT];        // per stage: key_pad bytes of the 64 keys, one per dword
+  __shared__ __attribute__((aligned(1024))) bf16_t sT[SUB_DQ_NST * RING_STAGE];  // per stage: K tile, V tile
+  __shared__ __attribute__((aligned(256))) unsigned sKP[SUB_DQ_NST * KT];        // per stage: key_pad bytes of the 64 keys, one per dword
   __shared__ __attribute__((aligned(16))) unsigned sPM[4][KT / 2];        // key masks of the wave's tile
   __shared__ __attribute__((aligned(16))) unsigned sOne[4];               // ones chunk: what the spare slots of K and V hold
   __shared__ SegTable sSeg[4];
@@ -49,7 +53,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WGS, WGS)))
   const SubHead sh = sub_head<DH>(hw, wave);
   int qs, q0, ord;
   tile_segment(g.q_order, g.q_tile_prefix, g.q_nord, tile, qs, q0, ord);
-  q0 *= 32 * QB;
+  q0 *= 32;
   int qoff, qlen;
   SegTable& sg = sSeg[wave];
   const unsigned row_set = seg_rows_table(sg, g, b, g.q_live[qs], lane, qs, qoff, qlen);
@@ -59,76 +63,36 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WGS, WGS)))
   const long stat0 = (g.cu ? (long)sh.h * g.R : ((long)b * g.H + sh.h) * g.T) + qoff;
   const bool spare = DH == 8 && hi != sh.half;   // this lane half's slots of the k-step are not the head's
 
-  const RingLane rl = ring_lane(wave, lane, sh.cg);
-  const unsigned ldb = (unsigned)ld * 2u;
-  const RingLaneOff rlo = ring_lane_off(rl, ldb, ldb);
-  const bool kp_copy = wave == 0 && key_pad != nullptr;   // this wave fetches a stage's key_pad bytes
-  TileCursor ic = {0u, 0, 0};
-  int islot = 0;
-  RingFeed feed = {nullptr, nullptr, 0};
-  const uint8_t* feed_kp = nullptr;
-  auto seg_begin = [&](int seg) __attribute__((always_inline)) {
-    const long row0 = row_b + seg_get(sg.off, seg);
-    feed.a = (const char*)(QKV + row0 * ld + d);
-    feed.b = feed.a + (size_t)d * 2;
-    feed.rows = seg_get(sg.rows, seg);
-    if (key_pad) feed_kp = key_pad + row0;
-  };
-  auto copy = [&]() __attribute__((always_inline)) {   // requests the feed's next tile
-    if (kp_copy) dma1_off(feed_kp, (unsigned)min(lane_id(), feed.rows - 1), sKP + islot * KT);
-    feed_kp += KT;
-    ring_feed_issue(rl, rlo, feed, ldb, ldb, wave, sT + islot * RING_STAGE);
-    islot = (islot + 1 == NST) ? 0 : islot + 1;
-  };
-  auto next_seg = [&]() __attribute__((always_inline)) { if (cursor_next_seg(ic, sg)) seg_begin(ic.seg); };
-  auto issue = [&]() __attribute__((always_inline)) {   // returns the stage's valid keys (key_pad aside), -1 if there is none
-    if (ic.left <= 0) return -1;
-    const int keys = ic.left;
-    copy();
-    ic.left -= KT;
-    if (ic.left <= 0) next_seg();
-    return keys;
-  };
+  KvStream<SUB_DQ_NST> ring(sg, sT, sKP, QKV + row_b * ld + d, key_pad ? key_pad + row_b : nullptr, ld, d, wave, lane, sh.cg);
   const int seg1 = row_set ? __builtin_ctz(row_set) : 0;   // its first tile goes ahead of everything
-  if (row_set) {
-    seg_begin(seg1);
-    copy();
-  }
+  if (row_set) ring.first(seg1);
   const int valid = valid_len ? valid_len[b * g.n_seg + min(lane, g.n_seg - 1)] : 0;
 
   // B operands: Q and dO rows, and the parts of -lse and -delta (in the spare slots, or a k-step of their own)
-  bf16x8 qreg[QB], greg[QB], ls[QB], dl[QB];
+  const int row = q0 + lo, rc = min(row, qlen - 1);
+  const long t = qrow0 + rc;
+  const int col = sh.cg * 64 + sh.s0 * 16 + hi * 8;
+  const u32x4 qv = *(const u32x4*)(QKV + t * ld + col), gv = *(const u32x4*)(dO + t * ldo + col);
+  const u32x4 ov = *(const u32x4*)(O + t * ldo + col);
+  const float lv = lse2[stat0 + rc];
+  float acc = 0.f;
 #pragma unroll
-  for (int qb = 0; qb < QB; ++qb) {
-    const int row = q0 + qb * 32 + lo, rc = min(row, qlen - 1);
-    const long t = qrow0 + rc;
-    const int col = sh.cg * 64 + sh.s0 * 16 + hi * 8;
-    const u32x4 qv = *(const u32x4*)(QKV + t * ld + col), gv = *(const u32x4*)(dO + t * ldo + col);
-    const u32x4 ov = *(const u32x4*)(O + t * ldo + col);
-    const float lv = lse2[stat0 + rc];
-    float acc = 0.f;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      acc = fmaf(__uint_as_float(gv[e] << 16), __uint_as_float(ov[e] << 16), acc);
-      acc = fmaf(__uint_as_float(gv[e] & 0xffff0000u), __uint_as_float(ov[e] & 0xffff0000u), acc);
-    }
-    if (spare) acc = 0.f;
-    acc += __shfl_xor(acc, 32, 64);
-    if (hi == 0 && row < qlen) delta[stat0 + rc] = -acc;
-    const u32x2 lp = bf16_parts(lv), dp = bf16_parts(-acc);
-    const u32x4 l4 = {lp[0], lp[1], 0u, 0u}, d4 = {dp[0], dp[1], 0u, 0u}, z = {0u, 0u, 0u, 0u};
-    qreg[qb] = as_bf16x8(spare ? l4 : qv);
-    greg[qb] = as_bf16x8(spare ? d4 : gv);
-    ls[qb] = as_bf16x8(hi == 0 ? l4 : z);
-    dl[qb] = as_bf16x8(hi == 0 ? d4 : z);
+  for (int e = 0; e < 4; ++e) {
+    acc = fmaf(__uint_as_float(gv[e] << 16), __uint_as_float(ov[e] << 16), acc);
+    acc = fmaf(__uint_as_float(gv[e] & 0xffff0000u), __uint_as_float(ov[e] & 0xffff0000u), acc);
   }
+  if (spare) acc = 0.f;
+  acc += __shfl_xor(acc, 32, 64);
+  if (hi == 0 && row < qlen) delta[stat0 + rc] = -acc;
+  const u32x2 lp = bf16_parts(lv), dp = bf16_parts(-acc);
+  const u32x4 l4 = {lp[0], lp[1], 0u, 0u}, d4 = {dp[0], dp[1], 0u, 0u}, z = {0u, 0u, 0u, 0u};
+  const bf16x8 qreg = as_bf16x8(spare ? l4 : qv), greg = as_bf16x8(spare ? d4 : gv);
+  const bf16x8 ls = as_bf16x8(hi == 0 ? l4 : z), dl = as_bf16x8(hi == 0 ? d4 : z);
   const bf16x8 ones = as_bf16x8(u32x4{ONES01, ONES2, 0u, 0u});
 
-  f32x16 dqacc[QB];
+  f32x16 dqacc;
 #pragma unroll
-  for (int qb = 0; qb < QB; ++qb)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) dqacc[qb][r] = 0.f;
+  for (int r = 0; r < 16; ++r) dqacc[r] = 0.f;
 
   // Row fragments of K and V: byte offset in a tile of the lane's 16 bytes, or the ones
   const int prow = perm32(lo);
@@ -138,32 +102,25 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WGS, WGS)))
 
   // The compiler does not see the asynchronous copies in its vmcnt bookkeeping: consuming the loaded registers here makes it
   // wait for their (ordinary) loads now, not inside the ring loop.
-#pragma unroll
-  for (int qb = 0; qb < QB; ++qb) asm volatile("" :: "v"(qreg[qb]), "v"(greg[qb]), "v"(ls[qb]), "v"(dl[qb]));
+  asm volatile("" :: "v"(qreg), "v"(greg), "v"(ls), "v"(dl));
 
   const unsigned key_set = valid_len ? seg_lens_table(sg, valid, row_set, lane) : row_set;
   int cslot = 0, keys1 = -1;
-  ic.rest = key_set;
   if (row_set) {   // the first stage is under way
-    ic.rest &= ~(1u << seg1);
-    keys1 = seg_get(sg.len, seg1);
-    ic.left = keys1 - KT;
-    if (ic.left <= 0) next_seg();
+    keys1 = ring.begin(seg1, key_set);
     if (keys1 == 0) {   // the segment has no valid key: what its rows hold must not meet a dS of 0
       cslot = 1;
-      keys1 = issue();
+      keys1 = ring.issue();
       if (keys1 < 0) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the copy ends before its stage is used otherwise
     }
   }
-  int keys2 = NST > 2 ? issue() : -1;
   while (keys1 >= 0) {
-    ring_wait(keys2 >= 0, kp_copy);
+    ring_wait(false);
     const int keys = keys1;
-    keys1 = keys2;
-    (NST > 2 ? keys2 : keys1) = issue();
+    keys1 = ring.issue();
     const bf16_t* sK = sT + cslot * RING_STAGE;
     const unsigned* kp = sKP + cslot * KT;
-    cslot = (cslot + 1 == NST) ? 0 : cslot + 1;
+    cslot ^= 1;
     const bool need_mask = keys < KT || key_pad != nullptr;
     if (need_mask) tile_masks(sPM[wave], key_pad ? kp : nullptr, keys);
     const unsigned tile_at = (unsigned)(uintptr_t)sK;
@@ -173,50 +130,32 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WGS, WGS)))
       if (kb == 1 && keys <= 32) break;
       const bf16x8 ak = lds_b128((kf_tile & (tile_at + kb * 32 * SW_LD * 2)) + kf);
       const bf16x8 av = lds_b128((kf_tile & (tile_at + (KT + kb * 32) * SW_LD * 2)) + kf);
-      f32x16 sacc[QB], pacc[QB];
+      f32x16 sacc = DH == 8 ? f32x16{} : mfma32(ones, ls, f32x16{}), pacc = DH == 8 ? f32x16{} : mfma32(ones, dl, f32x16{});
+      sacc = mfma32(ak, qreg, sacc);   // S^T  = K Q^T - lse
+      pacc = mfma32(av, greg, pacc);   // dP^T = V dO^T - delta
+      float ds[16];
 #pragma unroll
-      for (int qb = 0; qb < QB; ++qb) {
-        sacc[qb] = DH == 8 ? f32x16{} : mfma32(ones, ls[qb], f32x16{});
-        pacc[qb] = DH == 8 ? f32x16{} : mfma32(ones, dl[qb], f32x16{});
-        sacc[qb] = mfma32(ak, qreg[qb], sacc[qb]);   // S^T  = K Q^T - lse
-        pacc[qb] = mfma32(av, greg[qb], pacc[qb]);   // dP^T = V dO^T - delta
-      }
-      unsigned pmask[8];
-      if (need_mask) block_masks(sPM[wave], kb, hi, pmask);
-      bf16x8 dsb[QB][2];
-#pragma unroll
-      for (int qb = 0; qb < QB; ++qb) {
-        float ds[16];
-#pragma unroll
-        for (int r = 0; r < 16; ++r) ds[r] = fast_exp2(sacc[qb][r]) * pacc[qb][r];
-        dsb[qb][0] = pack8(ds);
-        dsb[qb][1] = pack8(ds + 8);
-        if (need_mask) {  // a masked key's dS is 0 whatever its row holds
-          dsb[qb][0] = and_bf16x8(dsb[qb][0], pmask);
-          dsb[qb][1] = and_bf16x8(dsb[qb][1], pmask + 4);
-        }
+      for (int r = 0; r < 16; ++r) ds[r] = fast_exp2(sacc[r]) * pacc[r];
+      bf16x8 dsb[2] = {pack8(ds), pack8(ds + 8)};
+      if (need_mask) {  // a masked key's dS is 0 whatever its row holds
+        unsigned pmask[8];
+        block_masks(sPM[wave], kb, hi, pmask);
+        dsb[0] = and_bf16x8(dsb[0], pmask);
+        dsb[1] = and_bf16x8(dsb[1], pmask + 4);
       }
 #pragma unroll
-      for (int half = 0; half < 2; ++half) {   // dQ^T += K^T dS^T
-        const bf16x8 a = lds_frag_tr_sw(sK, kb * 32 + half * 16, sh.db0 * 32, lane);
-#pragma unroll
-        for (int qb = 0; qb < QB; ++qb) dqacc[qb] = mfma32(a, dsb[qb][half], dqacc[qb]);
-      }
+      for (int half = 0; half < 2; ++half)   // dQ^T += K^T dS^T
+        dqacc = mfma32(lds_frag_tr_sw(sK, kb * 32 + half * 16, sh.db0 * 32, lane), dsb[half], dqacc);
     }
   }
 
+  if (row >= qlen) return;
 #pragma unroll
-  for (int qb = 0; qb < QB; ++qb) {
-    const int row = q0 + qb * 32 + lo;
-    if (row >= qlen) continue;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int dh0 = sh.db0 * 32 + 8 * i + 4 * hi;  // column inside the 64-column group
-      if (dh0 < sh.wo || dh0 >= sh.wo + DH) continue;
-      *(u32x2*)(dQKV + (qrow0 + row) * ldg + sh.cg * 64 + dh0) =
-          u32x2{pack_bf16(dqacc[qb][4 * i] * g.scale, dqacc[qb][4 * i + 1] * g.scale),
-                pack_bf16(dqacc[qb][4 * i + 2] * g.scale, dqacc[qb][4 * i + 3] * g.scale)};
-    }
+  for (int i = 0; i < 4; ++i) {
+    const int dh0 = sh.db0 * 32 + 8 * i + 4 * hi;  // column inside the 64-column group
+    if (dh0 < sh.wo || dh0 >= sh.wo + DH) continue;
+    *(u32x2*)(dQKV + (qrow0 + row) * ldg + sh.cg * 64 + dh0) =
+        u32x2{pack_bf16(dqacc[4 * i] * g.scale, dqacc[4 * i + 1] * g.scale), pack_bf16(dqacc[4 * i + 2] * g.scale, dqacc[4 * i + 3] * g.scale)};
   }
 }
 
@@ -395,12 +334,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WGS, WGS)))
   }
 }
 
-// Four workgroups per CU for dQ with one row block per wave (104 registers; two blocks and three workgroups: 21.8 against 22.4 us
-// at 32 x 50/500/375 rows, 8 heads of 8, but 26.7 against 21.7 at 8 heads of 16) and for dK/dV with one key block; two key blocks
-// halve the streamed rows and the statistics per score and take dK/dV at head dimension 8 from 24.3 to 23.4 us, while at 16 they
-// spill with three workgroups.
-constexpr int SUB_DQ_QB = 1, SUB_DQ_NST = 2, SUB_DQ_WGS = 4;
-int mfma_sub_dq_tile_rows() { return 32 * SUB_DQ_QB; }
+// dK/dV: two key blocks per wave halve the streamed rows and the statistics per score and take head dimension 8 from 24.3 to 23.4 us
+// at 32 x 50/500/375 rows, 8 heads, with three workgroups per CU; at 16 they spill, and one key block and four workgroups remain.
+int mfma_sub_dq_tile_rows() { return 32; }
 int mfma_sub_dkv_tile_rows(int dh) { return dh == 8 ? 64 : 32; }
 
 // g's tiles have the heights above; live segments only (the caller zero-fills the others)
@@ -408,8 +344,8 @@ void launch_mfma_sub_bwd(const Geo& g, const bf16_t* qkv, long ld, const bf16_t*
                          const int32_t* valid_len, const uint8_t* key_pad, float* delta, bf16_t* dqkv, long ldg, hipStream_t st) {
   const dim3 gq(g.q_tile_prefix[g.q_nord], g.H / 4, g.B), gk(g.k_tile_prefix[g.k_nord], g.H / 4, g.B);
   { ProfScope ps(PF_ATTN_DQ, st);
-    if (g.dh == 8) hipLaunchKernelGGL((sub_dq_kernel<8, SUB_DQ_QB, SUB_DQ_NST, SUB_DQ_WGS>), gq, dim3(256), 0, st, g, qkv, ld, o, d_o, ldo, lse2, valid_len, key_pad, delta, dqkv, ldg);
-    else hipLaunchKernelGGL((sub_dq_kernel<16, SUB_DQ_QB, SUB_DQ_NST, SUB_DQ_WGS>), gq, dim3(256), 0, st, g, qkv, ld, o, d_o, ldo, lse2, valid_len, key_pad, delta, dqkv, ldg); }
+    if (g.dh == 8) hipLaunchKernelGGL((sub_dq_kernel<8>), gq, dim3(256), 0, st, g, qkv, ld, o, d_o, ldo, lse2, valid_len, key_pad, delta, dqkv, ldg);
+    else hipLaunchKernelGGL((sub_dq_kernel<16>), gq, dim3(256), 0, st, g, qkv, ld, o, d_o, ldo, lse2, valid_len, key_pad, delta, dqkv, ldg); }
   { ProfScope ps(PF_ATTN_DKV, st);
     if (g.dh == 8) hipLaunchKernelGGL((sub_dkv_kernel<8, 2, 3>), gk, dim3(256), 0, st, g, qkv, ld, d_o, ldo, lse2, delta, valid_len, key_pad, dqkv, ldg);
     else hipLaunchKernelGGL((sub_dkv_kernel<16, 1, 4>), gk, dim3(256), 0, st, g, qkv, ld, d_o, ldo, lse2, delta, valid_len, key_pad, dqkv, ldg); }
