@@ -45,7 +45,6 @@ namespace imattn {
 // quarter of the VALU instructions of the row-per-lane kernel at these head sizes.
 // KS = 2: tiles of half the height, see split_rows.
 // PAIR: two problems of the same shape in one launch (two encoders side by side; see Geo::pair_B): grid z = 2 B.
-constexpr float ROW_SUM_MAX = 16777216.f;   // sum of exponentials relative to the reference, beyond which the reference moves
 constexpr float BF16_MAX = 3.3895313892515355e38f;
 constexpr int FWD_NST = 2;                  // stages of its ring
 template <int QB, int DH, int WGS, bool PAIR, int KS = 1>
@@ -57,7 +56,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WGS, WGS)))
   __shared__ __attribute__((aligned(256))) unsigned sKP[FWD_NST * KT];        // per stage: key_pad bytes of the 64 keys, one per dword
   __shared__ __attribute__((aligned(16))) unsigned sPM[4][KT / 2];            // key masks of the wave's tile
   __shared__ SegTable sSeg[4];
-  __shared__ int sRedo[4];
   // Sub-head mode: ones, four to each of the 16-key steps of a tile, where the step's V^T fragment has its rows in the tile.
   // The lanes whose four rows of the fragment are not the head's read them: those rows of O^T are then the row sum of P,
   // which the matrix cores take beside the product (a dot product per pair of probabilities otherwise, 8 of 40 vector
@@ -141,24 +139,17 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WGS, WGS)))
   }
 
   const int prow = perm32(lo);
-  constexpr float tau = 8.f;  // scores are exponents of 2 (Q carries scale * log2(e))
   // The negated reference of the query rows enters S^T through the matrix cores, as three bf16 parts that meet ones (bf16_parts):
   // in the lane half of the k-step that is not the head's (head dimension 8), or in an 8-deep k-step of their own, which has room
   // in the 128 registers where a seed of 16 accumulator registers has not.
-  u32x2 nmp[DH == 16 ? QB : 1];
-  f32x16 nm[DH == 64 ? QB : 1];
+  u32x2 nmp[DH == 8 ? 1 : QB];
   const bool spare = DH == 8 && hi != ((wo >> 3) & 1);
   const unsigned kf = spare ? (unsigned)(uintptr_t)(sOnes + 8) : (unsigned)(prow * SW_LD + (((2 * s0 + hi) ^ sw_f(prow)) << 3)) * 2u;
   const unsigned kf_tile = spare ? 0u : ~0u;
   auto set_reference = [&](int qb, float v) __attribute__((always_inline)) {   // v: negated
-    if (DH == 64) {
-#pragma unroll
-      for (int r = 0; r < 16; ++r) nm[DH == 64 ? qb : 0][r] = v;
-      return;
-    }
     const u32x2 pt = bf16_parts(v);
     if (DH == 8) qreg[qb][0] = spare ? as_bf16x8(u32x4{pt[0], pt[1], 0u, 0u}) : qreg[qb][0];
-    else nmp[DH == 16 ? qb : 0] = hi == 0 ? pt : u32x2{0u, 0u};
+    else nmp[DH == 8 ? 0 : qb] = hi == 0 ? pt : u32x2{0u, 0u};
   };
   // The compiler does not see the asynchronous copies in its vmcnt bookkeeping: consuming the Q
   // registers here makes it wait for their (ordinary) loads now, not inside the ring loop.
@@ -169,40 +160,51 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WGS, WGS)))
 
   const unsigned key_set = valid_len ? seg_lens_table(sg, valid, row_set, lane) : row_set;
 
-  // One pass over the live key tiles, for NQB of the wave's QB query blocks (NQB < QB: a tile of half the height).
+  // A row's reference is its largest score in the first 32-key block that has a valid key.  fp32 and bf16 share their exponent range,
+  // so probabilities above 1 lose nothing, and the reference moves only where one would exceed 2^24 (sub-head mode; at head dimension
+  // 64 a lane's part of a block's sum): almost every block is exponentiated as it leaves the matrix cores, no maximum is taken.
   //
-  // GUARD = false: the reference of a row is its largest score in the first 32-key block that has a valid key, and stays.  fp32 and
-  // bf16 share their exponent range, so probabilities far above 1 lose nothing; only the sum has to stay in range, which is
-  // checked once, behind the loop: no maximum, no rescaling and no branch on the scores per block.  (Four encoder layers at 32 x
-  // 50/500/375 rows, 8 heads of 8: 129 us; with a check of every block's sum, as in the other pass, 146.)
-  // Without any reference it is 127 us, but then the largest probability of the first block is rounded to bf16 like the others instead
-  // of being exactly 1, and with it the log-sum-exp that the backward takes all probabilities from.  Errors against fp64, rms of
-  // 6 seeds, times those with a running reference: y up to 1.03, dWo 1.04, dWv 1.05, dWq and dWk 1.04 at 8 and 30 keys, ordinary
-  // and peaked scores; with this one 0.99 to 1.00 everywhere.
-  // GUARD = true: a running reference m per query row; the pass that rows whose sum left the range take.
-  auto stream = [&](auto nqb_tag, auto guard_tag) __attribute__((always_inline)) {
+  // In sub-head mode, where row sums come out of the matrix cores too late for that, references are 23 larger than the score.  A
+  // probability of 2^24 is 2 then and sets bit 14 of its bf16, and eight three-way ORs and a compare find it for 32 x 64 scores.
+  // (Probabilities below 2^-103 of the largest vanish, and values of V below 1e-31.)
+  //
+  // Without any reference the largest probability of the first block is rounded to bf16 like the others instead of being exactly 1, and
+  // with it the log-sum-exp that the backward takes all probabilities from.  Errors against fp64, rms of 6 seeds, 40 shapes of 8
+  // to 1000 keys, ordinary and peaked scores, times those with a reference that moves in every block that needs it: y up to 1.03,
+  // dWo 1.04, dWv 1.05, dWq and dWk 1.04; as here 0.99 to 1.00.
+  // Time, us:                                            4 encoder layers of     16 x 2048 rows, 8 heads of 8, scores with a standard
+  //                                                      32 x 50/500/375 rows    deviation of 1.4 / 10 / 20 bits
+  //   row sums by dot products, first references in the
+  //     loop, three workgroups per CU                      147                     123 / 129 / 142
+  //   row sums by dot products                             137                     110 / 116 / 132
+  //   here                                                 131                      97 / 111 / 133
+  //   one check behind the loop, a second pass             129                      94 / 198 / 202
+  //   no reference                                         126                      92 / 127 / 202
+  auto row_max = [&](const f32x16& s) __attribute__((always_inline)) {   // of the lane's column of S^T, both lane halves
+    float mx = s[0];
+#pragma unroll
+    for (int r = 1; r < 16; ++r) mx = fmaxf(mx, s[r]);
+    const auto both = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
+    return fmaxf(__uint_as_float(both[0]), __uint_as_float(both[1]));
+  };
+  auto clamp_ref = [](float v) __attribute__((always_inline)) { return fminf(fmaxf(v, -BF16_MAX), BF16_MAX); };   // has a bf16
+  constexpr float REF_OFF = ONES ? 23.f : 0.f;
+  // One pass over the live key tiles, for NQB of the wave's QB query blocks (NQB < QB: a tile of half the height).
+  auto stream = [&](auto nqb_tag) __attribute__((always_inline)) {
     constexpr int NQB = decltype(nqb_tag)::value;
-    constexpr bool GUARD = decltype(guard_tag)::value;
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb) {
       m[qb] = IM_NEG_INF;
       l[qb] = 0.f;
-      if (!GUARD || DH == 8) set_reference(qb, 0.f);
+      set_reference(qb, 0.f);
 #pragma unroll
       for (int db = 0; db < NDB; ++db)
 #pragma unroll
         for (int r = 0; r < 16; ++r) oacc[db][qb][r] = 0.f;
     }
     static_assert(FWD_NST == 2, "the slot refilled while a tile is consumed is that of the tile before");
-    int cslot = 0, keys = 0, keys1;   // valid keys of the present tile, of the one requested after it (-1: there is none)
-    if (!GUARD && row_set) {   // the first one is under way
-      keys1 = ring.begin(seg1, key_set);
-    } else {
-      ring.slot = 0;
-      ring.at.rest = key_set;
-      ring.next_seg();
-      keys1 = ring.issue();
-    }
+    int cslot = 0, keys = 0, keys1 = row_set ? ring.begin(seg1, key_set) : -1;   // valid keys of the present tile, of the one
+                                                                                 // requested after it (-1: there is none)
     const bf16_t *sK = sT, *sV = sT;
     bool need_mask = false;   // tail tile or key_pad present (wave-uniform)
     auto advance = [&]() __attribute__((always_inline)) {   // to the next tile
@@ -223,14 +225,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WGS, WGS)))
                                  : lds_frag_sw(sK, kb * 32, prow, 2 * (s0 + s) + hi);
 #pragma unroll
         for (int qb = 0; qb < NQB; ++qb) {
-          if (s == 0) sacc[qb] = GUARD || DH == 8 ? f32x16{} : DH == 64 ? nm[DH == 64 ? qb : 0] : mfma32_k8(u32x2{ONES01, ONES2}, nmp[DH == 16 ? qb : 0], f32x16{});
+          if (s == 0) sacc[qb] = DH == 8 ? f32x16{} : mfma32_k8(u32x2{ONES01, ONES2}, nmp[DH == 8 ? 0 : qb], f32x16{});
           sacc[qb] = mfma32(a, qreg[qb][s], sacc[qb]);
         }
       }
     };
     // The references, from the first block with a valid key (wave-uniform); the tiles before it contribute nothing.
-    bool seen = GUARD;
-    while (!GUARD && !seen && keys1 >= 0) {
+    bool seen = false;
+    while (!seen && keys1 >= 0) {
       advance();
 #pragma unroll 1
       for (int kk = 0; kk < 2 / KS && !seen; ++kk) {
@@ -252,19 +254,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WGS, WGS)))
         }
         if (!seen) continue;
 #pragma unroll
-        for (int qb = 0; qb < NQB; ++qb) {
-          float mx = sacc[qb][0];
-#pragma unroll
-          for (int r = 1; r < 16; ++r) mx = fmaxf(mx, sacc[qb][r]);
-          const auto both = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
-          mx = fmaxf(__uint_as_float(both[0]), __uint_as_float(both[1]));
-          m[qb] = fminf(fmaxf(mx, -BF16_MAX), BF16_MAX);   // has a bf16 (a row beyond it leaves the range and is taken again)
-        }
+        for (int qb = 0; qb < NQB; ++qb) m[qb] = clamp_ref(row_max(sacc[qb]) + REF_OFF);
 #pragma unroll
         for (int qb = 0; qb < NQB; ++qb) set_reference(qb, -m[qb]);
       }
     }
-    if (GUARD && keys1 >= 0) advance();
     while (keys > 0) {   // a tile is there
       const unsigned vta = (vt_tile & (unsigned)(uintptr_t)sV) + vt0, vtb = (vt_tile & (unsigned)(uintptr_t)sV) + vt1;
       // The tile is processed as two blocks of 32 keys, each S^T -> softmax -> O^T (KS = 2: one by each of two waves).
@@ -273,68 +267,62 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WGS, WGS)))
         scores(sacc, kb);
         // ---- softmax ----
         bf16x8 pb[QB][2];
+        float rs[QB];
         unsigned pmask[8];   // the validity of the keys of a packed pair of probabilities
-        if (need_mask) {
-          block_masks(sPM[wave], kb, hi, pmask);
-          if (GUARD) {   // the maximum must not see masked keys
+        if (need_mask) block_masks(sPM[wave], kb, hi, pmask);
+        // P^T operands of a query block from its scores, 0 for a masked key whatever its row holds.  Not 0 on a lane whose row is to
+        // move its reference: by a bit of the packed probabilities, or by the lane's part of the row sum, which is taken over
+        // the bf16-rounded probabilities (the values that multiply V) with two-element dot products against (1, 1).
+        auto exponentiate = [&](int qb) __attribute__((always_inline)) {
+          float p[16];
 #pragma unroll
-            for (int r = 0; r < 16; ++r)
-#pragma unroll
-              for (int qb = 0; qb < NQB; ++qb) sacc[qb][r] = (pmask[r >> 1] >> (16 * (r & 1)) & 1u) ? sacc[qb][r] : IM_NEG_INF;
+          for (int r = 0; r < 16; ++r) p[r] = fast_exp2(sacc[qb][r]);
+          pb[qb][0] = pack8(p);
+          pb[qb][1] = pack8(p + 8);
+          if (need_mask) {
+            pb[qb][0] = and_bf16x8(pb[qb][0], pmask);
+            pb[qb][1] = and_bf16x8(pb[qb][1], pmask + 4);
           }
-        }
+          if (ONES) return (or_bf16x8(pb[qb][0]) | or_bf16x8(pb[qb][1])) & 0x40004000u;
+          rs[qb] = sum_bf16x8(pb[qb][1], sum_bf16x8(pb[qb][0], 0.f));
+          return rs[qb] > 0x1p24f ? 1u : 0u;
+        };
+        unsigned over = 0u;
 #pragma unroll
-        for (int qb = 0; qb < NQB; ++qb) {
-          // P^T operands of the block from its scores, 0 for a masked key whatever its row holds; the lane's part of the row
-          // sum is taken over the bf16-rounded probabilities (the values that multiply V) with two-element dot products
-          // against (1, 1)
-          auto exponentiate = [&](float sum) {
-            float p[16];
+        for (int qb = 0; qb < NQB; ++qb) over |= exponentiate(qb);
+        if (__builtin_expect(__any(over != 0u), 0)) {
+          asm volatile("" ::: "memory");  // a real branch: nothing of it is to be executed speculatively
 #pragma unroll
-            for (int r = 0; r < 16; ++r) p[r] = fast_exp2(sacc[qb][r]);
-            pb[qb][0] = pack8(p);
-            pb[qb][1] = pack8(p + 8);
-            if (!GUARD && need_mask) {
-              pb[qb][0] = and_bf16x8(pb[qb][0], pmask);
-              pb[qb][1] = and_bf16x8(pb[qb][1], pmask + 4);
-            }
-            if (ONES && !GUARD) return 0.f;
-            return sum_bf16x8(pb[qb][1], sum_bf16x8(pb[qb][0], sum));
-          };
-          if (!GUARD) {
-            l[qb] = exponentiate(l[qb]);
-            continue;
-          }
-          // A row without a reference yet, or a row sum of the block beyond 2^24 (or inf / NaN), sends the block
-          // through the rescaling branch, which recomputes it.
-          const float m0 = m[qb] == IM_NEG_INF ? 0.f : m[qb];
+          for (int qb = 0; qb < NQB; ++qb)
+            if (m[qb] == -BF16_MAX) set_reference(qb, 0.f);
+          scores(sacc, kb);   // again, so that the registers of these are free above
 #pragma unroll
-          for (int r = 0; r < 16; ++r) sacc[qb][r] -= m0;
-          float rs = exponentiate(0.f);
-          if (__builtin_expect(__any(m[qb] == IM_NEG_INF || !(rs <= ROW_SUM_MAX)), 0)) {
-            asm volatile("" ::: "memory");  // a real branch: nothing of it is to be executed speculatively
-            float mx = sacc[qb][0];
+          for (int qb = 0; qb < NQB; ++qb) {
+            if (need_mask)
 #pragma unroll
-            for (int r = 1; r < 16; ++r) mx = fmaxf(mx, sacc[qb][r]);
-            mx = fmaxf(mx, __shfl_xor(mx, 32, 64));  // block maximum relative to m (the raw maximum while m = -inf)
-            // The reference moves when a row has none yet, or when the block maximum exceeds it by more than
-            // 2^8 in the exponent domain: accumulator rescale, shifting the block's scores to the new reference.
-            const bool first = m[qb] == IM_NEG_INF;
-            const bool upd = first ? mx > IM_NEG_INF : mx > tau;
-            const float shift = upd ? mx : 0.f;
-            const float alpha = first ? 0.f : fast_exp2(-shift);
+              for (int r = 0; r < 16; ++r) sacc[qb][r] = (pmask[r >> 1] >> (16 * (r & 1)) & 1u) ? sacc[qb][r] : IM_NEG_INF;
+            // Rows that move: without a reference so far, or with a maximum 2^8 above the one that theirs was taken from.  The others
+            // get the same probabilities again.
+            const bool first = m[qb] == -BF16_MAX;
+            const float mx = row_max(sacc[qb]), from = first ? 0.f : m[qb];
+            const bool upd = first ? mx > IM_NEG_INF : mx > 8.f - REF_OFF;
+            const float to = clamp_ref(from + mx + REF_OFF), shift = upd ? to - from : 0.f, alpha = first ? 0.f : fast_exp2(-shift);
+            if (upd) m[qb] = to;
+            set_reference(qb, -m[qb]);
+            if (QB > 1 && !__any(upd)) continue;
             l[qb] *= alpha;
 #pragma unroll
             for (int db = 0; db < NDB; ++db)
 #pragma unroll
               for (int r = 0; r < 16; ++r) oacc[db][qb][r] *= alpha;
-            if (upd) m[qb] = first ? mx : m[qb] + mx;
 #pragma unroll
             for (int r = 0; r < 16; ++r) sacc[qb][r] -= shift;
-            rs = exponentiate(0.f);
+            exponentiate(qb);
           }
-          l[qb] += rs;
         }
+        if (!ONES)
+#pragma unroll
+          for (int qb = 0; qb < NQB; ++qb) l[qb] += rs[qb];
         // ---- O^T += V^T P^T over the 32 keys of the block ----
 #pragma unroll
         for (int db = 0; db < NDB; ++db)
@@ -348,9 +336,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WGS, WGS)))
       };
       if (KS == 2) {
         if (kg == 0 || keys > 32) block(kg);
-      } else if (GUARD) {
-#pragma unroll 1
-        for (int kb = 0; kb < 2 && (kb == 0 || keys > 32); ++kb) block(kb);
       } else {
         block(0);
         if (keys > 32) block(1);
@@ -364,74 +349,49 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WGS, WGS)))
     }
   };
 
+  if (HALF && half_tile) stream(std::integral_constant<int, 1>{});
+  else stream(std::integral_constant<int, QB>{});
+
   // ---- epilogue: normalise, write O rows, O^T columns and the log-sum-exp ----
-  // Returns whether a row left the range of the pass without a running reference: its sum, relative to the reference, above 2^24
-  // (where a running one moves), or below what the reference itself contributes (scores of -inf in the whole first block).  A row
-  // without a valid key has no reference and its results already: 0 and -inf.
-  bool redo[QB];
-  auto finish = [&](bool again) __attribute__((always_inline)) {
-    bool any = false;
-    if (KS == 2) {
-      // The two waves of a row block have every other key block each: a wave gives the other one 32 of the 64 columns,
-      // and both sums go together with their references (without one both are 0).
-      __syncthreads();   // the ring is read no more
-      float* ex = (float*)sT;   // per wave: 16 x 64 of the accumulator, then l and m
-      constexpr int EX = 18 * 64;
+  if (KS == 2) {
+    // The two waves of a row block have every other key block each: a wave gives the other one 32 of the 64 columns,
+    // and both sums go together with their references (without one both are 0).
+    __syncthreads();   // the ring is read no more
+    float* ex = (float*)sT;   // per wave: 16 x 64 of the accumulator, then l and m
+    constexpr int EX = 18 * 64;
 #pragma unroll
-      for (int r = 0; r < 16; ++r) ex[wave * EX + r * 64 + lane] = kg ? oacc[0][0][r] : oacc[NDB - 1][0][r];
-      ex[wave * EX + 16 * 64 + lane] = l[0];
-      ex[wave * EX + 17 * 64 + lane] = m[0];
-      __syncthreads();
-      const float* in = ex + (wave ^ 1) * EX;
-      const float m1 = in[17 * 64 + lane], l1 = in[16 * 64 + lane], mm = fmaxf(m[0], m1);
-      const float a0 = m[0] == IM_NEG_INF ? 0.f : fast_exp2(m[0] - mm), a1 = m1 == IM_NEG_INF ? 0.f : fast_exp2(m1 - mm);
-      m[0] = mm;
-      l[0] = !again && (l[0] > ROW_SUM_MAX || l1 > ROW_SUM_MAX) ? __builtin_inff() : a0 * l[0] + a1 * l1;   // (a sum can be infinite)
+    for (int r = 0; r < 16; ++r) ex[wave * EX + r * 64 + lane] = kg ? oacc[0][0][r] : oacc[NDB - 1][0][r];
+    ex[wave * EX + 16 * 64 + lane] = l[0];
+    ex[wave * EX + 17 * 64 + lane] = m[0];
+    __syncthreads();
+    const float* in = ex + (wave ^ 1) * EX;
+    const float m1 = in[17 * 64 + lane], l1 = in[16 * 64 + lane], mm = fmaxf(m[0], m1);
+    const float a0 = m[0] == IM_NEG_INF ? 0.f : fast_exp2(m[0] - mm), a1 = m1 == IM_NEG_INF ? 0.f : fast_exp2(m1 - mm);
+    m[0] = mm;
+    l[0] = a0 * l[0] + a1 * l1;
 #pragma unroll
-      for (int r = 0; r < 16; ++r) oacc[0][0][r] = a0 * (kg ? oacc[NDB - 1][0][r] : oacc[0][0][r]) + a1 * in[r * 64 + lane];
-    }
+    for (int r = 0; r < 16; ++r) oacc[0][0][r] = a0 * (kg ? oacc[NDB - 1][0][r] : oacc[0][0][r]) + a1 * in[r * 64 + lane];
+  }
 #pragma unroll
-    for (int qb = 0; qb < QB; ++qb) {
-      const float lt = ONES ? l[qb] : l[qb] + __shfl_xor(l[qb], 32, 64);
-      const float inv = lt > 0.f ? 1.f / lt : 0.f;
-      const int row = qrow[qb];
-      if (row >= qlen || (again && !redo[qb])) continue;
-      const long t = qrow0 + row;
-      if (hi == 0 && kg == 0 && lse2) lse2[(g.cu ? (long)h * g.R : ((long)b * g.H + h) * g.T) + qoff + row] = lt > 0.f ? -(m[qb] + log2f(lt)) : IM_NEG_INF;  // negated
+  for (int qb = 0; qb < QB; ++qb) {
+    const float lt = ONES ? l[qb] : l[qb] + __shfl_xor(l[qb], 32, 64);
+    const float inv = lt > 0.f ? 1.f / lt : 0.f;
+    const int row = qrow[qb];
+    if (row >= qlen) continue;
+    const long t = qrow0 + row;
+    if (hi == 0 && kg == 0 && lse2) lse2[(g.cu ? (long)h * g.R : ((long)b * g.H + h) * g.T) + qoff + row] = lt > 0.f ? -(m[qb] + log2f(lt)) : IM_NEG_INF;  // negated
 #pragma unroll
-      for (int db = 0; db < NDB / KS; ++db)
+    for (int db = 0; db < NDB / KS; ++db)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int dh0 = (KS == 2 ? kg : db0 + db) * 32 + 8 * i + 4 * hi;  // column inside the 64-column group
-          if (DH < 64 && (dh0 < wo || dh0 >= wo + DH)) continue;
-          float v[4];
+      for (int i = 0; i < 4; ++i) {
+        const int dh0 = (KS == 2 ? kg : db0 + db) * 32 + 8 * i + 4 * hi;  // column inside the 64-column group
+        if (DH < 64 && (dh0 < wo || dh0 >= wo + DH)) continue;
+        float v[4];
 #pragma unroll
-          for (int jj = 0; jj < 4; ++jj) v[jj] = oacc[db][qb][4 * i + jj] * inv;
-          const u32x2 pk = {pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3])};
-          *(u32x2*)(O + t * ldo + cg * 64 + dh0) = pk;
-        }
-      redo[qb] = (lt < 0.5f && m[qb] != IM_NEG_INF) || lt > ROW_SUM_MAX;
-      any |= redo[qb];
-    }
-    return any;
-  };
-  auto run = [&](auto guard_tag) __attribute__((always_inline)) {
-    if (HALF && half_tile) stream(std::integral_constant<int, 1>{}, guard_tag);
-    else stream(std::integral_constant<int, QB>{}, guard_tag);
-  };
-  run(std::integral_constant<bool, false>{});
-  // The rows of a workgroup that ask for it are taken again, together because the ring is the workgroup's; the other rows
-  // keep what they have.
-  const bool any = finish(false);
-  const bool wave_any = __any(any);
-  if (lane == 0) sRedo[wave] = wave_any;
-  __syncthreads();
-  int again = 0;
-#pragma unroll
-  for (int w = 0; w < 4; ++w) again |= sRedo[w];
-  if (__builtin_expect(__builtin_amdgcn_readfirstlane(again), 0)) {
-    run(std::integral_constant<bool, true>{});
-    finish(true);
+        for (int jj = 0; jj < 4; ++jj) v[jj] = oacc[db][qb][4 * i + jj] * inv;
+        const u32x2 pk = {pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3])};
+        *(u32x2*)(O + t * ldo + cg * 64 + dh0) = pk;
+      }
   }
 }
 

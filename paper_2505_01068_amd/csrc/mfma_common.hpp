@@ -79,6 +79,11 @@ __device__ __forceinline__ float sum_bf16x8(bf16x8 v, float acc) {
   return acc;
 }
 
+// bitwise or of the four packed pairs
+__device__ __forceinline__ unsigned or_bf16x8(bf16x8 v) {
+  const u32x4 u = __builtin_bit_cast(u32x4, v);
+  return u[0] | u[1] | u[2] | u[3];
+}
 __device__ __forceinline__ bf16x8 and_bf16x8(bf16x8 v, const unsigned* m) {
   union { bf16x8 v; u32x4 u; } x;
   x.v = v;

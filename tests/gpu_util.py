@@ -171,9 +171,9 @@ class PackedProblem(Problem):
         return errs
 
 
-def rows_leaving_the_range(p, cache, bits=24):
-    """[B, H, T_m]: rows of Problem p whose sum of exponentials exceeds 2^bits relative to the largest score of their first 32-key
-    block with a valid key (the blocks of a segment start at its first row): the bf16 forward takes them a second time."""
+def rows_outgrowing_the_first_block(p, cache, bits=24):
+    """[B, H, T_m]: rows of Problem p with a score more than `bits` (in the exponent of 2) above the largest one of their first 32-key
+    block with a valid key (the blocks of a segment start at its first row): the bf16 forward moves their reference."""
     g, seg = p.g, p.g["seg_len"]
     q, k, H = cache["q"], cache["k"], g["n_heads"]
     B_, T, d = q.shape
@@ -198,9 +198,6 @@ def rows_leaving_the_range(p, cache, bits=24):
             for c in range(0, m, 32):
                 ref = np.where(np.isinf(ref), s[..., c:c + 32].max(-1), ref)
         if cols:
-            a = np.concatenate(cols, -1)
-            top = a.max(-1)
             with np.errstate(invalid="ignore"):
-                total = np.where(np.isinf(top), -np.inf, top + np.log2(np.exp2(a - top[..., None]).sum(-1)))
-                out[:, :, off[i]:off[i] + n] = total - ref > bits
+                out[:, :, off[i]:off[i] + n] = np.concatenate(cols, -1).max(-1) - ref > bits
     return out

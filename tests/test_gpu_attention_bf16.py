@@ -6,7 +6,7 @@ import torch
 
 import oracle
 from paper_2505_01068_amd import synth
-from tests.gpu_util import Problem, assert_close, rel_err, rows_leaving_the_range, TOL
+from tests.gpu_util import Problem, assert_close, rel_err, rows_outgrowing_the_first_block, TOL
 
 pytestmark = pytest.mark.gpu
 
@@ -210,7 +210,7 @@ def test_c5_full_size_weight_gradients(c5_full):
 
 def test_mfma_zero_scale_and_large_scores():
     """scale = 0 gives uniform attention over valid keys (no NaN from -inf * 0); large, growing scores
-    move the softmax reference (sums far above what the first block's maximum allows)."""
+    move the softmax reference (scores far above the first block's maximum)."""
     say("[case] mfma scale=0 / growing scores")
     g = synth.attention_inputs(2, (70, 300, 129), 64, 1, "bf16", "valid_len", seed=31, bias=False)
     g0 = dict(g, scale=0.0)
@@ -224,8 +224,8 @@ def test_mfma_zero_scale_and_large_scores():
     # more than the bar (conditioning of the problem, not of the kernel)
     for lm in (oracle.IM_IFM_FORWARD, oracle.IM_DENSE):
         p = Problem(g1, lm)
-        n = int(rows_leaving_the_range(p, p.oracle_fwd(cache=True)[1]).sum())
-        say(f"    {n} rows leave the range of the first pass")
+        n = int(rows_outgrowing_the_first_block(p, p.oracle_fwd(cache=True)[1]).sum())
+        say(f"    {n} rows move their reference")
         assert n > 0
         p.check(backward=False, what=f"mfma growing scores lm={lm:#x}")
 

@@ -116,7 +116,7 @@ def test_model_at_the_benchmark_shape_and_depth(padding):
 @pytest.mark.parametrize("H", [8, 4])
 def test_model_scores_that_outgrow_the_first_block(H, padding):
     """The two inter-modal encoders in shared launches: every row of both scores one key of its second 32-key block 100 (head
-    dimension 8) or 80 (16) in the exponent of 2 above the others, so that each is taken again with a moving reference."""
+    dimension 8) or 80 (16) in the exponent of 2 above the others, so that each moves its reference."""
     say(f"[case] model, growing scores H={H} {padding}")
     d, seg, d_ff, at = 64, (50, 130, 75), 128, 40
     dh = d // H
