@@ -32,7 +32,12 @@
  *     against 64 bits are at or below those of fp32 multiply-adds.  A sum that comes
  *     out infinite or NaN is taken again with fp32 multiply-adds, so that infinities
  *     and values up to the largest fp32 number give what those give.  Operands below
- *     2^-110 (8e-34) keep an absolute accuracy of 2^-134 instead of 24 bits.
+ *     2^-110 (8e-34) keep an absolute accuracy of 2^-134 instead of 24 bits.  The
+ *     smallest inference calls (nothing saved, d_model <= 32, a few dozen rows per
+ *     sample) sum their projections in 64 bits on the vector ALUs instead, in one
+ *     launch.  y of the same problem with and without `saved`, with y over x, or at
+ *     another batch size therefore agrees to rounding (1e-7), not bit for bit; calls
+ *     with the same arguments do give the same bits.
  *   - Return value: IM_OK, or a negative error code.  Shape, pointer, alignment
  *     and workspace-size validation precedes any launch (a call rejected with
  *     IM_ERR_INVALID / UNSUPPORTED / WORKSPACE has enqueued nothing); IM_ERR_HIP
@@ -231,8 +236,8 @@ typedef struct {
   const void* bf;
 } gsit_model_t;
 
-/* Encoder layer, training.  gsit_layer_fwd_train computes the same y as gsit_layer_fwd and fills
- * `saved` (the attention's saved tensors, h = x + attention, the MLP's pre-activation and
+/* Encoder layer, training.  gsit_layer_fwd_train computes the y of gsit_layer_fwd (by other kernels: it
+ * agrees to rounding, not bit for bit) and fills `saved` (the attention's saved tensors, h = x + attention, the MLP's pre-activation and
  * activation); gsit_layer_bwd is the gradient of that forward (the calculus of the layer of Sec. 5;
  * the paper analyses no backward pass): given dy [B,T_m,d] it overwrites dx [B,T_m,d] (dtype of
  * shape->dtype) and, for every non-NULL field of `grads`, the fp32 gradient of the parameter of

@@ -161,8 +161,10 @@ __global__ __launch_bounds__(TINY_THREADS) void tiny_fwd_kernel(Geo g, TinyArgs 
 // Whether the call goes to the kernel above: fp32, width up to 32, head dimension up to 16, every query segment reads at most 40
 // rows, and the workgroups have a CU each.  Every workgroup repeats the projections of its keys, whose cost grows with their number
 // and the square of the width: us of a call, three launches / one, at d = 32 with 16 keys 16.3 / 9.9 (2 to 80 samples alike),
-// 40 keys 15.7 / 11.9, 64 keys 16.4 / 14.8 with 4 heads but 15.9 / 19.0 with 32; at d = 40 with 40 keys 16.1 / 16.8 and at d = 48
-// with 60 keys 16.3 / 21.4.
+// 40 keys 15.7 / 11.9, 64 keys 16.4 / 14.8 with 4 heads but 15.9 / 19.0 with 32; in a form of 64 columns, at d = 40 with 40 keys
+// 16.1 / 16.8 and at d = 48 with 60 keys 16.3 / 21.4.  The line at width 32 is that of the one form there is, not of the method: a
+// form of 40 columns takes 11.4 at d = 40 with 16 keys and 14.5 with 40 (16.3 and 17.2 in three launches), but 253 registers, and
+// 10 to 15 % more at d = 32.
 // y must not overlap x: a workgroup reads rows of x that another one has finished.
 bool tiny_fwd_ok(const Geo& g, const void* x, const void* y) {
   if (g.d > TINY_D || g.dh > 16) return false;

@@ -59,7 +59,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WGS, WGS)))
   // Sub-head mode: ones, four to each of the 16-key steps of a tile, where the step's V^T fragment has its rows in the tile.
   // The lanes whose four rows of the fragment are not the head's read them: those rows of O^T are then the row sum of P,
   // which the matrix cores take beside the product (a dot product per pair of probabilities otherwise, 8 of 40 vector
-  // instructions per 32 x 32 scores).
+  // instructions per 32 x 32 scores).  Between them, at head dimension 8, the ones that the reference's parts meet.
   constexpr bool ONES = DH != 64;
   __shared__ __attribute__((aligned(16))) bf16_t sOnes[ONES ? 3 * 16 * SW_LD + 4 : 4];
   const int tid = threadIdx.x, lane = tid & 63, lo = lane & 31, hi = lane >> 5;
@@ -397,9 +397,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WGS, WGS)))
 
 // ------------------------------------------------------------------------------------------
 // dQ (and delta = rowsum(dO * O)).  Same ownership as the forward: lane <-> query row.
-// The two constant accumulator seeds (negated lse, -delta: 32 registers) put the kernel at 194 registers
-// and two workgroups per CU; with them the softmax is exp2, one multiply and the bf16 pack per score, and
-// that was measured faster than three workgroups per CU with two more vector instructions per score.
+// With the two constant accumulator seeds (negated lse, -delta: 32 registers; 167 in all, three workgroups per CU) the softmax is exp2,
+// one multiply and the bf16 pack per score; without them the kernel is 7 % slower.
 template <int QB, int NST, int WGS, int KS = 1>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WGS, WGS))) void mfma_dq_kernel(Geo g, const bf16_t* __restrict__ QKV, long ld,
                                                       const bf16_t* __restrict__ O,
@@ -842,9 +841,9 @@ __global__ __launch_bounds__(256, 3) void mfma_dkv_kernel(Geo g, const bf16_t* _
 //   forward, head dim 64: 1 query block per wave, 4 waves, a 2-stage ring and 128 registers, so that four
 //     workgroups (16 waves) share a CU -- 10 % faster than 3 stages at three workgroups; 8-wave workgroups
 //     (256 query rows) were slower;
-//   forward, sub-head mode: 2 query blocks per wave (half the K/V tile traffic per score), 2 stages, 4 workgroups (115
-//     registers; four layers of 32 x 50/500/375 rows, no padding, intra-modal mask: 169 us with 3 stages and 3 workgroups, 160
-//     with 2 and 4, 150 with the row sums on the matrix cores);
+//   forward, sub-head mode: 2 query blocks per wave (half the K/V tile traffic per score), 2 stages, 4 workgroups (128
+//     registers; four layers of 32 x 50/500/375 rows, no padding, intra-modal mask, before the rows had references: 169 us with 3
+//     stages and 3 workgroups, 160 with 2 and 4, 150 with the row sums on the matrix cores);
 //   dQ, head dim 64: 3 stages, 3 workgroups per CU, accumulators seeded with -lse and -delta (unseeded: 7 % slower;
 //     4 workgroups need spills);
 //   dK/dV: 1 key block per wave, 3 workgroups per CU.  (Sub-head backward: mfma_attn_sub.hip.)
