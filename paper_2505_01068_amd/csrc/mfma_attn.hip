@@ -259,7 +259,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WGS, WGS)))
         for (int qb = 0; qb < NQB; ++qb) set_reference(qb, -m[qb]);
       }
     }
-    while (keys > 0) {   // a tile is there
+    while (seen && keys > 0) {
       const unsigned vta = (vt_tile & (unsigned)(uintptr_t)sV) + vt0, vtb = (vt_tile & (unsigned)(uintptr_t)sV) + vt1;
       // The tile is processed as two blocks of 32 keys, each S^T -> softmax -> O^T (KS = 2: one by each of two waves).
       auto block = [&](int kb) __attribute__((always_inline)) {
