@@ -139,17 +139,24 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WGS, WGS)))
   }
 
   const int prow = perm32(lo);
-  // The negated reference of the query rows enters S^T through the matrix cores, as three bf16 parts that meet ones (bf16_parts):
-  // in the lane half of the k-step that is not the head's (head dimension 8), or in an 8-deep k-step of their own, which has room
-  // in the 128 registers where a seed of 16 accumulator registers has not.
-  u32x2 nmp[DH == 8 ? 1 : QB];
+  // The negated reference of the query rows enters S^T through the matrix cores: as the seed of the accumulators (head dimension
+  // 64), or as three bf16 parts that meet ones (bf16_parts) -- in the lane half of the k-step that is not the head's (8), or in an
+  // 8-deep k-step of their own (16), where the seeds of two row blocks have no room in 128 registers.  (At 64 such a k-step takes
+  // 16 x 2048 rows, 2 heads, from 78 to 81 us.)
+  u32x2 nmp[DH == 16 ? QB : 1];
+  f32x16 nm;
   const bool spare = DH == 8 && hi != ((wo >> 3) & 1);
   const unsigned kf = spare ? (unsigned)(uintptr_t)(sOnes + 8) : (unsigned)(prow * SW_LD + (((2 * s0 + hi) ^ sw_f(prow)) << 3)) * 2u;
   const unsigned kf_tile = spare ? 0u : ~0u;
   auto set_reference = [&](int qb, float v) __attribute__((always_inline)) {   // v: negated
+    if (DH == 64) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r) nm[r] = v;
+      return;
+    }
     const u32x2 pt = bf16_parts(v);
     if (DH == 8) qreg[qb][0] = spare ? as_bf16x8(u32x4{pt[0], pt[1], 0u, 0u}) : qreg[qb][0];
-    else nmp[DH == 8 ? 0 : qb] = hi == 0 ? pt : u32x2{0u, 0u};
+    else nmp[DH == 16 ? qb : 0] = hi == 0 ? pt : u32x2{0u, 0u};
   };
   // The compiler does not see the asynchronous copies in its vmcnt bookkeeping: consuming the Q
   // registers here makes it wait for their (ordinary) loads now, not inside the ring loop.
@@ -225,7 +232,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WGS, WGS)))
                                  : lds_frag_sw(sK, kb * 32, prow, 2 * (s0 + s) + hi);
 #pragma unroll
         for (int qb = 0; qb < NQB; ++qb) {
-          if (s == 0) sacc[qb] = DH == 8 ? f32x16{} : mfma32_k8(u32x2{ONES01, ONES2}, nmp[DH == 8 ? 0 : qb], f32x16{});
+          if (s == 0) sacc[qb] = DH == 8 ? f32x16{} : DH == 64 ? nm : mfma32_k8(u32x2{ONES01, ONES2}, nmp[DH == 16 ? qb : 0], f32x16{});
           sacc[qb] = mfma32(a, qreg[qb][s], sacc[qb]);
         }
       }
